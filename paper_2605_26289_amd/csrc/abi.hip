@@ -57,6 +57,13 @@ int32_t guarded(F&& body) noexcept {
 
 }  // namespace
 
+// Which kernels carry an attention call.
+enum class Route {
+  kRef,      // scalar reference kernel: variant 1, a scale that is not positive and finite, fp32 pools
+  kTile,     // bf16, 128-wide heads, groups of 2^k <= 16 query heads: tile and stream kernels
+  kGeneral,  // bf16, any other shape: block kernel and the stream kernel's general form
+};
+
 struct dk_pool {
   dk_pool_desc desc;
   dk::Pool meta;
@@ -84,6 +91,32 @@ struct dk_pool {
     return {desc.k_arena, desc.v_arena, meta_arena_cells, desc.n_q_heads, desc.n_kv_heads, desc.head_dim, desc.dtype};
   }
   int64_t meta_arena_cells = 0;
+
+  // `scale_ok`: the scale is positive and finite (the MFMA kernels take the row maximum before scaling).
+  Route route(bool scale_ok, int32_t n_seqs, const int32_t* cu_delta) const {
+    if (variant == 1 || !scale_ok || desc.dtype != DK_BF16) return Route::kRef;
+    const int64_t group = desc.n_q_heads / desc.n_kv_heads;
+    if (desc.head_dim == 128 && group <= 16 && (group & (group - 1)) == 0) return Route::kTile;
+    // the general kernels divide packed row numbers (below group * delta) by a multiplication that is exact while
+    // row * (group - 1) < 2^32
+    int64_t most = 0;
+    if (cu_delta)
+      for (int32_t b = 0; b < n_seqs; ++b) most = std::max<int64_t>(most, (int64_t)cu_delta[b + 1] - cu_delta[b]);
+    return most < (int64_t(1) << 32) / (group * group) ? Route::kGeneral : Route::kRef;
+  }
+
+  dk::PlanConfig plan_config(Route r) const {
+    dk::PlanConfig c = cfg;
+    c.use_mfma = r != Route::kRef;
+    if (r == Route::kGeneral) {
+      // block kernel: items of 128 rows, two workgroups on a compute unit; an item's fixed cost (first tiles, merge of
+      // the half-waves, store) is about three of its shorter key steps
+      c.tile_rows = 128;
+      c.tile_wave_slots = 2 * cfg.tile_wave_slots;
+      c.tile_item_cost = std::min(cfg.tile_item_cost, 3);
+    }
+    return c;
+  }
 
   int32_t hip_fail(hipError_t e) {
     last_hip = (int32_t)e;
@@ -141,8 +174,6 @@ bool desc_ok(const dk_pool_desc* d, int32_t* why) {
   return true;
 }
 
-bool is_pow2(int32_t x) { return x > 0 && (x & (x - 1)) == 0; }
-
 }  // namespace
 
 extern "C" {
@@ -197,12 +228,11 @@ int32_t dk_pool_create(const dk_pool_desc* desc, dk_pool** pool_out) {
         p->ring_size = i + 1;
       }
     }
-    const int32_t group = desc->n_q_heads / desc->n_kv_heads;
     dk::PlanConfig& c = p->cfg;
     c.n_q_heads = desc->n_q_heads;
     c.n_kv_heads = desc->n_kv_heads;
     c.head_dim = desc->head_dim;
-    c.use_mfma = desc->dtype == DK_BF16 && desc->head_dim == 128 && is_pow2(group) && group <= 16;
+    c.use_mfma = true;  // (plan_config() decides for each call)
     c.tile_rows = 256;
     c.stream_rows = 96;
     c.kv_tile = 64;
@@ -409,10 +439,9 @@ int32_t dk_attend_workspace_bytes(dk_pool* pool, int32_t n_seqs, const int32_t* 
   return guarded([&]() -> int32_t {
     std::lock_guard<std::mutex> launch(pool->launch_mu);
     dk::AttendPlan& plan = pool->plan;
-    dk::PlanConfig cfg = pool->cfg;
-    if (pool->variant == 1) cfg.use_mfma = false;
-    std::lock_guard<std::mutex> lk(pool->meta.mutex());
     if (staged < 0 || staged > 2) return DK_ERR_INVALID;
+    const dk::PlanConfig cfg = pool->plan_config(pool->route(true, n_seqs, cu_delta));
+    std::lock_guard<std::mutex> lk(pool->meta.mutex());
     int32_t rc = dk::build_plan(pool->meta, cfg, n_seqs, slots, cu_delta, staged != 0, &plan, staged == 2);
     if (rc != DK_OK) return rc;
     *bytes_out = (int64_t)plan.total_bytes;
@@ -432,6 +461,15 @@ constexpr int32_t kNotFoldable = 1;
 constexpr int32_t kFoldMaxSeqs = 16;
 constexpr int64_t kFoldMaxTokens = 384;
 
+bool capturing(hipStream_t st) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &status) != hipSuccess) {  // the default stream while some other stream captures
+    (void)hipGetLastError();
+    return true;
+  }
+  return status != hipStreamCaptureStatusNone;
+}
+
 // Plans the call, uploads its descriptors into `workspace` and launches the attention kernels.  pool->launch_mu
 // is held.
 // fold_append: the call also appends all new tokens to their slots, provided that its descriptors fit the kernel
@@ -445,20 +483,32 @@ int32_t attend_locked(dk_pool* pool, int32_t n_seqs, const int32_t* slots, const
   const bool staged = k_new != nullptr;
   if (fold_append && !staged) return DK_ERR_INVALID;
   PhaseClock clk;
+  hipStream_t st = (hipStream_t)stream;
   dk::AttendPlan& plan = pool->plan;
-  dk::PlanConfig cfg = pool->cfg;
-  // the MFMA kernels take the row maximum before scaling, which needs a positive finite scale
-  if (pool->variant == 1 || !(scale > 0.f) || !(scale < 3.0e38f)) cfg.use_mfma = false;
-  {
-    std::lock_guard<std::mutex> lk(pool->meta.mutex());
-    int32_t rc = dk::build_plan(pool->meta, cfg, n_seqs, slots, cu_delta, staged, &plan, fold_append);
-    if (rc != DK_OK) return rc;
+  Route route = pool->route(scale > 0.f && scale < 3.0e38f, n_seqs, cu_delta);
+  bool inline_blob = false;
+  while (true) {
+    {
+      const dk::PlanConfig cfg = pool->plan_config(route);
+      std::lock_guard<std::mutex> lk(pool->meta.mutex());
+      int32_t rc = dk::build_plan(pool->meta, cfg, n_seqs, slots, cu_delta, staged, &plan, fold_append);
+      if (rc != DK_OK) return rc;
+    }
+    if (plan.total_tokens == 0) return DK_OK;
+    if (!q || !out) return DK_ERR_INVALID;
+    inline_blob = plan.blob_bytes <= (size_t)dk::INLINE_BLOB_BYTES && !plan.stream_queued;
+    if (fold_append && !(inline_blob && route != Route::kRef && (plan.tile_chains > 0 || plan.stream_chains > 0)))
+      return kNotFoldable;
+    if (route != Route::kGeneral) break;
+    // The reference kernel serves these shapes with a handful of descriptors, no partials and 2-byte accesses to q and
+    // out.  Where a caller has only made room for that -- a workspace or the static array without room for partials, a
+    // pool without staging memory, a capture that cannot take an upload, rows at odd addresses -- it still does.
+    const bool fits = (((uintptr_t)q | (uintptr_t)out) & 15) == 0 && workspace_bytes >= (int64_t)plan.total_bytes &&
+                      (inline_blob || (pool->ring_size > 0 && plan.blob_bytes <= pool->stage_cap && !capturing(st)));
+    if (fits) break;
+    if (fold_append) return kNotFoldable;
+    route = Route::kRef;
   }
-  if (plan.total_tokens == 0) return DK_OK;
-  if (!q || !out) return DK_ERR_INVALID;
-  const bool inline_blob = plan.blob_bytes <= (size_t)dk::INLINE_BLOB_BYTES && !plan.stream_queued;
-  if (fold_append && !(inline_blob && cfg.use_mfma && (plan.tile_chains > 0 || plan.stream_chains > 0)))
-    return kNotFoldable;
   if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < (int64_t)plan.total_bytes) return DK_ERR_WORKSPACE;
   // The bookkeeping half of a folded append.  From here on a failure must leave the pool as it was.
   std::vector<int64_t>& dst = pool->append_cells;
@@ -474,7 +524,6 @@ int32_t attend_locked(dk_pool* pool, int32_t n_seqs, const int32_t* slots, const
   };
   pool->host_us[DK_HOST_PLAN] += clk.lap();
 
-  hipStream_t st = (hipStream_t)stream;
   // Small descriptor blobs travel inside the kernel arguments; larger ones go through a staging buffer into
   // the workspace.
   dk::InlineBlob blob_args{};
@@ -527,6 +576,7 @@ int32_t attend_locked(dk_pool* pool, int32_t n_seqs, const int32_t* slots, const
   a.scale = scale;
   a.total_tokens = (int32_t)plan.total_tokens;
   a.cells = (const int32_t*)(desc + plan.off_cells);
+  a.general = route == Route::kGeneral;
 
   hipError_t e = hipSuccess;
   const bool timing = !pool->ev0.empty();
@@ -535,14 +585,15 @@ int32_t attend_locked(dk_pool* pool, int32_t n_seqs, const int32_t* slots, const
     e = hipEventRecord(pool->ev0[ev_slot], st);
     if (e != hipSuccess) return fail(pool->hip_fail(e));
   }
-  if (!cfg.use_mfma) {
+  if (route == Route::kRef) {
     e = dk::launch_attend_ref(a, st);
     if (e != hipSuccess) return fail(pool->hip_fail(e));
   } else {
     // a folded append is carried out by the first MFMA kernel of the call
     a.scatter = fold_append && plan.tile_chains > 0;
-    e = dk::launch_attend_tile(a, (const DkItem*)(desc + plan.off_tile), (const int32_t*)(desc + plan.off_tile_links),
-                               plan.tile_chains, st);
+    const auto launch_rows = a.general ? dk::launch_attend_block : dk::launch_attend_tile;
+    e = launch_rows(a, (const DkItem*)(desc + plan.off_tile), (const int32_t*)(desc + plan.off_tile_links),
+                    plan.tile_chains, st);
     if (e != hipSuccess) return fail(pool->hip_fail(e));
     a.scatter = fold_append && plan.tile_chains == 0;
     int32_t stream_rows = 0;

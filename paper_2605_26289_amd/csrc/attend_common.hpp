@@ -1,5 +1,5 @@
-// Shared device code of the bf16 MFMA attention kernels (gfx950, head_dim 128): descriptor access,
-// the walk over a slot's key segments, HBM -> LDS tile loads, MFMA operand reads and result stores.
+// Shared device code of the bf16 MFMA attention kernels (gfx950): descriptor access, the walk over a
+// slot's key segments, HBM -> LDS tile loads, MFMA operand reads and result stores.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -18,6 +18,21 @@ typedef __attribute__((address_space(1))) const void* glb_void_ptr;
 
 constexpr int D = 128;
 constexpr int ROW_BYTES = 256;
+
+// What the head dimension decides.  The swizzles spread the 16-byte chunks of consecutive K/V rows over the LDS banks
+// (64 banks of 4 bytes: one 256-byte row, or two 128-byte rows, per pass): K rows are read one per lane, 16 lanes to a
+// pass, V rows in blocks of four rows x 64 bytes.
+template <int HD>
+struct Geo {
+  static_assert(HD == 64 || HD == 128, "head dimensions of the MFMA kernels");
+  static constexpr int ROW = 2 * HD;             // bytes of a K/V/Q/O row
+  static constexpr int CHUNKS = ROW / 16;        // 16-byte chunks per row
+  static constexpr int ROWS_PER_KIB = 1024 / ROW;
+  static constexpr int KS = HD / 16;             // depth steps of S^T = K Q^T
+  static constexpr int DB = HD / 32;             // depth blocks of O^T = V^T P^T
+  static __device__ __forceinline__ int k_swizzle(int row) { return HD == 128 ? (row & 15) : ((row >> 1) & 7); }
+  static __device__ __forceinline__ int v_swizzle(int row) { return HD == 128 ? ((row & 3) << 2) : (((row >> 1) & 1) << 2); }
+};
 // Split partials: per (partial row, KV head) D unnormalised fp32 sums in `parts` (512-byte rows) and the pair
 // (running maximum in log2 units, weight sum) in `parts_ml`.
 
@@ -67,10 +82,26 @@ struct Ctx {
   float* __restrict__ parts_ml;
   float c;  // softmax scale * log2(e): scores are handled in log2 units
   int32_t n_q_heads, n_kv_heads, gshift;
+  int32_t group;    // query heads per KV head
+  uint32_t gmagic;  // ceil(2^32 / group), 0 for group 1: see row_token
   int64_t arena_cells;
   const int32_t* cells;  // small append-and-attend calls: arena cell of every new token
   int32_t n_scatter;     // how many tokens this launch writes into the arena (0: none)
 };
+
+// Token and head (inside the KV group) of a packed query row.  ANYG: any group size, by a multiply-high with the
+// rounded-up reciprocal -- exact while row * (group - 1) < 2^32, which the host checks for the whole batch before it
+// takes a kernel of this kind; otherwise the group is a power of two and this is a shift.
+template <bool ANYG>
+__device__ __forceinline__ int row_token(const Ctx& c, int row) {
+  if constexpr (ANYG) return c.gmagic ? (int)__umulhi((uint32_t)row, c.gmagic) : row;
+  else return row >> c.gshift;
+}
+template <bool ANYG>
+__device__ __forceinline__ int row_head(const Ctx& c, int row, int tok) {
+  if constexpr (ANYG) return row - tok * c.group;
+  else return row & ((1 << c.gshift) - 1);
+}
 
 // A run of at most KT consecutive K/V rows, all inside one segment.
 struct KvTile {
@@ -84,6 +115,7 @@ struct KvTile {
 // Walks the logical key positions [p, hi) of an entry, segment by segment.  The state of the segment
 // being walked (row pointers at position p, row stride, end position) is kept in a handful of scalars,
 // so the common step touches neither the segment table nor the kernel arguments.
+template <int HD = D>
 struct KvCursor {
   const DkSeg* segs;
   int32_t si, se, p, hi;
@@ -98,15 +130,15 @@ struct KvCursor {
     const int32_t off = p - s.pos;
     seg_end = s.pos + s.len;
     if (s.src == 0) {
-      const int64_t byte = ((int64_t)g * c.arena_cells + s.start + off) * ROW_BYTES;
+      const int64_t byte = ((int64_t)g * c.arena_cells + s.start + off) * Geo<HD>::ROW;
       k = c.k_arena + byte;
       v = c.v_arena + byte;
-      stride = ROW_BYTES;
+      stride = Geo<HD>::ROW;
     } else {
-      const int64_t byte = ((s.start + off) * c.n_kv_heads + g) * (int64_t)ROW_BYTES;
+      const int64_t byte = ((s.start + off) * c.n_kv_heads + g) * (int64_t)Geo<HD>::ROW;
       k = c.k_new + byte;
       v = c.v_new + byte;
-      stride = (uint32_t)c.n_kv_heads * ROW_BYTES;
+      stride = (uint32_t)c.n_kv_heads * Geo<HD>::ROW;
     }
   }
 
@@ -126,18 +158,18 @@ struct KvCursor {
   }
 };
 
-// One wavefront moves 4 rows (1 KiB) HBM -> LDS: lane l lands at lds + 16 l, i.e. row l / 16, chunk
-// slot l % 16, and fetches the chunk that the swizzle assigns to that slot.  Rows past the end of a
+// One wavefront moves 1 KiB (4 rows of 256 bytes or 8 of 128) HBM -> LDS: lane l lands at lds + 16 l, i.e. (256-byte
+// rows) row l / 16, chunk slot l % 16, and fetches the chunk that the swizzle assigns to that slot.  Rows past the end of a
 // ragged tile re-read the last valid row; their scores are masked.
 // The load is issued from inline assembly on purpose: the compiler then keeps no account of it and
 // inserts no vmcnt(0) of its own in front of later LDS reads, so a tile can stay in flight while
 // the previous one is being consumed.  Completion is awaited explicitly with wait_vmcnt<N>().
-template <bool IS_V>
-__device__ __forceinline__ void load_rows4(const char* gbase, uint32_t stride, int cnt, char* lds_region, int blk,
-                                           int lane) {
-  const int row = blk * 4 + (lane >> 4);
-  const int slot = lane & 15;
-  const int chunk = IS_V ? (slot ^ ((row & 3) << 2)) : (slot ^ (row & 15));
+template <bool IS_V, int HD = D>
+__device__ __forceinline__ void load_kib(const char* gbase, uint32_t stride, int cnt, char* lds_region, int blk, int lane) {
+  typedef Geo<HD> G;
+  const int row = blk * G::ROWS_PER_KIB + lane / G::CHUNKS;
+  const int slot = lane % G::CHUNKS;
+  const int chunk = slot ^ (IS_V ? G::v_swizzle(row) : G::k_swizzle(row));
   const uint32_t voff = (uint32_t)min(row, cnt - 1) * stride + chunk * 16;
   const uint32_t lds_addr = (uint32_t)(uintptr_t)(lds_void_ptr)(lds_region + blk * 1024);
   asm volatile(
@@ -153,29 +185,33 @@ __device__ __forceinline__ void load_rows4(const char* gbase, uint32_t stride, i
 // K[kb*32 + l%32][ks*16 + 8h .. +7], which the swizzle keeps in chunk (2ks + h) ^ (row & 15) of its row.
 // Because 2ks has bit 0 clear, that chunk is (2ks) ^ (h ^ (row & 15)): the per-lane part of the address
 // is computed once (k_lane_off) and each depth step only XORs in ks << 5.
+template <int HD = D>
 __device__ __forceinline__ uint32_t k_lane_off(int lane) {
   const int r = lane & 31;
-  return (uint32_t)(r * ROW_BYTES + (((lane >> 5) ^ (r & 15)) << 4));
+  return (uint32_t)(r * Geo<HD>::ROW + (((lane >> 5) ^ Geo<HD>::k_swizzle(r)) << 4));
 }
+template <int HD = D>
 __device__ __forceinline__ bf16x8 read_k_frag(const char* k_lds, uint32_t lane_off, int kb, int ks) {
-  return *(const bf16x8*)(k_lds + (lane_off ^ (uint32_t)(ks << 5)) + kb * (32 * ROW_BYTES));
+  return *(const bf16x8*)(k_lds + (lane_off ^ (uint32_t)(ks << 5)) + kb * (32 * Geo<HD>::ROW));
 }
 
 // A operand of O^T = V^T P^T for key step j (16 keys) and depth block db: lane (column l%32, half
 // h = l/32) holds V[16j + 8u + 4h + e][db*32 + l%32] for u = 0,1 and e = 0..3 -- the same key order
 // in which the S^T accumulators hand over P.  Two transposing 64-bit LDS reads: within 16 lanes, lane i
 // supplies the address of row i/4, 4-column piece i%4 and receives column i of the four rows.
-// The row's chunk is ((db ^ (row & 3)) << 2) | x, so again only db << 6 is XORed per read.
+// (256-byte rows) The row's chunk is ((db ^ (row & 3)) << 2) | x, so again only db << 6 is XORed per read.
+template <int HD = D>
 __device__ __forceinline__ uint32_t v_lane_off(int lane) {
   const int i = lane & 15, qd = lane >> 4;
   const int rsub = i >> 2;                         // row inside the 4-row block == row & 3
   const int x = ((qd & 1) << 1) | ((i & 3) >> 1);  // 16-byte chunk inside the 64-byte column block
-  return (uint32_t)((4 * (qd >> 1) + rsub) * ROW_BYTES + (rsub << 6) + (x << 4) + ((i & 1) << 3));
+  return (uint32_t)((4 * (qd >> 1) + rsub) * Geo<HD>::ROW + (Geo<HD>::v_swizzle(rsub) << 4) + (x << 4) + ((i & 1) << 3));
 }
+template <int HD = D>
 __device__ __forceinline__ bf16x8 read_v_frag(const char* v_lds, uint32_t lane_off, int j, int db) {
-  const char* p0 = v_lds + (lane_off ^ (uint32_t)(db << 6)) + j * (16 * ROW_BYTES);
+  const char* p0 = v_lds + (lane_off ^ (uint32_t)(db << 6)) + j * (16 * Geo<HD>::ROW);
   const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_ptr)p0);
-  const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_ptr)(p0 + 8 * ROW_BYTES));
+  const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_ptr)(p0 + 8 * Geo<HD>::ROW));
   return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
@@ -208,34 +244,41 @@ __device__ __forceinline__ void wait_q(const bf16x8 (&qf)[MB][8]) {
     for (int ks = 0; ks < 8; ++ks) asm volatile("" ::"v"(qf[mb][ks]));
 }
 
-// One K/V tile of KB*32 keys against MB*32 query rows: S^T, online softmax, O^T update.
-template <int MB>
-__device__ __forceinline__ void store_block(const Ctx& c, const DkEntry& e, const DkItem& it, int g, int row_local0,
-                                            int lane, int db, const f32x16 (&o)[MB], const float (&ltot)[MB]) {
-  const int h = lane >> 5;
-  const int gmask = (1 << c.gshift) - 1;
+// A pair of fp32 weights as hi + lo, both bf16: hi is the upper half of the bits (truncated), lo the rest rounded to
+// bf16.  What is lost is below 2^-16 of the weight.  Written to pair w of the two B-operand fragments.
+__device__ __forceinline__ void split_pair(float p0, float p1, bf16x8& hi, bf16x8& lo, int w) {
+  typedef __attribute__((ext_vector_type(4))) uint32_t words;
+  const uint32_t u0 = __float_as_uint(p0), u1 = __float_as_uint(p1);
+  words h = __builtin_bit_cast(words, hi);
+  h[w] = __builtin_amdgcn_perm(u1, u0, 0x07060302);  // upper halves of (p0, p1)
+  hi = __builtin_bit_cast(bf16x8, h);
+  lo[2 * w] = (__bf16)(p0 - __uint_as_float(u0 & 0xffff0000u));
+  lo[2 * w + 1] = (__bf16)(p1 - __uint_as_float(u1 & 0xffff0000u));
+}
+
+// Stores one row's results of a lane: quad i holds depths depth0 + 8 i .. + 3 (the order of the 32x32 accumulators,
+// depth0 including the half-wave's 4 h), as fp32 partials or, divided by the weight sum, as bf16 output.
+// rl: the row inside the item (rows past its end are skipped).
+template <int HD, bool ANYG, int NQ>
+__device__ __forceinline__ void store_quads(const Ctx& c, const DkEntry& e, const DkItem& it, int g, int rl, int depth0,
+                                            const f32x4 (&o)[NQ], float ltot) {
+  if (rl >= it.nrows) return;
+  if (it.part_row0 >= 0) {
+    float* p = c.parts + ((int64_t)(it.part_row0 + rl) * c.n_kv_heads + g) * HD + depth0;
 #pragma unroll
-  for (int mb = 0; mb < MB; ++mb) {
-    const int rl = row_local0 + mb * 32 + (lane & 31);
-    if (rl >= it.nrows) continue;
-    if (it.part_row0 >= 0) {
-      float* p = c.parts + ((int64_t)(it.part_row0 + rl) * c.n_kv_heads + g) * D + db * 32 + 4 * h;
+    for (int i = 0; i < NQ; ++i) *(f32x4*)(p + 8 * i) = o[i];
+  } else {
+    const int row = it.row0 + rl;
+    const int t = row_token<ANYG>(c, row);
+    const int head = g * c.group + row_head<ANYG>(c, row, t);
+    const float inv = 1.f / ltot;
+    __bf16* dst = c.out + ((int64_t)(e.tok0 + t) * c.n_q_heads + head) * HD + depth0;
 #pragma unroll
-      for (int r4 = 0; r4 < 4; ++r4)
-        *(f32x4*)(p + 8 * r4) = f32x4{o[mb][4 * r4], o[mb][4 * r4 + 1], o[mb][4 * r4 + 2], o[mb][4 * r4 + 3]};
-    } else {
-      const int row = it.row0 + rl;
-      const int tok = e.tok0 + (row >> c.gshift);
-      const int head = (g << c.gshift) + (row & gmask);
-      const float inv = 1.f / ltot[mb];
-      __bf16* dst = c.out + ((int64_t)tok * c.n_q_heads + head) * D + db * 32 + 4 * h;
+    for (int i = 0; i < NQ; ++i) {
+      bf16x4 v;
 #pragma unroll
-      for (int r4 = 0; r4 < 4; ++r4) {
-        bf16x4 v;
-#pragma unroll
-        for (int t = 0; t < 4; ++t) v[t] = (__bf16)(o[mb][4 * r4 + t] * inv);
-        *(bf16x4*)(dst + 8 * r4) = v;
-      }
+      for (int u = 0; u < 4; ++u) v[u] = (__bf16)(o[i][u] * inv);
+      *(bf16x4*)(dst + 8 * i) = v;
     }
   }
 }
@@ -315,11 +358,10 @@ __device__ __forceinline__ void store_rows_staged(const Ctx& c, const DkEntry& e
 }
 
 // Running maximum and weight sum of each row (partials) or the row's log-sum-exp (final output).
-template <int MB>
+template <int MB, bool ANYG = false>
 __device__ __forceinline__ void store_ml(const Ctx& c, const DkEntry& e, const DkItem& it, int g, int row_local0,
                                          int lane, const float (&m)[MB], const float (&ltot)[MB]) {
   if (lane >= 32) return;
-  const int gmask = (1 << c.gshift) - 1;
 #pragma unroll
   for (int mb = 0; mb < MB; ++mb) {
     const int rl = row_local0 + mb * 32 + lane;
@@ -329,9 +371,9 @@ __device__ __forceinline__ void store_ml(const Ctx& c, const DkEntry& e, const D
       *(float2*)p = make_float2(m[mb], ltot[mb]);
     } else if (c.lse) {
       const int row = it.row0 + rl;
-      const int tok = e.tok0 + (row >> c.gshift);
-      const int head = (g << c.gshift) + (row & gmask);
-      c.lse[(int64_t)tok * c.n_q_heads + head] = (m[mb] + __builtin_amdgcn_logf(ltot[mb])) * 0.6931471805599453f;
+      const int t = row_token<ANYG>(c, row);
+      const int head = g * c.group + row_head<ANYG>(c, row, t);
+      c.lse[(int64_t)(e.tok0 + t) * c.n_q_heads + head] = (m[mb] + __builtin_amdgcn_logf(ltot[mb])) * 0.6931471805599453f;
     }
   }
 }
@@ -348,31 +390,31 @@ __device__ __forceinline__ void wait_vmcnt() {
 // every workgroup copies an equal run right after its first K/V requests, whose latency covers the copy's.
 // The copy is cut into 16-byte pieces, piece p = (token, K or V, KV head, position in the row); a thread has four
 // loads in flight before its first store.
-template <bool INLINE>
+template <bool INLINE, int ROW = ROW_BYTES, int THREADS = 256>
 __device__ __forceinline__ void scatter_new_rows(const Ctx& c) {
   if (c.n_scatter <= 0) return;
   const int32_t* cells = resolve_desc<INLINE>(c.cells);
-  const int vecs = c.n_kv_heads * (ROW_BYTES / 16);  // pieces of one token's K (as many for V)
+  const int vecs = c.n_kv_heads * (ROW / 16);  // pieces of one token's K (as many for V)
   const int total = c.n_scatter * 2 * vecs;
-  const int per = ((total + (int)gridDim.x - 1) / (int)gridDim.x + 255) & ~255;
+  const int per = ((total + (int)gridDim.x - 1) / (int)gridDim.x + THREADS - 1) / THREADS * THREADS;
   const int begin = min(total, (int)blockIdx.x * per), end = min(total, begin + per);
   const auto locate = [&](int p, const char*& src, char*& dst) {
     p = min(p, end - 1);  // (threads past the end repeat the last piece: same bytes)
     const int t = p / (2 * vecs), r = p - t * (2 * vecs);
     const bool is_v = r >= vecs;
     const int j = is_v ? r - vecs : r;
-    const int g = j / (ROW_BYTES / 16), piece = j % (ROW_BYTES / 16);
+    const int g = j / (ROW / 16), piece = j % (ROW / 16);
     const int64_t cell = cells[t];
-    src = (is_v ? c.v_new : c.k_new) + ((int64_t)t * c.n_kv_heads + g) * ROW_BYTES + piece * 16;
-    dst = const_cast<char*>(is_v ? c.v_arena : c.k_arena) + ((int64_t)g * c.arena_cells + cell) * ROW_BYTES + piece * 16;
+    src = (is_v ? c.v_new : c.k_new) + ((int64_t)t * c.n_kv_heads + g) * ROW + piece * 16;
+    dst = const_cast<char*>(is_v ? c.v_arena : c.k_arena) + ((int64_t)g * c.arena_cells + cell) * ROW + piece * 16;
   };
-  for (int base = begin + (int)threadIdx.x; base < end; base += 4 * 256) {
+  for (int base = begin + (int)threadIdx.x; base < end; base += 4 * THREADS) {
     const char *s0, *s1, *s2, *s3;
     char *d0, *d1, *d2, *d3;
     locate(base, s0, d0);
-    locate(base + 256, s1, d1);
-    locate(base + 512, s2, d2);
-    locate(base + 768, s3, d3);
+    locate(base + THREADS, s1, d1);
+    locate(base + 2 * THREADS, s2, d2);
+    locate(base + 3 * THREADS, s3, d3);
     const uint4 v0 = *(const uint4*)s0, v1 = *(const uint4*)s1, v2 = *(const uint4*)s2, v3 = *(const uint4*)s3;
     *(uint4*)d0 = v0;
     *(uint4*)d1 = v1;
@@ -401,6 +443,8 @@ inline Ctx make_ctx(const AttendArgs& a, const DkItem* items) {
   int group = a.arena.n_q_heads / a.arena.n_kv_heads, sh = 0;
   while ((1 << sh) < group) ++sh;
   c.gshift = sh;
+  c.group = group;
+  c.gmagic = group > 1 ? (uint32_t)(((1ull << 32) + group - 1) / group) : 0u;
   c.arena_cells = a.arena.arena_cells;
   c.cells = a.cells;
   c.n_scatter = a.scatter ? a.total_tokens : 0;

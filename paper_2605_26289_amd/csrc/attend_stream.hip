@@ -1,4 +1,4 @@
-// bf16 MFMA delta-prefill attention kernels for gfx950 (head_dim 128).
+// bf16 MFMA delta-prefill attention kernels for gfx950.
 //
 // Both kernels compute, for the packed query rows of one KV head (row r = token r / G, head r % G of
 // the group), the transposed products S^T = K Q^T and O^T = V^T P^T with v_mfma_f32_32x32x16_bf16.
@@ -35,27 +35,44 @@ __device__ unsigned long long g_strace[256][8][12];
 #define DK_STR(seq, ph)
 #endif
 
-template <int MB>
+// HD: head dimension.  GEN: the general form, for everything but 128-wide heads in groups of 2^k <= 16 query heads per
+// KV head -- any group size, and the probabilities enter the second product as a sum of two bf16 (p = hi + lo, about
+// 2^-17 relative), i.e. with what matters of their 32 bits, for twice the PV products: the shapes it serves used to be
+// computed with fp32 probabilities, and next to HBM the extra MFMAs cost little.  Measured: 14 decoding or verifying
+// sessions of 512-4096 tokens, 32 query heads on 8 KV heads of 64, take 27 us here and took most of 1630 us in the
+// scalar kernel.
+// A tile is 8 KiB of K and 8 KiB of V: 32 keys of 256 bytes or 64 of 128.
+template <int HD>
+struct Tile {
+  static constexpr int KB = 128 / HD;  // 32-key blocks per tile
+  static constexpr int KT = 32 * KB;   // keys per tile
+};
+
+template <int MB, int HD>
 struct RowState {
-  f32x16 o[4][MB];  // O^T accumulators: [depth block][row block], unnormalised
+  f32x16 o[Geo<HD>::DB][MB];  // O^T accumulators: [depth block][row block], unnormalised
   float m[MB];      // running maximum of the scaled scores (log2 units), -inf before the first key
   float l[MB];      // this lane's share of the weight sum (the other half-wave holds the rest)
 };
 
-// All MFMA operand fragments of one 32-key tile, read out of its LDS stage in one go: once they are in
+// All MFMA operand fragments of one tile, read out of its LDS stage in one go: once they are in
 // registers the stage can take the next HBM load while the tile is still being computed.
+template <int HD>
 struct TileFrags {
-  bf16x8 k[8];     // [depth step]
-  bf16x8 v[2][4];  // [key step][depth block]
+  bf16x8 k[Tile<HD>::KB][Geo<HD>::KS];      // [key block][depth step]
+  bf16x8 v[2 * Tile<HD>::KB][Geo<HD>::DB];  // [key step][depth block]
 };
-__device__ __forceinline__ void read_frags(const char* k_lds, const char* v_lds, int lane, TileFrags& f) {
-  const uint32_t koff = k_lane_off(lane), voff = v_lane_off(lane);
+template <int HD>
+__device__ __forceinline__ void read_frags(const char* k_lds, const char* v_lds, int lane, TileFrags<HD>& f) {
+  const uint32_t koff = k_lane_off<HD>(lane), voff = v_lane_off<HD>(lane);
 #pragma unroll
-  for (int ks = 0; ks < 8; ++ks) f.k[ks] = read_k_frag(k_lds, koff, 0, ks);
+  for (int kb = 0; kb < Tile<HD>::KB; ++kb)
 #pragma unroll
-  for (int j = 0; j < 2; ++j)
+    for (int ks = 0; ks < Geo<HD>::KS; ++ks) f.k[kb][ks] = read_k_frag<HD>(k_lds, koff, kb, ks);
 #pragma unroll
-    for (int db = 0; db < 4; ++db) f.v[j][db] = read_v_frag(v_lds, voff, j, db);
+  for (int j = 0; j < 2 * Tile<HD>::KB; ++j)
+#pragma unroll
+    for (int db = 0; db < Geo<HD>::DB; ++db) f.v[j][db] = read_v_frag<HD>(v_lds, voff, j, db);
 }
 
 constexpr float STREAM_RESCALE_SLACK = 8.f;  // log2 units, as in the tile kernel
@@ -87,10 +104,10 @@ __device__ __forceinline__ float scale_acc(float o, float alpha) {
 // row blocks the unit's Q fragments stay in registers for the whole unit; with three (96 registers next to 192
 // of accumulators) they would not fit, so each tile reads them from the Q area in LDS again (24 ds_read_b128 per
 // tile next to the tile's own 16: LDS bandwidth is idle here).
-template <int MB>
+template <int MB, int HD>
 struct QFrags {
   static constexpr bool IN_LDS = MB > 2;
-  bf16x8 r[IN_LDS ? 1 : MB][8];
+  bf16x8 r[IN_LDS ? 1 : MB][Geo<HD>::KS];
   const char* q_lds;
   uint32_t koff;
   __device__ __forceinline__ void load() {
@@ -98,55 +115,69 @@ struct QFrags {
 #pragma unroll
       for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks) r[mb][ks] = read_k_frag(q_lds, koff, mb, ks);
+        for (int ks = 0; ks < Geo<HD>::KS; ++ks) r[mb][ks] = read_k_frag<HD>(q_lds, koff, mb, ks);
     }
   }
   __device__ __forceinline__ bf16x8 get(int mb, int ks) const {
-    if constexpr (IN_LDS) return read_k_frag(q_lds, koff, mb, ks);
+    if constexpr (IN_LDS) return read_k_frag<HD>(q_lds, koff, mb, ks);
     else return r[mb][ks];
   }
 };
 
-// One 32-key tile against MB*32 query rows, operands in registers: S^T, online softmax, O^T update.
-template <int MB>
-__device__ __forceinline__ void compute_tile(const TileFrags& f, const QFrags<MB>& qf, RowState<MB>& st,
+// One tile against MB*32 query rows, operands in registers: S^T, online softmax, O^T update.
+template <int MB, int HD, bool GEN>
+__device__ __forceinline__ void compute_tile(const TileFrags<HD>& f, const QFrags<MB, HD>& qf, RowState<MB, HD>& st,
                                              const int (&limit)[MB], float c, int lane, int cnt, int pos,
                                              bool need_mask) {
+  constexpr int KB = Tile<HD>::KB, KS = Geo<HD>::KS, DB = Geo<HD>::DB;
   const int h = lane >> 5;
-  bf16x8 pf[MB][2];
-  f32x16 s[MB];
+  bf16x8 pf[MB][2 * KB];
+  bf16x8 pl[GEN ? MB : 1][GEN ? 2 * KB : 1];
+  f32x16 s[KB][MB];
 #pragma unroll
-  for (int mb = 0; mb < MB; ++mb)
+  for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) s[mb][r] = 0.f;
+    for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-  for (int ks = 0; ks < 8; ++ks)
+      for (int r = 0; r < 16; ++r) s[kb][mb][r] = 0.f;
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb) s[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.k[ks], qf.get(mb, ks), s[mb], 0, 0, 0);
+  for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) {
+      const bf16x8 q = qf.get(mb, ks);
+#pragma unroll
+      for (int kb = 0; kb < KB; ++kb) s[kb][mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.k[kb][ks], q, s[kb][mb], 0, 0, 0);
+    }
 
   if (need_mask) {
-    // accumulator r is key 8*(r/4) + 4h + r%4 of the tile
+    // accumulator r of key block kb is key 32 kb + 8*(r/4) + 4h + r%4 of the tile
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) {
       const int lim = min(cnt - 1, limit[mb] - pos);
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int key = 8 * (r >> 2) + 4 * h + (r & 3);
-        if (key > lim) s[mb][r] = -INFINITY;
-      }
+      for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int key = 32 * kb + 8 * (r >> 2) + 4 * h + (r & 3);
+          if (key > lim) s[kb][mb][r] = -INFINITY;
+        }
     }
   }
 
   // row maxima; the reference maximum of a row is only raised (and O, l rescaled) when the tile outgrows
-  // it by more than the slack, so after the first tiles the 128 multiplies on O are rare
+  // it by more than the slack, so after the first tiles the multiplies on O are rare
   float mx[MB];
   bool grow = false;
 #pragma unroll
   for (int mb = 0; mb < MB; ++mb) {
-    float v = stream_max3(s[mb][0], s[mb][1], s[mb][2]);
+    float v = s[0][mb][15];
 #pragma unroll
-    for (int r = 3; r < 15; r += 2) v = stream_max3(v, s[mb][r], s[mb][r + 1]);
-    v = fmaxf(v, s[mb][15]);
+    for (int kb = 0; kb < KB; ++kb) {
+      if (kb > 0) v = fmaxf(v, s[kb][mb][15]);
+#pragma unroll
+      for (int r = 1; r < 15; r += 2) v = stream_max3(v, s[kb][mb][r], s[kb][mb][r + 1]);
+      v = fmaxf(v, s[kb][mb][0]);
+    }
     v = fmaxf(v, __shfl_xor(v, 32));
     mx[mb] = v * c;
     grow |= mx[mb] > st.m[mb] + STREAM_RESCALE_SLACK;
@@ -160,7 +191,7 @@ __device__ __forceinline__ void compute_tile(const TileFrags& f, const QFrags<MB
       st.m[mb] = mn;
       st.l[mb] *= alpha;
 #pragma unroll
-      for (int db = 0; db < 4; ++db)
+      for (int db = 0; db < DB; ++db)
 #pragma unroll
         for (int r = 0; r < 16; ++r) st.o[db][mb][r] = scale_acc(st.o[db][mb][r], alpha);
     }
@@ -171,25 +202,31 @@ __device__ __forceinline__ void compute_tile(const TileFrags& f, const QFrags<MB
     const float ms = (st.m[mb] == -INFINITY) ? 0.f : st.m[mb];
     float rs[2] = {0.f, 0.f};
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < 2 * KB; ++j)
 #pragma unroll
       for (int w = 0; w < 4; ++w) {
-        const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[mb][8 * j + 2 * w], c, -ms));
-        const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[mb][8 * j + 2 * w + 1], c, -ms));
+        const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[j >> 1][mb][8 * (j & 1) + 2 * w], c, -ms));
+        const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[j >> 1][mb][8 * (j & 1) + 2 * w + 1], c, -ms));
         rs[(j * 4 + w) & 1] += p0 + p1;  // (no v_dot2 here: the dot instructions queue behind the MFMAs)
-        pf[mb][j][2 * w] = (__bf16)p0;
-        pf[mb][j][2 * w + 1] = (__bf16)p1;
+        if constexpr (GEN) {
+          split_pair(p0, p1, pf[mb][j], pl[mb][j], w);
+        } else {
+          pf[mb][j][2 * w] = (__bf16)p0;
+          pf[mb][j][2 * w + 1] = (__bf16)p1;
+        }
       }
     st.l[mb] += rs[0] + rs[1];
   }
 
 #pragma unroll
-  for (int j = 0; j < 2; ++j)
+  for (int j = 0; j < 2 * KB; ++j)
 #pragma unroll
-    for (int db = 0; db < 4; ++db)
+    for (int db = 0; db < DB; ++db)
 #pragma unroll
-      for (int mb = 0; mb < MB; ++mb)
+      for (int mb = 0; mb < MB; ++mb) {
         st.o[db][mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.v[j][db], pf[mb][j], st.o[db][mb], 0, 0, 0);
+        if constexpr (GEN) st.o[db][mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.v[j][db], pl[mb][j], st.o[db][mb], 0, 0, 0);
+      }
 }
 
 // Accumulator r of depth block db is depth db*32 + 8*(r/4) + 4h + r%4: four consecutive depths per r/4.
@@ -219,8 +256,8 @@ __device__ __forceinline__ void compute_tile(const TileFrags& f, const QFrags<MB
 // (2 KiB); then the Q rows of the unit, laid out and swizzled like a K tile of MB * 32 rows; then the next
 // unit's descriptors as published by wavefront 0.
 // ------------------------------------------------------------------------------------------------
-constexpr int STREAM_KT = 32;
-constexpr int STREAM_STAGE_BYTES = 2 * STREAM_KT * ROW_BYTES;  // 16 KiB
+constexpr int STREAM_TILE_BYTES = 8192;                         // K or V of one tile
+constexpr int STREAM_STAGE_BYTES = 2 * STREAM_TILE_BYTES;      // 16 KiB
 constexpr int STREAM_WAVE_BYTES = 2 * STREAM_STAGE_BYTES;      // 32 KiB
 constexpr int STREAM_ML_OFFSET = 4 * STREAM_WAVE_BYTES;        // after the stages
 constexpr int STREAM_MAX_MB = 3;                               // row blocks of the widest instantiation
@@ -230,19 +267,19 @@ constexpr int STREAM_NEXT_OFFSET = STREAM_Q_OFFSET + STREAM_MAX_MB * 32 * ROW_BY
 constexpr int STREAM_LDS_BYTES = STREAM_NEXT_OFFSET + 128;
 static_assert(STREAM_LDS_BYTES <= 160 * 1024, "one workgroup per compute unit: all of its LDS, no more");
 
-// One wavefront moves 4 query rows (1 KiB) HBM -> LDS into the Q area: packed row `blk * 4 + l / 16` of the
-// unit (clamped to its last row), chunk slots swizzled as for a K tile so that read_k_frag serves as the
+// One wavefront moves 1 KiB of query rows HBM -> LDS into the Q area: packed row `blk * ROWS_PER_KIB + l / CHUNKS` of
+// the unit (clamped to its last row), chunk slots swizzled as for a K tile so that read_k_frag serves as the
 // reader of Q's B-operand fragments.  Every wavefront requests all rows itself: each only depends on its own
 // requests, and the four write the same bytes.
-__device__ __forceinline__ void load_q_rows4(const Ctx& c, const char* q_tok0, int g, int row0, int last_row,
-                                             char* q_lds, int blk, int lane) {
-  const int row = blk * 4 + (lane >> 4);
-  const int slot = lane & 15;
-  const int chunk = slot ^ (row & 15);
+template <int HD, bool GEN>
+__device__ __forceinline__ void load_q_kib(const Ctx& c, const char* q_tok0, int g, int row0, int last_row,
+                                           char* q_lds, int blk, int lane) {
+  typedef Geo<HD> G;
+  const int row = blk * G::ROWS_PER_KIB + lane / G::CHUNKS;
+  const int chunk = (lane % G::CHUNKS) ^ G::k_swizzle(row);
   const int arow = min(row0 + row, last_row);
-  const int gmask = (1 << c.gshift) - 1;
-  const uint32_t voff =
-      (uint32_t)(((arow >> c.gshift) * c.n_q_heads + (g << c.gshift) + (arow & gmask)) * ROW_BYTES + chunk * 16);
+  const int tok = row_token<GEN>(c, arow);
+  const uint32_t voff = (uint32_t)((tok * c.n_q_heads + g * c.group + row_head<GEN>(c, arow, tok)) * G::ROW + chunk * 16);
   const uint32_t lds_addr = (uint32_t)(uintptr_t)(lds_void_ptr)(q_lds + blk * 1024);
   asm volatile(
       "s_mov_b32 m0, %0\n\t"
@@ -266,7 +303,7 @@ __device__ __forceinline__ void lds_barrier() {
 // too little in flight to stream it well).
 // INLINE: the descriptors arrive inside the kernel arguments (first argument) and the descriptor pointers are byte
 // offsets into them; otherwise they point into the uploaded workspace.
-template <int MB, bool INLINE>
+template <int MB, int HD, bool GEN, bool INLINE>
 __global__ __launch_bounds__(256, 1) void attend_stream_kernel(BlobArg<INLINE> blob, Ctx c, const int32_t* links,
                                                                int n_chains, int32_t* queue, int n_units) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
@@ -281,7 +318,8 @@ __global__ __launch_bounds__(256, 1) void attend_stream_kernel(BlobArg<INLINE> b
   float* ml = (float*)(smem + STREAM_ML_OFFSET);  // [wave][row 0..95][m, l]
   char* q_lds = smem + STREAM_Q_OFFSET;
   int32_t* next_lds = (int32_t*)(smem + STREAM_NEXT_OFFSET);  // [0] unit, [4..11] its DkItem, [12..19] its DkEntry
-  const uint32_t koff = k_lane_off(lane);
+  constexpr int KT = Tile<HD>::KT, DB = Geo<HD>::DB;
+  const uint32_t koff = k_lane_off<HD>(lane);
   const bool queued = !INLINE && queue != nullptr;  // units are drawn from the queue (else: the planner's chains)
   int trace_seq = 0;
   (void)trace_seq;
@@ -291,35 +329,35 @@ __global__ __launch_bounds__(256, 1) void attend_stream_kernel(BlobArg<INLINE> b
   DkItem it = load_desc(c.items, unit / c.n_kv_heads);
   DkEntry e = load_desc(c.entries, it.entry);
   int g = unit % c.n_kv_heads;
-  KvCursor cur{c.segs, 0, 0, 0, 0};
+  KvCursor<HD> cur{c.segs, 0, 0, 0, 0};
   KvTile t0, t1, t2;  // being computed, next, the one after
   bool have0 = false, have1 = false;
 
   auto issue = [&](const KvTile& t, int stage) {
     char* kl = my + stage * STREAM_STAGE_BYTES;
-    char* vl = kl + STREAM_KT * ROW_BYTES;
+    char* vl = kl + STREAM_TILE_BYTES;
 #pragma unroll
-    for (int b = 0; b < 8; ++b) load_rows4<false>(t.k, t.stride, t.cnt, kl, b, lane);
+    for (int b = 0; b < 8; ++b) load_kib<false, HD>(t.k, t.stride, t.cnt, kl, b, lane);
 #pragma unroll
-    for (int b = 0; b < 8; ++b) load_rows4<true>(t.v, t.stride, t.cnt, vl, b, lane);
+    for (int b = 0; b < 8; ++b) load_kib<true, HD>(t.v, t.stride, t.cnt, vl, b, lane);
   };
   // this wavefront's quarter of the unit's keys: cursor, first tile requested into stage 0
   auto open_keys = [&](const DkItem& u, const DkEntry& ue, int ug) {
-    const int ntile = (u.kv_hi - u.kv_lo + STREAM_KT - 1) / STREAM_KT;
-    const int per = (ntile + 3) / 4 * STREAM_KT;
+    const int ntile = (u.kv_hi - u.kv_lo + KT - 1) / KT;
+    const int per = (ntile + 3) / 4 * KT;
     const int lo = min(u.kv_hi, u.kv_lo + wave * per);
     const int hi = min(u.kv_hi, lo + per);
-    cur = KvCursor{c.segs, ue.seg_begin, ue.seg_end, lo, hi};
-    have0 = cur.next(c, ug, STREAM_KT, t0);
+    cur = KvCursor<HD>{c.segs, ue.seg_begin, ue.seg_end, lo, hi};
+    have0 = cur.next(c, ug, KT, t0);
     if (have0) issue(t0, 0);
   };
   auto open_q = [&](const DkItem& u, const DkEntry& ue, int ug) {
-    const char* q_tok0 = (const char*)c.q + (int64_t)ue.tok0 * c.n_q_heads * ROW_BYTES;
+    const char* q_tok0 = (const char*)c.q + (int64_t)ue.tok0 * c.n_q_heads * Geo<HD>::ROW;
 #pragma unroll
-    for (int b = 0; b < MB * 8; ++b) load_q_rows4(c, q_tok0, ug, u.row0, u.row0 + u.nrows - 1, q_lds, b, lane);
+    for (int b = 0; b < MB * 32 / Geo<HD>::ROWS_PER_KIB; ++b) load_q_kib<HD, GEN>(c, q_tok0, ug, u.row0, u.row0 + u.nrows - 1, q_lds, b, lane);
   };
   auto open_second = [&](int ug) {
-    have1 = have0 && cur.next(c, ug, STREAM_KT, t1);
+    have1 = have0 && cur.next(c, ug, KT, t1);
     if (have1) issue(t1, 1);
   };
 
@@ -329,7 +367,7 @@ __global__ __launch_bounds__(256, 1) void attend_stream_kernel(BlobArg<INLINE> b
   if (wave == 0) DK_STR(0, 10);  // (kernel entry, a few scalar loads late)
   // small append-and-attend calls: this workgroup's share of the new rows goes into the arena now, under the
   // latency of the first unit's requests
-  scatter_new_rows<INLINE>(c);
+  scatter_new_rows<INLINE, Geo<HD>::ROW>(c);
 
   while (true) {
     // The descriptors of the next unit are fetched while this one is being streamed, so that a unit change
@@ -354,25 +392,25 @@ __global__ __launch_bounds__(256, 1) void attend_stream_kernel(BlobArg<INLINE> b
       drew = true;
     };
     const int last_row = it.row0 + it.nrows - 1;
-    const int min_limit = e.n + (it.row0 >> c.gshift);
+    const int min_limit = e.n + row_token<GEN>(c, it.row0);
 
-    RowState<MB> st;
+    RowState<MB, HD> st;
     int limit[MB];
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) {
       st.m[mb] = -INFINITY;
       st.l[mb] = 0.f;
 #pragma unroll
-      for (int db = 0; db < 4; ++db)
+      for (int db = 0; db < DB; ++db)
 #pragma unroll
         for (int r = 0; r < 16; ++r) st.o[db][mb][r] = 0.f;
-      limit[mb] = e.n + (min(it.row0 + mb * 32 + (lane & 31), last_row) >> c.gshift);
+      limit[mb] = e.n + row_token<GEN>(c, min(it.row0 + mb * 32 + (lane & 31), last_row));
     }
 
     // Everything requested before the second tile has arrived: the unit's Q rows and its first tile.
     if (wave == 0) DK_STR(trace_seq, 0);
     if (have1) wait_vmcnt<16>(); else wait_vmcnt<0>();
-    QFrags<MB> qf;
+    QFrags<MB, HD> qf;
     qf.q_lds = q_lds;
     qf.koff = koff;
     qf.load();
@@ -383,16 +421,16 @@ __global__ __launch_bounds__(256, 1) void attend_stream_kernel(BlobArg<INLINE> b
     // wavefront) are in flight while one is being computed -- with only the other stage loading, HBM
     // latency would not be covered.
     int stage = 0;
-    TileFrags fr;
+    TileFrags<HD> fr;
     // (wavefront 0's share of the unit is at least this many tiles: ragged segment ends only add some)
-    const int my_tiles = ((it.kv_hi - it.kv_lo + STREAM_KT - 1) / STREAM_KT + 3) / 4;
+    const int my_tiles = ((it.kv_hi - it.kv_lo + KT - 1) / KT + 3) / 4;
     const int draw_at = my_tiles / 2;
     int iter = 0;
     while (have0) {
       if (have1) wait_vmcnt<16>(); else wait_vmcnt<0>();
       const char* kl = my + stage * STREAM_STAGE_BYTES;
-      read_frags(kl, kl + STREAM_KT * ROW_BYTES, lane, fr);
-      const bool have2 = have1 && cur.next(c, g, STREAM_KT, t2);
+      read_frags<HD>(kl, kl + STREAM_TILE_BYTES, lane, fr);
+      const bool have2 = have1 && cur.next(c, g, KT, t2);
       if (drawer && !drew && iter >= draw_at) draw();
       ++iter;
       if (have2) {
@@ -400,8 +438,8 @@ __global__ __launch_bounds__(256, 1) void attend_stream_kernel(BlobArg<INLINE> b
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         issue(t2, stage);
       }
-      const bool need_mask = t0.cnt < STREAM_KT || t0.pos + STREAM_KT - 1 > min_limit;
-      compute_tile<MB>(fr, qf, st, limit, c.c, lane, t0.cnt, t0.pos, need_mask);
+      const bool need_mask = t0.cnt < KT || t0.pos + KT - 1 > min_limit;
+      compute_tile<MB, HD, GEN>(fr, qf, st, limit, c.c, lane, t0.cnt, t0.pos, need_mask);
       t0 = t1;
       t1 = t2;
       have0 = have1;
@@ -445,13 +483,15 @@ __global__ __launch_bounds__(256, 1) void attend_stream_kernel(BlobArg<INLINE> b
       }
     }
     int next_g = 0;
-    const int db = wave;
+    // the four wavefronts share out the depth blocks: a whole one each (HD 128) or half of one (HD 64)
+    constexpr int NACC = DB * 4;  // accumulators of a row block per wavefront after the merge
+    const int db = wave * DB / 4, r0 = wave * NACC % 16;
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) {
       // row block mb of every wavefront's O goes through the wavefronts' second stages: [db][r][lane]
       float* mine = (float*)(my + STREAM_STAGE_BYTES);
 #pragma unroll
-      for (int d4 = 0; d4 < 4; ++d4)
+      for (int d4 = 0; d4 < DB; ++d4)
 #pragma unroll
         for (int r = 0; r < 16; ++r) mine[(d4 * 16 + r) * 64 + lane] = st.o[d4][mb][r];
       lds_barrier();
@@ -491,23 +531,23 @@ __global__ __launch_bounds__(256, 1) void attend_stream_kernel(BlobArg<INLINE> b
       }
       const float ms = (mx == -INFINITY) ? 0.f : mx;
       float lsum = 0.f;
-      f32x16 acc[1];
+      f32x4 acc[NACC / 4];
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[0][r] = 0.f;
+      for (int i = 0; i < NACC / 4; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int w = 0; w < 4; ++w) {
         const float f = __builtin_amdgcn_exp2f(mw[w] - ms);
         lsum += f * lw[w];
         const float* theirs = (const float*)(smem + w * STREAM_WAVE_BYTES + STREAM_STAGE_BYTES);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[0][r] += f * theirs[(db * 16 + r) * 64 + lane];
+        for (int r = 0; r < NACC; ++r) acc[r >> 2][r & 3] += f * theirs[(db * 16 + r0 + r) * 64 + lane];
       }
       // the buffer has been read everywhere: the next row block, or the next unit's second tile, may overwrite it
       if (mb + 1 < MB || next_unit >= 0) lds_barrier();
       // (one row block's result at a time: the merged rows of all blocks together would not fit the registers)
       const float mm[1] = {mx}, ll[1] = {lsum};
-      store_block<1>(c, e, it, g, mb * 32, lane, db, acc, ll);
-      if (wave == 0) store_ml<1>(c, e, it, g, mb * 32, lane, mm, ll);
+      store_quads<HD, GEN>(c, e, it, g, row, db * 32 + 2 * r0 + 4 * (lane >> 5), acc, lsum);
+      if (wave == 0) store_ml<1, GEN>(c, e, it, g, mb * 32, lane, mm, ll);
     }
     // (after the stores: the wait that opens the next unit lets exactly this request stay in flight)
     if (next_unit >= 0) open_second(next_g);
@@ -524,40 +564,56 @@ __global__ __launch_bounds__(256, 1) void attend_stream_kernel(BlobArg<INLINE> b
   }
 }
 
+
+namespace {
+
+template <int MB, int HD, bool GEN, bool INLINE>
+hipError_t launch_one(const BlobArg<INLINE>& blob, const Ctx& c, const int32_t* links, int32_t n_chains, int32_t* queue,
+                      int32_t n_units, hipStream_t stream) {
+  // once per process and instantiation, whatever thread or pool gets here first
+  static std::once_flag once;
+  static hipError_t status = hipSuccess;
+  std::call_once(once, [] {
+    status = hipFuncSetAttribute((const void*)attend_stream_kernel<MB, HD, GEN, INLINE>,
+                                 hipFuncAttributeMaxDynamicSharedMemorySize, STREAM_LDS_BYTES);
+  });
+  if (status != hipSuccess) return status;
+  attend_stream_kernel<MB, HD, GEN, INLINE>
+      <<<dim3((unsigned)n_chains), 256, STREAM_LDS_BYTES, stream>>>(blob, c, links, n_chains, queue, n_units);
+  return hipGetLastError();
+}
+
+template <int HD, bool GEN, bool INLINE>
+hipError_t launch_rows(int32_t max_rows, const BlobArg<INLINE>& blob, const Ctx& c, const int32_t* links,
+                       int32_t n_chains, int32_t* queue, int32_t n_units, hipStream_t stream) {
+  if (max_rows <= 32) return launch_one<1, HD, GEN, INLINE>(blob, c, links, n_chains, queue, n_units, stream);
+  if (max_rows <= 64) return launch_one<2, HD, GEN, INLINE>(blob, c, links, n_chains, queue, n_units, stream);
+  return launch_one<3, HD, GEN, INLINE>(blob, c, links, n_chains, queue, n_units, stream);
+}
+
+template <bool INLINE>
+hipError_t launch_shape(const AttendArgs& a, int32_t max_rows, const BlobArg<INLINE>& blob, const Ctx& c,
+                        const int32_t* links, int32_t n_chains, int32_t* queue, int32_t n_units, hipStream_t stream) {
+  if (a.arena.head_dim == 64) return launch_rows<64, true, INLINE>(max_rows, blob, c, links, n_chains, queue, n_units, stream);
+  if (a.general) return launch_rows<128, true, INLINE>(max_rows, blob, c, links, n_chains, queue, n_units, stream);
+  return launch_rows<128, false, INLINE>(max_rows, blob, c, links, n_chains, queue, n_units, stream);
+}
+
+}  // namespace
+
 }  // namespace mfma
 
 hipError_t launch_attend_stream(const AttendArgs& a, const DkItem* items, const int32_t* links, int32_t n_chains,
                                 int32_t max_rows, int32_t* queue, int32_t n_units, hipStream_t stream) {
   using namespace mfma;
   if (n_chains <= 0) return hipSuccess;
-  if (a.arena.head_dim != D || a.arena.dtype != 1 || max_rows > STREAM_MAX_MB * 32) return hipErrorInvalidValue;
+  if (a.arena.dtype != 1 || max_rows > STREAM_MAX_MB * 32) return hipErrorInvalidValue;
+  if (a.arena.head_dim != 128 && !(a.arena.head_dim == 64 && a.general)) return hipErrorInvalidValue;
   if (queue && a.inline_blob) return hipErrorInvalidValue;  // the queue's counter needs device memory
-  // once per process, whatever thread or pool gets here first
-  static std::once_flag attr_once;
-  static hipError_t attr_status = hipSuccess;
-  std::call_once(attr_once, [] {
-    const void* kernels[6] = {(const void*)attend_stream_kernel<1, false>, (const void*)attend_stream_kernel<1, true>,
-                              (const void*)attend_stream_kernel<2, false>, (const void*)attend_stream_kernel<2, true>,
-                              (const void*)attend_stream_kernel<3, false>, (const void*)attend_stream_kernel<3, true>};
-    for (const void* k : kernels)
-      if (attr_status == hipSuccess)
-        attr_status = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, STREAM_LDS_BYTES);
-  });
-  if (attr_status != hipSuccess) return attr_status;
   const Ctx c = make_ctx(a, items);
-  const dim3 grid((unsigned)n_chains);
-  if (a.inline_blob) {
-    BlobArg<true> blob{*a.inline_blob};
-    if (max_rows <= 32) attend_stream_kernel<1, true><<<grid, 256, STREAM_LDS_BYTES, stream>>>(blob, c, links, n_chains, queue, n_units);
-    else if (max_rows <= 64) attend_stream_kernel<2, true><<<grid, 256, STREAM_LDS_BYTES, stream>>>(blob, c, links, n_chains, queue, n_units);
-    else attend_stream_kernel<3, true><<<grid, 256, STREAM_LDS_BYTES, stream>>>(blob, c, links, n_chains, queue, n_units);
-  } else {
-    const BlobArg<false> none{0};
-    if (max_rows <= 32) attend_stream_kernel<1, false><<<grid, 256, STREAM_LDS_BYTES, stream>>>(none, c, links, n_chains, queue, n_units);
-    else if (max_rows <= 64) attend_stream_kernel<2, false><<<grid, 256, STREAM_LDS_BYTES, stream>>>(none, c, links, n_chains, queue, n_units);
-    else attend_stream_kernel<3, false><<<grid, 256, STREAM_LDS_BYTES, stream>>>(none, c, links, n_chains, queue, n_units);
-  }
-  return hipGetLastError();
+  if (a.inline_blob)
+    return launch_shape<true>(a, max_rows, BlobArg<true>{*a.inline_blob}, c, links, n_chains, queue, n_units, stream);
+  return launch_shape<false>(a, max_rows, BlobArg<false>{0}, c, links, n_chains, queue, n_units, stream);
 }
 
 }  // namespace dk

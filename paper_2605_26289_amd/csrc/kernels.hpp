@@ -57,21 +57,26 @@ struct AttendArgs {
   // blob); the MFMA kernel launched with `scatter` set also writes the rows of k_new / v_new into those cells.
   const int32_t* cells = nullptr;
   bool scatter = false;
+  // The shape takes the general MFMA kernels: 64-wide heads or a group that is no power of two up to 16.
+  bool general = false;
 };
 
 // Scalar reference kernel: one wavefront per (token, query head).  Any supported shape and dtype.
 hipError_t launch_attend_ref(const AttendArgs& a, hipStream_t stream);
-// bf16 MFMA kernels (head_dim 128).
+// bf16 MFMA kernels: the tile kernel takes 128-wide heads in groups of 2^k, the block kernel any other supported shape
+// (items of at most 128 rows), the stream kernel both.
 // One workgroup per (chain, KV head): chain c is items links[c], links[n_chains + that item], ... until a link
 // is negative; every chain holds at least one item.
 hipError_t launch_attend_tile(const AttendArgs& a, const DkItem* items, const int32_t* links, int32_t n_chains,
                               hipStream_t stream);
+hipError_t launch_attend_block(const AttendArgs& a, const DkItem* items, const int32_t* links, int32_t n_chains,
+                               hipStream_t stream);
 // Unit u = item u / n_kv_heads for KV head u % n_kv_heads; n_chains workgroups.
 // queue == nullptr: workgroup w walks the chain links[w], links[n_chains + that unit], ... until a link is negative.
 // queue != nullptr (DEVICE int32, holding n_chains when the kernel starts; not with an inline blob): workgroup w
 // starts with unit w and draws every further unit from the counter (atomic add) until it reaches n_units; the
 // units are expected longest first.  `links` is not read then.
-// max_rows: the largest DkItem::nrows among the items (at most 64).
+// max_rows: the largest DkItem::nrows among the items (at most 96).
 hipError_t launch_attend_stream(const AttendArgs& a, const DkItem* items, const int32_t* links, int32_t n_chains,
                                 int32_t max_rows, int32_t* queue, int32_t n_units, hipStream_t stream);
 // max_rows: the largest DkMerge::nrows among them (sizes the grid).

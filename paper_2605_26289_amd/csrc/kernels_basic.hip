@@ -291,7 +291,8 @@ __global__ __launch_bounds__(256) void attend_merge_kernel(BlobParam<INLINE> blo
                                                            const float* __restrict__ parts_ml, __bf16* __restrict__ out,
                                                            float* __restrict__ lse, int32_t n_q_heads,
                                                            int32_t n_kv_heads) {
-  static_assert(D == 128, "two floats per lane");
+  static_assert(D == 128 || D == 64, "two floats per lane, or one");
+  typedef float vec __attribute__((ext_vector_type(D / 64)));
   (void)blob;
   merges = from_blob<INLINE>(merges);
   entries = from_blob<INLINE>(entries);
@@ -313,15 +314,15 @@ __global__ __launch_bounds__(256) void attend_merge_kernel(BlobParam<INLINE> blo
   for (int i = 0; i < MERGE_ROWS; ++i) {
     live[i] = r0 + i < mg.nrows;
     const int64_t prow = (int64_t)(mg.part_row0 + (live[i] ? r0 + i : r0)) * n_kv_heads + g;
-    p0[i] = parts + prow * D + lane * 2;
+    p0[i] = parts + prow * D + lane * (D / 64);
     ml0[i] = parts_ml + prow * 2;
   }
 
-  float2 acc[MERGE_ROWS];
+  vec acc[MERGE_ROWS];
   float lsum[MERGE_ROWS], mmax[MERGE_ROWS];
 #pragma unroll
   for (int i = 0; i < MERGE_ROWS; ++i) {
-    acc[i] = make_float2(0.f, 0.f);
+    acc[i] = 0.f;
     lsum[i] = 0.f;
     float m = -INFINITY;
     for (int s = lane; s < mg.nsplit; s += 64) m = fmaxf(m, ml0[i][s * srow * 2]);
@@ -347,26 +348,24 @@ __global__ __launch_bounds__(256) void attend_merge_kernel(BlobParam<INLINE> blo
     const int cnt = min(64, mg.nsplit - s0);
     int s = 0;
     for (; s + 2 <= cnt; s += 2) {
-      float2 v0[MERGE_ROWS], v1[MERGE_ROWS];
+      vec v0[MERGE_ROWS], v1[MERGE_ROWS];
 #pragma unroll
       for (int i = 0; i < MERGE_ROWS; ++i) {
-        v0[i] = *(const float2*)(p0[i] + (s0 + s) * stride);
-        v1[i] = *(const float2*)(p0[i] + (s0 + s + 1) * stride);
+        v0[i] = *(const vec*)(p0[i] + (s0 + s) * stride);
+        v1[i] = *(const vec*)(p0[i] + (s0 + s + 1) * stride);
       }
 #pragma unroll
       for (int i = 0; i < MERGE_ROWS; ++i) {
         const float w0 = __shfl(w_mine[i], s), w1 = __shfl(w_mine[i], s + 1);
-        acc[i].x += w0 * v0[i].x + w1 * v1[i].x;
-        acc[i].y += w0 * v0[i].y + w1 * v1[i].y;
+        acc[i] += w0 * v0[i] + w1 * v1[i];
       }
     }
     if (s < cnt) {
 #pragma unroll
       for (int i = 0; i < MERGE_ROWS; ++i) {
-        const float2 v = *(const float2*)(p0[i] + (s0 + s) * stride);
+        const vec v = *(const vec*)(p0[i] + (s0 + s) * stride);
         const float w = __shfl(w_mine[i], s);
-        acc[i].x += w * v.x;
-        acc[i].y += w * v.y;
+        acc[i] += w * v;
       }
     }
   }
@@ -382,9 +381,9 @@ __global__ __launch_bounds__(256) void attend_merge_kernel(BlobParam<INLINE> blo
     const int tok = e.tok0 + row / group;
     const int h = g * group + row % group;
     const float inv = 1.f / lsum[i];
-    __bf16* o = out + ((int64_t)tok * n_q_heads + h) * D + lane * 2;
-    o[0] = (__bf16)(acc[i].x * inv);
-    o[1] = (__bf16)(acc[i].y * inv);
+    __bf16* o = out + ((int64_t)tok * n_q_heads + h) * D + lane * (D / 64);
+#pragma unroll
+    for (int u = 0; u < D / 64; ++u) o[u] = (__bf16)(acc[i][u] * inv);
     if (lse && lane == 0) lse[(int64_t)tok * n_q_heads + h] = (mmax[i] + log2f(lsum[i])) * 0.6931471805599453f;
   }
 }
@@ -392,17 +391,24 @@ __global__ __launch_bounds__(256) void attend_merge_kernel(BlobParam<INLINE> blo
 hipError_t launch_attend_merge(const AttendArgs& a, const DkMerge* merges, int32_t n_merges, int32_t max_rows,
                                hipStream_t stream) {
   if (n_merges <= 0) return hipSuccess;
-  if (a.arena.head_dim != 128 || max_rows <= 0) return hipErrorInvalidValue;
+  if (max_rows <= 0) return hipErrorInvalidValue;
   const int rows_per_block = 4 * MERGE_ROWS;
   dim3 grid((unsigned)n_merges, (unsigned)a.arena.n_kv_heads, (unsigned)((max_rows + rows_per_block - 1) / rows_per_block));
-  if (a.inline_blob)
-    attend_merge_kernel<128, true><<<grid, 256, 0, stream>>>(BlobParam<true>{*a.inline_blob}, merges, a.entries, a.parts,
-                                                             a.parts_ml, (__bf16*)a.out, a.lse, a.arena.n_q_heads,
-                                                             a.arena.n_kv_heads);
-  else
-    attend_merge_kernel<128, false><<<grid, 256, 0, stream>>>(BlobParam<false>{0}, merges, a.entries, a.parts,
-                                                              a.parts_ml, (__bf16*)a.out, a.lse, a.arena.n_q_heads,
-                                                              a.arena.n_kv_heads);
+#define DK_MERGE(D)                                                                                                  \
+  do {                                                                                                               \
+    if (a.inline_blob)                                                                                               \
+      attend_merge_kernel<D, true><<<grid, 256, 0, stream>>>(BlobParam<true>{*a.inline_blob}, merges, a.entries,     \
+                                                             a.parts, a.parts_ml, (__bf16*)a.out, a.lse,             \
+                                                             a.arena.n_q_heads, a.arena.n_kv_heads);                 \
+    else                                                                                                             \
+      attend_merge_kernel<D, false><<<grid, 256, 0, stream>>>(BlobParam<false>{0}, merges, a.entries, a.parts,       \
+                                                              a.parts_ml, (__bf16*)a.out, a.lse, a.arena.n_q_heads,  \
+                                                              a.arena.n_kv_heads);                                   \
+  } while (0)
+  if (a.arena.head_dim == 128) DK_MERGE(128);
+  else if (a.arena.head_dim == 64) DK_MERGE(64);
+  else return hipErrorInvalidValue;
+#undef DK_MERGE
   return hipGetLastError();
 }
 

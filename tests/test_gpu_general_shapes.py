@@ -1,0 +1,110 @@
+"""The general MFMA kernels (64-wide heads, groups of query heads that are no power of two up to 16) against the oracle, at
+the edges of their row blocks, key tiles and key splits, and against the reference kernel where a call falls back to it.
+
+Bound: the probabilities enter the second product with 16 bits of mantissa and everything else is fp32, so a result is off
+by the rounding of the bf16 store, at most 2^-8 |o|, plus about 2^-16 of the largest |v| (asserted: 2^-14)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from gpu_util import Mirror, to_dev
+from paper_2605_26289_amd import binding as dk
+from paper_2605_26289_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(out, ref, vmax, what):
+    g = out.float().cpu().numpy().astype(np.float64)
+    assert np.isfinite(g).all(), what
+    diff, bound = np.abs(g - ref), 2.0 ** -8 * np.abs(ref) + 2.0 ** -14 * vmax
+    assert (diff <= bound).all(), (what, float((diff / bound).max()), float(diff.max()))
+
+
+SHAPES = [(4, 4, 64), (8, 2, 64), (14, 2, 64), (6, 2, 128), (5, 1, 128), (32, 1, 128), (24, 8, 128)]
+# packed rows on both sides of the stream kernel's blocks (32, 64, 96) and of the block kernel's 128, keys on both sides of
+# the tiles of 32 and 64 keys, and ranges long enough to be cut
+SIZES = [(0, 1), (1, 2), (63, 1), (64, 9), (200, 21), (31, 33), (700, 43), (3000, 2), (2500, 65), (129, 150)]
+
+
+@pytest.mark.parametrize("hq,hkv,d", SHAPES)
+def test_shapes_that_no_tile_kernel_serves(hq, hkv, d):
+    sh = wl.Shape(hq, hkv, d, "bf16")
+    for n, delta in SIZES:
+        m = Mirror(sh, 2, n + delta + 256, granule=32, seed=hq * 1000 + n + delta)
+        m.pool.k_arena.fill_(float("nan"))  # cells outside the slots must never reach a result
+        m.pool.v_arena.fill_(float("nan"))
+        s, t = m.acquire(), m.acquire()
+        if n:
+            m.append([s], [n])
+            m.alias(s, t, max(1, n - 5)) if n > 1 else None
+        nt = m.pool.length(t)
+        q = m.draw(2 * delta, hq)
+        kn, vn = m.draw(2 * delta, hkv), m.draw(2 * delta, hkv)
+        cu = [0, delta, 2 * delta]
+        lse = torch.empty((2 * delta, hq), dtype=torch.float32, device="cuda")
+        out = m.pool.attend([s, t], cu, to_dev(q, "bf16"), sh.scale, to_dev(kn, "bf16"), to_dev(vn, "bf16"), lse=lse)
+        refs = [oracle.delta_attend(q[cu[b]:cu[b + 1]], *m.cache(x), kn[cu[b]:cu[b + 1]], vn[cu[b]:cu[b + 1]], sh.scale)
+                for b, x in enumerate((s, t))]
+        ref, ref_lse = np.concatenate([r[0] for r in refs]), np.concatenate([r[1] for r in refs])
+        vmax = max(np.abs(vn).max(), np.abs(m.cache(s)[1]).max() if n else 0.0)
+        _check(out, ref, vmax, ("staged", n, delta))
+        assert np.abs(lse.cpu().numpy() - ref_lse).max() < 1e-4, (n, delta)
+        # the same rows appended and attended in one call
+        out = m.pool.append_attend([s, t], cu, to_dev(q, "bf16"), to_dev(kn, "bf16"), to_dev(vn, "bf16"), sh.scale)
+        _check(out, ref, vmax, ("fused", n, delta))
+        for b, x in enumerate((s, t)):
+            m.model.append(x, kn[cu[b]:cu[b + 1]], vn[cu[b]:cu[b + 1]])
+            m.check_gather(x)
+        assert m.pool.length(t) == nt + delta
+        m.pool.close()
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(8, 2, 64), (12, 4, 128)])
+def test_general_kernels_walk_chains_and_queues(hq, hkv, d):
+    """More units than workgroups: planned chains and the run-time queue of the stream kernel, chains of the block kernel,
+    next to empty entries; the scores keep outgrowing the reference maximum."""
+    sh = wl.Shape(hq, hkv, d, "bf16")
+    rng = np.random.default_rng(3)
+    n_slots = 600
+    m = Mirror(sh, n_slots, n_slots * 260, granule=16, seed=d)
+    slots = [m.acquire() for _ in range(n_slots)]
+    hist = rng.integers(1, 200, size=n_slots).tolist()
+    m.append(slots, hist)
+    deltas = rng.integers(0, 4, size=n_slots).tolist()
+    for i in rng.choice(n_slots, 12, replace=False):
+        deltas[i] = int(rng.integers(30, 90))
+    total = sum(deltas)
+    q, kn, vn = m.draw(total, hq), m.draw(total, hkv), m.draw(total, hkv)
+    kn = wl.round_to_bf16(kn + 4.0 * np.sign(q[:, :: hq // hkv]))  # later keys score far higher
+    for queue in (1, 0):
+        dk.set_tuning(m.pool.handle, "stream_queue", queue)
+        cu = np.concatenate([[0], np.cumsum(deltas)]).astype(np.int32)
+        out = m.pool.attend(slots, cu, to_dev(q, "bf16"), sh.scale, to_dev(kn, "bf16"), to_dev(vn, "bf16"))
+        ref, _ = oracle.delta_attend_batch(q, [m.cache(s) for s in slots], kn, vn, cu, sh.scale)
+        _check(out, ref, max(np.abs(vn).max(), 5.0), queue)
+    m.pool.close()
+
+
+def test_calls_that_only_have_room_for_the_reference_kernel_still_run():
+    """No room for partials, or rows at an address that is no multiple of 16: the result is the reference kernel's."""
+    sh = wl.Shape(6, 2, 128, "bf16")
+    m = Mirror(sh, 1, 8192, seed=9)
+    s = m.acquire()
+    m.append([s], [6000])
+    q, kn, vn = (to_dev(m.draw(3, h), "bf16") for h in (6, 2, 2))
+    h = m.pool.handle
+    need = dk.attend_workspace_bytes(h, [s], [0, 3], True)
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    general, short, odd, ref = (torch.empty_like(q) for _ in range(4))
+    dk.delta_attend(h, [s], [0, 3], q, general, sh.scale, kn, vn, workspace=ws)
+    dk.delta_attend(h, [s], [0, 3], q, short, sh.scale, kn, vn, workspace=ws[:4096])
+    shifted = torch.empty(q.numel() + 1, dtype=q.dtype, device="cuda")[1:].view_as(q).copy_(q)
+    dk.delta_attend(h, [s], [0, 3], shifted, odd, sh.scale, kn, vn, workspace=ws)
+    dk.set_attend_variant(h, 1)
+    assert dk.attend_workspace_bytes(h, [s], [0, 3], True) <= 4096 < need
+    dk.delta_attend(h, [s], [0, 3], q, ref, sh.scale, kn, vn, workspace=ws[:4096])
+    assert torch.equal(short, ref) and torch.equal(odd, ref)
+    assert (general.float() - ref.float()).abs().max().item() < 2e-2
+    m.pool.close()
