@@ -12,7 +12,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libdeltakv.so")
 BUILD_DIR = os.path.join(HERE, "_build")
 
-SOURCES = ["pool.cpp", "plan.cpp", "radix.cpp", "pld.cpp", "sched.cpp", "abi.hip", "kernels_basic.hip", "attend_stream.hip", "attend_tile.hip", "attend_block.hip",
+SOURCES = ["pool.cpp", "plan.cpp", "radix.cpp", "pld.cpp", "sched.cpp", "abi.hip", "kernels_basic.hip", "attend_stream.hip", "attend_tile.hip", "attend_block.hip", "attend_f32.hip",
            "verify.hip"]
 
 HIP_FLAGS = [

@@ -59,9 +59,10 @@ int32_t guarded(F&& body) noexcept {
 
 // Which kernels carry an attention call.
 enum class Route {
-  kRef,      // scalar reference kernel: variant 1, a scale that is not positive and finite, fp32 pools
+  kRef,      // scalar reference kernel: variant 1, a scale that is not positive and finite
   kTile,     // bf16, 128-wide heads, groups of 2^k <= 16 query heads: tile and stream kernels
   kGeneral,  // bf16, any other shape: block kernel and the stream kernel's general form
+  kF32,      // fp32 pools
 };
 
 struct dk_pool {
@@ -94,18 +95,19 @@ struct dk_pool {
 
   // `scale_ok`: the scale is positive and finite (the MFMA kernels take the row maximum before scaling).
   Route route(bool scale_ok, int32_t n_seqs, const int32_t* cu_delta) const {
-    if (variant == 1 || !scale_ok || desc.dtype != DK_BF16) return Route::kRef;
+    if (variant == 1 || !scale_ok) return Route::kRef;
     const int64_t group = desc.n_q_heads / desc.n_kv_heads;
-    if (desc.head_dim == 128 && group <= 16 && (group & (group - 1)) == 0) return Route::kTile;
-    // the general kernels divide packed row numbers (below group * delta) by a multiplication that is exact while
+    if (desc.dtype == DK_BF16 && desc.head_dim == 128 && group <= 16 && (group & (group - 1)) == 0) return Route::kTile;
+    // the others divide packed row numbers (below group * delta) by a multiplication that is exact while
     // row * (group - 1) < 2^32
     int64_t most = 0;
     if (cu_delta)
       for (int32_t b = 0; b < n_seqs; ++b) most = std::max<int64_t>(most, (int64_t)cu_delta[b + 1] - cu_delta[b]);
-    return most < (int64_t(1) << 32) / (group * group) ? Route::kGeneral : Route::kRef;
+    if (most >= (int64_t(1) << 32) / (group * group)) return Route::kRef;
+    return desc.dtype == DK_BF16 ? Route::kGeneral : Route::kF32;
   }
 
-  dk::PlanConfig plan_config(Route r) const {
+  dk::PlanConfig plan_config(Route r, int32_t n_seqs, const int32_t* cu_delta) const {
     dk::PlanConfig c = cfg;
     c.use_mfma = r != Route::kRef;
     if (r == Route::kGeneral) {
@@ -114,6 +116,18 @@ struct dk_pool {
       c.tile_rows = 128;
       c.tile_wave_slots = 2 * cfg.tile_wave_slots;
       c.tile_item_cost = std::min(cfg.tile_item_cost, 3);
+    }
+    if (r == Route::kF32) {
+      // fp32 kernel: every row goes through it, in items of 32 rows once those fill the chip, else of 16.  A workgroup
+      // works through 128 keys of 64 in about a microsecond; a cut costs a merge launch (6 us), so no piece is made
+      // shorter than that is worth.
+      int64_t items = 0;
+      const int64_t group = desc.n_q_heads / desc.n_kv_heads;
+      if (cu_delta)
+        for (int32_t b = 0; b < n_seqs; ++b) items += (group * ((int64_t)cu_delta[b + 1] - cu_delta[b]) + 31) / 32;
+      c.tile_rows = items * desc.n_kv_heads >= 256 ? 32 : 16;
+      c.stream_rows = 0;
+      c.tile_min_chunk = std::max(cfg.tile_min_chunk, 65536 / desc.head_dim);
     }
     return c;
   }
@@ -440,7 +454,7 @@ int32_t dk_attend_workspace_bytes(dk_pool* pool, int32_t n_seqs, const int32_t* 
     std::lock_guard<std::mutex> launch(pool->launch_mu);
     dk::AttendPlan& plan = pool->plan;
     if (staged < 0 || staged > 2) return DK_ERR_INVALID;
-    const dk::PlanConfig cfg = pool->plan_config(pool->route(true, n_seqs, cu_delta));
+    const dk::PlanConfig cfg = pool->plan_config(pool->route(true, n_seqs, cu_delta), n_seqs, cu_delta);
     std::lock_guard<std::mutex> lk(pool->meta.mutex());
     int32_t rc = dk::build_plan(pool->meta, cfg, n_seqs, slots, cu_delta, staged != 0, &plan, staged == 2);
     if (rc != DK_OK) return rc;
@@ -487,9 +501,11 @@ int32_t attend_locked(dk_pool* pool, int32_t n_seqs, const int32_t* slots, const
   dk::AttendPlan& plan = pool->plan;
   Route route = pool->route(scale > 0.f && scale < 3.0e38f, n_seqs, cu_delta);
   bool inline_blob = false;
+  int32_t tile_rows = 0;
   while (true) {
     {
-      const dk::PlanConfig cfg = pool->plan_config(route);
+      const dk::PlanConfig cfg = pool->plan_config(route, n_seqs, cu_delta);
+      tile_rows = cfg.tile_rows;
       std::lock_guard<std::mutex> lk(pool->meta.mutex());
       int32_t rc = dk::build_plan(pool->meta, cfg, n_seqs, slots, cu_delta, staged, &plan, fold_append);
       if (rc != DK_OK) return rc;
@@ -499,9 +515,9 @@ int32_t attend_locked(dk_pool* pool, int32_t n_seqs, const int32_t* slots, const
     inline_blob = plan.blob_bytes <= (size_t)dk::INLINE_BLOB_BYTES && !plan.stream_queued;
     if (fold_append && !(inline_blob && route != Route::kRef && (plan.tile_chains > 0 || plan.stream_chains > 0)))
       return kNotFoldable;
-    if (route != Route::kGeneral) break;
-    // The reference kernel serves these shapes with a handful of descriptors, no partials and 2-byte accesses to q and
-    // out.  Where a caller has only made room for that -- a workspace or the static array without room for partials, a
+    if (route == Route::kRef || route == Route::kTile) break;
+    // The reference kernel serves these shapes with a handful of descriptors, no partials and single-element accesses to
+    // q and out.  Where a caller has only made room for that -- a workspace or the static array without room for partials, a
     // pool without staging memory, a capture that cannot take an upload, rows at odd addresses -- it still does.
     const bool fits = (((uintptr_t)q | (uintptr_t)out) & 15) == 0 && workspace_bytes >= (int64_t)plan.total_bytes &&
                       (inline_blob || (pool->ring_size > 0 && plan.blob_bytes <= pool->stage_cap && !capturing(st)));
@@ -591,9 +607,11 @@ int32_t attend_locked(dk_pool* pool, int32_t n_seqs, const int32_t* slots, const
   } else {
     // a folded append is carried out by the first MFMA kernel of the call
     a.scatter = fold_append && plan.tile_chains > 0;
-    const auto launch_rows = a.general ? dk::launch_attend_block : dk::launch_attend_tile;
-    e = launch_rows(a, (const DkItem*)(desc + plan.off_tile), (const int32_t*)(desc + plan.off_tile_links),
-                    plan.tile_chains, st);
+    const DkItem* items = (const DkItem*)(desc + plan.off_tile);
+    const int32_t* links = (const int32_t*)(desc + plan.off_tile_links);
+    if (route == Route::kF32) e = dk::launch_attend_f32(a, items, links, plan.tile_chains, tile_rows, st);
+    else if (route == Route::kGeneral) e = dk::launch_attend_block(a, items, links, plan.tile_chains, st);
+    else e = dk::launch_attend_tile(a, items, links, plan.tile_chains, st);
     if (e != hipSuccess) return fail(pool->hip_fail(e));
     a.scatter = fold_append && plan.tile_chains == 0;
     int32_t stream_rows = 0;

@@ -93,7 +93,7 @@ __global__ __launch_bounds__(256, 2) void attend_block_kernel(BlobArg<INLINE> bl
       for (int ks = 0; ks < G::KS; ++ks) qf[ks] = *(const bf16x8*)(qp + ks * 16);
     }
 
-    KvCursor<HD> cur{c.segs, e.seg_begin, e.seg_end, it.kv_lo, it.kv_hi};
+    KvCursor<G::ROW> cur{c.segs, e.seg_begin, e.seg_end, it.kv_lo, it.kv_hi};
     // tiles requested and not yet computed, oldest first: (valid rows, position of row 0)
     int cnt[B::STAGES] = {}, pos[B::STAGES] = {};
     int stage_wr = 0;
@@ -216,6 +216,13 @@ __global__ __launch_bounds__(256, 2) void attend_block_kernel(BlobArg<INLINE> bl
         store_quads<HD, true>(c, e, it, g, wave * 32 + (lane & 31), db * 32 + 4 * h, quads, lt[0]);
       }
       store_ml<1, true>(c, e, it, g, wave * 32, lane, mm, lt);
+      float z = 0.f;  // NaN if any of the row's sums is not finite
+#pragma unroll
+      for (int db = 0; db < G::DB; ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) z = __builtin_fmaf(o[db][r], 0.f, z);
+      const uint64_t bad = __builtin_amdgcn_ballot_w64(z != 0.f);
+      if (bad != 0) redo_rows<__bf16, HD, true>(c, e, it, g, wave * 32, (uint32_t)(bad | bad >> 32), m, lt[0], lane);
     }
   }
 }

@@ -115,7 +115,7 @@ struct KvTile {
 // Walks the logical key positions [p, hi) of an entry, segment by segment.  The state of the segment
 // being walked (row pointers at position p, row stride, end position) is kept in a handful of scalars,
 // so the common step touches neither the segment table nor the kernel arguments.
-template <int HD = D>
+template <int ROW = ROW_BYTES>
 struct KvCursor {
   const DkSeg* segs;
   int32_t si, se, p, hi;
@@ -130,15 +130,15 @@ struct KvCursor {
     const int32_t off = p - s.pos;
     seg_end = s.pos + s.len;
     if (s.src == 0) {
-      const int64_t byte = ((int64_t)g * c.arena_cells + s.start + off) * Geo<HD>::ROW;
+      const int64_t byte = ((int64_t)g * c.arena_cells + s.start + off) * ROW;
       k = c.k_arena + byte;
       v = c.v_arena + byte;
-      stride = Geo<HD>::ROW;
+      stride = ROW;
     } else {
-      const int64_t byte = ((s.start + off) * c.n_kv_heads + g) * (int64_t)Geo<HD>::ROW;
+      const int64_t byte = ((s.start + off) * c.n_kv_heads + g) * (int64_t)ROW;
       k = c.k_new + byte;
       v = c.v_new + byte;
-      stride = (uint32_t)c.n_kv_heads * Geo<HD>::ROW;
+      stride = (uint32_t)c.n_kv_heads * ROW;
     }
   }
 
@@ -353,6 +353,65 @@ __device__ __forceinline__ void store_rows_staged(const Ctx& c, const DkEntry& e
         }
       }
       __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+}
+
+// A product of matrix instructions multiplies every V row of a tile into every query row, hidden keys with weight zero --
+// and 0 * inf or 0 * NaN is NaN.  So where V holds such values at positions some of a tile's rows may not see, those rows
+// come out non-finite although what they attend to is not.  Kernels of shapes that were always free of that look at
+// their sums once, before the store, and have the non-finite rows (nobody pays for this otherwise) done again, key by key
+// over the visible keys alone, relative to the row's maximum m and weight sum l, which V has no part in.
+// Returns the rows of `bad` (bit i: row rl0 + i, its m and l in lane i) to memory; T: element type, ANYG as in row_token.
+__device__ __forceinline__ float wide(float x) { return x; }
+__device__ __forceinline__ float wide(__bf16 x) { return (float)x; }
+template <typename T, int HD, bool ANYG>
+__device__ __forceinline__ void redo_rows(const Ctx& c, const DkEntry& e, const DkItem& it, int g, int rl0, uint32_t bad,
+                                          float m_lane, float l_lane, int lane) {
+  constexpr int ROW = HD * (int)sizeof(T), PER_LANE = HD / 64, VEC = 16 / (int)sizeof(T);
+  typedef T vec __attribute__((ext_vector_type(VEC)));
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // after the ordinary store of the same rows
+  while (bad != 0) {
+    const int i = __builtin_ctz(bad);
+    bad &= bad - 1;
+    const int rl = rl0 + i;
+    if (rl >= it.nrows) break;
+    const float m = __shfl(m_lane, i), l = __shfl(l_lane, i);
+    const int row = it.row0 + rl;
+    const int tok = row_token<ANYG>(c, row);
+    const int64_t orow = (int64_t)(e.tok0 + tok) * c.n_q_heads + g * c.group + row_head<ANYG>(c, row, tok);
+    const T* q = (const T*)c.q + orow * HD;
+    float acc[PER_LANE];
+#pragma unroll
+    for (int u = 0; u < PER_LANE; ++u) acc[u] = 0.f;
+    KvCursor<ROW> cur{c.segs, e.seg_begin, e.seg_end, it.kv_lo, min(it.kv_hi, e.n + tok + 1)};
+    KvTile t;
+    while (cur.next(c, g, 64, t)) {
+      const char* k = t.k + (uint32_t)min(lane, t.cnt - 1) * t.stride;
+      float s = 0.f;
+#pragma unroll 1
+      for (int d = 0; d < HD; d += VEC) {
+        const vec kv = *(const vec*)(k + d * sizeof(T)), qv = *(const vec*)(q + d);
+#pragma unroll
+        for (int u = 0; u < VEC; ++u) s += wide(kv[u]) * wide(qv[u]);
+      }
+      const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s, c.c, -m));
+#pragma unroll 1
+      for (int j = 0; j < t.cnt; ++j) {
+        const float pj = __shfl(p, j);
+        const T* v = (const T*)(t.v + (uint32_t)j * t.stride) + lane * PER_LANE;
+#pragma unroll
+        for (int u = 0; u < PER_LANE; ++u) acc[u] += pj * wide(v[u]);
+      }
+    }
+    if (it.part_row0 >= 0) {
+      float* p = c.parts + ((int64_t)(it.part_row0 + rl) * c.n_kv_heads + g) * HD + lane * PER_LANE;
+#pragma unroll
+      for (int u = 0; u < PER_LANE; ++u) p[u] = acc[u];
+    } else {
+      T* p = (T*)c.out + orow * HD + lane * PER_LANE;
+#pragma unroll
+      for (int u = 0; u < PER_LANE; ++u) p[u] = (T)(acc[u] / l);
     }
   }
 }

@@ -329,7 +329,7 @@ __global__ __launch_bounds__(256, 1) void attend_stream_kernel(BlobArg<INLINE> b
   DkItem it = load_desc(c.items, unit / c.n_kv_heads);
   DkEntry e = load_desc(c.entries, it.entry);
   int g = unit % c.n_kv_heads;
-  KvCursor<HD> cur{c.segs, 0, 0, 0, 0};
+  KvCursor<Geo<HD>::ROW> cur{c.segs, 0, 0, 0, 0};
   KvTile t0, t1, t2;  // being computed, next, the one after
   bool have0 = false, have1 = false;
 
@@ -347,7 +347,7 @@ __global__ __launch_bounds__(256, 1) void attend_stream_kernel(BlobArg<INLINE> b
     const int per = (ntile + 3) / 4 * KT;
     const int lo = min(u.kv_hi, u.kv_lo + wave * per);
     const int hi = min(u.kv_hi, lo + per);
-    cur = KvCursor<HD>{c.segs, ue.seg_begin, ue.seg_end, lo, hi};
+    cur = KvCursor<Geo<HD>::ROW>{c.segs, ue.seg_begin, ue.seg_end, lo, hi};
     have0 = cur.next(c, ug, KT, t0);
     if (have0) issue(t0, 0);
   };
@@ -483,6 +483,8 @@ __global__ __launch_bounds__(256, 1) void attend_stream_kernel(BlobArg<INLINE> b
       }
     }
     int next_g = 0;
+    uint32_t bad_rows[MB];  // GEN: rows whose sums are not finite, see redo_rows
+    float bad_m[MB], bad_l[MB];
     // the four wavefronts share out the depth blocks: a whole one each (HD 128) or half of one (HD 64)
     constexpr int NACC = DB * 4;  // accumulators of a row block per wavefront after the merge
     const int db = wave * DB / 4, r0 = wave * NACC % 16;
@@ -548,6 +550,32 @@ __global__ __launch_bounds__(256, 1) void attend_stream_kernel(BlobArg<INLINE> b
       const float mm[1] = {mx}, ll[1] = {lsum};
       store_quads<HD, GEN>(c, e, it, g, row, db * 32 + 2 * r0 + 4 * (lane >> 5), acc, lsum);
       if (wave == 0) store_ml<1, GEN>(c, e, it, g, mb * 32, lane, mm, ll);
+      if constexpr (GEN) {
+        float z = 0.f;  // NaN if any of the row's sums is not finite
+#pragma unroll
+        for (int i = 0; i < NACC / 4; ++i)
+#pragma unroll
+          for (int u = 0; u < 4; ++u) z = __builtin_fmaf(acc[i][u], 0.f, z);
+        const uint64_t bad = __builtin_amdgcn_ballot_w64(z != 0.f);
+        bad_rows[mb] = (uint32_t)(bad | bad >> 32);
+        bad_m[mb] = mx;
+        bad_l[mb] = lsum;
+      }
+    }
+    if constexpr (GEN) {
+      uint32_t any = bad_rows[0];
+#pragma unroll
+      for (int mb = 1; mb < MB; ++mb) any |= bad_rows[mb];
+      if (any != 0) {
+#pragma unroll 1
+        for (int mb = 0; mb < MB; ++mb) {
+          const int i1 = MB > 1 ? 1 : 0, i2 = MB > 2 ? 2 : 0;
+          const uint32_t rows = mb == 0 ? bad_rows[0] : mb == 1 ? bad_rows[i1] : bad_rows[i2];
+          const float m = mb == 0 ? bad_m[0] : mb == 1 ? bad_m[i1] : bad_m[i2];
+          const float l = mb == 0 ? bad_l[0] : mb == 1 ? bad_l[i1] : bad_l[i2];
+          redo_rows<__bf16, HD, true>(c, e, it, g, mb * 32, rows, m, l, lane);
+        }
+      }
     }
     // (after the stores: the wait that opens the next unit lets exactly this request stay in flight)
     if (next_unit >= 0) open_second(next_g);

@@ -71,6 +71,9 @@ hipError_t launch_attend_tile(const AttendArgs& a, const DkItem* items, const in
                               hipStream_t stream);
 hipError_t launch_attend_block(const AttendArgs& a, const DkItem* items, const int32_t* links, int32_t n_chains,
                                hipStream_t stream);
+// fp32 kernel; tile_rows: the most rows of an item, 16 or 32.
+hipError_t launch_attend_f32(const AttendArgs& a, const DkItem* items, const int32_t* links, int32_t n_chains,
+                             int32_t tile_rows, hipStream_t stream);
 // Unit u = item u / n_kv_heads for KV head u % n_kv_heads; n_chains workgroups.
 // queue == nullptr: workgroup w walks the chain links[w], links[n_chains + that unit], ... until a link is negative.
 // queue != nullptr (DEVICE int32, holding n_chains when the kernel starts; not with an inline blob): workgroup w

@@ -284,11 +284,11 @@ hipError_t launch_attend_ref(const AttendArgs& a, hipStream_t stream) {
 // ---------------------------------------------------------------------------------------------
 constexpr int MERGE_ROWS = 4;  // rows per wavefront; a workgroup of four wavefronts covers 16 rows
 
-template <int D, bool INLINE>
+template <typename T, int D, bool INLINE>
 __global__ __launch_bounds__(256) void attend_merge_kernel(BlobParam<INLINE> blob, const DkMerge* merges,
                                                            const DkEntry* entries,
                                                            const float* __restrict__ parts,
-                                                           const float* __restrict__ parts_ml, __bf16* __restrict__ out,
+                                                           const float* __restrict__ parts_ml, T* __restrict__ out,
                                                            float* __restrict__ lse, int32_t n_q_heads,
                                                            int32_t n_kv_heads) {
   static_assert(D == 128 || D == 64, "two floats per lane, or one");
@@ -381,9 +381,9 @@ __global__ __launch_bounds__(256) void attend_merge_kernel(BlobParam<INLINE> blo
     const int tok = e.tok0 + row / group;
     const int h = g * group + row % group;
     const float inv = 1.f / lsum[i];
-    __bf16* o = out + ((int64_t)tok * n_q_heads + h) * D + lane * (D / 64);
+    T* o = out + ((int64_t)tok * n_q_heads + h) * D + lane * (D / 64);
 #pragma unroll
-    for (int u = 0; u < D / 64; ++u) o[u] = (__bf16)(acc[i][u] * inv);
+    for (int u = 0; u < D / 64; ++u) store_out(o + u, acc[i][u] * inv);
     if (lse && lane == 0) lse[(int64_t)tok * n_q_heads + h] = (mmax[i] + log2f(lsum[i])) * 0.6931471805599453f;
   }
 }
@@ -394,19 +394,21 @@ hipError_t launch_attend_merge(const AttendArgs& a, const DkMerge* merges, int32
   if (max_rows <= 0) return hipErrorInvalidValue;
   const int rows_per_block = 4 * MERGE_ROWS;
   dim3 grid((unsigned)n_merges, (unsigned)a.arena.n_kv_heads, (unsigned)((max_rows + rows_per_block - 1) / rows_per_block));
-#define DK_MERGE(D)                                                                                                  \
+#define DK_MERGE(T, D)                                                                                                  \
   do {                                                                                                               \
     if (a.inline_blob)                                                                                               \
-      attend_merge_kernel<D, true><<<grid, 256, 0, stream>>>(BlobParam<true>{*a.inline_blob}, merges, a.entries,     \
-                                                             a.parts, a.parts_ml, (__bf16*)a.out, a.lse,             \
+      attend_merge_kernel<T, D, true><<<grid, 256, 0, stream>>>(BlobParam<true>{*a.inline_blob}, merges, a.entries,     \
+                                                             a.parts, a.parts_ml, (T*)a.out, a.lse,             \
                                                              a.arena.n_q_heads, a.arena.n_kv_heads);                 \
     else                                                                                                             \
-      attend_merge_kernel<D, false><<<grid, 256, 0, stream>>>(BlobParam<false>{0}, merges, a.entries, a.parts,       \
-                                                              a.parts_ml, (__bf16*)a.out, a.lse, a.arena.n_q_heads,  \
+      attend_merge_kernel<T, D, false><<<grid, 256, 0, stream>>>(BlobParam<false>{0}, merges, a.entries, a.parts,       \
+                                                              a.parts_ml, (T*)a.out, a.lse, a.arena.n_q_heads,  \
                                                               a.arena.n_kv_heads);                                   \
   } while (0)
-  if (a.arena.head_dim == 128) DK_MERGE(128);
-  else if (a.arena.head_dim == 64) DK_MERGE(64);
+  if (a.arena.dtype == 0 && a.arena.head_dim == 64) DK_MERGE(float, 64);
+  else if (a.arena.dtype == 0 && a.arena.head_dim == 128) DK_MERGE(float, 128);
+  else if (a.arena.dtype == 1 && a.arena.head_dim == 64) DK_MERGE(__bf16, 64);
+  else if (a.arena.dtype == 1 && a.arena.head_dim == 128) DK_MERGE(__bf16, 128);
   else return hipErrorInvalidValue;
 #undef DK_MERGE
   return hipGetLastError();

@@ -1,8 +1,11 @@
-"""The general MFMA kernels (64-wide heads, groups of query heads that are no power of two up to 16) against the oracle, at
-the edges of their row blocks, key tiles and key splits, and against the reference kernel where a call falls back to it.
+"""The general MFMA kernels (64-wide heads, groups of query heads that are no power of two up to 16) and the fp32 kernel
+against the oracle, at the edges of their row blocks, key tiles and key splits, and against the reference kernel where a
+call falls back to it.
 
-Bound: the probabilities enter the second product with 16 bits of mantissa and everything else is fp32, so a result is off
-by the rounding of the bf16 store, at most 2^-8 |o|, plus about 2^-16 of the largest |v| (asserted: 2^-14)."""
+Bounds.  bf16: the probabilities enter the second product with 16 bits of mantissa and everything else is fp32, so a result is off
+by the rounding of the bf16 store, at most 2^-8 |o|, plus about 2^-16 of the largest |v| (asserted: 2^-14).  fp32: a score
+sums up to 128 products of order one, a result a few thousand weighted values: a few 2^-22 of the largest |v| (asserted:
+2^-18)."""
 import numpy as np
 import pytest
 import torch
@@ -15,22 +18,25 @@ from paper_2605_26289_amd import workloads as wl
 pytestmark = pytest.mark.gpu
 
 
-def _check(out, ref, vmax, what):
+def _check(out, ref, vmax, what, dtype="bf16"):
     g = out.float().cpu().numpy().astype(np.float64)
     assert np.isfinite(g).all(), what
-    diff, bound = np.abs(g - ref), 2.0 ** -8 * np.abs(ref) + 2.0 ** -14 * vmax
+    diff = np.abs(g - ref)
+    bound = 2.0 ** -8 * np.abs(ref) + 2.0 ** -14 * vmax if dtype == "bf16" else np.full_like(ref, 2.0 ** -18 * vmax)
     assert (diff <= bound).all(), (what, float((diff / bound).max()), float(diff.max()))
 
 
-SHAPES = [(4, 4, 64), (8, 2, 64), (14, 2, 64), (6, 2, 128), (5, 1, 128), (32, 1, 128), (24, 8, 128)]
+SHAPES = [(4, 4, 64, "bf16"), (8, 2, 64, "bf16"), (14, 2, 64, "bf16"), (6, 2, 128, "bf16"), (5, 1, 128, "bf16"),
+          (32, 1, 128, "bf16"), (24, 8, 128, "bf16"), (4, 1, 64, "f32"), (4, 4, 64, "f32"), (6, 2, 64, "f32"),
+          (8, 2, 128, "f32"), (5, 1, 128, "f32"), (32, 8, 128, "f32")]
 # packed rows on both sides of the stream kernel's blocks (32, 64, 96) and of the block kernel's 128, keys on both sides of
-# the tiles of 32 and 64 keys, and ranges long enough to be cut
+# the tiles of 16, 32 and 64 keys (and, fp32, on both sides of what takes items of 16 or 32 rows), and ranges long enough to be cut
 SIZES = [(0, 1), (1, 2), (63, 1), (64, 9), (200, 21), (31, 33), (700, 43), (3000, 2), (2500, 65), (129, 150)]
 
 
-@pytest.mark.parametrize("hq,hkv,d", SHAPES)
-def test_shapes_that_no_tile_kernel_serves(hq, hkv, d):
-    sh = wl.Shape(hq, hkv, d, "bf16")
+@pytest.mark.parametrize("hq,hkv,d,dtype", SHAPES)
+def test_shapes_that_no_tile_kernel_serves(hq, hkv, d, dtype):
+    sh = wl.Shape(hq, hkv, d, dtype)
     for n, delta in SIZES:
         m = Mirror(sh, 2, n + delta + 256, granule=32, seed=hq * 1000 + n + delta)
         m.pool.k_arena.fill_(float("nan"))  # cells outside the slots must never reach a result
@@ -44,16 +50,16 @@ def test_shapes_that_no_tile_kernel_serves(hq, hkv, d):
         kn, vn = m.draw(2 * delta, hkv), m.draw(2 * delta, hkv)
         cu = [0, delta, 2 * delta]
         lse = torch.empty((2 * delta, hq), dtype=torch.float32, device="cuda")
-        out = m.pool.attend([s, t], cu, to_dev(q, "bf16"), sh.scale, to_dev(kn, "bf16"), to_dev(vn, "bf16"), lse=lse)
+        out = m.pool.attend([s, t], cu, to_dev(q, dtype), sh.scale, to_dev(kn, dtype), to_dev(vn, dtype), lse=lse)
         refs = [oracle.delta_attend(q[cu[b]:cu[b + 1]], *m.cache(x), kn[cu[b]:cu[b + 1]], vn[cu[b]:cu[b + 1]], sh.scale)
                 for b, x in enumerate((s, t))]
         ref, ref_lse = np.concatenate([r[0] for r in refs]), np.concatenate([r[1] for r in refs])
         vmax = max(np.abs(vn).max(), np.abs(m.cache(s)[1]).max() if n else 0.0)
-        _check(out, ref, vmax, ("staged", n, delta))
+        _check(out, ref, vmax, ("staged", n, delta), dtype)
         assert np.abs(lse.cpu().numpy() - ref_lse).max() < 1e-4, (n, delta)
         # the same rows appended and attended in one call
-        out = m.pool.append_attend([s, t], cu, to_dev(q, "bf16"), to_dev(kn, "bf16"), to_dev(vn, "bf16"), sh.scale)
-        _check(out, ref, vmax, ("fused", n, delta))
+        out = m.pool.append_attend([s, t], cu, to_dev(q, dtype), to_dev(kn, dtype), to_dev(vn, dtype), sh.scale)
+        _check(out, ref, vmax, ("fused", n, delta), dtype)
         for b, x in enumerate((s, t)):
             m.model.append(x, kn[cu[b]:cu[b + 1]], vn[cu[b]:cu[b + 1]])
             m.check_gather(x)
@@ -107,4 +113,29 @@ def test_calls_that_only_have_room_for_the_reference_kernel_still_run():
     dk.delta_attend(h, [s], [0, 3], q, ref, sh.scale, kn, vn, workspace=ws[:4096])
     assert torch.equal(short, ref) and torch.equal(odd, ref)
     assert (general.float() - ref.float()).abs().max().item() < 2e-2
+    m.pool.close()
+
+
+@pytest.mark.parametrize("hq,hkv,d,dtype", [(8, 2, 64, "bf16"), (6, 2, 128, "bf16"), (4, 1, 64, "f32"), (6, 2, 128, "f32")])
+@pytest.mark.parametrize("n,delta", [(100, 8), (40, 70), (5000, 5)])
+def test_values_a_row_may_not_see_never_reach_it(hq, hkv, d, dtype, n, delta):
+    """Infinities and NaN in V at some of the new tokens: rows before them stay finite and right, rows from them on carry
+    them on, exactly as the reference kernel has it."""
+    sh = wl.Shape(hq, hkv, d, dtype)
+    m = Mirror(sh, 1, n + 512, seed=4)
+    s = m.acquire()
+    m.append([s], [n])
+    q, kn, vn = (to_dev(m.draw(delta, x), dtype) for x in (hq, hkv, hkv))
+    vn[delta // 2, 0, 3] = float("inf")
+    vn[delta // 2 + 1, hkv - 1, 5] = float("nan")
+    vn[delta - 1, 0, d - 1] = float("-inf")
+    kn[delta - 1, 0, 7] = float("nan")
+    out = m.pool.attend([s], [0, delta], q, sh.scale, kn, vn)
+    dk.set_attend_variant(m.pool.handle, 1)
+    ref = m.pool.attend([s], [0, delta], q, sh.scale, kn, vn)
+    assert torch.equal(torch.isfinite(out), torch.isfinite(ref)) and torch.equal(torch.isnan(out), torch.isnan(ref))
+    assert torch.equal(out[torch.isinf(out)], ref[torch.isinf(ref)])
+    ok = torch.isfinite(ref)
+    assert ok[: delta // 2].all()
+    assert (out[ok].float() - ref[ok].float()).abs().max().item() <= (2.0 ** -6 if dtype == "bf16" else 2.0 ** -17)
     m.pool.close()
