@@ -622,9 +622,13 @@ int32_t attend_locked(dk_pool* pool, int32_t n_seqs, const int32_t* slots, const
                                  (int32_t)plan.stream_units, st);
     if (e != hipSuccess) return fail(pool->hip_fail(e));
     a.scatter = false;
-    int32_t max_rows = 0;
-    for (const DkMerge& mg : plan.merges) max_rows = std::max(max_rows, mg.nrows);
-    e = dk::launch_attend_merge(a, (const DkMerge*)(desc + plan.off_merges), (int32_t)plan.merges.size(), max_rows, st);
+    int32_t max_rows = 0, max_split = 0;
+    for (const DkMerge& mg : plan.merges) {
+      max_rows = std::max(max_rows, mg.nrows);
+      max_split = std::max(max_split, mg.nsplit);
+    }
+    e = dk::launch_attend_merge(a, (const DkMerge*)(desc + plan.off_merges), (int32_t)plan.merges.size(), max_rows,
+                                max_split, st);
     if (e != hipSuccess) return fail(pool->hip_fail(e));
   }
   if (timing) {  // the interval covers every kernel of the call, the merge of split key ranges included

@@ -41,5 +41,6 @@ struct DkMerge {
   int32_t nrows;
   int32_t part_row0;  // split s lives at part_row0 + s * nrows
   int32_t nsplit;
-  int32_t pad[3];
+  int32_t tok0;  // of the entry
+  int32_t pad[2];
 };

@@ -82,9 +82,9 @@ hipError_t launch_attend_f32(const AttendArgs& a, const DkItem* items, const int
 // max_rows: the largest DkItem::nrows among the items (at most 96).
 hipError_t launch_attend_stream(const AttendArgs& a, const DkItem* items, const int32_t* links, int32_t n_chains,
                                 int32_t max_rows, int32_t* queue, int32_t n_units, hipStream_t stream);
-// max_rows: the largest DkMerge::nrows among them (sizes the grid).
+// max_rows, max_split: the largest DkMerge::nrows and ::nsplit among them (size the grid, choose the form).
 hipError_t launch_attend_merge(const AttendArgs& a, const DkMerge* merges, int32_t n_merges, int32_t max_rows,
-                               hipStream_t stream);
+                               int32_t max_split, hipStream_t stream);
 
 // Greedy verification (argmax per logits row, accepted-draft count and next token per slot).
 int64_t verify_workspace_bytes(int32_t total_rows, int64_t vocab, int32_t dtype);

@@ -117,6 +117,11 @@ __device__ inline float to_float(float x) { return x; }
 __device__ inline float to_float(__bf16 x) { return (float)x; }
 __device__ inline void store_out(float* p, float x) { *p = x; }
 __device__ inline void store_out(__bf16* p, float x) { *p = (__bf16)x; }
+typedef __bf16 bf16_quad __attribute__((ext_vector_type(4)));
+__device__ inline void store_quad(float* p, float4 x) { *(float4*)p = x; }
+__device__ inline void store_quad(__bf16* p, float4 x) {
+  *(bf16_quad*)p = bf16_quad{(__bf16)x.x, (__bf16)x.y, (__bf16)x.z, (__bf16)x.w};
+}
 
 // 16-byte row loads, widened to float
 template <typename T> struct VEC;
@@ -276,142 +281,128 @@ hipError_t launch_attend_ref(const AttendArgs& a, hipStream_t stream) {
 // Merge of split key ranges.  Each split left, per (row, KV head), D unnormalised fp32 sums (parts) and its
 // running maximum m (log2 units) with its weight sum l (parts_ml).
 //   O = sum_s 2^(m_s-M) o_s / sum_s 2^(m_s-M) l_s.
-// A wavefront merges MERGE_ROWS rows of one KV head at a time: for each row every lane first takes one split
-// and fetches its (m, l), which gives the common maximum, the weights and the weight sum in one round trip;
-// then the lanes cover D and add the splits' sums, the loads of all the rows and of two splits in flight
-// together.  (One row per wavefront left most of a launch's time to workgroup turnover when rows are split
-// only two or three ways.)
+// What a launch takes is mostly latency: the partial rows of one turn are a few MB.  So D / 4 lanes cover a row of one KV
+// head (16 bytes each), ROWS rows per lane group, and the sums of up to AHEAD splits of all of them are requested
+// before the (m, l) pairs are looked at -- rows cut in a few pieces, as all of the tile kernel's are, take two round trips:
+// the merge record, and everything else.  Two rows and four splits at a time, or one row and eight where some row is cut
+// in more than four (a few rows of a long session: the chain of rounds counts, not the rows).  Measured, before (one row
+// per wavefront at a time, the sums requested after the weights) and after: 16 sessions of up to 256 rows cut in two to
+// six, 17.2 -> 11.7 us; one session of 3044 rows cut in three, 16.1 -> 11.4; four rows cut in six, 5.3 -> 4.3.
 // ---------------------------------------------------------------------------------------------
-constexpr int MERGE_ROWS = 4;  // rows per wavefront; a workgroup of four wavefronts covers 16 rows
-
-template <typename T, int D, bool INLINE>
+template <typename T, int D, int ROWS, int AHEAD, bool INLINE>
 __global__ __launch_bounds__(256) void attend_merge_kernel(BlobParam<INLINE> blob, const DkMerge* merges,
-                                                           const DkEntry* entries,
                                                            const float* __restrict__ parts,
                                                            const float* __restrict__ parts_ml, T* __restrict__ out,
                                                            float* __restrict__ lse, int32_t n_q_heads,
                                                            int32_t n_kv_heads) {
-  static_assert(D == 128 || D == 64, "two floats per lane, or one");
-  typedef float vec __attribute__((ext_vector_type(D / 64)));
+  constexpr int LANES = D / 4;                // lanes per row
+  constexpr int GROUPS = 256 / LANES;         // lane groups per workgroup
   (void)blob;
   merges = from_blob<INLINE>(merges);
-  entries = from_blob<INLINE>(entries);
   const DkMerge mg = merges[blockIdx.x];
-  const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  const int r0 = (blockIdx.z * 4 + wave) * MERGE_ROWS;
+  const int lane = threadIdx.x % LANES, grp = threadIdx.x / LANES;
+  const int r0 = (blockIdx.z * GROUPS + grp) * ROWS;
   if (r0 >= mg.nrows) return;
-  const DkEntry e = entries[mg.entry];
   const int g = blockIdx.y;
   const int group = n_q_heads / n_kv_heads;
   const int64_t srow = (int64_t)mg.nrows * n_kv_heads;  // partial rows from one split of a row to the next
-  const int64_t stride = srow * D;
 
-  const float* p0[MERGE_ROWS];
-  const float* ml0[MERGE_ROWS];
-  bool live[MERGE_ROWS];
+  const float4* p[ROWS];
+  const float2* ml[ROWS];
+  float4 acc[ROWS];
+  float lsum[ROWS], m[ROWS];
 #pragma unroll
-  for (int i = 0; i < MERGE_ROWS; ++i) {
-    live[i] = r0 + i < mg.nrows;
-    const int64_t prow = (int64_t)(mg.part_row0 + (live[i] ? r0 + i : r0)) * n_kv_heads + g;
-    p0[i] = parts + prow * D + lane * (D / 64);
-    ml0[i] = parts_ml + prow * 2;
-  }
-
-  vec acc[MERGE_ROWS];
-  float lsum[MERGE_ROWS], mmax[MERGE_ROWS];
-#pragma unroll
-  for (int i = 0; i < MERGE_ROWS; ++i) {
-    acc[i] = 0.f;
+  for (int i = 0; i < ROWS; ++i) {  // (a row past the end repeats the last one and is not stored)
+    const int64_t prow = (int64_t)(mg.part_row0 + min(r0 + i, mg.nrows - 1)) * n_kv_heads + g;
+    p[i] = (const float4*)(parts + prow * D) + lane;
+    ml[i] = (const float2*)parts_ml + prow;
+    acc[i] = make_float4(0.f, 0.f, 0.f, 0.f);
     lsum[i] = 0.f;
-    float m = -INFINITY;
-    for (int s = lane; s < mg.nsplit; s += 64) m = fmaxf(m, ml0[i][s * srow * 2]);
-    mmax[i] = m;
+    m[i] = -INFINITY;
   }
+  for (int s0 = 0; s0 < mg.nsplit; s0 += AHEAD) {
+    float4 v[ROWS][AHEAD];
+    float2 w[ROWS][AHEAD];
 #pragma unroll
-  for (int off = 32; off; off >>= 1)
+    for (int k = 0; k < AHEAD; ++k) {  // (a split past the end repeats the last one with weight zero)
+      const int64_t at = min(s0 + k, mg.nsplit - 1) * srow;
 #pragma unroll
-    for (int i = 0; i < MERGE_ROWS; ++i) mmax[i] = fmaxf(mmax[i], __shfl_xor(mmax[i], off));
-
-  for (int s0 = 0; s0 < mg.nsplit; s0 += 64) {
-    const int mine = s0 + lane;
-    float w_mine[MERGE_ROWS];
-#pragma unroll
-    for (int i = 0; i < MERGE_ROWS; ++i) {
-      w_mine[i] = 0.f;
-      if (mine < mg.nsplit) {
-        const float2 ml = *(const float2*)(ml0[i] + mine * srow * 2);  // second touch: served from cache
-        w_mine[i] = (ml.x == -INFINITY) ? 0.f : exp2f(ml.x - mmax[i]);
-        lsum[i] += w_mine[i] * ml.y;
+      for (int i = 0; i < ROWS; ++i) {
+        w[i][k] = ml[i][at];
+        v[i][k] = p[i][at * LANES];
       }
     }
-    const int cnt = min(64, mg.nsplit - s0);
-    int s = 0;
-    for (; s + 2 <= cnt; s += 2) {
-      vec v0[MERGE_ROWS], v1[MERGE_ROWS];
 #pragma unroll
-      for (int i = 0; i < MERGE_ROWS; ++i) {
-        v0[i] = *(const vec*)(p0[i] + (s0 + s) * stride);
-        v1[i] = *(const vec*)(p0[i] + (s0 + s + 1) * stride);
+    for (int i = 0; i < ROWS; ++i) {
+      float mn = m[i];
+#pragma unroll
+      for (int k = 0; k < AHEAD; ++k) {
+        if (s0 + k >= mg.nsplit) w[i][k] = make_float2(-INFINITY, 0.f);
+        mn = fmaxf(mn, w[i][k].x);
       }
+      const float ms = (mn == -INFINITY) ? 0.f : mn;
+      const float a = exp2f(m[i] - ms);
+      m[i] = mn;
+      lsum[i] *= a;
+      acc[i].x *= a;
+      acc[i].y *= a;
+      acc[i].z *= a;
+      acc[i].w *= a;
 #pragma unroll
-      for (int i = 0; i < MERGE_ROWS; ++i) {
-        const float w0 = __shfl(w_mine[i], s), w1 = __shfl(w_mine[i], s + 1);
-        acc[i] += w0 * v0[i] + w1 * v1[i];
-      }
-    }
-    if (s < cnt) {
-#pragma unroll
-      for (int i = 0; i < MERGE_ROWS; ++i) {
-        const vec v = *(const vec*)(p0[i] + (s0 + s) * stride);
-        const float w = __shfl(w_mine[i], s);
-        acc[i] += w * v;
+      for (int k = 0; k < AHEAD; ++k) {
+        if (s0 + k >= mg.nsplit) continue;
+        const float f = exp2f(w[i][k].x - ms);
+        lsum[i] += f * w[i][k].y;
+        acc[i].x += f * v[i][k].x;
+        acc[i].y += f * v[i][k].y;
+        acc[i].z += f * v[i][k].z;
+        acc[i].w += f * v[i][k].w;
       }
     }
   }
 #pragma unroll
-  for (int off = 32; off; off >>= 1)
-#pragma unroll
-    for (int i = 0; i < MERGE_ROWS; ++i) lsum[i] += __shfl_xor(lsum[i], off);
-
-#pragma unroll
-  for (int i = 0; i < MERGE_ROWS; ++i) {
-    if (!live[i]) continue;
+  for (int i = 0; i < ROWS; ++i) {
+    if (r0 + i >= mg.nrows) continue;
     const int row = mg.row0 + r0 + i;
-    const int tok = e.tok0 + row / group;
+    const int tok = mg.tok0 + row / group;
     const int h = g * group + row % group;
     const float inv = 1.f / lsum[i];
-    T* o = out + ((int64_t)tok * n_q_heads + h) * D + lane * (D / 64);
-#pragma unroll
-    for (int u = 0; u < D / 64; ++u) store_out(o + u, acc[i][u] * inv);
-    if (lse && lane == 0) lse[(int64_t)tok * n_q_heads + h] = (mmax[i] + log2f(lsum[i])) * 0.6931471805599453f;
+    store_quad(out + ((int64_t)tok * n_q_heads + h) * D + lane * 4,
+               make_float4(acc[i].x * inv, acc[i].y * inv, acc[i].z * inv, acc[i].w * inv));
+    if (lse && lane == 0) lse[(int64_t)tok * n_q_heads + h] = (m[i] + log2f(lsum[i])) * 0.6931471805599453f;
   }
 }
 
+namespace {
+
+template <typename T, int D, int ROWS, int AHEAD>
+hipError_t launch_merge(const AttendArgs& a, const DkMerge* merges, int32_t n_merges, int32_t max_rows, hipStream_t stream) {
+  constexpr int rows_per_block = 1024 / D * ROWS;
+  const dim3 grid((unsigned)n_merges, (unsigned)a.arena.n_kv_heads, (unsigned)((max_rows + rows_per_block - 1) / rows_per_block));
+  if (a.inline_blob)
+    attend_merge_kernel<T, D, ROWS, AHEAD, true><<<grid, 256, 0, stream>>>(
+        BlobParam<true>{*a.inline_blob}, merges, a.parts, a.parts_ml, (T*)a.out, a.lse, a.arena.n_q_heads, a.arena.n_kv_heads);
+  else
+    attend_merge_kernel<T, D, ROWS, AHEAD, false><<<grid, 256, 0, stream>>>(
+        BlobParam<false>{0}, merges, a.parts, a.parts_ml, (T*)a.out, a.lse, a.arena.n_q_heads, a.arena.n_kv_heads);
+  return hipGetLastError();
+}
+
+}  // namespace
+
 hipError_t launch_attend_merge(const AttendArgs& a, const DkMerge* merges, int32_t n_merges, int32_t max_rows,
-                               hipStream_t stream) {
+                               int32_t max_split, hipStream_t stream) {
   if (n_merges <= 0) return hipSuccess;
   if (max_rows <= 0) return hipErrorInvalidValue;
-  const int rows_per_block = 4 * MERGE_ROWS;
-  dim3 grid((unsigned)n_merges, (unsigned)a.arena.n_kv_heads, (unsigned)((max_rows + rows_per_block - 1) / rows_per_block));
-#define DK_MERGE(T, D)                                                                                                  \
-  do {                                                                                                               \
-    if (a.inline_blob)                                                                                               \
-      attend_merge_kernel<T, D, true><<<grid, 256, 0, stream>>>(BlobParam<true>{*a.inline_blob}, merges, a.entries,     \
-                                                             a.parts, a.parts_ml, (T*)a.out, a.lse,             \
-                                                             a.arena.n_q_heads, a.arena.n_kv_heads);                 \
-    else                                                                                                             \
-      attend_merge_kernel<T, D, false><<<grid, 256, 0, stream>>>(BlobParam<false>{0}, merges, a.entries, a.parts,       \
-                                                              a.parts_ml, (T*)a.out, a.lse, a.arena.n_q_heads,  \
-                                                              a.arena.n_kv_heads);                                   \
-  } while (0)
+#define DK_MERGE(T, D)                                                                   \
+  return max_split > 4 ? launch_merge<T, D, 1, 8>(a, merges, n_merges, max_rows, stream) \
+                       : launch_merge<T, D, 2, 4>(a, merges, n_merges, max_rows, stream)
   if (a.arena.dtype == 0 && a.arena.head_dim == 64) DK_MERGE(float, 64);
-  else if (a.arena.dtype == 0 && a.arena.head_dim == 128) DK_MERGE(float, 128);
-  else if (a.arena.dtype == 1 && a.arena.head_dim == 64) DK_MERGE(__bf16, 64);
-  else if (a.arena.dtype == 1 && a.arena.head_dim == 128) DK_MERGE(__bf16, 128);
-  else return hipErrorInvalidValue;
+  if (a.arena.dtype == 0 && a.arena.head_dim == 128) DK_MERGE(float, 128);
+  if (a.arena.dtype == 1 && a.arena.head_dim == 64) DK_MERGE(__bf16, 64);
+  if (a.arena.dtype == 1 && a.arena.head_dim == 128) DK_MERGE(__bf16, 128);
 #undef DK_MERGE
-  return hipGetLastError();
+  return hipErrorInvalidValue;
 }
 
 }  // namespace dk

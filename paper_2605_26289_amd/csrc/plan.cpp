@@ -31,7 +31,7 @@ void cut_stream_items(const std::vector<RowTile>& tiles, int32_t kv_tile, int32_
     if (ns > 1) {
       part0 = (int32_t)*part_rows;
       *part_rows += (int64_t)ns * t.nrows;
-      merges->push_back({t.entry, t.row0, t.nrows, part0, ns, {0, 0, 0}});
+      merges->push_back({t.entry, t.row0, t.nrows, part0, ns, 0, {0, 0}});
     }
     for (int32_t sp = 0; sp < ns; ++sp) {
       DkItem it{};
@@ -204,7 +204,7 @@ void cut_tile_items(AttendPlan* p, const PlanConfig& cfg) {
     if (count[t] > 1) {
       part0[t] = (int32_t)p->part_rows;
       p->part_rows += (int64_t)count[t] * tiles[t].nrows;
-      p->merges.push_back({tiles[t].entry, tiles[t].row0, tiles[t].nrows, part0[t], count[t], {0, 0, 0}});
+      p->merges.push_back({tiles[t].entry, tiles[t].row0, tiles[t].nrows, part0[t], count[t], 0, {0, 0}});
       count[t] = 0;  // from here on: pieces of the tile emitted so far
     } else {
       count[t] = -1;
@@ -292,6 +292,7 @@ int32_t build_plan(Pool& pool, const PlanConfig& cfg, int32_t n_seqs, const int3
   cut_tile_items(p, cfg);
   cut_stream_items(stream_tiles, cfg.kv_tile, cfg.stream_target, cfg.stream_min_chunk, &p->stream_items, &p->merges,
                    &p->part_rows);
+  for (DkMerge& m : p->merges) m.tok0 = p->entries[(size_t)m.entry].tok0;
   // Streaming units: with at least four units per workgroup they form a queue that the workgroups draw from at
   // run time (measured: +3-5 % on 700 decode slots, +1.5 % on 2048, because the compute units do not stream equally
   // fast; with two units per workgroup, as in a 64-slot verification batch, the queue has nothing to balance with
