@@ -113,6 +113,7 @@ struct dk_pool {
     if (r == Route::kGeneral) {
       // block kernel: items of 128 rows, two workgroups on a compute unit; an item's fixed cost (first tiles, merge of
       // the half-waves, store) is about three of its shorter key steps
+      c.small_units = 0;
       c.tile_rows = 128;
       c.tile_wave_slots = 2 * cfg.tile_wave_slots;
       c.tile_item_cost = std::min(cfg.tile_item_cost, 3);
@@ -127,6 +128,7 @@ struct dk_pool {
         for (int32_t b = 0; b < n_seqs; ++b) items += (group * ((int64_t)cu_delta[b + 1] - cu_delta[b]) + 31) / 32;
       c.tile_rows = items * desc.n_kv_heads >= 256 ? 32 : 16;
       c.stream_rows = 0;
+      c.small_units = 0;
       c.tile_min_chunk = std::max(cfg.tile_min_chunk, 65536 / desc.head_dim);
     }
     return c;
@@ -263,6 +265,7 @@ int32_t dk_pool_create(const dk_pool_desc* desc, dk_pool** pool_out) {
     // than the even ones while the whole chip pulls on HBM: chains planned on the host give them that much less.
     for (int x = 0; x < 8; ++x) c.xcd_speed[x] = (x & 1) ? 0.95f : 1.f;
     c.stream_queue = 1;
+    c.small_units = 256;
     c.inline_blob_bytes = dk::INLINE_BLOB_BYTES;
     *pool_out = p;
     return DK_OK;
@@ -556,7 +559,7 @@ int32_t attend_locked(dk_pool* pool, int32_t n_seqs, const int32_t* slots, const
   put(plan.off_tile, plan.tile_items.data(), plan.tile_items.size() * sizeof(DkItem));
   put(plan.off_tile_links, plan.tile_links.data(), plan.tile_links.size() * sizeof(int32_t));
   put(plan.off_stream, plan.stream_items.data(), plan.stream_items.size() * sizeof(DkItem));
-  put(plan.off_links, plan.stream_links.data(), plan.stream_links.size() * sizeof(int32_t));
+  if (!plan.stream_single) put(plan.off_links, plan.stream_links.data(), plan.stream_links.size() * sizeof(int32_t));
   put(plan.off_merges, plan.merges.data(), plan.merges.size() * sizeof(DkMerge));
   if (plan.stream_queued) {  // the queue's counter: the first stream_chains units are taken when the kernel starts
     const int32_t first[4] = {plan.stream_chains, 0, 0, 0};
@@ -617,7 +620,7 @@ int32_t attend_locked(dk_pool* pool, int32_t n_seqs, const int32_t* slots, const
     int32_t stream_rows = 0;
     for (const DkItem& it : plan.stream_items) stream_rows = std::max(stream_rows, it.nrows);
     e = dk::launch_attend_stream(a, (const DkItem*)(desc + plan.off_stream), (const int32_t*)(desc + plan.off_links),
-                                 plan.stream_chains, stream_rows,
+                                 plan.stream_single, plan.stream_chains, stream_rows,
                                  plan.stream_queued ? (int32_t*)(ws + plan.off_queue) : nullptr,
                                  (int32_t)plan.stream_units, st);
     if (e != hipSuccess) return fail(pool->hip_fail(e));

@@ -242,7 +242,8 @@ __device__ __forceinline__ void compute_tile(const TileFrags<HD>& f, const QFrag
 // barrier (no wavefront reads the current Q any more then), and the second tile as soon as the merge buffer
 // has been read.  The merge thus runs under the latency of those requests instead of in front of it.
 //
-// Which unit comes next.  Small launches (descriptors in the kernel arguments) walk the chains the planner linked.
+// Which unit comes next.  With at most one unit per workgroup there is none; otherwise small launches (descriptors in
+// the kernel arguments) walk the chains the planner linked.
 // Otherwise the units form one queue, longest first: workgroup w starts with unit w and every further unit is
 // drawn from a counter in device memory (uploaded with the descriptors, starting at the number of workgroups) by
 // one atomic add.  The compute units do not stream equally fast -- by 10 % and more between XCDs, differently from
@@ -325,7 +326,8 @@ __global__ __launch_bounds__(256, 1) void attend_stream_kernel(BlobArg<INLINE> b
   (void)trace_seq;
 
   // ---- the unit being streamed, and the requests that open a unit ----------------------------------
-  int unit = queued ? (int)blockIdx.x : load_desc(links, blockIdx.x);
+  const bool single = n_chains == 0;  // one unit per workgroup, no links
+  int unit = queued || single ? (int)blockIdx.x : load_desc(links, blockIdx.x);
   DkItem it = load_desc(c.items, unit / c.n_kv_heads);
   DkEntry e = load_desc(c.entries, it.entry);
   int g = unit % c.n_kv_heads;
@@ -375,7 +377,7 @@ __global__ __launch_bounds__(256, 1) void attend_stream_kernel(BlobArg<INLINE> b
     int next_unit = -1;
     DkItem next_it = it;
     DkEntry next_e = e;
-    if (!queued) {
+    if (!queued && !single) {
       next_unit = load_desc(links, n_chains + unit);
       if (next_unit >= 0) {
         next_it = load_desc(c.items, next_unit / c.n_kv_heads);
@@ -596,8 +598,8 @@ __global__ __launch_bounds__(256, 1) void attend_stream_kernel(BlobArg<INLINE> b
 namespace {
 
 template <int MB, int HD, bool GEN, bool INLINE>
-hipError_t launch_one(const BlobArg<INLINE>& blob, const Ctx& c, const int32_t* links, int32_t n_chains, int32_t* queue,
-                      int32_t n_units, hipStream_t stream) {
+hipError_t launch_one(const BlobArg<INLINE>& blob, const Ctx& c, const int32_t* links, bool single, int32_t n_chains,
+                      int32_t* queue, int32_t n_units, hipStream_t stream) {
   // once per process and instantiation, whatever thread or pool gets here first
   static std::once_flag once;
   static hipError_t status = hipSuccess;
@@ -607,32 +609,34 @@ hipError_t launch_one(const BlobArg<INLINE>& blob, const Ctx& c, const int32_t* 
   });
   if (status != hipSuccess) return status;
   attend_stream_kernel<MB, HD, GEN, INLINE>
-      <<<dim3((unsigned)n_chains), 256, STREAM_LDS_BYTES, stream>>>(blob, c, links, n_chains, queue, n_units);
+      <<<dim3((unsigned)n_chains), 256, STREAM_LDS_BYTES, stream>>>(blob, c, links, single ? 0 : n_chains, queue, n_units);
   return hipGetLastError();
 }
 
 template <int HD, bool GEN, bool INLINE>
 hipError_t launch_rows(int32_t max_rows, const BlobArg<INLINE>& blob, const Ctx& c, const int32_t* links,
-                       int32_t n_chains, int32_t* queue, int32_t n_units, hipStream_t stream) {
-  if (max_rows <= 32) return launch_one<1, HD, GEN, INLINE>(blob, c, links, n_chains, queue, n_units, stream);
-  if (max_rows <= 64) return launch_one<2, HD, GEN, INLINE>(blob, c, links, n_chains, queue, n_units, stream);
-  return launch_one<3, HD, GEN, INLINE>(blob, c, links, n_chains, queue, n_units, stream);
+                       bool single, int32_t n_chains, int32_t* queue, int32_t n_units, hipStream_t stream) {
+  if (max_rows <= 32) return launch_one<1, HD, GEN, INLINE>(blob, c, links, single, n_chains, queue, n_units, stream);
+  if (max_rows <= 64) return launch_one<2, HD, GEN, INLINE>(blob, c, links, single, n_chains, queue, n_units, stream);
+  return launch_one<3, HD, GEN, INLINE>(blob, c, links, single, n_chains, queue, n_units, stream);
 }
 
 template <bool INLINE>
 hipError_t launch_shape(const AttendArgs& a, int32_t max_rows, const BlobArg<INLINE>& blob, const Ctx& c,
-                        const int32_t* links, int32_t n_chains, int32_t* queue, int32_t n_units, hipStream_t stream) {
-  if (a.arena.head_dim == 64) return launch_rows<64, true, INLINE>(max_rows, blob, c, links, n_chains, queue, n_units, stream);
-  if (a.general) return launch_rows<128, true, INLINE>(max_rows, blob, c, links, n_chains, queue, n_units, stream);
-  return launch_rows<128, false, INLINE>(max_rows, blob, c, links, n_chains, queue, n_units, stream);
+                        const int32_t* links, bool single, int32_t n_chains, int32_t* queue, int32_t n_units,
+                        hipStream_t stream) {
+  if (a.arena.head_dim == 64) return launch_rows<64, true, INLINE>(max_rows, blob, c, links, single, n_chains, queue, n_units, stream);
+  if (a.general) return launch_rows<128, true, INLINE>(max_rows, blob, c, links, single, n_chains, queue, n_units, stream);
+  return launch_rows<128, false, INLINE>(max_rows, blob, c, links, single, n_chains, queue, n_units, stream);
 }
 
 }  // namespace
 
 }  // namespace mfma
 
-hipError_t launch_attend_stream(const AttendArgs& a, const DkItem* items, const int32_t* links, int32_t n_chains,
-                                int32_t max_rows, int32_t* queue, int32_t n_units, hipStream_t stream) {
+hipError_t launch_attend_stream(const AttendArgs& a, const DkItem* items, const int32_t* links, bool single,
+                                int32_t n_chains, int32_t max_rows, int32_t* queue, int32_t n_units,
+                                hipStream_t stream) {
   using namespace mfma;
   if (n_chains <= 0) return hipSuccess;
   if (a.arena.dtype != 1 || max_rows > STREAM_MAX_MB * 32) return hipErrorInvalidValue;
@@ -640,8 +644,8 @@ hipError_t launch_attend_stream(const AttendArgs& a, const DkItem* items, const 
   if (queue && a.inline_blob) return hipErrorInvalidValue;  // the queue's counter needs device memory
   const Ctx c = make_ctx(a, items);
   if (a.inline_blob)
-    return launch_shape<true>(a, max_rows, BlobArg<true>{*a.inline_blob}, c, links, n_chains, queue, n_units, stream);
-  return launch_shape<false>(a, max_rows, BlobArg<false>{0}, c, links, n_chains, queue, n_units, stream);
+    return launch_shape<true>(a, max_rows, BlobArg<true>{*a.inline_blob}, c, links, single, n_chains, queue, n_units, stream);
+  return launch_shape<false>(a, max_rows, BlobArg<false>{0}, c, links, single, n_chains, queue, n_units, stream);
 }
 
 }  // namespace dk

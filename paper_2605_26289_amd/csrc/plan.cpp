@@ -235,6 +235,93 @@ void cut_tile_items(AttendPlan* p, const PlanConfig& cfg) {
     }
   }
 }
+// Small batches: what they take is latency, not bandwidth or arithmetic.  A unit of the streaming kernel costs a fixed
+// part (descriptors, first requests, merge of the four wavefronts, store) and then about a microsecond per 128 keys,
+// nearly independent of how many rows it serves -- a compute unit takes in 64 KiB of K/V per microsecond, half of what a
+// tile-kernel step of the same keys lasts -- so while every unit can have a compute unit of its own, short row tiles on
+// many compute units beat long ones on few, and a turn of a few hundred rows runs better here than in the tile kernel,
+// which pays 9 us an item, 1.8 us per 64 keys and mostly a merge launch.  Measured, one 150-token turn of one session
+// (32 query heads on 8 KV heads, us per step, tile kernel / 32-row units): 300 cached tokens 28.7 / 18.3, 800 33.5 / 17.8,
+// 2000 36 / 24, 4000 45 / 37, 8000 51 / 66; 300 tokens on 1500: 42 / 33 (64-row units); 20 tokens on 4000: 28 / 21.
+// The constants are those measurements, in microseconds; the plan of least estimated time is taken.
+struct StreamShape {
+  int32_t rows = 0;   // rows per streaming tile; 0: none found
+  int32_t chunk = 0;  // keys per unit
+  double us = 0;
+};
+constexpr double kUnitFixed[4] = {0, 8.5, 9.0, 10.0};    // by row blocks of 32
+constexpr double kUnitPer128[4] = {0, 1.08, 1.45, 2.0};  // per 128 keys
+constexpr double kMergeUs = 5.0, kMergeSplitUs = 0.1;    // merge launch, and each split it reads
+constexpr double kKeysPerUs = 10500.0;                   // all compute units together, from HBM (5.4 TB/s)
+
+double stream_us(int32_t tile_rows, int64_t longest, int64_t chunk, int64_t unit_keys) {
+  const int mb = std::min(3, (tile_rows + 31) / 32);
+  const int64_t split = (longest + chunk - 1) / chunk;
+  const double walk = std::max(kUnitPer128[mb] * (double)std::min(longest, chunk) / 128.0, (double)unit_keys / kKeysPerUs);
+  return kUnitFixed[mb] + walk + (split > 1 ? kMergeUs + kMergeSplitUs * (double)split : 0.0);
+}
+
+// Descriptor bytes of a plan, alignment padding included.
+size_t blob_estimate(const AttendPlan& p, bool with_cells, size_t tile_items, size_t stream_items, size_t links, size_t merges) {
+  return p.entries.size() * sizeof(DkEntry) + p.segs.size() * sizeof(DkSeg) + (tile_items + stream_items) * sizeof(DkItem) +
+         merges * sizeof(DkMerge) + (links + (with_cells ? (size_t)p.total_tokens : 0)) * sizeof(int32_t) + 8 * 16;
+}
+
+// The best way to run the whole batch through the streaming kernel with at most one unit per workgroup and at most
+// max_blob bytes of descriptors.
+StreamShape small_shape(const AttendPlan& p, const PlanConfig& cfg, int32_t group, bool with_cells, size_t max_blob) {
+  StreamShape best;
+  int32_t most_rows = 0;
+  int64_t longest = 0;
+  for (const DkEntry& e : p.entries)
+    if (e.delta > 0) {
+      most_rows = std::max(most_rows, group * e.delta);
+      longest = std::max<int64_t>(longest, (int64_t)e.n + e.delta);
+    }
+  if (most_rows == 0) return best;
+  static const int32_t splits[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32};
+  for (int32_t r = 32; r <= 96; r += 32) {
+    if (r > 32 && r - 32 >= most_rows) break;
+    for (const int32_t k : splits) {
+      const int64_t chunk = ((longest + k - 1) / k + cfg.kv_tile - 1) / cfg.kv_tile * cfg.kv_tile;
+      if (k > 1 && chunk < 128) break;
+      int64_t units = 0, keys = 0, merges = 0;
+      for (const DkEntry& e : p.entries)
+        if (e.delta > 0) {
+          const int64_t tiles = ((int64_t)group * e.delta + r - 1) / r, n = (int64_t)e.n + e.delta;
+          units += tiles * ((n + chunk - 1) / chunk);
+          keys += n;  // (further tiles of the same rows find the keys in L2)
+          if (n > chunk) merges += tiles;
+        }
+      if (units * cfg.n_kv_heads > std::min(cfg.small_units, cfg.stream_chains)) break;
+      if (blob_estimate(p, with_cells, 0, (size_t)units, 0, (size_t)merges) > max_blob) continue;
+      const double us = stream_us(std::min(r, most_rows), longest, chunk, keys * cfg.n_kv_heads);
+      if (best.rows == 0 || us < best.us) best = {r, (int32_t)chunk, us};
+    }
+  }
+  return best;
+}
+
+// Estimated time of the plan that the rules for large batches make.
+double planned_us(const AttendPlan& p, const PlanConfig& cfg) {
+  double us = 0;
+  if (p.tile_chains > 0) {
+    const int64_t load = *std::max_element(p.chain_load.begin(), p.chain_load.end());
+    us += 10.0 + 1.8 * (double)load;
+  }
+  if (!p.stream_items.empty()) {
+    int32_t rows = 0;
+    int64_t longest = 0, keys = 0;
+    for (const DkItem& it : p.stream_items) {
+      rows = std::max(rows, it.nrows);
+      longest = std::max<int64_t>(longest, it.kv_hi - it.kv_lo);
+      keys += it.kv_hi - it.kv_lo;
+    }
+    us += stream_us(rows, longest, longest, keys * cfg.n_kv_heads);
+  }
+  if (!p.merges.empty()) us += kMergeUs + 2.0;
+  return us;
+}
 }  // namespace
 
 int32_t build_plan(Pool& pool, const PlanConfig& cfg, int32_t n_seqs, const int32_t* slots, const int32_t* cu_delta,
@@ -292,6 +379,33 @@ int32_t build_plan(Pool& pool, const PlanConfig& cfg, int32_t n_seqs, const int3
   cut_tile_items(p, cfg);
   cut_stream_items(stream_tiles, cfg.kv_tile, cfg.stream_target, cfg.stream_min_chunk, &p->stream_items, &p->merges,
                    &p->part_rows);
+  if (cfg.small_units > 0 && (int64_t)(tile_tiles.size() + stream_tiles.size()) * cfg.n_kv_heads <= cfg.small_units) {
+    // (a call whose descriptors travel in the kernel arguments goes on doing so)
+    const size_t units = p->stream_items.size() * (size_t)cfg.n_kv_heads;
+    const size_t chains = std::min(units, (size_t)std::max(cfg.stream_chains, 1));
+    const size_t links = p->tile_links.size() + (units == chains ? 0 : units + chains);
+    const size_t blob = blob_estimate(*p, with_cells, p->tile_items.size(), p->stream_items.size(), links, p->merges.size());
+    const StreamShape s = small_shape(*p, cfg, group, with_cells,
+                                      blob <= (size_t)cfg.inline_blob_bytes ? (size_t)cfg.inline_blob_bytes : SIZE_MAX);
+    if (s.rows > 0 && s.us < planned_us(*p, cfg)) {
+      p->tile_items.clear();
+      p->tile_links.clear();
+      p->tile_chains = 0;
+      p->stream_items.clear();
+      p->merges.clear();
+      p->part_rows = 0;
+      stream_tiles.clear();
+      for (int32_t ei = 0; ei < (int32_t)p->entries.size(); ++ei) {
+        const DkEntry& e = p->entries[ei];
+        const int32_t rows = group * e.delta;
+        for (int32_t r0 = 0; r0 < rows; r0 += s.rows) {
+          const int32_t nr = std::min(s.rows, rows - r0);
+          stream_tiles.push_back({ei, r0, nr, e.n + (r0 + nr - 1) / group + 1});
+        }
+      }
+      cut_stream_items(stream_tiles, cfg.kv_tile, INT32_MAX, s.chunk, &p->stream_items, &p->merges, &p->part_rows);
+    }
+  }
   for (DkMerge& m : p->merges) m.tok0 = p->entries[(size_t)m.entry].tok0;
   // Streaming units: with at least four units per workgroup they form a queue that the workgroups draw from at
   // run time (measured: +3-5 % on 700 decode slots, +1.5 % on 2048, because the compute units do not stream equally
@@ -311,6 +425,7 @@ int32_t build_plan(Pool& pool, const PlanConfig& cfg, int32_t n_seqs, const int3
   } else {
     chain_units(p->stream_items, cfg, p->heap, p->tail, &p->stream_links, &p->stream_chains);
   }
+  p->stream_single = !p->stream_queued && p->stream_units == p->stream_chains;
 
   size_t off = 0;
   p->off_entries = off;
@@ -324,7 +439,7 @@ int32_t build_plan(Pool& pool, const PlanConfig& cfg, int32_t n_seqs, const int3
   p->off_stream = off;
   off = align_up(off + p->stream_items.size() * sizeof(DkItem), 16);
   p->off_links = off;
-  off = align_up(off + p->stream_links.size() * sizeof(int32_t), 16);
+  if (!p->stream_single) off = align_up(off + p->stream_links.size() * sizeof(int32_t), 16);
   p->off_merges = off;
   off = align_up(off + p->merges.size() * sizeof(DkMerge), 16);
   p->off_queue = off;

@@ -26,6 +26,7 @@ struct PlanConfig {
   int32_t stream_item_cost;  // fixed cost of an item in the chain balance, in keys
   float xcd_speed[8];        // relative K/V streaming rate of the XCD that workgroup w lands on (w % 8)
   int32_t stream_queue;      // 1: streaming units are drawn from a queue at run time when the blob is uploaded
+  int32_t small_units;       // a batch of at most this many streaming units may be planned as a small one (0: never)
   int32_t inline_blob_bytes; // a descriptor blob up to this size travels in the kernel arguments
 };
 
@@ -65,6 +66,8 @@ struct AttendPlan {
   // ... or, when stream_queued, starts with unit w and draws every further unit from a counter (off_queue, one
   // int32 that is uploaded holding stream_chains): the units are in longest-first order, no links are built.
   bool stream_queued = false;
+  // ... or has one unit per workgroup, unit w for workgroup w: the links say nothing and are not part of the blob.
+  bool stream_single = false;
   int64_t stream_units = 0;
   size_t off_queue = 0;
   // Tile kernel: tile_wave_slots workgroups per KV head, workgroup c of a head walks the items
