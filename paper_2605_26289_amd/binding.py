@@ -41,6 +41,9 @@ _lib = None
 
 _I32P = C.POINTER(C.c_int32)
 _I64P = C.POINTER(C.c_int64)
+# Arrays the binding marshals on every step are passed as plain addresses: making a typed ctypes pointer for each costs
+# about a microsecond, and a small call is a dozen microseconds altogether.
+_ARRAY = C.c_void_p
 
 SIGNATURES = {
     "dk_meta_bytes": (C.c_int32, [C.POINTER(PoolDesc), _I64P]),
@@ -53,15 +56,15 @@ SIGNATURES = {
     "dk_seq_len": (C.c_int32, [C.c_void_p, C.c_int32, _I64P]),
     "dk_seq_alias": (C.c_int32, [C.c_void_p, C.c_int32, C.c_int32, C.c_int64, C.c_int64]),
     "dk_seq_trim": (C.c_int32, [C.c_void_p, C.c_int32, C.c_int64]),
-    "dk_seq_trim_batch": (C.c_int32, [C.c_void_p, C.c_int32, _I32P, _I64P]),
-    "dk_kv_append": (C.c_int32, [C.c_void_p, C.c_int32, _I32P, _I32P, _I32P, C.c_void_p, C.c_void_p, C.c_void_p]),
-    "dk_kv_reserve": (C.c_int32, [C.c_void_p, C.c_int32, _I32P, _I32P, _I32P, _I64P]),
-    "dk_attend_workspace_bytes": (C.c_int32, [C.c_void_p, C.c_int32, _I32P, _I32P, C.c_int32, _I64P]),
-    "dk_delta_attend": (C.c_int32, [C.c_void_p, C.c_int32, _I32P, _I32P, C.c_void_p, C.c_void_p, C.c_void_p,
+    "dk_seq_trim_batch": (C.c_int32, [C.c_void_p, C.c_int32, _ARRAY, _ARRAY]),
+    "dk_kv_append": (C.c_int32, [C.c_void_p, C.c_int32, _ARRAY, _ARRAY, _ARRAY, C.c_void_p, C.c_void_p, C.c_void_p]),
+    "dk_kv_reserve": (C.c_int32, [C.c_void_p, C.c_int32, _ARRAY, _ARRAY, _ARRAY, _ARRAY]),
+    "dk_attend_workspace_bytes": (C.c_int32, [C.c_void_p, C.c_int32, _ARRAY, _ARRAY, C.c_int32, _I64P]),
+    "dk_delta_attend": (C.c_int32, [C.c_void_p, C.c_int32, _ARRAY, _ARRAY, C.c_void_p, C.c_void_p, C.c_void_p,
                                     C.c_float, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int64, C.c_void_p]),
-    "dk_append_attend": (C.c_int32, [C.c_void_p, C.c_int32, _I32P, _I32P, C.c_void_p, C.c_void_p, C.c_void_p,
+    "dk_append_attend": (C.c_int32, [C.c_void_p, C.c_int32, _ARRAY, _ARRAY, C.c_void_p, C.c_void_p, C.c_void_p,
                                      C.c_float, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int64, C.c_void_p]),
-    "dk_delta_attend_noalloc": (C.c_int32, [C.c_void_p, C.c_int32, _I32P, _I32P, C.c_void_p, C.c_void_p, C.c_void_p,
+    "dk_delta_attend_noalloc": (C.c_int32, [C.c_void_p, C.c_int32, _ARRAY, _ARRAY, C.c_void_p, C.c_void_p, C.c_void_p,
                                             C.c_float, C.c_void_p, C.c_void_p, C.c_void_p]),
     "dk_staging_wait": (C.c_int32, [C.c_void_p]),
     "dk_seq_cells": (C.c_int32, [C.c_void_p, C.c_int32, _I64P, C.c_int64]),
@@ -130,9 +133,19 @@ def _ptr(t) -> Optional[int]:
     return None if t is None else int(t.data_ptr())
 
 
+def _array(values, dtype=np.int32):
+    """(array kept alive by the caller, its address) for an argument declared _ARRAY"""
+    if values is None:
+        return None, None
+    arr = np.ascontiguousarray(values, dtype=dtype)
+    return arr, arr.ctypes.data
+
+
 def _stream(stream) -> Optional[int]:
     if stream is None:
         import torch
+        if torch.cuda.is_initialized():  # the handle alone: building a Stream object takes 3 us
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()) or None
         stream = torch.cuda.current_stream()
     h = int(stream.cuda_stream) if hasattr(stream, "cuda_stream") else int(stream)
     return h or None
@@ -155,15 +168,16 @@ def set_tuning(pool, name: str, value: float) -> None:
     _check(lib().dk_set_tuning(pool, name.encode(), float(value)), f"set_tuning({name})")
 
 
-def _launch(call, where: str, pool, stream):
+def _launch(call, args, where: str, pool):
     """Runs a launching call; when every staging buffer is still in flight (BUSY) waits for one to come free and repeats.
     The C ABI itself never waits: back-pressure is the caller's policy, and this is the binding's."""
-    rc = call()
+    rc = call(*args)
     while rc == BUSY:
         # wait for the oldest upload only: the work queued behind it keeps the device busy meanwhile
         _check(lib().dk_staging_wait(pool), "staging_wait", pool)
-        rc = call()
-    _check(rc, where, pool)
+        rc = call(*args)
+    if rc != OK:
+        _check(rc, where, pool)
 
 
 def staging_wait(pool) -> None:
@@ -205,9 +219,9 @@ def seq_trim(pool, slot: int, new_len: int) -> None:
 
 
 def seq_trim_batch(pool, slots, new_len) -> None:
-    s_arr, s_p = _i32(slots)
-    n_arr = np.ascontiguousarray(new_len, dtype=np.int64)
-    _check(lib().dk_seq_trim_batch(pool, len(s_arr), s_p, n_arr.ctypes.data_as(_I64P)), "seq_trim_batch")
+    s_arr, s_p = _array(slots)
+    n_arr, n_p = _array(new_len, np.int64)
+    _check(lib().dk_seq_trim_batch(pool, len(s_arr), s_p, n_p), "seq_trim_batch")
 
 
 def seq_cells(pool, slot: int) -> np.ndarray:
@@ -232,27 +246,26 @@ def pool_stats(pool):
 
 # --------------------------------------------------------------------------- GPU calls
 def kv_append(pool, slots, cu_delta, k_new, v_new, n_accept=None, stream=None) -> None:
-    s_arr, s_p = _i32(slots)
-    c_arr, c_p = _i32(cu_delta)
-    a_arr, a_p = _i32(n_accept)
-    st = _stream(stream)
-    _launch(lambda: lib().dk_kv_append(pool, len(s_arr), s_p, c_p, a_p, _ptr(k_new), _ptr(v_new), st),
-            "kv_append", pool, stream)
+    s_arr, s_p = _array(slots)
+    c_arr, c_p = _array(cu_delta)
+    a_arr, a_p = _array(n_accept)
+    _launch(lib().dk_kv_append, (pool, len(s_arr), s_p, c_p, a_p, _ptr(k_new), _ptr(v_new), _stream(stream)),
+            "kv_append", pool)
 
 
 def kv_reserve(pool, slots, cu_delta, n_accept=None) -> np.ndarray:
-    s_arr, s_p = _i32(slots)
-    c_arr, c_p = _i32(cu_delta)
-    a_arr, a_p = _i32(n_accept)
+    s_arr, s_p = _array(slots)
+    c_arr, c_p = _array(cu_delta)
+    a_arr, a_p = _array(n_accept)
     out = np.full(int(c_arr[-1]) if len(c_arr) else 0, -2, dtype=np.int64)
-    _check(lib().dk_kv_reserve(pool, len(s_arr), s_p, c_p, a_p, out.ctypes.data_as(_I64P)), "kv_reserve")
+    _check(lib().dk_kv_reserve(pool, len(s_arr), s_p, c_p, a_p, out.ctypes.data), "kv_reserve")
     return out
 
 
 def attend_workspace_bytes(pool, slots, cu_delta, staged) -> int:
     """staged: False / 0 appended mode, True / 1 staged mode, 2 for append_attend."""
-    s_arr, s_p = _i32(slots)
-    c_arr, c_p = _i32(cu_delta)
+    s_arr, s_p = _array(slots)
+    c_arr, c_p = _array(cu_delta)
     out = C.c_int64()
     _check(lib().dk_attend_workspace_bytes(pool, len(s_arr), s_p, c_p, int(staged), C.byref(out)),
            "attend_workspace_bytes", pool)
@@ -261,24 +274,20 @@ def attend_workspace_bytes(pool, slots, cu_delta, staged) -> int:
 
 def delta_attend(pool, slots, cu_delta, q, out, scale: float, k_new=None, v_new=None, lse=None,
                  workspace=None, stream=None) -> None:
-    s_arr, s_p = _i32(slots)
-    c_arr, c_p = _i32(cu_delta)
+    s_arr, s_p = _array(slots)
+    c_arr, c_p = _array(cu_delta)
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    st = _stream(stream)
-    _launch(lambda: lib().dk_delta_attend(pool, len(s_arr), s_p, c_p, _ptr(q), _ptr(k_new), _ptr(v_new),
-                                          float(scale), _ptr(out), _ptr(lse), _ptr(workspace), ws_bytes, st),
-            "delta_attend", pool, stream)
+    _launch(lib().dk_delta_attend, (pool, len(s_arr), s_p, c_p, _ptr(q), _ptr(k_new), _ptr(v_new), float(scale), _ptr(out),
+                                    _ptr(lse), _ptr(workspace), ws_bytes, _stream(stream)), "delta_attend", pool)
 
 
 def append_attend(pool, slots, cu_delta, q, k_new, v_new, out, scale: float, lse=None, workspace=None,
                   stream=None) -> None:
-    s_arr, s_p = _i32(slots)
-    c_arr, c_p = _i32(cu_delta)
+    s_arr, s_p = _array(slots)
+    c_arr, c_p = _array(cu_delta)
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    st = _stream(stream)
-    _launch(lambda: lib().dk_append_attend(pool, len(s_arr), s_p, c_p, _ptr(q), _ptr(k_new), _ptr(v_new),
-                                           float(scale), _ptr(out), _ptr(lse), _ptr(workspace), ws_bytes, st),
-            "append_attend", pool, stream)
+    _launch(lib().dk_append_attend, (pool, len(s_arr), s_p, c_p, _ptr(q), _ptr(k_new), _ptr(v_new), float(scale), _ptr(out),
+                                     _ptr(lse), _ptr(workspace), ws_bytes, _stream(stream)), "append_attend", pool)
 
 
 STATIC_SCRATCH_BYTES = 32 << 20
@@ -286,12 +295,10 @@ STATIC_SCRATCH_BYTES = 32 << 20
 
 def delta_attend_noalloc(pool, slots, cu_delta, q, out, scale: float, k_new=None, v_new=None, lse=None,
                          stream=None) -> None:
-    s_arr, s_p = _i32(slots)
-    c_arr, c_p = _i32(cu_delta)
-    st = _stream(stream)
-    _launch(lambda: lib().dk_delta_attend_noalloc(pool, len(s_arr), s_p, c_p, _ptr(q), _ptr(k_new), _ptr(v_new),
-                                                  float(scale), _ptr(out), _ptr(lse), st),
-            "delta_attend_noalloc", pool, stream)
+    s_arr, s_p = _array(slots)
+    c_arr, c_p = _array(cu_delta)
+    _launch(lib().dk_delta_attend_noalloc, (pool, len(s_arr), s_p, c_p, _ptr(q), _ptr(k_new), _ptr(v_new), float(scale),
+                                            _ptr(out), _ptr(lse), _stream(stream)), "delta_attend_noalloc", pool)
 
 
 def verify_workspace_bytes(total_rows: int, vocab: int, dtype: int) -> int:
@@ -400,8 +407,7 @@ def prefill_groups(prompts, n_past, prefix_id, window: int = 8):
 
 
 def seq_gather(pool, slot: int, k_out, v_out, stream=None) -> None:
-    st = _stream(stream)
-    _launch(lambda: lib().dk_seq_gather(pool, slot, _ptr(k_out), _ptr(v_out), st), "seq_gather", pool, stream)
+    _launch(lib().dk_seq_gather, (pool, slot, _ptr(k_out), _ptr(v_out), _stream(stream)), "seq_gather", pool)
 
 
 def set_attend_variant(pool, variant: int) -> None:
