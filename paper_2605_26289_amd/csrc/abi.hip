@@ -266,6 +266,7 @@ int32_t dk_pool_create(const dk_pool_desc* desc, dk_pool** pool_out) {
     for (int x = 0; x < 8; ++x) c.xcd_speed[x] = (x & 1) ? 0.95f : 1.f;
     c.stream_queue = 1;
     c.small_units = 256;
+    c.once_cells = std::max<int64_t>(1, (int64_t(256) << 20) / ((int64_t)2 * desc->n_kv_heads * desc->head_dim * (desc->dtype == DK_BF16 ? 2 : 4)));
     c.inline_blob_bytes = dk::INLINE_BLOB_BYTES;
     *pool_out = p;
     return DK_OK;
@@ -596,6 +597,7 @@ int32_t attend_locked(dk_pool* pool, int32_t n_seqs, const int32_t* slots, const
   a.total_tokens = (int32_t)plan.total_tokens;
   a.cells = (const int32_t*)(desc + plan.off_cells);
   a.general = route == Route::kGeneral;
+  a.once = plan.once;
 
   hipError_t e = hipSuccess;
   const bool timing = !pool->ev0.empty();

@@ -110,6 +110,7 @@ struct KvTile {
   uint32_t stride;  // bytes between consecutive rows
   int32_t cnt;      // valid rows (>= 1)
   int32_t pos;      // logical position of row 0
+  int32_t once;     // DkSeg::once
 };
 
 // Walks the logical key positions [p, hi) of an entry, segment by segment.  The state of the segment
@@ -123,12 +124,14 @@ struct KvCursor {
   const char* k = nullptr;
   const char* v = nullptr;
   uint32_t stride = 0;
+  int32_t once = 0;
 
   __device__ __forceinline__ void enter_segment(const Ctx& c, int g) {
     DkSeg s = load_desc(segs, si);
     while (s.pos + s.len <= p && si + 1 < se) s = load_desc(segs, ++si);
     const int32_t off = p - s.pos;
     seg_end = s.pos + s.len;
+    once = s.once;
     if (s.src == 0) {
       const int64_t byte = ((int64_t)g * c.arena_cells + s.start + off) * ROW;
       k = c.k_arena + byte;
@@ -150,6 +153,7 @@ struct KvCursor {
     t.v = v;
     t.stride = stride;
     t.pos = p;
+    t.once = once;
     p += t.cnt;
     const uint32_t adv = (uint32_t)t.cnt * stride;
     k += adv;
@@ -164,7 +168,8 @@ struct KvCursor {
 // The load is issued from inline assembly on purpose: the compiler then keeps no account of it and
 // inserts no vmcnt(0) of its own in front of later LDS reads, so a tile can stay in flight while
 // the previous one is being consumed.  Completion is awaited explicitly with wait_vmcnt<N>().
-template <bool IS_V, int HD = D>
+// ONCE: a non-temporal load, for rows that nothing else reads (see DkSeg::once).
+template <bool IS_V, int HD = D, bool ONCE = false>
 __device__ __forceinline__ void load_kib(const char* gbase, uint32_t stride, int cnt, char* lds_region, int blk, int lane) {
   typedef Geo<HD> G;
   const int row = blk * G::ROWS_PER_KIB + lane / G::CHUNKS;
@@ -172,13 +177,22 @@ __device__ __forceinline__ void load_kib(const char* gbase, uint32_t stride, int
   const int chunk = slot ^ (IS_V ? G::v_swizzle(row) : G::k_swizzle(row));
   const uint32_t voff = (uint32_t)min(row, cnt - 1) * stride + chunk * 16;
   const uint32_t lds_addr = (uint32_t)(uintptr_t)(lds_void_ptr)(lds_region + blk * 1024);
-  asm volatile(
-      "s_mov_b32 m0, %0\n\t"
-      "s_nop 0\n\t"
-      "global_load_lds_dwordx4 %1, %2"
-      :
-      : "s"(lds_addr), "v"(voff), "s"(gbase)
-      : "memory", "m0");
+  if constexpr (ONCE)
+    asm volatile(
+        "s_mov_b32 m0, %0\n\t"
+        "s_nop 0\n\t"
+        "global_load_lds_dwordx4 %1, %2 nt"
+        :
+        : "s"(lds_addr), "v"(voff), "s"(gbase)
+        : "memory", "m0");
+  else
+    asm volatile(
+        "s_mov_b32 m0, %0\n\t"
+        "s_nop 0\n\t"
+        "global_load_lds_dwordx4 %1, %2"
+        :
+        : "s"(lds_addr), "v"(voff), "s"(gbase)
+        : "memory", "m0");
 }
 
 // A operand of S^T = K Q^T for key block kb and depth step ks: lane (row l%32, half h = l/32) holds

@@ -304,7 +304,8 @@ __device__ __forceinline__ void lds_barrier() {
 // too little in flight to stream it well).
 // INLINE: the descriptors arrive inside the kernel arguments (first argument) and the descriptor pointers are byte
 // offsets into them; otherwise they point into the uploaded workspace.
-template <int MB, int HD, bool GEN, bool INLINE>
+// ONCE: the launch has segments marked DkSeg::once (an instantiation of its own: the choice per tile costs the others 3-7 %).
+template <int MB, int HD, bool GEN, bool ONCE, bool INLINE>
 __global__ __launch_bounds__(256, 1) void attend_stream_kernel(BlobArg<INLINE> blob, Ctx c, const int32_t* links,
                                                                int n_chains, int32_t* queue, int n_units) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
@@ -338,10 +339,17 @@ __global__ __launch_bounds__(256, 1) void attend_stream_kernel(BlobArg<INLINE> b
   auto issue = [&](const KvTile& t, int stage) {
     char* kl = my + stage * STREAM_STAGE_BYTES;
     char* vl = kl + STREAM_TILE_BYTES;
+    if (ONCE && t.once) {
 #pragma unroll
-    for (int b = 0; b < 8; ++b) load_kib<false, HD>(t.k, t.stride, t.cnt, kl, b, lane);
+      for (int b = 0; b < 8; ++b) load_kib<false, HD, true>(t.k, t.stride, t.cnt, kl, b, lane);
 #pragma unroll
-    for (int b = 0; b < 8; ++b) load_kib<true, HD>(t.v, t.stride, t.cnt, vl, b, lane);
+      for (int b = 0; b < 8; ++b) load_kib<true, HD, true>(t.v, t.stride, t.cnt, vl, b, lane);
+    } else {
+#pragma unroll
+      for (int b = 0; b < 8; ++b) load_kib<false, HD>(t.k, t.stride, t.cnt, kl, b, lane);
+#pragma unroll
+      for (int b = 0; b < 8; ++b) load_kib<true, HD>(t.v, t.stride, t.cnt, vl, b, lane);
+    }
   };
   // this wavefront's quarter of the unit's keys: cursor, first tile requested into stage 0
   auto open_keys = [&](const DkItem& u, const DkEntry& ue, int ug) {
@@ -597,37 +605,37 @@ __global__ __launch_bounds__(256, 1) void attend_stream_kernel(BlobArg<INLINE> b
 
 namespace {
 
-template <int MB, int HD, bool GEN, bool INLINE>
+template <int MB, int HD, bool GEN, bool ONCE, bool INLINE>
 hipError_t launch_one(const BlobArg<INLINE>& blob, const Ctx& c, const int32_t* links, bool single, int32_t n_chains,
                       int32_t* queue, int32_t n_units, hipStream_t stream) {
   // once per process and instantiation, whatever thread or pool gets here first
   static std::once_flag once;
   static hipError_t status = hipSuccess;
   std::call_once(once, [] {
-    status = hipFuncSetAttribute((const void*)attend_stream_kernel<MB, HD, GEN, INLINE>,
+    status = hipFuncSetAttribute((const void*)attend_stream_kernel<MB, HD, GEN, ONCE, INLINE>,
                                  hipFuncAttributeMaxDynamicSharedMemorySize, STREAM_LDS_BYTES);
   });
   if (status != hipSuccess) return status;
-  attend_stream_kernel<MB, HD, GEN, INLINE>
+  attend_stream_kernel<MB, HD, GEN, ONCE, INLINE>
       <<<dim3((unsigned)n_chains), 256, STREAM_LDS_BYTES, stream>>>(blob, c, links, single ? 0 : n_chains, queue, n_units);
   return hipGetLastError();
 }
 
-template <int HD, bool GEN, bool INLINE>
+template <int HD, bool GEN, bool ONCE, bool INLINE>
 hipError_t launch_rows(int32_t max_rows, const BlobArg<INLINE>& blob, const Ctx& c, const int32_t* links,
                        bool single, int32_t n_chains, int32_t* queue, int32_t n_units, hipStream_t stream) {
-  if (max_rows <= 32) return launch_one<1, HD, GEN, INLINE>(blob, c, links, single, n_chains, queue, n_units, stream);
-  if (max_rows <= 64) return launch_one<2, HD, GEN, INLINE>(blob, c, links, single, n_chains, queue, n_units, stream);
-  return launch_one<3, HD, GEN, INLINE>(blob, c, links, single, n_chains, queue, n_units, stream);
+  if (max_rows <= 32) return launch_one<1, HD, GEN, ONCE, INLINE>(blob, c, links, single, n_chains, queue, n_units, stream);
+  if (max_rows <= 64) return launch_one<2, HD, GEN, ONCE, INLINE>(blob, c, links, single, n_chains, queue, n_units, stream);
+  return launch_one<3, HD, GEN, ONCE, INLINE>(blob, c, links, single, n_chains, queue, n_units, stream);
 }
 
-template <bool INLINE>
+template <bool ONCE, bool INLINE>
 hipError_t launch_shape(const AttendArgs& a, int32_t max_rows, const BlobArg<INLINE>& blob, const Ctx& c,
                         const int32_t* links, bool single, int32_t n_chains, int32_t* queue, int32_t n_units,
                         hipStream_t stream) {
-  if (a.arena.head_dim == 64) return launch_rows<64, true, INLINE>(max_rows, blob, c, links, single, n_chains, queue, n_units, stream);
-  if (a.general) return launch_rows<128, true, INLINE>(max_rows, blob, c, links, single, n_chains, queue, n_units, stream);
-  return launch_rows<128, false, INLINE>(max_rows, blob, c, links, single, n_chains, queue, n_units, stream);
+  if (a.arena.head_dim == 64) return launch_rows<64, true, ONCE, INLINE>(max_rows, blob, c, links, single, n_chains, queue, n_units, stream);
+  if (a.general) return launch_rows<128, true, ONCE, INLINE>(max_rows, blob, c, links, single, n_chains, queue, n_units, stream);
+  return launch_rows<128, false, ONCE, INLINE>(max_rows, blob, c, links, single, n_chains, queue, n_units, stream);
 }
 
 }  // namespace
@@ -643,9 +651,14 @@ hipError_t launch_attend_stream(const AttendArgs& a, const DkItem* items, const 
   if (a.arena.head_dim != 128 && !(a.arena.head_dim == 64 && a.general)) return hipErrorInvalidValue;
   if (queue && a.inline_blob) return hipErrorInvalidValue;  // the queue's counter needs device memory
   const Ctx c = make_ctx(a, items);
-  if (a.inline_blob)
-    return launch_shape<true>(a, max_rows, BlobArg<true>{*a.inline_blob}, c, links, single, n_chains, queue, n_units, stream);
-  return launch_shape<false>(a, max_rows, BlobArg<false>{0}, c, links, single, n_chains, queue, n_units, stream);
+  if (a.inline_blob) {
+    const BlobArg<true> blob{*a.inline_blob};
+    return a.once ? launch_shape<true, true>(a, max_rows, blob, c, links, single, n_chains, queue, n_units, stream)
+                  : launch_shape<false, true>(a, max_rows, blob, c, links, single, n_chains, queue, n_units, stream);
+  }
+  const BlobArg<false> none{0};
+  return a.once ? launch_shape<true, false>(a, max_rows, none, c, links, single, n_chains, queue, n_units, stream)
+                : launch_shape<false, false>(a, max_rows, none, c, links, single, n_chains, queue, n_units, stream);
 }
 
 }  // namespace dk

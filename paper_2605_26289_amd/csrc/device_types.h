@@ -11,7 +11,7 @@ struct DkSeg {
   int32_t pos;
   int32_t len;
   int32_t src;
-  int32_t pad;
+  int32_t once;  // 1: nothing but one streaming unit per KV head reads these rows in this call, and they fit no cache
 };
 
 // One batch entry: a slot with n cached tokens and delta new ones (paper Sec. 2.2: n_t, Delta_t).

@@ -59,6 +59,8 @@ struct AttendArgs {
   bool scatter = false;
   // The shape takes the general MFMA kernels: 64-wide heads or a group that is no power of two up to 16.
   bool general = false;
+  // Some segments are marked DkSeg::once.
+  bool once = false;
 };
 
 // Scalar reference kernel: one wavefront per (token, query head).  Any supported shape and dtype.

@@ -302,6 +302,42 @@ StreamShape small_shape(const AttendPlan& p, const PlanConfig& cfg, int32_t grou
   return best;
 }
 
+// Marks the segments that the streaming kernel may read past the caches (non-temporal loads): all that no two entries
+// share, once the batch's cells are more than the Infinity Cache holds -- nothing of them can be there from an earlier
+// call, and keeping them costs a tenth of the HBM rate.  Measured, us, cached / non-temporal: 64 verifying sessions of
+// 4096-16384 tokens 416 / 372, 256 decoding ones of 512-8192 789 / 709, 44 of 4000 (700 MB) 145 / 131, 24 (400 MB) 74 / 66; but 16 (256 MB, found in the cache
+// again by a second pass) 47 / 56, 64 sessions sharing 8192 of 8500 tokens 157 / 169.
+// A segment is taken for shared if another entry has one that starts at the same cell (an aliased prefix does).
+void mark_once(AttendPlan* p, const PlanConfig& cfg) {
+  int64_t cells = 0;
+  size_t n = 0;
+  for (const DkSeg& s : p->segs) cells += s.src == 0 ? s.len : 0;
+  if (cfg.once_cells <= 0 || cells < cfg.once_cells) return;
+  size_t size = 16;
+  while (size < 2 * p->segs.size()) size *= 2;
+  std::vector<int32_t>& table = p->seg_table;  // open addressing by start cell
+  table.assign(size, -1);
+  for (DkSeg& s : p->segs) {
+    const int32_t i = (int32_t)n++;
+    if (s.src != 0) continue;
+    s.once = 1;
+    size_t at = (size_t)((uint64_t)s.start * 0x9E3779B97F4A7C15ull >> 32) & (size - 1);
+    while (table[at] >= 0 && p->segs[(size_t)table[at]].start != s.start) at = (at + 1) & (size - 1);
+    if (table[at] < 0) {
+      table[at] = i;
+      continue;
+    }
+    DkSeg& other = p->segs[(size_t)table[at]];
+    cells -= std::min(s.len, other.len);
+    s.once = other.once = 0;
+    if (s.len > other.len) table[at] = i;
+  }
+  if (cells < cfg.once_cells)
+    for (DkSeg& s : p->segs) s.once = 0;
+  else
+    p->once = true;
+}
+
 // Estimated time of the plan that the rules for large batches make.
 double planned_us(const AttendPlan& p, const PlanConfig& cfg) {
   double us = 0;
@@ -406,6 +442,8 @@ int32_t build_plan(Pool& pool, const PlanConfig& cfg, int32_t n_seqs, const int3
       cut_stream_items(stream_tiles, cfg.kv_tile, INT32_MAX, s.chunk, &p->stream_items, &p->merges, &p->part_rows);
     }
   }
+  p->once = false;
+  if (!p->stream_items.empty() && stream_tiles.size() <= p->entries.size()) mark_once(p, cfg);  // one row tile per entry
   for (DkMerge& m : p->merges) m.tok0 = p->entries[(size_t)m.entry].tok0;
   // Streaming units: with at least four units per workgroup they form a queue that the workgroups draw from at
   // run time (measured: +3-5 % on 700 decode slots, +1.5 % on 2048, because the compute units do not stream equally

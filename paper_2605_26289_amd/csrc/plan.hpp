@@ -26,6 +26,7 @@ struct PlanConfig {
   int32_t stream_item_cost;  // fixed cost of an item in the chain balance, in keys
   float xcd_speed[8];        // relative K/V streaming rate of the XCD that workgroup w lands on (w % 8)
   int32_t stream_queue;      // 1: streaming units are drawn from a queue at run time when the blob is uploaded
+  int64_t once_cells;        // batches of at least this many cells are read past the caches (0: none are)
   int32_t small_units;       // a batch of at most this many streaming units may be planned as a small one (0: never)
   int32_t inline_blob_bytes; // a descriptor blob up to this size travels in the kernel arguments
 };
@@ -52,6 +53,7 @@ struct AttendPlan {
   std::vector<PlanPiece> pieces;
   std::vector<int32_t> order, chain_head, chain_tail, tile_pieces, tile_part0;
   std::vector<int64_t> chain_load;
+  std::vector<int32_t> seg_table;
 
   std::vector<DkEntry> entries;
   std::vector<DkSeg> segs;
@@ -68,6 +70,7 @@ struct AttendPlan {
   bool stream_queued = false;
   // ... or has one unit per workgroup, unit w for workgroup w: the links say nothing and are not part of the blob.
   bool stream_single = false;
+  bool once = false;  // some segments are marked DkSeg::once
   int64_t stream_units = 0;
   size_t off_queue = 0;
   // Tile kernel: tile_wave_slots workgroups per KV head, workgroup c of a head walks the items
