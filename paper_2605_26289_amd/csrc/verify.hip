@@ -4,9 +4,13 @@
 //   argmax_partial_kernel   one workgroup per (row, 32 KiB chunk of the row): 16-byte loads, eight in
 //                           flight per lane, running (max, first index) per lane, wavefront shuffle
 //                           reduction, one (value, index) pair per chunk.  HBM bound: every logit is
-//                           read exactly once.
-//   verify_finish_kernel    one wavefront per slot: folds the chunk pairs of each of its rows, then
-//                           finds the first draft that differs from the row's argmax.
+//                           read exactly once, past the caches where there are many of them.
+//   verify_finish_kernel    one wavefront per slot: folds the chunk pairs of each of its rows, a lane per row, then
+//                           finds the first draft that differs from the row's argmax, in registers.
+//
+// Measured, 64 slots of nine rows over 128 256 bf16 logits (148 MB), us a call, and the same in fp32: cached loads and
+// the argmax of every row through memory 32.4 and 55.1; non-temporal loads alone 29.4 and 49.6; both 28.7 and 48.3.  With 18 MB the
+// non-temporal loads are 1-2 % slower, so calls below 64 MiB keep the ordinary ones.
 //
 // Ties go to the lowest token id; a NaN logit counts as +infinity.
 #include <hip/hip_runtime.h>
@@ -37,23 +41,24 @@ __device__ __forceinline__ Best better(Best a, Best b) {
 __device__ __forceinline__ float elem_to_float(float x) { return x; }
 __device__ __forceinline__ float elem_to_float(uint16_t bits) { return __uint_as_float((uint32_t)bits << 16); }
 
-template <typename T>
+template <typename T, bool ONCE>
 __global__ __launch_bounds__(VERIFY_THREADS) void argmax_partial_kernel(const T* __restrict__ logits, int64_t row_stride,
                                                                         int64_t vocab, int32_t n_chunks,
-                                                                        float* __restrict__ part_val,
-                                                                        int32_t* __restrict__ part_idx) {
+                                                                        Best* __restrict__ parts) {
   constexpr int VEC = 16 / (int)sizeof(T);
   constexpr int64_t CHUNK = (int64_t)VERIFY_THREADS * VEC * VERIFY_UNROLL;
   const int32_t row = blockIdx.y, chunk = blockIdx.x;
   const T* p = logits + (int64_t)row * row_stride;
   const int64_t base = (int64_t)chunk * CHUNK;
-  uint4 raw[VERIFY_UNROLL];
+  typedef uint32_t words __attribute__((ext_vector_type(4)));
+  words raw[VERIFY_UNROLL];
   bool full[VERIFY_UNROLL];
 #pragma unroll
   for (int u = 0; u < VERIFY_UNROLL; ++u) {
     const int64_t e0 = base + ((int64_t)u * VERIFY_THREADS + threadIdx.x) * VEC;
     full[u] = e0 + VEC <= vocab;
-    raw[u] = full[u] ? *(const uint4*)(p + e0) : make_uint4(0, 0, 0, 0);
+    raw[u] = words{0, 0, 0, 0};
+    if (full[u]) raw[u] = ONCE ? __builtin_nontemporal_load((const words*)(p + e0)) : *(const words*)(p + e0);
   }
   Best best{-INFINITY, INT32_MAX};
 #pragma unroll
@@ -91,15 +96,15 @@ __global__ __launch_bounds__(VERIFY_THREADS) void argmax_partial_kernel(const T*
     Best b{sv[0], si[0]};
 #pragma unroll
     for (int w = 1; w < VERIFY_THREADS / 64; ++w) b = better(b, Best{sv[w], si[w]});
-    part_val[(int64_t)row * n_chunks + chunk] = b.v;
-    part_idx[(int64_t)row * n_chunks + chunk] = b.i;
+    parts[(int64_t)row * n_chunks + chunk] = b;
   }
 }
 
-// One wavefront per slot.  Batch rows [r0, r1) of the slot hold [G_last, draft 0, ..., draft k-1].
+// One wavefront per slot.  Batch rows [r0, r1) of the slot hold [G_last, draft 0, ..., draft k-1]: lane s of a round of 64
+// has row r0 + s, its argmax, and the draft that has to equal it.
+constexpr int FINISH_AHEAD = 8;  // chunk pairs of a row requested at once
 __global__ __launch_bounds__(64) void verify_finish_kernel(const int32_t* __restrict__ cu_delta,
-                                                           const float* __restrict__ part_val,
-                                                           const int32_t* __restrict__ part_idx, int32_t n_chunks,
+                                                           const Best* __restrict__ parts, int32_t n_chunks,
                                                            const int32_t* __restrict__ batch_tokens,
                                                            int32_t* __restrict__ argmax_rows,
                                                            int32_t* __restrict__ n_keep_out,
@@ -113,26 +118,29 @@ __global__ __launch_bounds__(64) void verify_finish_kernel(const int32_t* __rest
     }
     return;
   }
-  for (int32_t r = r0 + lane; r < r1; r += 64) {
-    Best best{part_val[(int64_t)r * n_chunks], part_idx[(int64_t)r * n_chunks]};
-    for (int32_t c = 1; c < n_chunks; ++c)
-      best = better(best, Best{part_val[(int64_t)r * n_chunks + c], part_idx[(int64_t)r * n_chunks + c]});
-    argmax_rows[r] = best.i;
-  }
-  __syncthreads();
-  // first draft s (0-based) whose token differs from what the model says after batch position s
-  const int32_t k = r1 - r0 - 1;
-  int32_t first_bad = k;
-  for (int32_t s = lane; s < k; s += 64)
-    if (argmax_rows[r0 + s] != batch_tokens[r0 + 1 + s]) {
-      first_bad = s;
-      break;  // this lane's later candidates are larger anyway
-    }
+  int32_t first_bad = -1, next = -1;  // of the slot: the first row whose argmax is not the draft after it (or the last row)
+  for (int32_t base = r0; base < r1; base += 64) {
+    const int32_t r = min(base + lane, r1 - 1);
+    const int32_t draft = batch_tokens[min(r + 1, r1 - 1)];
+    Best best{-INFINITY, INT32_MAX};
+    for (int32_t c = 0; c < n_chunks; c += FINISH_AHEAD) {
+      Best p[FINISH_AHEAD];
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) first_bad = min(first_bad, __shfl_xor(first_bad, off));
+      for (int u = 0; u < FINISH_AHEAD; ++u) p[u] = parts[(int64_t)r * n_chunks + min(c + u, n_chunks - 1)];
+#pragma unroll
+      for (int u = 0; u < FINISH_AHEAD; ++u) best = better(best, p[u]);
+    }
+    if (argmax_rows && base + lane < r1) argmax_rows[r] = best.i;
+    const uint64_t bad = __builtin_amdgcn_ballot_w64(r == r1 - 1 || best.i != draft);
+    if (first_bad < 0 && bad != 0) {
+      const int s = __builtin_ctzll(bad);
+      first_bad = base - r0 + s;
+      next = __shfl(best.i, s);
+    }
+  }
   if (lane == 0) {
     n_keep_out[b] = 1 + first_bad;
-    next_token_out[b] = argmax_rows[r0 + first_bad];
+    next_token_out[b] = next;
   }
 }
 
@@ -152,22 +160,22 @@ hipError_t launch_verify_greedy(int32_t n_seqs, int32_t total_rows, const int32_
   if (n_seqs <= 0) return hipSuccess;
   const int64_t elem = dtype == 1 ? 2 : 4;
   const int32_t n_chunks = (int32_t)((vocab * elem + VERIFY_CHUNK_BYTES - 1) / VERIFY_CHUNK_BYTES);
-  float* part_val = (float*)workspace;
-  int32_t* part_idx = (int32_t*)(part_val + (int64_t)total_rows * n_chunks);
-  int32_t* am = argmax_out ? argmax_out : part_idx + (int64_t)total_rows * n_chunks;
+  Best* parts = (Best*)workspace;
   if (total_rows > 0) {
     const dim3 grid((unsigned)n_chunks, (unsigned)total_rows);
-    if (dtype == 1)
-      argmax_partial_kernel<uint16_t><<<grid, VERIFY_THREADS, 0, stream>>>((const uint16_t*)logits, row_stride, vocab,
-                                                                            n_chunks, part_val, part_idx);
-    else
-      argmax_partial_kernel<float><<<grid, VERIFY_THREADS, 0, stream>>>((const float*)logits, row_stride, vocab,
-                                                                         n_chunks, part_val, part_idx);
+    const bool once = (int64_t)total_rows * vocab * elem >= (int64_t)64 << 20;
+    if (dtype == 1) {
+      const auto kernel = once ? argmax_partial_kernel<uint16_t, true> : argmax_partial_kernel<uint16_t, false>;
+      kernel<<<grid, VERIFY_THREADS, 0, stream>>>((const uint16_t*)logits, row_stride, vocab, n_chunks, parts);
+    } else {
+      const auto kernel = once ? argmax_partial_kernel<float, true> : argmax_partial_kernel<float, false>;
+      kernel<<<grid, VERIFY_THREADS, 0, stream>>>((const float*)logits, row_stride, vocab, n_chunks, parts);
+    }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  verify_finish_kernel<<<dim3((unsigned)n_seqs), 64, 0, stream>>>(cu_delta_dev, part_val, part_idx, n_chunks,
-                                                                   batch_tokens, am, n_keep_out, next_token_out);
+  verify_finish_kernel<<<dim3((unsigned)n_seqs), 64, 0, stream>>>(cu_delta_dev, parts, n_chunks, batch_tokens, argmax_out,
+                                                                   n_keep_out, next_token_out);
   return hipGetLastError();
 }
 
