@@ -115,6 +115,13 @@ struct dk_pool {
       // the half-waves, store) is about three of its shorter key steps
       c.small_units = 0;
       c.tile_rows = 128;
+      // With 64-wide heads the stream kernel's third row block is slower than the block kernel (16 sessions of 12-24 new
+      // tokens on 500-4000: 57 us / 42 us); a batch with any longer entry runs in the block kernel as a whole, as long as
+      // the short ones read no more than some 800 MB there, 20 % slower than the stream kernel does, but beside the others
+      // and without a launch of their own (two chunks of 256 tokens and 14 decoding sessions 77 us / 64 us, two of 512 and
+      // 46 longer ones 219 / 189; 64 verifying sessions alone, 1.3 GB: stream kernel 243, block kernel 298).
+      if (desc.head_dim == 64) c.stream_rows = std::min(c.stream_rows, 64);
+      c.join_keys = (int64_t(800) << 20) / ((int64_t)4 * desc.n_kv_heads * desc.head_dim);
       c.tile_wave_slots = 2 * cfg.tile_wave_slots;
       c.tile_item_cost = std::min(cfg.tile_item_cost, 3);
     }

@@ -412,6 +412,14 @@ int32_t build_plan(Pool& pool, const PlanConfig& cfg, int32_t n_seqs, const int3
       }
     }
   }
+  if (!tile_tiles.empty() && !stream_tiles.empty()) {
+    int64_t keys = 0;
+    for (const RowTile& t : stream_tiles) keys += t.kv_hi;
+    if (keys <= cfg.join_keys) {
+      tile_tiles.insert(tile_tiles.end(), stream_tiles.begin(), stream_tiles.end());
+      stream_tiles.clear();
+    }
+  }
   cut_tile_items(p, cfg);
   cut_stream_items(stream_tiles, cfg.kv_tile, cfg.stream_target, cfg.stream_min_chunk, &p->stream_items, &p->merges,
                    &p->part_rows);
