@@ -113,8 +113,12 @@ struct dk_pool {
     if (r == Route::kGeneral) {
       // block kernel: items of 128 rows, two workgroups on a compute unit; an item's fixed cost (first tiles, merge of
       // the half-waves, store) is about three of its shorter key steps
-      c.small_units = 0;
       c.tile_rows = 128;
+      if (desc.head_dim == 64) {
+        c.row_fixed_us = 8.f;
+        c.row_step_us = 1.4f;
+        c.unit_scale = 0.75f;
+      }
       // With 64-wide heads the stream kernel's third row block is slower than the block kernel (16 sessions of 12-24 new
       // tokens on 500-4000: 57 us / 42 us); a batch with any longer entry runs in the block kernel as a whole, as long as
       // the short ones read no more than some 800 MB there, 20 % slower than the stream kernel does, but beside the others
@@ -273,6 +277,9 @@ int32_t dk_pool_create(const dk_pool_desc* desc, dk_pool** pool_out) {
     for (int x = 0; x < 8; ++x) c.xcd_speed[x] = (x & 1) ? 0.95f : 1.f;
     c.stream_queue = 1;
     c.small_units = 256;
+    c.row_fixed_us = 10.f;
+    c.row_step_us = 1.8f;
+    c.unit_scale = 1.f;
     c.once_cells = std::max<int64_t>(1, (int64_t(256) << 20) / ((int64_t)2 * desc->n_kv_heads * desc->head_dim * (desc->dtype == DK_BF16 ? 2 : 4)));
     c.inline_blob_bytes = dk::INLINE_BLOB_BYTES;
     *pool_out = p;

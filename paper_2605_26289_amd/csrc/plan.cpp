@@ -243,7 +243,9 @@ void cut_tile_items(AttendPlan* p, const PlanConfig& cfg) {
 // which pays 9 us an item, 1.8 us per 64 keys and mostly a merge launch.  Measured, one 150-token turn of one session
 // (32 query heads on 8 KV heads, us per step, tile kernel / 32-row units): 300 cached tokens 28.7 / 18.3, 800 33.5 / 17.8,
 // 2000 36 / 24, 4000 45 / 37, 8000 51 / 66; 300 tokens on 1500: 42 / 33 (64-row units); 20 tokens on 4000: 28 / 21.
-// The constants are those measurements, in microseconds; the plan of least estimated time is taken.
+// The constants are those measurements, in microseconds; the plan of least estimated time is taken.  (64-wide heads and
+// odd groups, block kernel / here: 150 tokens on 800 cached 17 / 12.6 with 64-wide heads, 22 / 16 with three heads to a
+// KV head; 9-40 tokens of two sessions, seven heads to a KV head, 20 / 16; 100 tokens on 4000, 64-wide, 23.6 / 27.8.)
 struct StreamShape {
   int32_t rows = 0;   // rows per streaming tile; 0: none found
   int32_t chunk = 0;  // keys per unit
@@ -254,10 +256,10 @@ constexpr double kUnitPer128[4] = {0, 1.08, 1.45, 2.0};  // per 128 keys
 constexpr double kMergeUs = 5.0, kMergeSplitUs = 0.1;    // merge launch, and each split it reads
 constexpr double kKeysPerUs = 10500.0;                   // all compute units together, from HBM (5.4 TB/s)
 
-double stream_us(int32_t tile_rows, int64_t longest, int64_t chunk, int64_t unit_keys) {
+double stream_us(const PlanConfig& cfg, int32_t tile_rows, int64_t longest, int64_t chunk, int64_t unit_keys) {
   const int mb = std::min(3, (tile_rows + 31) / 32);
   const int64_t split = (longest + chunk - 1) / chunk;
-  const double walk = std::max(kUnitPer128[mb] * (double)std::min(longest, chunk) / 128.0, (double)unit_keys / kKeysPerUs);
+  const double walk = cfg.unit_scale * std::max(kUnitPer128[mb] * (double)std::min(longest, chunk) / 128.0, (double)unit_keys / kKeysPerUs);
   return kUnitFixed[mb] + walk + (split > 1 ? kMergeUs + kMergeSplitUs * (double)split : 0.0);
 }
 
@@ -295,7 +297,7 @@ StreamShape small_shape(const AttendPlan& p, const PlanConfig& cfg, int32_t grou
         }
       if (units * cfg.n_kv_heads > std::min(cfg.small_units, cfg.stream_chains)) break;
       if (blob_estimate(p, with_cells, 0, (size_t)units, 0, (size_t)merges) > max_blob) continue;
-      const double us = stream_us(std::min(r, most_rows), longest, chunk, keys * cfg.n_kv_heads);
+      const double us = stream_us(cfg, std::min(r, most_rows), longest, chunk, keys * cfg.n_kv_heads);
       if (best.rows == 0 || us < best.us) best = {r, (int32_t)chunk, us};
     }
   }
@@ -343,7 +345,7 @@ double planned_us(const AttendPlan& p, const PlanConfig& cfg) {
   double us = 0;
   if (p.tile_chains > 0) {
     const int64_t load = *std::max_element(p.chain_load.begin(), p.chain_load.end());
-    us += 10.0 + 1.8 * (double)load;
+    us += cfg.row_fixed_us + cfg.row_step_us * (double)load;
   }
   if (!p.stream_items.empty()) {
     int32_t rows = 0;
@@ -353,7 +355,7 @@ double planned_us(const AttendPlan& p, const PlanConfig& cfg) {
       longest = std::max<int64_t>(longest, it.kv_hi - it.kv_lo);
       keys += it.kv_hi - it.kv_lo;
     }
-    us += stream_us(rows, longest, longest, keys * cfg.n_kv_heads);
+    us += stream_us(cfg, rows, longest, longest, keys * cfg.n_kv_heads);
   }
   if (!p.merges.empty()) us += kMergeUs + 2.0;
   return us;

@@ -28,6 +28,8 @@ struct PlanConfig {
   int32_t stream_queue;      // 1: streaming units are drawn from a queue at run time when the blob is uploaded
   int64_t join_keys;         // short entries join the row-tile kernel's launch if they see at most this many keys (0: never)
   int64_t once_cells;        // batches of at least this many cells are read past the caches (0: none are)
+  float row_fixed_us, row_step_us;  // estimated cost of the row-tile kernel: a launch, and an item's 64-key step
+  float unit_scale;          // cost of a streaming unit's keys against 128-wide heads
   int32_t small_units;       // a batch of at most this many streaming units may be planned as a small one (0: never)
   int32_t inline_blob_bytes; // a descriptor blob up to this size travels in the kernel arguments
 };

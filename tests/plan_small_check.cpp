@@ -37,6 +37,9 @@ static dk::PlanConfig config(int hq, int hkv, int small) {
   for (float& x : c.xcd_speed) x = 1.f;
   c.stream_queue = 1;
   c.small_units = small;
+  c.row_fixed_us = 10.f;
+  c.row_step_us = 1.8f;
+  c.unit_scale = 1.f;
   c.inline_blob_bytes = 3072;
   return c;
 }
