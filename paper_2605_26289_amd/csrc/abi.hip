@@ -92,6 +92,7 @@ struct dk_pool {
     return {desc.k_arena, desc.v_arena, meta_arena_cells, desc.n_q_heads, desc.n_kv_heads, desc.head_dim, desc.dtype};
   }
   int64_t meta_arena_cells = 0;
+  int32_t arrival_slice = -1;  // of the streaming kernel's counters; -1: none was free
 
   // `scale_ok`: the scale is positive and finite (the MFMA kernels take the row maximum before scaling).
   Route route(bool scale_ok, int32_t n_seqs, const int32_t* cu_delta) const {
@@ -189,6 +190,27 @@ struct dk_pool {
 
 namespace {
 
+// Slices of the arrival counters, one per live pool.  They are handed out in the order in which they came back, so that a
+// slice is not taken again while work of the pool that had it could still be running.
+std::mutex g_slice_mu;
+int32_t g_slice_queue[dk::ARRIVAL_SLICES];
+int32_t g_slice_fresh = 0, g_slice_head = 0, g_slice_count = 0;  // never used yet; ring of returned ones
+
+int32_t take_slice() {
+  std::lock_guard<std::mutex> lk(g_slice_mu);
+  if (g_slice_fresh < dk::ARRIVAL_SLICES) return g_slice_fresh++;
+  if (g_slice_count == 0) return -1;
+  const int32_t s = g_slice_queue[g_slice_head];
+  g_slice_head = (g_slice_head + 1) % dk::ARRIVAL_SLICES;
+  --g_slice_count;
+  return s;
+}
+void give_slice(int32_t s) {
+  if (s < 0) return;
+  std::lock_guard<std::mutex> lk(g_slice_mu);
+  g_slice_queue[(g_slice_head + g_slice_count++) % dk::ARRIVAL_SLICES] = s;
+}
+
 bool desc_ok(const dk_pool_desc* d, int32_t* why) {
   *why = DK_ERR_INVALID;
   if (!d || d->n_slots <= 0 || d->n_session_slots < 0 || d->n_session_slots > d->n_slots) return false;
@@ -277,11 +299,13 @@ int32_t dk_pool_create(const dk_pool_desc* desc, dk_pool** pool_out) {
     for (int x = 0; x < 8; ++x) c.xcd_speed[x] = (x & 1) ? 0.95f : 1.f;
     c.stream_queue = 1;
     c.small_units = 256;
+    c.arrivals = dk::ARRIVALS_PER_SLICE;
     c.row_fixed_us = 10.f;
     c.row_step_us = 1.8f;
     c.unit_scale = 1.f;
     c.once_cells = std::max<int64_t>(1, (int64_t(256) << 20) / ((int64_t)2 * desc->n_kv_heads * desc->head_dim * (desc->dtype == DK_BF16 ? 2 : 4)));
     c.inline_blob_bytes = dk::INLINE_BLOB_BYTES;
+    p->arrival_slice = take_slice();
     *pool_out = p;
     return DK_OK;
   });
@@ -292,6 +316,7 @@ int32_t dk_pool_destroy(dk_pool* pool) {
   for (int i = 0; i < pool->ring_size; ++i)
     if (pool->ring[i].in_flight) (void)hipEventSynchronize(pool->ring[i].done);
   pool->drop_events();
+  give_slice(pool->arrival_slice);
   delete pool;
   return DK_OK;
 }
@@ -612,6 +637,9 @@ int32_t attend_locked(dk_pool* pool, int32_t n_seqs, const int32_t* slots, const
   a.cells = (const int32_t*)(desc + plan.off_cells);
   a.general = route == Route::kGeneral;
   a.once = plan.once;
+  // (a captured launch may be replayed beside later calls of this pool, or after it is gone: it does not count)
+  const bool merged = route != Route::kRef && plan.stream_merges && pool->arrival_slice >= 0 && !capturing(st);
+  if (merged) a.arrival_slice = pool->arrival_slice;
 
   hipError_t e = hipSuccess;
   const bool timing = !pool->ev0.empty();
@@ -641,6 +669,7 @@ int32_t attend_locked(dk_pool* pool, int32_t n_seqs, const int32_t* slots, const
                                  (int32_t)plan.stream_units, st);
     if (e != hipSuccess) return fail(pool->hip_fail(e));
     a.scatter = false;
+    if (merged) plan.merges.clear();
     int32_t max_rows = 0, max_split = 0;
     for (const DkMerge& mg : plan.merges) {
       max_rows = std::max(max_rows, mg.nrows);

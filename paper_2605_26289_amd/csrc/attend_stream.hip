@@ -298,6 +298,90 @@ __device__ __forceinline__ void lds_barrier() {
   asm volatile("" ::: "memory");
 }
 
+// Arrival counters: zero whenever no kernel that uses them runs (the last arrival takes its counter back to zero).
+__device__ uint32_t g_arrivals[ARRIVAL_SLICES * ARRIVALS_PER_SLICE];
+
+// Split rows of a small batch, merged by the workgroup that finishes the last of the splits (every workgroup has one unit):
+// a merge launch costs the stream 5 us and the host 4 more, of 14 and 16 for one decoding session on 3000 tokens.  The
+// partial rows were written by workgroups on other XCDs, whose L2 is not this one's: every wavefront waits for its own
+// stores, the workgroup meets, one lane writes the L2 back and counts (release), and the last one to count invalidates
+// its caches (acquire) before it reads.  Nobody waits for anybody: a workgroup that is not the last one ends.
+// D / 4 lanes take a row; with few rows the splits of one row are spread over several lane groups, whose sums meet in LDS.
+// The order of the additions depends on the plan alone, not on who comes last.
+template <int HD, bool GEN>
+__device__ __forceinline__ void merge_if_last(const Ctx& c, const DkEntry& e, const DkItem& it, int g, uint32_t* arrivals,
+                                              char* smem) {
+  constexpr int LANES = HD / 4, GROUPS = 256 / LANES, AHEAD = 8;
+  const int nsplit = it.merge & 255;
+  uint32_t* counter = arrivals + (it.merge >> 8) * c.n_kv_heads + g;
+  uint32_t* seen = (uint32_t*)(smem + STREAM_NEXT_OFFSET);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    const uint32_t before = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    *seen = before;
+    if (before == (uint32_t)nsplit - 1) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __syncthreads();
+  if (*seen != (uint32_t)nsplit - 1) return;
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+
+  int spread = 1;  // lane groups per row
+  while (2 * spread * it.nrows <= GROUPS) spread *= 2;
+  const int lane = threadIdx.x % LANES, grp = threadIdx.x / LANES;
+  const int first = grp % spread;
+  f32x4* xo = (f32x4*)smem;                       // [lane group][lane]
+  float2* xml = (float2*)(smem + 256 * 16);       // [lane group]
+  const int64_t srow = (int64_t)it.nrows * c.n_kv_heads;  // partial rows from one split of a row to the next
+  for (int r0 = 0; r0 < it.nrows; r0 += GROUPS / spread) {
+    const int rl = r0 + grp / spread;
+    const int64_t prow = (int64_t)(it.part_base + min(rl, it.nrows - 1)) * c.n_kv_heads + g;
+    const f32x4* p = (const f32x4*)(c.parts + prow * HD) + lane;
+    const float2* ml = (const float2*)c.parts_ml + prow;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    float l = 0.f, m = -INFINITY;
+    const auto add = [&](float wm, float wl, const f32x4& v) {
+      const float mn = fmaxf(m, wm);
+      const float ms = (mn == -INFINITY) ? 0.f : mn;
+      const float a = __builtin_amdgcn_exp2f(m - ms), f = __builtin_amdgcn_exp2f(wm - ms);
+      m = mn;
+      l = l * a + f * wl;
+      acc = acc * a + f * v;
+    };
+    for (int s0 = first; s0 < nsplit; s0 += spread * AHEAD) {
+      f32x4 v[AHEAD];
+      float2 w[AHEAD];
+#pragma unroll
+      for (int k = 0; k < AHEAD; ++k) {  // (a split past the end repeats the last one and is left out below)
+        const int64_t at = min(s0 + k * spread, nsplit - 1) * srow;
+        w[k] = ml[at];
+        v[k] = p[at * LANES];
+      }
+#pragma unroll
+      for (int k = 0; k < AHEAD; ++k)
+        if (s0 + k * spread < nsplit) add(w[k].x, w[k].y, v[k]);
+    }
+    if (spread > 1) {  // (one round: the rows fit the lane groups)
+      xo[threadIdx.x] = acc;
+      if (lane == 0) xml[grp] = make_float2(m, l);
+      __syncthreads();
+      if (first == 0)
+        for (int k = 1; k < spread; ++k) add(xml[grp + k].x, xml[grp + k].y, xo[threadIdx.x + k * LANES]);
+    }
+    if (first != 0 || rl >= it.nrows) continue;
+    const int row = it.row0 + rl;
+    const int tok = row_token<GEN>(c, row);
+    const int64_t orow = (int64_t)(e.tok0 + tok) * c.n_q_heads + g * c.group + row_head<GEN>(c, row, tok);
+    const float inv = 1.f / l;
+    bf16x4 o;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) o[u] = (__bf16)(acc[u] * inv);
+    *(bf16x4*)(c.out + orow * HD + lane * 4) = o;
+    if (c.lse && lane == 0) c.lse[orow] = (m + log2f(l)) * 0.6931471805599453f;
+  }
+}
+
 // MB = 32-row blocks per unit: 1 when no unit of the launch has more than 32 packed rows (Delta <= 32 / G:
 // decode and short verify steps then skip the all-padding blocks), 2 up to 64 rows, else 3 (up to 96 rows: between
 // 64 and 96 rows a unit is still far below the MFMA/HBM ridge, and the tile kernel, built for 256-row tiles, keeps
@@ -307,7 +391,7 @@ __device__ __forceinline__ void lds_barrier() {
 // ONCE: the launch has segments marked DkSeg::once (an instantiation of its own: the choice per tile costs the others 3-7 %).
 template <int MB, int HD, bool GEN, bool ONCE, bool INLINE>
 __global__ __launch_bounds__(256, 1) void attend_stream_kernel(BlobArg<INLINE> blob, Ctx c, const int32_t* links,
-                                                               int n_chains, int32_t* queue, int n_units) {
+                                                               int n_chains, int32_t* queue, int n_units, int arrival_slice) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   (void)blob;
   c.entries = resolve_desc<INLINE>(c.entries);
@@ -594,7 +678,11 @@ __global__ __launch_bounds__(256, 1) void attend_stream_kernel(BlobArg<INLINE> b
     if (threadIdx.x == 0 && trace_seq < 8 && blockIdx.x < 256) g_strace[blockIdx.x][trace_seq][8] = (unsigned long long)(it.kv_hi - it.kv_lo);
     ++trace_seq;
 #endif
-    if (next_unit < 0) break;
+    if (next_unit < 0) {
+      if (arrival_slice >= 0 && it.merge != 0)
+        merge_if_last<HD, GEN>(c, e, it, g, g_arrivals + arrival_slice * ARRIVALS_PER_SLICE, smem);
+      break;
+    }
     unit = next_unit;
     it = next_it;
     e = next_e;
@@ -607,7 +695,7 @@ namespace {
 
 template <int MB, int HD, bool GEN, bool ONCE, bool INLINE>
 hipError_t launch_one(const BlobArg<INLINE>& blob, const Ctx& c, const int32_t* links, bool single, int32_t n_chains,
-                      int32_t* queue, int32_t n_units, hipStream_t stream) {
+                      int32_t* queue, int32_t n_units, int32_t slice, hipStream_t stream) {
   // once per process and instantiation, whatever thread or pool gets here first
   static std::once_flag once;
   static hipError_t status = hipSuccess;
@@ -617,25 +705,27 @@ hipError_t launch_one(const BlobArg<INLINE>& blob, const Ctx& c, const int32_t* 
   });
   if (status != hipSuccess) return status;
   attend_stream_kernel<MB, HD, GEN, ONCE, INLINE>
-      <<<dim3((unsigned)n_chains), 256, STREAM_LDS_BYTES, stream>>>(blob, c, links, single ? 0 : n_chains, queue, n_units);
+      <<<dim3((unsigned)n_chains), 256, STREAM_LDS_BYTES, stream>>>(blob, c, links, single ? 0 : n_chains, queue, n_units, slice);
   return hipGetLastError();
 }
 
 template <int HD, bool GEN, bool ONCE, bool INLINE>
 hipError_t launch_rows(int32_t max_rows, const BlobArg<INLINE>& blob, const Ctx& c, const int32_t* links,
-                       bool single, int32_t n_chains, int32_t* queue, int32_t n_units, hipStream_t stream) {
-  if (max_rows <= 32) return launch_one<1, HD, GEN, ONCE, INLINE>(blob, c, links, single, n_chains, queue, n_units, stream);
-  if (max_rows <= 64) return launch_one<2, HD, GEN, ONCE, INLINE>(blob, c, links, single, n_chains, queue, n_units, stream);
-  return launch_one<3, HD, GEN, ONCE, INLINE>(blob, c, links, single, n_chains, queue, n_units, stream);
+                       bool single, int32_t n_chains, int32_t* queue, int32_t n_units, int32_t slice,
+                       hipStream_t stream) {
+  if (max_rows <= 32) return launch_one<1, HD, GEN, ONCE, INLINE>(blob, c, links, single, n_chains, queue, n_units, slice, stream);
+  if (max_rows <= 64) return launch_one<2, HD, GEN, ONCE, INLINE>(blob, c, links, single, n_chains, queue, n_units, slice, stream);
+  return launch_one<3, HD, GEN, ONCE, INLINE>(blob, c, links, single, n_chains, queue, n_units, slice, stream);
 }
 
 template <bool ONCE, bool INLINE>
 hipError_t launch_shape(const AttendArgs& a, int32_t max_rows, const BlobArg<INLINE>& blob, const Ctx& c,
                         const int32_t* links, bool single, int32_t n_chains, int32_t* queue, int32_t n_units,
                         hipStream_t stream) {
-  if (a.arena.head_dim == 64) return launch_rows<64, true, ONCE, INLINE>(max_rows, blob, c, links, single, n_chains, queue, n_units, stream);
-  if (a.general) return launch_rows<128, true, ONCE, INLINE>(max_rows, blob, c, links, single, n_chains, queue, n_units, stream);
-  return launch_rows<128, false, ONCE, INLINE>(max_rows, blob, c, links, single, n_chains, queue, n_units, stream);
+  const int32_t slice = a.arrival_slice;
+  if (a.arena.head_dim == 64) return launch_rows<64, true, ONCE, INLINE>(max_rows, blob, c, links, single, n_chains, queue, n_units, slice, stream);
+  if (a.general) return launch_rows<128, true, ONCE, INLINE>(max_rows, blob, c, links, single, n_chains, queue, n_units, slice, stream);
+  return launch_rows<128, false, ONCE, INLINE>(max_rows, blob, c, links, single, n_chains, queue, n_units, slice, stream);
 }
 
 }  // namespace

@@ -31,7 +31,9 @@ struct DkItem {
   int32_t nrows;
   int32_t kv_lo, kv_hi;
   int32_t part_row0;  // >= 0: write fp32 partial rows here; < 0: write the final output
-  int32_t pad[2];
+  // Streaming items whose rows are split: what the workgroup that finishes the last split merges them by.
+  int32_t merge;      // 256 * index of the merge record + nsplit (both below 256), else 0
+  int32_t part_base;  // DkMerge::part_row0
 };
 
 // Rows whose key range was split over several items and must be merged.

@@ -61,7 +61,14 @@ struct AttendArgs {
   bool general = false;
   // Some segments are marked DkSeg::once.
   bool once = false;
+  // >= 0: the streaming kernel merges split rows itself, with this slice of the arrival counters (see launch_attend_stream).
+  int32_t arrival_slice = -1;
 };
+
+// Arrival counters of the streaming kernel, in the library's device image: zero between launches.  A pool has one slice, and
+// the launches of a pool are ordered, so no two kernels that may overlap count in the same one.
+constexpr int32_t ARRIVAL_SLICES = 1024;
+constexpr int32_t ARRIVALS_PER_SLICE = 256;
 
 // Scalar reference kernel: one wavefront per (token, query head).  Any supported shape and dtype.
 hipError_t launch_attend_ref(const AttendArgs& a, hipStream_t stream);

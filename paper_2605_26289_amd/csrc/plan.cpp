@@ -41,6 +41,10 @@ void cut_stream_items(const std::vector<RowTile>& tiles, int32_t kv_tile, int32_
       it.kv_lo = (int32_t)(sp * each);
       it.kv_hi = sp + 1 == ns ? t.kv_hi : (int32_t)((sp + 1) * each);
       it.part_row0 = ns > 1 ? part0 + sp * t.nrows : -1;
+      if (ns > 1 && ns < 256 && merges->size() <= 256) {
+        it.merge = (int32_t)(merges->size() - 1) * 256 + ns;
+        it.part_base = part0;
+      }
       items->push_back(it);
     }
   }
@@ -254,13 +258,16 @@ struct StreamShape {
 constexpr double kUnitFixed[4] = {0, 8.5, 9.0, 10.0};    // by row blocks of 32
 constexpr double kUnitPer128[4] = {0, 1.08, 1.45, 2.0};  // per 128 keys
 constexpr double kMergeUs = 5.0, kMergeSplitUs = 0.1;    // merge launch, and each split it reads
+constexpr double kMergeInsideUs = 3.0;                   // merge by the streaming kernel itself
+constexpr int32_t kMergeInsideRows = 8, kMergeInsideParts = 64;  // most rows, and partial rows, of such a merge
 constexpr double kKeysPerUs = 10500.0;                   // all compute units together, from HBM (5.4 TB/s)
 
 double stream_us(const PlanConfig& cfg, int32_t tile_rows, int64_t longest, int64_t chunk, int64_t unit_keys) {
   const int mb = std::min(3, (tile_rows + 31) / 32);
   const int64_t split = (longest + chunk - 1) / chunk;
   const double walk = cfg.unit_scale * std::max(kUnitPer128[mb] * (double)std::min(longest, chunk) / 128.0, (double)unit_keys / kKeysPerUs);
-  return kUnitFixed[mb] + walk + (split > 1 ? kMergeUs + kMergeSplitUs * (double)split : 0.0);
+  const double merge = cfg.arrivals > 0 && tile_rows <= kMergeInsideRows && split * tile_rows <= kMergeInsideParts ? kMergeInsideUs : kMergeUs;
+  return kUnitFixed[mb] + walk + (split > 1 ? merge + kMergeSplitUs * (double)split : 0.0);
 }
 
 // Descriptor bytes of a plan, alignment padding included.
@@ -474,6 +481,13 @@ int32_t build_plan(Pool& pool, const PlanConfig& cfg, int32_t n_seqs, const int3
     chain_units(p->stream_items, cfg, p->heap, p->tail, &p->stream_links, &p->stream_chains);
   }
   p->stream_single = !p->stream_queued && p->stream_units == p->stream_chains;
+  // Merging inside the streaming kernel: nothing else has split rows, every workgroup has one unit, every (row tile, KV
+  // head) a counter of its own, and the last workgroup of a row tile reads all of its partial rows in a round or two --
+  // one workgroup is slow with more (us per step, merge launch / inside: one token on 3000 cached 13.8 / 12.0, with 64-wide
+  // heads 13.9 / 10.8; 9 tokens, 36 rows, on 2000 13.7 / 20.0; 20 tokens on 4000 15 / 25).
+  p->stream_merges = p->stream_single && p->tile_chains == 0 && !p->merges.empty() &&
+                     p->merges.size() * (size_t)cfg.n_kv_heads <= (size_t)cfg.arrivals;
+  for (const DkMerge& m : p->merges) p->stream_merges &= m.nrows <= kMergeInsideRows && m.nsplit * m.nrows <= kMergeInsideParts;
 
   size_t off = 0;
   p->off_entries = off;

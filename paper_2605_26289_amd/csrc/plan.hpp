@@ -30,6 +30,7 @@ struct PlanConfig {
   int64_t once_cells;        // batches of at least this many cells are read past the caches (0: none are)
   float row_fixed_us, row_step_us;  // estimated cost of the row-tile kernel: a launch, and an item's 64-key step
   float unit_scale;          // cost of a streaming unit's keys against 128-wide heads
+  int32_t arrivals;          // counters for merges inside the streaming kernel (0: none)
   int32_t small_units;       // a batch of at most this many streaming units may be planned as a small one (0: never)
   int32_t inline_blob_bytes; // a descriptor blob up to this size travels in the kernel arguments
 };
@@ -73,6 +74,8 @@ struct AttendPlan {
   bool stream_queued = false;
   // ... or has one unit per workgroup, unit w for workgroup w: the links say nothing and are not part of the blob.
   bool stream_single = false;
+  // The streaming kernel can merge the split rows itself (the workgroup that finishes the last split of a row tile does).
+  bool stream_merges = false;
   bool once = false;  // some segments are marked DkSeg::once
   int64_t stream_units = 0;
   size_t off_queue = 0;
