@@ -268,7 +268,7 @@ int32_t dk_pool_create(const dk_pool_desc* desc, dk_pool** pool_out) {
       p->stage_cap = (size_t)(desc->host_staging_bytes / depth) & ~(size_t)255;
       for (int i = 0; i < depth; ++i) {
         p->ring[i].host = (char*)desc->host_staging + (size_t)i * p->stage_cap;
-        const hipError_t e = hipEventCreateWithFlags(&p->ring[i].done, hipEventDisableTiming);
+        const hipError_t e = hipEventCreateWithFlags(&p->ring[i].done, hipEventDisableTiming | hipEventDisableSystemFence);
         if (e != hipSuccess) {
           p->drop_events();
           delete p;
