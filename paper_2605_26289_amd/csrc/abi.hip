@@ -413,6 +413,27 @@ int32_t append_locked(dk_pool* pool, int32_t n_seqs, const int32_t* slots, const
     pool->host_us[DK_HOST_APPEND_LAUNCH] += clk.lap();
     return e == hipSuccess ? DK_OK : undo(pool->hip_fail(e));
   }
+  // Where the tokens go in few runs of cells (a run or two per slot, unless the arena is fragmented) the runs travel in the
+  // kernel arguments; otherwise a table of every token's cell is uploaded.
+  if (total <= INT32_MAX / 2) {
+    dk::KvRuns runs;
+    int32_t n_runs = 0;
+    int64_t t = 0;
+    while (t < total && n_runs < dk::KV_INLINE_MAX_RUNS) {
+      runs.tok[n_runs] = (int32_t)t;
+      runs.cell[n_runs++] = (int32_t)dst[t];
+      const int64_t step = dst[t] >= 0;
+      for (++t; t < total && dst[t] == dst[t - 1] + step; ++t) {
+      }
+    }
+    if (t == total) {
+      runs.tok[n_runs] = (int32_t)total;
+      hipError_t e = dk::launch_kv_scatter_runs(pool->view(), pool->desc.k_arena, pool->desc.v_arena, runs, n_runs,
+                                                (int32_t)total, k_new, v_new, st);
+      pool->host_us[DK_HOST_APPEND_LAUNCH] += clk.lap();
+      return e == hipSuccess ? DK_OK : undo(pool->hip_fail(e));
+    }
+  }
   for (int64_t base = 0; base < total; base += per_launch) {
     const int32_t n = (int32_t)std::min<int64_t>(per_launch, total - base);
     Staging* s;

@@ -28,6 +28,16 @@ constexpr int32_t KV_INLINE_MAX_TOKENS = 896;
 hipError_t launch_kv_scatter_inline(const ArenaView& a, void* k_arena, void* v_arena, const int64_t* cell_of_host,
                                     int32_t n_tok, const void* k_new, const void* v_new, hipStream_t stream);
 
+// Longer appends carry the runs of consecutive cells that their tokens go to, at most this many of them: tok[r] is the
+// first token of run r (tok[n_runs] the number of tokens), cell[r] its first cell (-1: a run of tokens that are not kept).
+constexpr int32_t KV_INLINE_MAX_RUNS = 440;
+struct KvRuns {
+  int32_t tok[KV_INLINE_MAX_RUNS + 1];
+  int32_t cell[KV_INLINE_MAX_RUNS];
+};
+hipError_t launch_kv_scatter_runs(const ArenaView& a, void* k_arena, void* v_arena, const KvRuns& runs, int32_t n_runs,
+                                  int32_t n_tok, const void* k_new, const void* v_new, hipStream_t stream);
+
 // Descriptors of at most this many bytes are passed to the kernels inside their arguments instead of being
 // uploaded first: a short turn then costs no host-to-device copy (and no staging buffer).
 constexpr int32_t INLINE_BLOB_BYTES = 3072;
