@@ -158,8 +158,8 @@ hipError_t launch_kv_gather(const ArenaView& a, const int32_t* cell_of_dev, int6
 // ---------------------------------------------------------------------------------------------
 // Reference attention kernel.  One wavefront per (new token i, query head h).  Each lane walks
 // the visible keys lane, lane+64, ... of every segment with its own online-softmax state; the 64
-// states are merged through LDS at the end.  Used for fp32 pools, for shapes the MFMA kernels do
-// not cover, and as a second GPU implementation in the tests.
+// states are merged through LDS at the end.  Used for scales that are not positive and finite, for calls that
+// leave the matrix-core kernels no room (see the fallback in abi.hip), and as a second GPU implementation in the tests.
 // Row i of an entry sees positions 0 .. n+i (bottom-right causal alignment).
 // ---------------------------------------------------------------------------------------------
 __device__ inline float to_float(float x) { return x; }
