@@ -12,27 +12,28 @@
 
 namespace dk {
 
+// Every field starts as zero ("never", "none"), however the object that holds it is made.
 struct PlanConfig {
-  int32_t n_q_heads, n_kv_heads, head_dim;
-  bool use_mfma;          // bf16, D == 128, power-of-two group: the tiled kernels apply
-  int32_t tile_rows;      // packed query rows per workgroup of the tile kernel
-  int32_t stream_rows;    // max packed rows handled by the streaming (small-Delta) kernel
-  int32_t kv_tile;        // keys per inner step; split boundaries are multiples of it
-  int32_t tile_wave_slots;  // tile-kernel workgroups of one KV head that run at a time (its share of the CUs)
-  int32_t stream_target;  // same, streaming kernel
-  int32_t tile_min_chunk, stream_min_chunk;  // smallest key range worth its own item
-  int32_t tile_item_cost;    // fixed cost of a tile item inside a chain, in key tiles (store phase, pipeline ramp)
-  int32_t stream_chains;     // workgroups of the streaming kernel: one per compute unit
-  int32_t stream_item_cost;  // fixed cost of an item in the chain balance, in keys
-  float xcd_speed[8];        // relative K/V streaming rate of the XCD that workgroup w lands on (w % 8)
-  int32_t stream_queue;      // 1: streaming units are drawn from a queue at run time when the blob is uploaded
-  int64_t join_keys;         // short entries join the row-tile kernel's launch if they see at most this many keys (0: never)
-  int64_t once_cells;        // batches of at least this many cells are read past the caches (0: none are)
-  float row_fixed_us, row_step_us;  // estimated cost of the row-tile kernel: a launch, and an item's 64-key step
-  float unit_scale;          // cost of a streaming unit's keys against 128-wide heads
-  int32_t arrivals;          // counters for merges inside the streaming kernel (0: none)
-  int32_t small_units;       // a batch of at most this many streaming units may be planned as a small one (0: never)
-  int32_t inline_blob_bytes; // a descriptor blob up to this size travels in the kernel arguments
+  int32_t n_q_heads = 0, n_kv_heads = 0, head_dim = 0;
+  bool use_mfma = false;  // bf16, D == 128, power-of-two group: the tiled kernels apply
+  int32_t tile_rows = 0;  // packed query rows per workgroup of the tile kernel
+  int32_t stream_rows = 0;  // max packed rows handled by the streaming (small-Delta) kernel
+  int32_t kv_tile = 0;  // keys per inner step; split boundaries are multiples of it
+  int32_t tile_wave_slots = 0;  // tile-kernel workgroups of one KV head that run at a time (its share of the CUs)
+  int32_t stream_target = 0;  // same, streaming kernel
+  int32_t tile_min_chunk = 0, stream_min_chunk = 0;  // smallest key range worth its own item
+  int32_t tile_item_cost = 0;  // fixed cost of a tile item inside a chain, in key tiles (store phase, pipeline ramp)
+  int32_t stream_chains = 0;  // workgroups of the streaming kernel: one per compute unit
+  int32_t stream_item_cost = 0;  // fixed cost of an item in the chain balance, in keys
+  float xcd_speed[8] = {};  // relative K/V streaming rate of the XCD that workgroup w lands on (w % 8)
+  int32_t stream_queue = 0;  // 1: streaming units are drawn from a queue at run time when the blob is uploaded
+  int64_t join_keys = 0;  // short entries join the row-tile kernel's launch if they see at most this many keys (0: never)
+  int64_t once_cells = 0;  // batches of at least this many cells are read past the caches (0: none are)
+  float row_fixed_us = 0, row_step_us = 0;  // estimated cost of the row-tile kernel: a launch, and an item's 64-key step
+  float unit_scale = 0;  // cost of a streaming unit's keys against 128-wide heads
+  int32_t arrivals = 0;  // counters for merges inside the streaming kernel (0: none)
+  int32_t small_units = 0;  // a batch of at most this many streaming units may be planned as a small one (0: never)
+  int32_t inline_blob_bytes = 0;  // a descriptor blob up to this size travels in the kernel arguments
 };
 
 // One packed row tile of an entry before its key range is cut: rows [row0, row0 + nrows) see keys [0, kv_hi).

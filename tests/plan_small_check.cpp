@@ -5,6 +5,7 @@
 #include <cstdio>
 #include <map>
 #include <mutex>
+#include <new>
 #include <random>
 #include <vector>
 
@@ -44,7 +45,25 @@ static dk::PlanConfig config(int hq, int hkv, int small) {
   return c;
 }
 
+// A configuration made in storage that held something else, as a member of an object with a constructor of its own is:
+// what its maker does not set is zero, not what the storage held.
+struct Holder {
+  int other;
+  dk::PlanConfig cfg;
+  explicit Holder(int o) : other(o) {}
+};
+static void check_fields_start_at_zero() {
+  alignas(Holder) static unsigned char storage[sizeof(Holder)];
+  for (unsigned char& b : storage) b = 0x5a;
+  const Holder* h = new (storage) Holder(1);
+  CHECK(h->cfg.join_keys == 0);
+  CHECK(h->cfg.once_cells == 0);
+  CHECK(h->cfg.arrivals == 0);
+  CHECK(h->cfg.small_units == 0);
+}
+
 int main() {
+  check_fields_start_at_zero();
   std::mt19937 rng(7);
   auto uni = [&](int lo, int hi) { return lo + (int)(rng() % (unsigned)(hi - lo + 1)); };
   int small = 0, cut = 0;
