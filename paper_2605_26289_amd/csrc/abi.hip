@@ -523,10 +523,10 @@ int32_t dk_attend_workspace_bytes(dk_pool* pool, int32_t n_seqs, const int32_t* 
     int32_t rc = dk::build_plan(pool->meta, cfg, n_seqs, slots, cu_delta, staged != 0, &plan, staged == 2);
     if (rc != DK_OK) return rc;
     *bytes_out = (int64_t)plan.total_bytes;
-    // dk_append_attend may also plan the batch after its append, in appended mode: the same work items over slots
+    // dk_append_attend may also plan the batch after its append, in appended mode: without the table of cells, over slots
     // that then have more runs of cells (at worst one per granule the append takes)
     if (staged == 2)
-      *bytes_out += ((int64_t)n_seqs * 8 + plan.total_tokens / pool->granule_cells + 16) * (int64_t)sizeof(DkSeg) + 4096;
+      *bytes_out = (int64_t)plan.largest_bytes + ((int64_t)n_seqs * 8 + plan.total_tokens / pool->granule_cells + 16) * (int64_t)sizeof(DkSeg) + 4096;
     return DK_OK;
   });
 }

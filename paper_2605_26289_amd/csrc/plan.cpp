@@ -276,9 +276,16 @@ size_t blob_estimate(const AttendPlan& p, bool with_cells, size_t tile_items, si
          merges * sizeof(DkMerge) + (links + (with_cells ? (size_t)p.total_tokens : 0)) * sizeof(int32_t) + 8 * 16;
 }
 
+// Workspace of a plan: its descriptors, then its partial rows.
+size_t workspace_of(const PlanConfig& cfg, size_t blob_bytes, int64_t part_rows) {
+  return align_up(align_up(blob_bytes, 256) + (size_t)part_rows * cfg.n_kv_heads * (cfg.head_dim + 2) * sizeof(float), 256) + 256;
+}
+
 // The best way to run the whole batch through the streaming kernel with at most one unit per workgroup and at most
-// max_blob bytes of descriptors.
-StreamShape small_shape(const AttendPlan& p, const PlanConfig& cfg, int32_t group, bool with_cells, size_t max_blob) {
+// max_blob bytes of descriptors, in less than `below` microseconds.  *largest_bytes is raised to the workspace of every
+// such plan of any descriptor size.
+StreamShape small_shape(const AttendPlan& p, const PlanConfig& cfg, int32_t group, bool with_cells, size_t max_blob, double below,
+                        size_t* largest_bytes) {
   StreamShape best;
   int32_t most_rows = 0;
   int64_t longest = 0;
@@ -294,17 +301,24 @@ StreamShape small_shape(const AttendPlan& p, const PlanConfig& cfg, int32_t grou
     for (const int32_t k : splits) {
       const int64_t chunk = ((longest + k - 1) / k + cfg.kv_tile - 1) / cfg.kv_tile * cfg.kv_tile;
       if (k > 1 && chunk < 128) break;
-      int64_t units = 0, keys = 0, merges = 0;
+      int64_t units = 0, keys = 0, merges = 0, parts = 0;
       for (const DkEntry& e : p.entries)
         if (e.delta > 0) {
           const int64_t tiles = ((int64_t)group * e.delta + r - 1) / r, n = (int64_t)e.n + e.delta;
-          units += tiles * ((n + chunk - 1) / chunk);
+          const int64_t split = (n + chunk - 1) / chunk;
+          units += tiles * split;
           keys += n;  // (further tiles of the same rows find the keys in L2)
-          if (n > chunk) merges += tiles;
+          if (split > 1) {
+            merges += tiles;
+            parts += (int64_t)group * e.delta * split;
+          }
         }
       if (units * cfg.n_kv_heads > std::min(cfg.small_units, cfg.stream_chains)) break;
-      if (blob_estimate(p, with_cells, 0, (size_t)units, 0, (size_t)merges) > max_blob) continue;
       const double us = stream_us(cfg, std::min(r, most_rows), longest, chunk, keys * cfg.n_kv_heads);
+      if (!(us < below)) continue;
+      const size_t blob = blob_estimate(p, with_cells, 0, (size_t)units, 0, (size_t)merges);
+      *largest_bytes = std::max(*largest_bytes, workspace_of(cfg, blob, parts));
+      if (blob > max_blob) continue;
       if (best.rows == 0 || us < best.us) best = {r, (int32_t)chunk, us};
     }
   }
@@ -432,15 +446,18 @@ int32_t build_plan(Pool& pool, const PlanConfig& cfg, int32_t n_seqs, const int3
   cut_tile_items(p, cfg);
   cut_stream_items(stream_tiles, cfg.kv_tile, cfg.stream_target, cfg.stream_min_chunk, &p->stream_items, &p->merges,
                    &p->part_rows);
+  p->largest_bytes = 0;
   if (cfg.small_units > 0 && (int64_t)(tile_tiles.size() + stream_tiles.size()) * cfg.n_kv_heads <= cfg.small_units) {
     // (a call whose descriptors travel in the kernel arguments goes on doing so)
     const size_t units = p->stream_items.size() * (size_t)cfg.n_kv_heads;
     const size_t chains = std::min(units, (size_t)std::max(cfg.stream_chains, 1));
     const size_t links = p->tile_links.size() + (units == chains ? 0 : units + chains);
     const size_t blob = blob_estimate(*p, with_cells, p->tile_items.size(), p->stream_items.size(), links, p->merges.size());
+    p->largest_bytes = workspace_of(cfg, blob, p->part_rows);
     const StreamShape s = small_shape(*p, cfg, group, with_cells,
-                                      blob <= (size_t)cfg.inline_blob_bytes ? (size_t)cfg.inline_blob_bytes : SIZE_MAX);
-    if (s.rows > 0 && s.us < planned_us(*p, cfg)) {
+                                      blob <= (size_t)cfg.inline_blob_bytes ? (size_t)cfg.inline_blob_bytes : SIZE_MAX,
+                                      planned_us(*p, cfg), &p->largest_bytes);
+    if (s.rows > 0) {
       p->tile_items.clear();
       p->tile_links.clear();
       p->tile_chains = 0;
@@ -509,10 +526,9 @@ int32_t build_plan(Pool& pool, const PlanConfig& cfg, int32_t n_seqs, const int3
   p->off_cells = off;
   if (with_cells) off = align_up(off + (size_t)p->total_tokens * sizeof(int32_t), 16);
   p->blob_bytes = off;  // descriptors: small blobs travel in the kernel arguments, larger ones are uploaded
-  off = align_up(off, 256);
-  p->off_parts = off;
-  off += (size_t)p->part_rows * cfg.n_kv_heads * (cfg.head_dim + 2) * sizeof(float);
-  p->total_bytes = align_up(off, 256) + 256;
+  p->off_parts = align_up(off, 256);
+  p->total_bytes = workspace_of(cfg, p->blob_bytes, p->part_rows);
+  p->largest_bytes = std::max(p->largest_bytes, p->total_bytes);
   return OK;
 }
 

@@ -89,6 +89,10 @@ struct AttendPlan {
   size_t blob_bytes = 0;   // descriptors
   size_t off_parts = 0;    // fp32 partial rows, each (head_dim + 2) floats per KV head
   size_t total_bytes = 0;  // whole workspace
+  // Whether a small batch is planned as one, and how it is then cut, depends on the size of its descriptors: on how many
+  // segments its slots have, and on with_cells.  This is the largest workspace that a plan of the same batch comes to
+  // whatever the outcome (up to the segments themselves).
+  size_t largest_bytes = 0;
 };
 
 // Caller holds pool.mutex().  with_cells reserves, inside the descriptor blob, one int32 per new token for the
