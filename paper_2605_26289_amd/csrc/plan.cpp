@@ -270,10 +270,13 @@ double stream_us(const PlanConfig& cfg, int32_t tile_rows, int64_t longest, int6
   return kUnitFixed[mb] + walk + (split > 1 ? merge + kMergeSplitUs * (double)split : 0.0);
 }
 
-// Descriptor bytes of a plan, alignment padding included.
-size_t blob_estimate(const AttendPlan& p, bool with_cells, size_t tile_items, size_t stream_items, size_t links, size_t merges) {
-  return p.entries.size() * sizeof(DkEntry) + p.segs.size() * sizeof(DkSeg) + (tile_items + stream_items) * sizeof(DkItem) +
-         merges * sizeof(DkMerge) + (links + (with_cells ? (size_t)p.total_tokens : 0)) * sizeof(int32_t) + 8 * 16;
+// Descriptor bytes of a plan, as build_plan lays them out (a queue's counter, never in the kernel arguments, left out).
+size_t blob_size(const AttendPlan& p, bool with_cells, size_t tile_items, size_t tile_links, size_t stream_items, size_t stream_links,
+                 size_t merges) {
+  const auto part = [](size_t n, size_t each) { return align_up(n * each, 16); };
+  return part(p.entries.size(), sizeof(DkEntry)) + part(p.segs.size(), sizeof(DkSeg)) + part(tile_items, sizeof(DkItem)) +
+         part(tile_links, sizeof(int32_t)) + part(stream_items, sizeof(DkItem)) + part(stream_links, sizeof(int32_t)) +
+         part(merges, sizeof(DkMerge)) + part(with_cells ? (size_t)p.total_tokens : 0, sizeof(int32_t));
 }
 
 // Workspace of a plan: its descriptors, then its partial rows.
@@ -316,7 +319,7 @@ StreamShape small_shape(const AttendPlan& p, const PlanConfig& cfg, int32_t grou
       if (units * cfg.n_kv_heads > std::min(cfg.small_units, cfg.stream_chains)) break;
       const double us = stream_us(cfg, std::min(r, most_rows), longest, chunk, keys * cfg.n_kv_heads);
       if (!(us < below)) continue;
-      const size_t blob = blob_estimate(p, with_cells, 0, (size_t)units, 0, (size_t)merges);
+      const size_t blob = blob_size(p, with_cells, 0, 0, (size_t)units, 0, (size_t)merges);
       *largest_bytes = std::max(*largest_bytes, workspace_of(cfg, blob, parts));
       if (blob > max_blob) continue;
       if (best.rows == 0 || us < best.us) best = {r, (int32_t)chunk, us};
@@ -451,8 +454,8 @@ int32_t build_plan(Pool& pool, const PlanConfig& cfg, int32_t n_seqs, const int3
     // (a call whose descriptors travel in the kernel arguments goes on doing so)
     const size_t units = p->stream_items.size() * (size_t)cfg.n_kv_heads;
     const size_t chains = std::min(units, (size_t)std::max(cfg.stream_chains, 1));
-    const size_t links = p->tile_links.size() + (units == chains ? 0 : units + chains);
-    const size_t blob = blob_estimate(*p, with_cells, p->tile_items.size(), p->stream_items.size(), links, p->merges.size());
+    const size_t blob = blob_size(*p, with_cells, p->tile_items.size(), p->tile_links.size(), p->stream_items.size(),
+                                  units == chains ? 0 : units + chains, p->merges.size());
     p->largest_bytes = workspace_of(cfg, blob, p->part_rows);
     const StreamShape s = small_shape(*p, cfg, group, with_cells,
                                       blob <= (size_t)cfg.inline_blob_bytes ? (size_t)cfg.inline_blob_bytes : SIZE_MAX,
