@@ -95,19 +95,29 @@ struct dk_pool {
   int32_t arrival_slice = -1;  // of the streaming kernel's counters; -1: none was free
 
   // `scale_ok`: the scale is positive and finite (the MFMA kernels take the row maximum before scaling).
-  Route route(bool scale_ok, int32_t n_seqs, const int32_t* cu_delta) const {
-    if (variant == 1 || !scale_ok) return Route::kRef;
+  // The batch is checked before its lengths are looked at.
+  int32_t choose_route(bool scale_ok, int32_t n_seqs, const int32_t* slots, const int32_t* cu_delta, Route* route) {
+    *route = Route::kRef;
+    if (variant == 1 || !scale_ok) return DK_OK;
     const int64_t group = desc.n_q_heads / desc.n_kv_heads;
-    if (desc.dtype == DK_BF16 && desc.head_dim == 128 && group <= 16 && (group & (group - 1)) == 0) return Route::kTile;
+    if (desc.dtype == DK_BF16 && desc.head_dim == 128 && group <= 16 && (group & (group - 1)) == 0) {
+      *route = Route::kTile;
+      return DK_OK;
+    }
+    {
+      std::lock_guard<std::mutex> lk(meta.mutex());
+      const int32_t rc = meta.check_batch(n_seqs, slots, cu_delta);
+      if (rc != DK_OK) return rc;
+    }
     // the others divide packed row numbers (below group * delta) by a multiplication that is exact while
     // row * (group - 1) < 2^32
     int64_t most = 0;
-    if (cu_delta)
-      for (int32_t b = 0; b < n_seqs; ++b) most = std::max<int64_t>(most, (int64_t)cu_delta[b + 1] - cu_delta[b]);
-    if (most >= (int64_t(1) << 32) / (group * group)) return Route::kRef;
-    return desc.dtype == DK_BF16 ? Route::kGeneral : Route::kF32;
+    for (int32_t b = 0; b < n_seqs; ++b) most = std::max<int64_t>(most, (int64_t)cu_delta[b + 1] - cu_delta[b]);
+    if (most < (int64_t(1) << 32) / (group * group)) *route = desc.dtype == DK_BF16 ? Route::kGeneral : Route::kF32;
+    return DK_OK;
   }
 
+  // (of a batch that choose_route() has let pass)
   dk::PlanConfig plan_config(Route r, int32_t n_seqs, const int32_t* cu_delta) const {
     dk::PlanConfig c = cfg;
     c.use_mfma = r != Route::kRef;
@@ -136,8 +146,7 @@ struct dk_pool {
       // shorter than that is worth.
       int64_t items = 0;
       const int64_t group = desc.n_q_heads / desc.n_kv_heads;
-      if (cu_delta)
-        for (int32_t b = 0; b < n_seqs; ++b) items += (group * ((int64_t)cu_delta[b + 1] - cu_delta[b]) + 31) / 32;
+      for (int32_t b = 0; b < n_seqs; ++b) items += (group * ((int64_t)cu_delta[b + 1] - cu_delta[b]) + 31) / 32;
       c.tile_rows = items * desc.n_kv_heads >= 256 ? 32 : 16;
       c.stream_rows = 0;
       c.small_units = 0;
@@ -518,9 +527,12 @@ int32_t dk_attend_workspace_bytes(dk_pool* pool, int32_t n_seqs, const int32_t* 
     std::lock_guard<std::mutex> launch(pool->launch_mu);
     dk::AttendPlan& plan = pool->plan;
     if (staged < 0 || staged > 2) return DK_ERR_INVALID;
-    const dk::PlanConfig cfg = pool->plan_config(pool->route(true, n_seqs, cu_delta), n_seqs, cu_delta);
+    Route route;
+    int32_t rc = pool->choose_route(true, n_seqs, slots, cu_delta, &route);
+    if (rc != DK_OK) return rc;
+    const dk::PlanConfig cfg = pool->plan_config(route, n_seqs, cu_delta);
     std::lock_guard<std::mutex> lk(pool->meta.mutex());
-    int32_t rc = dk::build_plan(pool->meta, cfg, n_seqs, slots, cu_delta, staged != 0, &plan, staged == 2);
+    rc = dk::build_plan(pool->meta, cfg, n_seqs, slots, cu_delta, staged != 0, &plan, staged == 2);
     if (rc != DK_OK) return rc;
     *bytes_out = (int64_t)plan.total_bytes;
     // dk_append_attend may also plan the batch after its append, in appended mode: without the table of cells, over slots
@@ -563,7 +575,9 @@ int32_t attend_locked(dk_pool* pool, int32_t n_seqs, const int32_t* slots, const
   PhaseClock clk;
   hipStream_t st = (hipStream_t)stream;
   dk::AttendPlan& plan = pool->plan;
-  Route route = pool->route(scale > 0.f && scale < 3.0e38f, n_seqs, cu_delta);
+  Route route;
+  const int32_t checked = pool->choose_route(scale > 0.f && scale < 3.0e38f, n_seqs, slots, cu_delta, &route);
+  if (checked != DK_OK) return checked;
   bool inline_blob = false;
   int32_t tile_rows = 0;
   while (true) {

@@ -1,8 +1,14 @@
 """Workspace sizes of the attention calls (host planner through the C ABI, no GPU)."""
+import os
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 
 from paper_2605_26289_amd import binding as dk
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
 def _pool(n_slots, arena_cells, hq, hkv, d=128, dtype=dk.BF16, granule=0):
@@ -50,3 +56,20 @@ def test_the_query_for_append_attend_covers_random_batches(seed):
         granule = int(rng.choice([16, 64, 256]))
         asked, needed = _fused_and_appended(hq, hkv, hist, delta, d, dtype, granule)
         assert asked >= needed, (hq, hkv, d, dtype, hist, delta, granule, asked, needed)
+
+
+@pytest.mark.parametrize("hq,hkv,d,dtype", [(8, 2, 128, dk.BF16), (8, 2, 64, dk.BF16), (6, 2, 128, dk.BF16), (8, 2, 128, dk.F32)])
+def test_a_batch_longer_than_the_pool_is_refused_before_its_arrays_are_read(hq, hkv, d, dtype):
+    """n_seqs is checked against the slots, entry by entry: the arrays of a wrong call need not reach as far as it says.
+    (In a process of its own, which a read past their end would kill.)"""
+    code = f"""
+import ctypes as C, numpy as np
+from paper_2605_26289_amd import binding as dk
+pool = dk.pool_create(dk.PoolDesc(2, 0, 4096, 0, {hq}, {hkv}, {d}, {dtype}, 256 * 10, 256 * 20, 256 * 30, 1 << 20))
+s = dk.seq_acquire(pool)
+slots, cu = np.array([s, s], dtype=np.int32), np.array([0, 0, 0], dtype=np.int32)
+out = C.c_int64()
+print(dk.STATUS_NAMES[dk.lib().dk_attend_workspace_bytes(pool, 1 << 30, slots.ctypes.data, cu.ctypes.data, 1, C.byref(out))])
+"""
+    run = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=120)
+    assert run.returncode == 0 and run.stdout.strip() == "DUP_SLOT", (run.returncode, run.stdout, run.stderr[-500:])
