@@ -424,7 +424,7 @@ int32_t append_locked(dk_pool* pool, int32_t n_seqs, const int32_t* slots, const
   }
   // Where the tokens go in few runs of cells (a run or two per slot, unless the arena is fragmented) the runs travel in the
   // kernel arguments; otherwise a table of every token's cell is uploaded.
-  if (total <= INT32_MAX / 2) {
+  if (total <= INT32_MAX / 2 && dk::kv_runs_in_one_launch(pool->view(), total)) {
     dk::KvRuns runs;
     int32_t n_runs = 0;
     int64_t t = 0;

@@ -35,6 +35,12 @@ struct KvRuns {
   int32_t tok[KV_INLINE_MAX_RUNS + 1];
   int32_t cell[KV_INLINE_MAX_RUNS];
 };
+// A launch has fewer than 2^32 threads, one for every 16 bytes of K: appends of 64 GiB and more go by table, in pieces.
+constexpr bool kv_runs_in_one_launch(const ArenaView& a, int64_t n_tok) {
+  return n_tok * a.n_kv_heads * (a.head_dim * (a.dtype == 0 ? 4 : 2) / 16) < (int64_t(1) << 32) - 256;
+}
+static_assert(kv_runs_in_one_launch({nullptr, nullptr, 0, 8, 8, 128, 1}, 33554429) &&
+              !kv_runs_in_one_launch({nullptr, nullptr, 0, 8, 8, 128, 1}, 33554431), "8 KV heads of 128, bf16: 128 pieces a token");
 hipError_t launch_kv_scatter_runs(const ArenaView& a, void* k_arena, void* v_arena, const KvRuns& runs, int32_t n_runs,
                                   int32_t n_tok, const void* k_new, const void* v_new, hipStream_t stream);
 
