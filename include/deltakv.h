@@ -9,8 +9,8 @@
  *   - every function returns an int32_t status (DK_OK == 0, errors negative), never
  *     throws, aborts or prints;
  *   - a call that fails leaves the pool's state unchanged;
- *   - calls that launch GPU work (dk_kv_append, dk_delta_attend, dk_append_attend,
- *     dk_delta_attend_noalloc, dk_seq_gather, dk_verify_greedy) are
+ *   - calls that launch GPU work (dk_kv_append, dk_delta_attend, dk_append_attend, their _sized
+ *     forms, dk_delta_attend_noalloc, dk_seq_gather, dk_verify_greedy) are
  *     asynchronous on the HIP stream passed as `stream` (a hipStream_t cast to void*,
  *     NULL = the default stream).  They never wait for the device and never allocate
  *     device or pinned memory: descriptors travel through the caller's staging memory
@@ -183,12 +183,25 @@ int32_t dk_kv_reserve(dk_pool* pool, int32_t n_seqs, const int32_t* slots, const
  *          (slots, cu_delta, mode) and the same slot lengths; DK_ERR_WORKSPACE otherwise
  *          (dk_attend_workspace_bytes: staged = 0 appended mode, 1 staged mode, 2 dk_append_attend)
  * Entries with Delta_b == 0 produce no rows; n_b == 0 is legal.
+ *
+ * Calls that only the scalar kernel can carry.  Pools of fp32, of 64-wide heads, or with a number of query heads per KV
+ * head that is no power of two up to 16 were once served by the scalar kernel alone, which needs a few KiB of workspace, no
+ * partial rows and no alignment.  A call on such a pool that has room for no more still runs, 10 to 30 times slower:
+ *   - the workspace (or the built-in array of dk_delta_attend_noalloc) is smaller than dk_attend_workspace_bytes() says but
+ *     large enough for the scalar kernel;
+ *   - the descriptors need an upload and the stream is being captured, or the pool has no staging memory (or too little);
+ *   - q or out is not 16-byte aligned.
+ * dk_delta_attend_sized / dk_append_attend_sized return DK_ERR_WORKSPACE in the first case, for callers who grow their
+ * workspace on demand; in all else they are dk_delta_attend / dk_append_attend.  dk_last_plan() tells which kernel ran.
  */
 int32_t dk_attend_workspace_bytes(dk_pool* pool, int32_t n_seqs, const int32_t* slots, const int32_t* cu_delta,
                                   int32_t staged, int64_t* bytes_out);
 int32_t dk_delta_attend(dk_pool* pool, int32_t n_seqs, const int32_t* slots, const int32_t* cu_delta, const void* q,
                         const void* k_new, const void* v_new, float scale, void* out, float* lse, void* workspace,
                         int64_t workspace_bytes, void* stream);
+int32_t dk_delta_attend_sized(dk_pool* pool, int32_t n_seqs, const int32_t* slots, const int32_t* cu_delta, const void* q,
+                              const void* k_new, const void* v_new, float scale, void* out, float* lse, void* workspace,
+                              int64_t workspace_bytes, void* stream);
 
 /*
  * append_attend: Decode(sigma, batch) of paper Alg. 1 as one call -- appends all Delta_b new tokens of every entry
@@ -205,6 +218,9 @@ int32_t dk_delta_attend(dk_pool* pool, int32_t n_seqs, const int32_t* slots, con
 int32_t dk_append_attend(dk_pool* pool, int32_t n_seqs, const int32_t* slots, const int32_t* cu_delta, const void* q,
                          const void* k_new, const void* v_new, float scale, void* out, float* lse, void* workspace,
                          int64_t workspace_bytes, void* stream);
+int32_t dk_append_attend_sized(dk_pool* pool, int32_t n_seqs, const int32_t* slots, const int32_t* cu_delta, const void* q,
+                               const void* k_new, const void* v_new, float scale, void* out, float* lse, void* workspace,
+                               int64_t workspace_bytes, void* stream);
 
 /*
  * delta_attend for callers that cannot allocate and have no workspace to hand over: code under HIP graph
@@ -342,6 +358,21 @@ int32_t dk_seq_stats(dk_pool* pool, int32_t slot, int64_t* segments_out, int64_t
  * dk_pool_destroy and dk_attend_times that waits.  DK_ERR_WORKSPACE for a pool without staging memory.
  */
 int32_t dk_staging_wait(dk_pool* pool);
+
+/*
+ * What the last attention call that was enqueued, or the last dk_attend_workspace_bytes(), of this pool planned: HOST int64
+ * [DK_PLAN_FIELDS].  DK_ERR_INVALID before the first of them.
+ */
+enum { DK_ROUTE_SCALAR = 0, DK_ROUTE_TILE = 1, DK_ROUTE_GENERAL = 2, DK_ROUTE_F32 = 3 };
+enum {
+  DK_PLAN_ROUTE = 0,        /* scalar kernel; tile, general or fp32 kernel, each of the first two beside the streaming kernel */
+  DK_PLAN_ROW_ITEMS = 1,    /* work items of the tile, block or fp32 kernel */
+  DK_PLAN_STREAM_ITEMS = 2, /* work items of the streaming kernel */
+  DK_PLAN_MERGES = 3,       /* row tiles whose key range is split */
+  DK_PLAN_BYTES = 4,        /* workspace */
+  DK_PLAN_FIELDS = 5
+};
+int32_t dk_last_plan(dk_pool* pool, int64_t* fields_out);
 
 /* Kernel selection for dk_delta_attend: 0 automatic (default), 1 force the scalar reference kernel. */
 int32_t dk_set_attend_variant(dk_pool* pool, int32_t variant);

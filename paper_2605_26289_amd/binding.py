@@ -64,6 +64,11 @@ SIGNATURES = {
                                     C.c_float, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int64, C.c_void_p]),
     "dk_append_attend": (C.c_int32, [C.c_void_p, C.c_int32, _ARRAY, _ARRAY, C.c_void_p, C.c_void_p, C.c_void_p,
                                      C.c_float, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int64, C.c_void_p]),
+    "dk_delta_attend_sized": (C.c_int32, [C.c_void_p, C.c_int32, _ARRAY, _ARRAY, C.c_void_p, C.c_void_p, C.c_void_p,
+                                          C.c_float, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int64, C.c_void_p]),
+    "dk_append_attend_sized": (C.c_int32, [C.c_void_p, C.c_int32, _ARRAY, _ARRAY, C.c_void_p, C.c_void_p, C.c_void_p,
+                                           C.c_float, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int64, C.c_void_p]),
+    "dk_last_plan": (C.c_int32, [C.c_void_p, _I64P]),
     "dk_delta_attend_noalloc": (C.c_int32, [C.c_void_p, C.c_int32, _ARRAY, _ARRAY, C.c_void_p, C.c_void_p, C.c_void_p,
                                             C.c_float, C.c_void_p, C.c_void_p, C.c_void_p]),
     "dk_staging_wait": (C.c_int32, [C.c_void_p]),
@@ -273,21 +278,33 @@ def attend_workspace_bytes(pool, slots, cu_delta, staged) -> int:
 
 
 def delta_attend(pool, slots, cu_delta, q, out, scale: float, k_new=None, v_new=None, lse=None,
-                 workspace=None, stream=None) -> None:
+                 workspace=None, stream=None, sized: bool = False) -> None:
+    """sized: refuse (WORKSPACE) a workspace that only the scalar kernel could do with."""
     s_arr, s_p = _array(slots)
     c_arr, c_p = _array(cu_delta)
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _launch(lib().dk_delta_attend, (pool, len(s_arr), s_p, c_p, _ptr(q), _ptr(k_new), _ptr(v_new), float(scale), _ptr(out),
+    _launch(lib().dk_delta_attend_sized if sized else lib().dk_delta_attend, (pool, len(s_arr), s_p, c_p, _ptr(q), _ptr(k_new), _ptr(v_new), float(scale), _ptr(out),
                                     _ptr(lse), _ptr(workspace), ws_bytes, _stream(stream)), "delta_attend", pool)
 
 
 def append_attend(pool, slots, cu_delta, q, k_new, v_new, out, scale: float, lse=None, workspace=None,
-                  stream=None) -> None:
+                  stream=None, sized: bool = False) -> None:
+    """sized: as in delta_attend"""
     s_arr, s_p = _array(slots)
     c_arr, c_p = _array(cu_delta)
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _launch(lib().dk_append_attend, (pool, len(s_arr), s_p, c_p, _ptr(q), _ptr(k_new), _ptr(v_new), float(scale), _ptr(out),
+    _launch(lib().dk_append_attend_sized if sized else lib().dk_append_attend, (pool, len(s_arr), s_p, c_p, _ptr(q), _ptr(k_new), _ptr(v_new), float(scale), _ptr(out),
                                      _ptr(lse), _ptr(workspace), ws_bytes, _stream(stream)), "append_attend", pool)
+
+
+ROUTES = ("scalar", "tile", "general", "f32")
+
+
+def last_plan(pool) -> dict:
+    """What the last attention call or workspace query of the pool planned (dk_last_plan)."""
+    out = (C.c_int64 * 5)()
+    _check(lib().dk_last_plan(pool, out), "last_plan")
+    return {"route": ROUTES[out[0]], "row_items": out[1], "stream_items": out[2], "merges": out[3], "bytes": out[4]}
 
 
 STATIC_SCRATCH_BYTES = 32 << 20

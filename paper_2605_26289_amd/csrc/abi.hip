@@ -59,10 +59,10 @@ int32_t guarded(F&& body) noexcept {
 
 // Which kernels carry an attention call.
 enum class Route {
-  kRef,      // scalar reference kernel: variant 1, a scale that is not positive and finite
-  kTile,     // bf16, 128-wide heads, groups of 2^k <= 16 query heads: tile and stream kernels
-  kGeneral,  // bf16, any other shape: block kernel and the stream kernel's general form
-  kF32,      // fp32 pools
+  kRef = DK_ROUTE_SCALAR,       // scalar reference kernel: variant 1, a scale that is not positive and finite
+  kTile = DK_ROUTE_TILE,        // bf16, 128-wide heads, groups of 2^k <= 16 query heads: tile and stream kernels
+  kGeneral = DK_ROUTE_GENERAL,  // bf16, any other shape: block kernel and the stream kernel's general form
+  kF32 = DK_ROUTE_F32,          // fp32 pools
 };
 
 struct dk_pool {
@@ -82,6 +82,7 @@ struct dk_pool {
   int64_t host_calls[2] = {0, 0};  // dk_delta_attend*, dk_kv_append
   std::mutex launch_mu;  // serialises GPU-launching calls (shared staging ring, dev_meta and plan)
   dk::AttendPlan plan;   // reused from call to call so that steady-state planning allocates nothing
+  int64_t last_plan[DK_PLAN_FIELDS] = {-1};  // see dk_last_plan
   std::vector<int64_t> append_cells, append_old_len;  // likewise, for the bookkeeping of appends
 
   dk_pool(const dk_pool_desc& d, int32_t granule)
@@ -153,6 +154,14 @@ struct dk_pool {
       c.tile_min_chunk = std::max(cfg.tile_min_chunk, 65536 / desc.head_dim);
     }
     return c;
+  }
+
+  void keep_plan(Route r) {
+    last_plan[DK_PLAN_ROUTE] = (int64_t)r;
+    last_plan[DK_PLAN_ROW_ITEMS] = (int64_t)plan.tile_items.size();
+    last_plan[DK_PLAN_STREAM_ITEMS] = (int64_t)plan.stream_items.size();
+    last_plan[DK_PLAN_MERGES] = (int64_t)plan.merges.size();
+    last_plan[DK_PLAN_BYTES] = (int64_t)plan.total_bytes;
   }
 
   int32_t hip_fail(hipError_t e) {
@@ -534,6 +543,7 @@ int32_t dk_attend_workspace_bytes(dk_pool* pool, int32_t n_seqs, const int32_t* 
     std::lock_guard<std::mutex> lk(pool->meta.mutex());
     rc = dk::build_plan(pool->meta, cfg, n_seqs, slots, cu_delta, staged != 0, &plan, staged == 2);
     if (rc != DK_OK) return rc;
+    pool->keep_plan(route);
     *bytes_out = (int64_t)plan.total_bytes;
     // dk_append_attend may also plan the batch after its append, in appended mode: without the table of cells, over slots
     // that then have more runs of cells (at worst one per granule the append takes)
@@ -566,9 +576,10 @@ bool capturing(hipStream_t st) {
 // arguments and an MFMA kernel runs (otherwise kNotFoldable is returned and nothing has happened): the attention is
 // planned on the slots as they are (staged mode), the bookkeeping follows, and the rows are written into the arena
 // by the attention kernel itself.
+// full_size: a workspace that only the scalar kernel could do with is refused (the *_sized entry points).
 int32_t attend_locked(dk_pool* pool, int32_t n_seqs, const int32_t* slots, const int32_t* cu_delta, const void* q,
                       const void* k_new, const void* v_new, float scale, void* out, float* lse, void* workspace,
-                      int64_t workspace_bytes, void* stream, bool fold_append) {
+                      int64_t workspace_bytes, void* stream, bool fold_append, bool full_size) {
   if ((k_new == nullptr) != (v_new == nullptr)) return DK_ERR_INVALID;
   const bool staged = k_new != nullptr;
   if (fold_append && !staged) return DK_ERR_INVALID;
@@ -596,14 +607,18 @@ int32_t attend_locked(dk_pool* pool, int32_t n_seqs, const int32_t* slots, const
     if (route == Route::kRef || route == Route::kTile) break;
     // The reference kernel serves these shapes with a handful of descriptors, no partials and single-element accesses to
     // q and out.  Where a caller has only made room for that -- a workspace or the static array without room for partials, a
-    // pool without staging memory, a capture that cannot take an upload, rows at odd addresses -- it still does.
-    const bool fits = (((uintptr_t)q | (uintptr_t)out) & 15) == 0 && workspace_bytes >= (int64_t)plan.total_bytes &&
+    // pool without staging memory, a capture that cannot take an upload, rows at odd addresses -- it still does; but a caller
+    // who can make more room is told to.
+    const bool room = workspace_bytes >= (int64_t)plan.total_bytes;
+    const bool fits = (((uintptr_t)q | (uintptr_t)out) & 15) == 0 &&
                       (inline_blob || (pool->ring_size > 0 && plan.blob_bytes <= pool->stage_cap && !capturing(st)));
-    if (fits) break;
+    if (fits && room) break;
+    if (fits && full_size) return DK_ERR_WORKSPACE;
     if (fold_append) return kNotFoldable;
     route = Route::kRef;
   }
   if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < (int64_t)plan.total_bytes) return DK_ERR_WORKSPACE;
+  pool->keep_plan(route);
   // The bookkeeping half of a folded append.  From here on a failure must leave the pool as it was.
   std::vector<int64_t>& dst = pool->append_cells;
   std::vector<int64_t>& old_len = pool->append_old_len;
@@ -726,10 +741,10 @@ int32_t attend_locked(dk_pool* pool, int32_t n_seqs, const int32_t* slots, const
 
 int32_t attend_impl(dk_pool* pool, int32_t n_seqs, const int32_t* slots, const int32_t* cu_delta, const void* q,
                     const void* k_new, const void* v_new, float scale, void* out, float* lse, void* workspace,
-                    int64_t workspace_bytes, void* stream) {
+                    int64_t workspace_bytes, void* stream, bool full_size) {
   std::lock_guard<std::mutex> launch(pool->launch_mu);
   return attend_locked(pool, n_seqs, slots, cu_delta, q, k_new, v_new, scale, out, lse, workspace, workspace_bytes,
-                       stream, false);
+                       stream, false, full_size);
 }
 
 // dk_append_attend.  A small call (its descriptors and cell table fit the kernel arguments) is one launch: the
@@ -738,20 +753,20 @@ int32_t attend_impl(dk_pool* pool, int32_t n_seqs, const int32_t* slots, const i
 // separate copy kernel does, and attending the new rows from the arena beats reading them token-major).
 int32_t append_attend_impl(dk_pool* pool, int32_t n_seqs, const int32_t* slots, const int32_t* cu_delta,
                            const void* q, const void* k_new, const void* v_new, float scale, void* out, float* lse,
-                           void* workspace, int64_t workspace_bytes, void* stream) {
+                           void* workspace, int64_t workspace_bytes, void* stream, bool full_size) {
   std::lock_guard<std::mutex> launch(pool->launch_mu);
   const int64_t total = (n_seqs > 0 && cu_delta) ? cu_delta[n_seqs] : 0;
   if (total > 0 && (!k_new || !v_new)) return DK_ERR_INVALID;
   if (n_seqs <= kFoldMaxSeqs && total <= kFoldMaxTokens) {
     const int32_t rc = attend_locked(pool, n_seqs, slots, cu_delta, q, k_new, v_new, scale, out, lse, workspace,
-                                     workspace_bytes, stream, true);
+                                     workspace_bytes, stream, true, full_size);
     if (rc != kNotFoldable) return rc;
   }
   if (total > 0 && (!q || !out)) return DK_ERR_INVALID;
   int32_t rc = append_locked(pool, n_seqs, slots, cu_delta, nullptr, k_new, v_new, stream);
   if (rc != DK_OK) return rc;
   rc = attend_locked(pool, n_seqs, slots, cu_delta, q, nullptr, nullptr, scale, out, lse, workspace, workspace_bytes,
-                     stream, false);
+                     stream, false, full_size);
   // (the copy kernel already enqueued wrote cells that the rolled-back slots no longer own: harmless, they are free)
   if (rc != DK_OK) undo_append(pool, n_seqs, slots, pool->append_old_len);
   return rc;
@@ -800,7 +815,7 @@ int32_t dk_delta_attend_noalloc(dk_pool* pool, int32_t n_seqs, const int32_t* sl
     if (rc != DK_OK) return rc;
     // a call that needs more than the array holds is turned down by the size check (DK_ERR_WORKSPACE)
     return attend_impl(pool, n_seqs, slots, cu_delta, q, k_new, v_new, scale, out, lse, ws,
-                       (int64_t)DK_STATIC_SCRATCH_BYTES, stream);
+                       (int64_t)DK_STATIC_SCRATCH_BYTES, stream, false);
   });
 }
 
@@ -810,7 +825,17 @@ int32_t dk_append_attend(dk_pool* pool, int32_t n_seqs, const int32_t* slots, co
   if (!pool) return DK_ERR_INVALID;
   return guarded([&]() -> int32_t {
     return append_attend_impl(pool, n_seqs, slots, cu_delta, q, k_new, v_new, scale, out, lse, workspace,
-                              workspace_bytes, stream);
+                              workspace_bytes, stream, false);
+  });
+}
+
+int32_t dk_append_attend_sized(dk_pool* pool, int32_t n_seqs, const int32_t* slots, const int32_t* cu_delta, const void* q,
+                               const void* k_new, const void* v_new, float scale, void* out, float* lse, void* workspace,
+                               int64_t workspace_bytes, void* stream) {
+  if (!pool) return DK_ERR_INVALID;
+  return guarded([&]() -> int32_t {
+    return append_attend_impl(pool, n_seqs, slots, cu_delta, q, k_new, v_new, scale, out, lse, workspace,
+                              workspace_bytes, stream, true);
   });
 }
 
@@ -820,8 +845,26 @@ int32_t dk_delta_attend(dk_pool* pool, int32_t n_seqs, const int32_t* slots, con
   if (!pool) return DK_ERR_INVALID;
   return guarded([&]() -> int32_t {
     return attend_impl(pool, n_seqs, slots, cu_delta, q, k_new, v_new, scale, out, lse, workspace, workspace_bytes,
-                       stream);
+                       stream, false);
   });
+}
+
+int32_t dk_delta_attend_sized(dk_pool* pool, int32_t n_seqs, const int32_t* slots, const int32_t* cu_delta, const void* q,
+                              const void* k_new, const void* v_new, float scale, void* out, float* lse, void* workspace,
+                              int64_t workspace_bytes, void* stream) {
+  if (!pool) return DK_ERR_INVALID;
+  return guarded([&]() -> int32_t {
+    return attend_impl(pool, n_seqs, slots, cu_delta, q, k_new, v_new, scale, out, lse, workspace, workspace_bytes,
+                       stream, true);
+  });
+}
+
+int32_t dk_last_plan(dk_pool* pool, int64_t* fields_out) {
+  if (!pool || !fields_out) return DK_ERR_INVALID;
+  std::lock_guard<std::mutex> launch(pool->launch_mu);
+  if (pool->last_plan[DK_PLAN_ROUTE] < 0) return DK_ERR_INVALID;
+  for (int i = 0; i < DK_PLAN_FIELDS; ++i) fields_out[i] = pool->last_plan[i];
+  return DK_OK;
 }
 
 }  // extern "C"

@@ -102,12 +102,12 @@ class DevicePool:
         if self.workspace is None:
             self.ensure_workspace(slots, cu_delta, k_new is not None)
         try:  # the library checks the size itself: only a call that outgrows the buffer pays for a size query
-            dk.delta_attend(self.handle, slots, cu_delta, q, out, scale, k_new, v_new, lse, self.workspace)
+            dk.delta_attend(self.handle, slots, cu_delta, q, out, scale, k_new, v_new, lse, self.workspace, sized=True)
         except dk.DeltaKVError as e:
             if e.name != "WORKSPACE":
                 raise
             ws = self.ensure_workspace(slots, cu_delta, k_new is not None)
-            dk.delta_attend(self.handle, slots, cu_delta, q, out, scale, k_new, v_new, lse, ws)
+            dk.delta_attend(self.handle, slots, cu_delta, q, out, scale, k_new, v_new, lse, ws, sized=True)
         return out
 
     def append_attend(self, slots, cu_delta, q, k_new, v_new, scale: float, out=None, lse=None):
@@ -117,12 +117,12 @@ class DevicePool:
         if self.workspace is None:
             self.ensure_workspace(slots, cu_delta, 2)
         try:
-            dk.append_attend(self.handle, slots, cu_delta, q, k_new, v_new, out, scale, lse, self.workspace)
+            dk.append_attend(self.handle, slots, cu_delta, q, k_new, v_new, out, scale, lse, self.workspace, sized=True)
         except dk.DeltaKVError as e:
             if e.name != "WORKSPACE":
                 raise
             ws = self.ensure_workspace(slots, cu_delta, 2)
-            dk.append_attend(self.handle, slots, cu_delta, q, k_new, v_new, out, scale, lse, ws)
+            dk.append_attend(self.handle, slots, cu_delta, q, k_new, v_new, out, scale, lse, ws, sized=True)
         return out
 
     def gather(self, slot: int):

@@ -1,0 +1,102 @@
+"""Pools whose batches change from call to call: the workspace grows with them, whatever the shape, and the kernel that
+serves a batch does not depend on what the pool did before."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2605_26289_amd import DevicePool
+from paper_2605_26289_amd import binding as dk
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [(32, 8, 64, "bf16"), (24, 8, 128, "bf16"), (4, 1, 64, "f32"), (8, 2, 128, "f32"), (32, 8, 128, "bf16")]
+HIST = [2000, 1700, 900, 2400]
+
+
+def _rows(gen, n, heads, d, dtype):
+    return torch.randn((n, heads, d), generator=gen, device="cuda").to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+
+
+def _pool(hq, hkv, d, dtype, hist, cells):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(d + hq)
+    pool = DevicePool(len(hist), cells, hq, hkv, d, dtype)
+    slots = [pool.acquire() for _ in hist]
+    pool.append(slots, np.concatenate([[0], np.cumsum(hist)]), _rows(gen, sum(hist), hkv, d, dtype), _rows(gen, sum(hist), hkv, d, dtype))
+    return pool, slots, gen
+
+
+@pytest.mark.parametrize("hq,hkv,d,dtype", SHAPES)
+@pytest.mark.parametrize("mode", ["staged", "appended", "fused"])
+def test_a_larger_batch_after_a_small_one_runs_as_on_a_fresh_pool(hq, hkv, d, dtype, mode):
+    big = [700, 500, 1, 9]
+    results = []
+    for small_first in (True, False):
+        pool, slots, gen = _pool(hq, hkv, d, dtype, HIST, sum(HIST) + sum(big) + 8192)
+        scale = d ** -0.5
+        if small_first:  # one decoding step, attended and dropped again
+            own = torch.Generator(device="cuda")
+            own.manual_seed(1)
+            one = np.arange(len(slots) + 1)
+            pool.attend(slots, one, _rows(own, len(slots), hq, d, dtype), scale, _rows(own, len(slots), hkv, d, dtype),
+                        _rows(own, len(slots), hkv, d, dtype))
+            held = pool.workspace.numel()
+        cu = np.concatenate([[0], np.cumsum(big)])
+        q, k, v = (_rows(gen, sum(big), h, d, dtype) for h in (hq, hkv, hkv))
+        if mode == "staged":
+            out = pool.attend(slots, cu, q, scale, k, v)
+        elif mode == "fused":
+            out = pool.append_attend(slots, cu, q, k, v, scale)
+        else:
+            pool.append(slots, cu, k, v)
+            out = pool.attend(slots, cu, q, scale)
+        plan = dk.last_plan(pool.handle)
+        assert plan["route"] != "scalar" and plan["bytes"] <= pool.workspace.numel(), plan
+        if small_first:
+            assert pool.workspace.numel() > held
+        results.append(out)
+        pool.close()
+    assert torch.equal(*results)
+
+
+def test_a_batch_that_cannot_be_folded_runs_on_a_fresh_pool():
+    """The plan made after the append has partial rows where the one made before it has none."""
+    hist, delta = [23, 50, 2030, 200], [68, 269, 1, 128]
+    outs = []
+    for fused in (True, False):
+        pool, slots, gen = _pool(32, 8, 128, "bf16", hist, 8192)
+        cu = np.concatenate([[0], np.cumsum(delta)])
+        q, k, v = (_rows(gen, sum(delta), h, 128, "bf16") for h in (32, 8, 8))
+        if fused:
+            outs.append(pool.append_attend(slots, cu, q, k, v, 128 ** -0.5))
+        else:
+            pool.append(slots, cu, k, v)
+            outs.append(pool.attend(slots, cu, q, 128 ** -0.5))
+        assert [pool.length(s) for s in slots] == [h + n for h, n in zip(hist, delta)]
+        pool.close()
+    assert torch.equal(*outs)
+
+
+@pytest.mark.parametrize("hq,hkv,d,dtype", SHAPES[:4])
+def test_a_short_workspace_is_refused_or_served_by_the_scalar_kernel_as_asked(hq, hkv, d, dtype):
+    pool, slots, gen = _pool(hq, hkv, d, dtype, [6000], 8192)
+    h, cu = pool.handle, [0, 3]
+    q, k, v = (_rows(gen, 3, x, d, dtype) for x in (hq, hkv, hkv))
+    need = dk.attend_workspace_bytes(h, slots, cu, 1)
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    out = torch.full_like(q, 7.0)
+    assert need > 4096
+    for name, call in (("attend", lambda: dk.delta_attend(h, slots, cu, q, out, 0.1, k, v, workspace=ws[:4096], sized=True)),
+                       ("fused", lambda: dk.append_attend(h, slots, cu, q, k, v, out, 0.1, workspace=ws[:4096], sized=True))):
+        with pytest.raises(dk.DeltaKVError, match="WORKSPACE"):
+            call()
+        assert pool.length(slots[0]) == 6000, name
+    torch.cuda.synchronize()
+    assert (out == 7.0).all()
+    dk.delta_attend(h, slots, cu, q, out, 0.1, k, v, workspace=ws[:4096])
+    assert dk.last_plan(h)["route"] == "scalar"
+    short = out.clone()
+    dk.delta_attend(h, slots, cu, q, out, 0.1, k, v, workspace=ws, sized=True)
+    assert dk.last_plan(h)["route"] != "scalar"
+    assert (out.float() - short.float()).abs().max().item() < 2e-2
+    pool.close()
