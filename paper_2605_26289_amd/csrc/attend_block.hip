@@ -222,7 +222,11 @@ __global__ __launch_bounds__(256, 2) void attend_block_kernel(BlobArg<INLINE> bl
 #pragma unroll
         for (int r = 0; r < 16; ++r) z = __builtin_fmaf(o[db][r], 0.f, z);
       const uint64_t bad = __builtin_amdgcn_ballot_w64(z != 0.f);
-      if (bad != 0) redo_rows<__bf16, HD, true>(c, e, it, g, wave * 32, (uint32_t)(bad | bad >> 32), m, lt[0], lane);
+      if (bad != 0) {
+#pragma unroll 1
+        for (int db = 0; db < G::DB; ++db)  // (one at a time: all of them do not fit the registers)
+          redo_rows<HD, true>(c, e, it, g, wave * 32, (uint32_t)(bad | bad >> 32), m, lt[0], lane, db, [](int) { return true; });
+      }
     }
   }
 }

@@ -373,59 +373,122 @@ __device__ __forceinline__ void store_rows_staged(const Ctx& c, const DkEntry& e
 
 // A product of matrix instructions multiplies every V row of a tile into every query row, hidden keys with weight zero --
 // and 0 * inf or 0 * NaN is NaN.  So where V holds such values at positions some of a tile's rows may not see, those rows
-// come out non-finite although what they attend to is not.  Kernels of shapes that were always free of that look at
-// their sums once, before the store, and have the non-finite rows (nobody pays for this otherwise) done again, key by key
-// over the visible keys alone, relative to the row's maximum m and weight sum l, which V has no part in.
-// Returns the rows of `bad` (bit i: row rl0 + i, its m and l in lane i) to memory; T: element type, ANYG as in row_token.
-__device__ __forceinline__ float wide(float x) { return x; }
-__device__ __forceinline__ float wide(__bf16 x) { return (float)x; }
-template <typename T, int HD, bool ANYG>
-__device__ __forceinline__ void redo_rows(const Ctx& c, const DkEntry& e, const DkItem& it, int g, int rl0, uint32_t bad,
-                                          float m_lane, float l_lane, int lane) {
-  constexpr int ROW = HD * (int)sizeof(T), PER_LANE = HD / 64, VEC = 16 / (int)sizeof(T);
-  typedef T vec __attribute__((ext_vector_type(VEC)));
+// come out non-finite although what they attend to is not (and an infinity the row does see may come out as NaN, where the
+// lower half of its weight is zero).  Kernels of shapes that were always free of that look at their sums once, before the
+// store, and have the row blocks with non-finite sums done again (nobody pays for this otherwise): by the same products, but
+// with the non-finite elements of V taken out, so that the sums are those of the finite ones; then a depth that has such
+// elements at positions a row sees is set to what they make of it -- infinite if they are infinities of one sign, else NaN.
+// The first position of each kind decides that, since a row sees all positions up to its limit.
+//
+// One wavefront does a row block over all keys of its item, straight from memory, relative to each row's final maximum m and
+// weight sum l, which V has no part in; a row whose weight sum is NaN has a NaN weight, is NaN throughout, and stays as it
+// is.  Every element is written by the wavefront that stored it before, so the bits are the same on every call.
+// The value may well be one that every row sees, in every item of a long turn, so this has to keep up with the scalar kernel,
+// which has a wavefront for every row.  Measured, a session of 2000 tokens with an infinity at its start, us a call, this /
+// scalar kernel / one wavefront going row by row and key by key, as it was first: 32 heads of 64, 9 new tokens 24 / 41 / 763,
+// 256 new tokens 136 / 496 / 8800; 24 heads of 128 on 8, 200 new tokens 120 / 615 / 7194; fp32, 8 heads of 128 on 2, 150 new
+// tokens 169 / 443 / 3025.  (Slower than the scalar kernel: fp32 decoding with 64-wide heads, 96 / 61, bound by the latency
+// of a block's loads.)
+struct NonFinite {  // first positions of a depth's non-finite elements
+  int32_t nan = INT32_MAX, pos = INT32_MAX, neg = INT32_MAX;
+  __device__ __forceinline__ bool see(uint32_t bits, int32_t at) {  // an element's fp32 bits; true if it is not finite
+    nan = min(nan, (bits & 0x7fffffffu) > 0x7f800000u ? at : INT32_MAX);
+    pos = min(pos, bits == 0x7f800000u ? at : INT32_MAX);
+    neg = min(neg, bits == 0xff800000u ? at : INT32_MAX);
+    return (bits & 0x7f800000u) == 0x7f800000u;
+  }
+  __device__ __forceinline__ void merge_lanes(int mask) {
+    nan = min(nan, __shfl_xor(nan, mask));
+    pos = min(pos, __shfl_xor(pos, mask));
+    neg = min(neg, __shfl_xor(neg, mask));
+  }
+  __device__ __forceinline__ NonFinite of_lane(int lane) const { return {__shfl(nan, lane), __shfl(pos, lane), __shfl(neg, lane)}; }
+  // the sum of a row that sees the positions up to `limit`
+  __device__ __forceinline__ float apply(float sum, int32_t limit) const {
+    if (nan <= limit || (pos <= limit && neg <= limit)) return __uint_as_float(0x7fc00000u);
+    if (pos <= limit) return INFINITY;
+    return neg <= limit ? -INFINITY : sum;
+  }
+};
+
+// bf16: rows rl0 .. rl0 + 31 of the item (bit i of `bad`: row rl0 + i is to be replaced; m and l in lanes i and 32 + i), depth
+// block db; of it, the quads of depths that owns() says this wavefront has stored.
+template <int HD, bool ANYG, typename Owns>
+__device__ __forceinline__ void redo_rows(const Ctx& c, const DkEntry& e, const DkItem& it, int g, int rl0, uint32_t bad, float m,
+                                          float l, int lane, int db, Owns owns) {
+  typedef Geo<HD> G;
+  asm volatile("" : "+v"(lane));  // (per-lane offsets are made here, not hoisted into registers that the key loop needs)
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // after the ordinary store of the same rows
-  while (bad != 0) {
-    const int i = __builtin_ctz(bad);
-    bad &= bad - 1;
-    const int rl = rl0 + i;
-    if (rl >= it.nrows) break;
-    const float m = __shfl(m_lane, i), l = __shfl(l_lane, i);
-    const int row = it.row0 + rl;
-    const int tok = row_token<ANYG>(c, row);
-    const int64_t orow = (int64_t)(e.tok0 + tok) * c.n_q_heads + g * c.group + row_head<ANYG>(c, row, tok);
-    const T* q = (const T*)c.q + orow * HD;
-    float acc[PER_LANE];
+  const int col = lane & 31, h = lane >> 5;
+  const int last_row = it.row0 + it.nrows - 1;
+  const int row = min(it.row0 + rl0 + col, last_row);
+  const int tok = row_token<ANYG>(c, row);
+  const int limit = e.n + tok;
+  const int64_t orow = (int64_t)(e.tok0 + tok) * c.n_q_heads + g * c.group + row_head<ANYG>(c, row, tok);
+  bf16x8 qf[G::KS];
 #pragma unroll
-    for (int u = 0; u < PER_LANE; ++u) acc[u] = 0.f;
-    KvCursor<ROW> cur{c.segs, e.seg_begin, e.seg_end, it.kv_lo, min(it.kv_hi, e.n + tok + 1)};
-    KvTile t;
-    while (cur.next(c, g, 64, t)) {
-      const char* k = t.k + (uint32_t)min(lane, t.cnt - 1) * t.stride;
-      float s = 0.f;
-#pragma unroll 1
-      for (int d = 0; d < HD; d += VEC) {
-        const vec kv = *(const vec*)(k + d * sizeof(T)), qv = *(const vec*)(q + d);
+  for (int ks = 0; ks < G::KS; ++ks) qf[ks] = *(const bf16x8*)(c.q + orow * HD + ks * 16 + 8 * h);
+  f32x16 o;
+  NonFinite nf;
 #pragma unroll
-        for (int u = 0; u < VEC; ++u) s += wide(kv[u]) * wide(qv[u]);
-      }
-      const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s, c.c, -m));
-#pragma unroll 1
-      for (int j = 0; j < t.cnt; ++j) {
-        const float pj = __shfl(p, j);
-        const T* v = (const T*)(t.v + (uint32_t)j * t.stride) + lane * PER_LANE;
+  for (int r = 0; r < 16; ++r) o[r] = 0.f;
+  const int max_limit = e.n + row_token<ANYG>(c, min(it.row0 + rl0 + 31, last_row));
+  KvCursor<G::ROW> cur{c.segs, e.seg_begin, e.seg_end, it.kv_lo, min(it.kv_hi, max_limit + 1)};
+  KvTile t;
+  while (cur.next(c, g, 32, t)) {
+    const char* kp = t.k + (uint32_t)min(col, t.cnt - 1) * t.stride + 16 * h;
+    bf16x8 kf[G::KS];
 #pragma unroll
-        for (int u = 0; u < PER_LANE; ++u) acc[u] += pj * wide(v[u]);
-      }
+    for (int ks = 0; ks < G::KS; ++ks) kf[ks] = *(const bf16x8*)(kp + 32 * ks);
+    uint16_t vb[2][8];  // element 4 u + i of key step j is key 16 j + 8 u + 4 h + i, depth 32 db + col
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int x = 0; x < 8; ++x)
+        vb[j][x] = *(const uint16_t*)(t.v + (uint32_t)min(16 * j + 8 * (x >> 2) + 4 * h + (x & 3), t.cnt - 1) * t.stride + 64 * db + 2 * col);
+    f32x16 s;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[r] = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < G::KS; ++ks) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], qf[ks], s, 0, 0, 0);
+    const int lim = min(t.cnt - 1, limit - t.pos) - 4 * h;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], c.c, -m));
+      s[r] = 8 * (r >> 2) + (r & 3) > lim ? 0.f : p;
     }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      bf16x8 hi, lo;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) split_pair(s[8 * j + 2 * w], s[8 * j + 2 * w + 1], hi, lo, w);
+      bf16x8 v;
+#pragma unroll
+      for (int x = 0; x < 8; ++x) {
+        const bool odd = nf.see((uint32_t)vb[j][x] << 16, t.pos + min(16 * j + 8 * (x >> 2) + 4 * h + (x & 3), t.cnt - 1));
+        v[x] = __builtin_bit_cast(__bf16, (uint16_t)(odd ? 0 : vb[j][x]));
+      }
+      o = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, hi, o, 0, 0, 0);
+      o = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, lo, o, 0, 0, 0);
+    }
+  }
+  const bool mine = (bad >> col & 1) != 0 && rl0 + col < it.nrows && l == l;
+  const float inv = 1.f / l;
+  nf.merge_lanes(32);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    f32x4 x;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) x[r] = nf.of_lane(8 * i + 4 * h + r).apply(o[4 * i + r], limit);
+    const int depth = 32 * db + 8 * i + 4 * h;
+    if (!mine || !owns(depth)) continue;
     if (it.part_row0 >= 0) {
-      float* p = c.parts + ((int64_t)(it.part_row0 + rl) * c.n_kv_heads + g) * HD + lane * PER_LANE;
-#pragma unroll
-      for (int u = 0; u < PER_LANE; ++u) p[u] = acc[u];
+      *(f32x4*)(c.parts + ((int64_t)(it.part_row0 + rl0 + col) * c.n_kv_heads + g) * HD + depth) = x;
     } else {
-      T* p = (T*)c.out + orow * HD + lane * PER_LANE;
+      bf16x4 y;
 #pragma unroll
-      for (int u = 0; u < PER_LANE; ++u) p[u] = (T)(acc[u] / l);
+      for (int r = 0; r < 4; ++r) y[r] = (__bf16)(x[r] * inv);
+      *(bf16x4*)(c.out + orow * HD + depth) = y;
     }
   }
 }

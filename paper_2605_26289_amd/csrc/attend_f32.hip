@@ -44,6 +44,66 @@ struct F32Geo {
   static constexpr int LDS_BYTES = ML_OFFSET + F32_WAVES * RB * 16 * 8;
 };
 
+// redo_rows for fp32: rows rl0 .. rl0 + 15 of the item (m and l of row rl0 + i in the lanes of column i), the depths
+// 64 u + 4 (4 h + r) .. + 3 that this wavefront has stored.
+template <int HD>
+__device__ __forceinline__ void redo_quad(const Ctx& c, const DkEntry& e, const DkItem& it, int g, int rl0, uint32_t bad, float m, float l,
+                                          int lane, int u, int r) {
+  constexpr int ROW = 4 * HD, NI = HD / 16;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // after the ordinary store of the same rows
+  const int col = lane & 15, h = lane >> 4;
+  const int last_row = it.row0 + it.nrows - 1;
+  const int row = min(it.row0 + rl0 + col, last_row);
+  const int tok = row_token<true>(c, row);
+  const int limit = e.n + tok;
+  const int64_t orow = (int64_t)(e.tok0 + tok) * c.n_q_heads + g * c.group + row_head<true>(c, row, tok);
+  f32x4 qf[NI], o[4];
+  NonFinite nf[4];
+#pragma unroll
+  for (int i = 0; i < NI; ++i) qf[i] = *(const f32x4*)((const float*)c.q + orow * HD + 16 * i + 4 * h);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) o[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int max_limit = e.n + row_token<true>(c, min(it.row0 + rl0 + 15, last_row));
+  KvCursor<ROW> cur{c.segs, e.seg_begin, e.seg_end, it.kv_lo, min(it.kv_hi, max_limit + 1)};
+  KvTile t;
+  while (cur.next(c, g, F32_KT, t)) {
+    const char* kp = t.k + (uint32_t)min(col, t.cnt - 1) * t.stride + 16 * h;
+    f32x4 kf[NI], vf[4];
+#pragma unroll
+    for (int i = 0; i < NI; ++i) kf[i] = *(const f32x4*)(kp + 64 * i);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) vf[k] = *(const f32x4*)(t.v + (uint32_t)min(4 * h + k, t.cnt - 1) * t.stride + 16 * col + 256 * u);
+    f32x4 s[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) s[j & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[i][j], qf[i][j], s[j & 1], 0, 0, 0);
+    const int lim = min(t.cnt - 1, limit - t.pos) - 4 * h;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[0][k] + s[1][k], c.c, -m));
+      if (k > lim) p = 0.f;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const bool odd = nf[j].see(__float_as_uint(vf[k][j]), t.pos + min(4 * h + k, t.cnt - 1));
+        o[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(odd ? 0.f : vf[k][j], p, o[j], 0, 0, 0);
+      }
+    }
+  }
+  f32x4 x;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    nf[j].merge_lanes(16);
+    nf[j].merge_lanes(32);
+    const float sum = r == 0 ? o[j][0] : r == 1 ? o[j][1] : r == 2 ? o[j][2] : o[j][3];
+    x[j] = nf[j].of_lane(4 * h + r).apply(sum, limit);
+  }
+  if ((bad >> col & 1) == 0 || rl0 + col >= it.nrows || l != l) return;
+  const int depth = 64 * u + 4 * (4 * h + r);
+  if (it.part_row0 >= 0) *(f32x4*)(c.parts + ((int64_t)(it.part_row0 + rl0 + col) * c.n_kv_heads + g) * HD + depth) = x;
+  else *(f32x4*)((float*)c.out + orow * HD + depth) = x * (1.f / l);
+}
+
 }  // namespace
 
 // grid = n_chains * n_kv_heads, as the tile kernel: workgroup w walks chain w / n_kv_heads of the planner's items.
@@ -243,7 +303,7 @@ __global__ __launch_bounds__(64 * F32_WAVES, 2) void attend_f32_kernel(BlobArg<I
       }
       if (bad != 0) {
         bad |= bad >> 32;
-        redo_rows<float, HD, true>(c, e, it, g, rb * 16, (uint32_t)(bad | bad >> 16) & 0xffffu, mm, lsum, el);
+        redo_quad<HD>(c, e, it, g, rb * 16, (uint32_t)(bad | bad >> 16) & 0xffffu, mm, lsum, el, u, r);
       }
     }
   }

@@ -667,7 +667,7 @@ __global__ __launch_bounds__(256, 1) void attend_stream_kernel(BlobArg<INLINE> b
           const uint32_t rows = mb == 0 ? bad_rows[0] : mb == 1 ? bad_rows[i1] : bad_rows[i2];
           const float m = mb == 0 ? bad_m[0] : mb == 1 ? bad_m[i1] : bad_m[i2];
           const float l = mb == 0 ? bad_l[0] : mb == 1 ? bad_l[i1] : bad_l[i2];
-          redo_rows<__bf16, HD, true>(c, e, it, g, mb * 32, rows, m, l, lane);
+          if (rows != 0) redo_rows<HD, true>(c, e, it, g, mb * 32, rows, m, l, lane, db, [&](int depth) { return depth / (HD / 4) == wave; });
         }
       }
     }

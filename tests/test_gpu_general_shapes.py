@@ -139,3 +139,55 @@ def test_values_a_row_may_not_see_never_reach_it(hq, hkv, d, dtype, n, delta):
     assert ok[: delta // 2].all()
     assert (out[ok].float() - ref[ok].float()).abs().max().item() <= (2.0 ** -6 if dtype == "bf16" else 2.0 ** -17)
     m.pool.close()
+
+
+def _time_us(call, reps=5):
+    call()
+    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    a.record()
+    for _ in range(reps):
+        call()
+    b.record()
+    torch.cuda.synchronize()
+    return a.elapsed_time(b) / reps * 1e3
+
+
+@pytest.mark.parametrize("hq,hkv,d,dtype", [(32, 8, 64, "bf16"), (24, 8, 128, "bf16"), (5, 1, 128, "bf16"), (8, 2, 64, "f32"), (8, 2, 128, "f32")])
+@pytest.mark.parametrize("delta", [1, 9, 200, 600])
+def test_infinities_in_a_sessions_history_are_carried_on_at_no_great_cost(hq, hkv, d, dtype, delta):
+    """Non-finite values that every row sees: all rows are done again, over the keys they see, with the reference kernel's
+    results, the same bits on every call, and in no more than twice the reference kernel's time (it walked them row by row
+    once, 15 times as long as that kernel)."""
+    sh = wl.Shape(hq, hkv, d, dtype)
+    n = 2000
+    m = Mirror(sh, 1, n + 1024, seed=6)
+    s = m.acquire()
+    k, v = (to_dev(m.draw(n, hkv), dtype) for _ in range(2))
+    v[5] = float("inf")
+    v[700, hkv - 1, 1::2] = float("nan")
+    v[1500, 0, 2::4] = float("-inf")
+    m.pool.append([s], [0, n], k, v)
+    q, kn, vn = (to_dev(m.draw(delta, x), dtype) for x in (hq, hkv, hkv))
+    vn[delta // 2, 0, 3] = float("nan")
+    out = torch.empty_like(q)
+    call = lambda: m.pool.attend([s], [0, delta], q, sh.scale, kn, vn, out=out)  # noqa: E731
+    call()
+    first = out.clone()
+    assert dk.last_plan(m.pool.handle)["route"] != "scalar"
+    whole = torch.int16 if dtype == "bf16" else torch.int32
+    for _ in range(8):
+        out.zero_()
+        call()
+        assert torch.equal(out.view(whole), first.view(whole))
+    us = _time_us(call)
+    dk.set_attend_variant(m.pool.handle, 1)
+    call()
+    assert torch.equal(torch.isnan(out), torch.isnan(first)) and torch.equal(torch.isinf(out), torch.isinf(first))
+    assert torch.equal(out[torch.isinf(out)], first[torch.isinf(first)])
+    ok = torch.isfinite(out)
+    if ok.any():
+        assert (out[ok].float() - first[ok].float()).abs().max().item() <= (2.0 ** -6 if dtype == "bf16" else 2.0 ** -17)
+    scalar_us = _time_us(call)
+    print(f"[non-finite] {hq}/{hkv}/{d} {dtype} delta {delta}: {us:.0f} us, scalar kernel {scalar_us:.0f} us")
+    assert us <= 2.0 * scalar_us + 50.0
+    m.pool.close()
