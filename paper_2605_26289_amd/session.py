@@ -5,7 +5,7 @@ PyTorch is used for allocation and streams only.
 from __future__ import annotations
 
 import contextlib
-from typing import Iterator, Optional, Sequence
+from typing import Iterator, List, Optional, Sequence
 
 import torch
 
@@ -42,6 +42,9 @@ class DevicePool:
         desc.host_staging_bytes = dk.staging_bytes(desc)
         self.handle = dk.pool_create(desc)
         self.workspace: Optional[torch.Tensor] = None
+        # Workspaces that were outgrown: a captured call goes on using the one it was captured with.  Each is at least twice
+        # the one before it, so that together they are no larger than the current one.
+        self._outgrown: List[torch.Tensor] = []
 
     def close(self) -> None:
         if self.handle is not None:
@@ -93,7 +96,11 @@ class DevicePool:
     def ensure_workspace(self, slots, cu_delta, staged) -> torch.Tensor:
         need = dk.attend_workspace_bytes(self.handle, slots, cu_delta, staged)
         if self.workspace is None or self.workspace.numel() < need:
-            self.workspace = torch.empty(int(need * 1.25) + 4096, dtype=torch.uint8, device=self.device)
+            size = int(need * 1.25) + 4096
+            if self.workspace is not None:
+                size = max(size, 2 * self.workspace.numel())
+                self._outgrown.append(self.workspace)
+            self.workspace = torch.empty(size, dtype=torch.uint8, device=self.device)
         return self.workspace
 
     def attend(self, slots, cu_delta, q, scale: float, k_new=None, v_new=None, out=None, lse=None):

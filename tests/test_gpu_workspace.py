@@ -100,3 +100,38 @@ def test_a_short_workspace_is_refused_or_served_by_the_scalar_kernel_as_asked(hq
     assert dk.last_plan(h)["route"] != "scalar"
     assert (out.float() - short.float()).abs().max().item() < 2e-2
     pool.close()
+
+
+@pytest.mark.parametrize("hq,hkv,d,dtype", SHAPES)
+def test_a_captured_call_keeps_its_workspace_when_the_pool_outgrows_it(hq, hkv, d, dtype):
+    """The partial rows of a captured decoding step lie in the workspace of that time: replays after the pool has grown must
+    neither lose them nor write over memory that has been given to somebody else."""
+    pool, slots, gen = _pool(hq, hkv, d, dtype, [6000], 16384)
+    scale = d ** -0.5
+    q, k, v = (_rows(gen, 1, x, d, dtype) for x in (hq, hkv, hkv))
+    want = pool.attend(slots, [0, 1], q, scale, k, v)
+    assert dk.last_plan(pool.handle)["merges"] > 0
+    out, held = torch.empty_like(want), pool.workspace.numel()
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        pool.attend(slots, [0, 1], q, scale, k, v, out=out)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        pool.attend(slots, [0, 1], q, scale, k, v, out=out)
+    replays = []
+    for rows in (0, 300, 3000):
+        if rows:
+            pool.attend(slots, [0, rows], _rows(gen, rows, hq, d, dtype), scale, _rows(gen, rows, hkv, d, dtype), _rows(gen, rows, hkv, d, dtype))
+        fill = [torch.full((held,), 77, dtype=torch.uint8, device="cuda") for _ in range(8)]
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        replays.append(out.clone())
+        assert all((f == 77).all() for f in fill), rows
+    assert pool.workspace.numel() >= 2 * held
+    assert sum(w.numel() for w in pool._outgrown) <= pool.workspace.numel()
+    assert all(torch.equal(r, replays[0]) for r in replays)
+    # (a captured call merges its splits by another kernel: another order of additions)
+    assert (replays[0].float() - want.float()).abs().max().item() <= 2.0 ** -7
+    pool.close()
