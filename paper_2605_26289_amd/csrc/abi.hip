@@ -349,7 +349,12 @@ int32_t dk_set_tuning(dk_pool* pool, const char* name, double value) {
     *dst = (int32_t)value;
     return DK_OK;
   };
-  if (key == "stream_rows") return whole(32, 96, &c.stream_rows);
+  if (key == "stream_rows") {
+    const int32_t rc = whole(32, 96, &c.stream_rows);
+    if (rc == DK_OK) c.small_rows = c.stream_rows;  // whoever sets a limit means it for small batches too
+    return rc;
+  }
+  if (key == "small_units") return whole(0, 1 << 16, &c.small_units);
   if (key == "stream_target") return whole(1, 1 << 20, &c.stream_target);
   if (key == "stream_min_chunk") return whole(64, 1 << 24, &c.stream_min_chunk);
   if (key == "stream_chains") return whole(1, 1 << 16, &c.stream_chains);

@@ -297,7 +297,7 @@ StreamShape small_shape(const AttendPlan& p, const PlanConfig& cfg, int32_t grou
       most_rows = std::max(most_rows, group * e.delta);
       longest = std::max<int64_t>(longest, (int64_t)e.n + e.delta);
     }
-  if (most_rows == 0) return best;
+  if (most_rows == 0 || (cfg.small_rows > 0 && most_rows > cfg.small_rows)) return best;
   static const int32_t splits[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32};
   for (int32_t r = 32; r <= 96; r += 32) {
     if (r > 32 && r - 32 >= most_rows) break;

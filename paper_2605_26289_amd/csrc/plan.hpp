@@ -33,6 +33,7 @@ struct PlanConfig {
   float unit_scale = 0;  // cost of a streaming unit's keys against 128-wide heads
   int32_t arrivals = 0;  // counters for merges inside the streaming kernel (0: none)
   int32_t small_units = 0;  // a batch of at most this many streaming units may be planned as a small one (0: never)
+  int32_t small_rows = 0;   // ... unless an entry has more packed rows than this (0: however many)
   int32_t inline_blob_bytes = 0;  // a descriptor blob up to this size travels in the kernel arguments
 };
 

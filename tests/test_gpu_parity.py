@@ -18,6 +18,13 @@ pytestmark = pytest.mark.gpu
 SMALL = wl.Shape(8, 2, 128, "bf16")
 
 
+def _assert_tile_kernel(m, deltas):
+    """With the rule for small batches off, the tile kernel had every entry of more than 96 packed rows."""
+    plan = dk.last_plan(m.pool.handle)
+    group = m.shape.n_q_heads // m.shape.n_kv_heads
+    assert plan["route"] == "tile" and (plan["row_items"] > 0) == any(d * group > 96 for d in deltas), plan
+
+
 def _run_turns(w: wl.Workload, granule=0, variant=0, check_every=1):
     """Plays a workload turn by turn (append then attend, or staged attend then append) against the oracle."""
     sh = w.shape
@@ -112,13 +119,14 @@ def test_config5_scaled_spec_verify(variant):
     _run_turns(wl.scaled(wl.config5(n_slots=16), 0.125), variant=variant)
 
 
-@pytest.mark.parametrize("variant", [0, 1])
+@pytest.mark.parametrize("variant,small_units", [(0, 256), (0, 0), (1, 256)])
 @pytest.mark.parametrize("n,delta", [(0, 1), (0, 5), (1, 1), (63, 1), (64, 2), (65, 16), (200, 17), (3, 70), (0, 300),
                                      (129, 64), (1000, 9), (257, 130), (0, 20), (31, 21), (200, 24), (1000, 22)])
-def test_edge_shapes_appended_and_staged_agree_with_oracle(n, delta, variant):
+def test_edge_shapes_appended_and_staged_agree_with_oracle(n, delta, variant, small_units):
     sh = SMALL
     m = Mirror(sh, 2, 4096, granule=16, seed=n * 1000 + delta)
     dk.set_attend_variant(m.pool.handle, variant)
+    dk.set_tuning(m.pool.handle, "small_units", small_units)
     s, t = m.acquire(), m.acquire()
     if n:
         k0, v0, _ = m.append([s], [n])
@@ -129,6 +137,8 @@ def test_edge_shapes_appended_and_staged_agree_with_oracle(n, delta, variant):
     out_s = m.pool.attend([s], [0, delta], to_dev(q, sh.dtype), sh.scale, to_dev(kn, sh.dtype), to_dev(vn, sh.dtype))
     ref, _ = oracle.delta_attend(q, *m.cache(s), kn, vn, sh.scale)
     check_close(out_s, ref, sh.dtype, "staged", row_scaled=True)
+    if variant == 0 and small_units == 0:
+        _assert_tile_kernel(m, [delta])
     # appended on slot t
     m.append([t], [delta], kn, vn)
     out_a, _, _ = m.attend_appended([t], [delta], q)
@@ -245,14 +255,15 @@ def test_errors_from_gpu_entry_points():
     m.pool.close()
 
 
-@pytest.mark.parametrize("delta", [4, 9, 22, 300])
-def test_growing_scores_exercise_the_lazy_rescale(delta):
+@pytest.mark.parametrize("delta,small_units", [(4, 256), (9, 256), (22, 256), (300, 256), (300, 0)])
+def test_growing_scores_exercise_the_lazy_rescale(delta, small_units):
     """Keys whose scores keep outgrowing the reference maximum (by far more than the rescale slack, several
     times along the prefix, and again inside the new block): the deferred O rescale of the tile kernel and the
     conditional rescale of the stream kernel (one, two and three row blocks) must both land on the oracle's
     result."""
     sh = SMALL
     m = Mirror(sh, 1, 8192, seed=23)
+    dk.set_tuning(m.pool.handle, "small_units", small_units)
     s = m.acquire()
     n = 1500
     rng = np.random.default_rng(23)
@@ -270,15 +281,19 @@ def test_growing_scores_exercise_the_lazy_rescale(delta):
     out, lse, _ = m.attend_appended([s], [delta], q, lse=True)
     ref, ref_lse = m.oracle_appended([s], [delta], q)
     check_close(out, ref, sh.dtype, "growing scores", row_scaled=True)
+    if small_units == 0:
+        _assert_tile_kernel(m, [delta])
     assert np.abs(lse.cpu().numpy() - ref_lse).max() < 5e-3 * max(1.0, np.abs(ref_lse).max() / 10)
     m.pool.close()
 
 
-def test_split_chunks_with_rows_that_see_nothing_of_a_chunk():
+@pytest.mark.parametrize("small_units", [256, 0])
+def test_split_chunks_with_rows_that_see_nothing_of_a_chunk(small_units):
     """A long prefix forces the planner to split the keys; with a diagonal inside the last chunk some rows of a
     row tile see none of that chunk's keys (their partial is empty) and the merge must ignore it."""
     sh = SMALL
     m = Mirror(sh, 1, 1 << 15, seed=29)
+    dk.set_tuning(m.pool.handle, "small_units", small_units)
     s = m.acquire()
     n, delta = 9000, 200
     m.append([s], [n])
@@ -287,15 +302,20 @@ def test_split_chunks_with_rows_that_see_nothing_of_a_chunk():
     out_s = m.pool.attend([s], [0, delta], to_dev(q, sh.dtype), sh.scale, to_dev(kn, sh.dtype), to_dev(vn, sh.dtype))
     ref, _ = oracle.delta_attend(q, *m.cache(s), kn, vn, sh.scale)
     check_close(out_s, ref, sh.dtype, "split, staged")
+    assert dk.last_plan(m.pool.handle)["merges"] > 0
+    if small_units == 0:
+        _assert_tile_kernel(m, [delta])
     m.pool.close()
 
 
 @pytest.mark.parametrize("hq,hkv", [(4, 4), (4, 2), (16, 2), (16, 1), (6, 2)])
-@pytest.mark.parametrize("n,delta", [(300, 3), (500, 6), (700, 100), (40, 260)])
-def test_group_sizes_from_mha_to_sixteen_heads_per_kv_head(hq, hkv, n, delta):
-    """G = Hq/Hkv of 1, 2, 8, 16 (MFMA kernels, rows packed G per token) and 3 (not a power of two: reference kernel)."""
+@pytest.mark.parametrize("n,delta,small_units", [(300, 3, 256), (500, 6, 256), (700, 100, 256), (40, 260, 256), (700, 100, 0), (40, 260, 0)])
+def test_group_sizes_from_mha_to_sixteen_heads_per_kv_head(hq, hkv, n, delta, small_units):
+    """G = Hq/Hkv of 1, 2, 8, 16 (tile and streaming kernel, rows packed G per token) and 3 (not a power of two: block kernel
+    and the streaming kernel's general form); the longer turns planned as small batches and not."""
     sh = wl.Shape(hq, hkv, 128, "bf16")
     m = Mirror(sh, 2, 4096, granule=32, seed=hq * 100 + hkv * 10 + delta)
+    dk.set_tuning(m.pool.handle, "small_units", small_units)
     s = m.acquire()
     m.append([s], [n])
     kn, vn = m.draw(delta, hkv), m.draw(delta, hkv)
@@ -303,15 +323,20 @@ def test_group_sizes_from_mha_to_sixteen_heads_per_kv_head(hq, hkv, n, delta):
     out = m.pool.attend([s], [0, delta], to_dev(q, "bf16"), sh.scale, to_dev(kn, "bf16"), to_dev(vn, "bf16"))
     ref, _ = oracle.delta_attend(q, *m.cache(s), kn, vn, sh.scale)
     check_close(out, ref, "bf16", f"G={hq // hkv}", row_scaled=True)
+    if small_units == 0:
+        plan = dk.last_plan(m.pool.handle)
+        assert plan["route"] == ("general" if hq // hkv == 3 else "tile")
+        assert (plan["row_items"] > 0) == (delta * (hq // hkv) > 96)
     m.pool.close()
 
 
-@pytest.mark.parametrize("n,delta", [(1000, 9), (900, 21), (777, 200), (130, 70)])
-def test_cells_outside_the_slot_never_reach_the_result(n, delta):
+@pytest.mark.parametrize("n,delta,small_units", [(1000, 9, 256), (900, 21, 256), (777, 200, 256), (130, 70, 256), (777, 200, 0), (130, 70, 0)])
+def test_cells_outside_the_slot_never_reach_the_result(n, delta, small_units):
     """Arena canary: every cell the slots do not own holds NaN.  Ragged tiles, clamped rows, the dummy loads past
     the end of a key range and aliased prefixes must only ever touch owned cells, or the output turns NaN."""
     sh = SMALL
     m = Mirror(sh, 3, 8192, granule=16, seed=31)
+    dk.set_tuning(m.pool.handle, "small_units", small_units)
     m.pool.k_arena.fill_(float("nan"))
     m.pool.v_arena.fill_(float("nan"))
     a, b = m.acquire(), m.acquire()
@@ -325,6 +350,8 @@ def test_cells_outside_the_slot_never_reach_the_result(n, delta):
     ref_a, _ = oracle.delta_attend(q[:delta], *m.cache(a), kn[:delta], vn[:delta], sh.scale)
     ref_b, _ = oracle.delta_attend(q[delta:], *m.cache(b), kn[delta:], vn[delta:], sh.scale)
     check_close(out, np.concatenate([ref_a, ref_b]), sh.dtype, "canary", row_scaled=True)
+    if small_units == 0:
+        _assert_tile_kernel(m, [delta, delta])
     m.append([a, b], [delta, delta], kn, vn)   # appended mode reads the same cells back
     out2, _, _ = m.attend_appended([a, b], [delta, delta], q)
     check_close(out2, np.concatenate([ref_a, ref_b]), sh.dtype, "canary appended", row_scaled=True)
@@ -395,9 +422,10 @@ APPEND_ATTEND_CASES = {
     "tile": (wl.PRODUCTION, [900, 0, 3000], [[300, 70, 129], [64, 17, 700]]),
     "stream": (wl.PRODUCTION, [5, 0, 2100, 333, 64], [[9, 1, 16, 0, 3], [1, 1, 9, 2, 0]]),
     "mixed": (SMALL, [1200, 40, 0, 700], [[400, 1, 3, 16], [2, 260, 9, 0]]),
-    "fp32 reference path": (wl.Shape(4, 2, 64, "f32"), [200, 0, 31], [[150, 3, 1], [1, 40, 0]]),
+    "fp32": (wl.Shape(4, 2, 64, "f32"), [200, 0, 31], [[150, 3, 1], [1, 40, 0]]),
     "long single turn": (wl.PRODUCTION, [0], [[1500], [1100]]),
-    # small calls: the copy is folded into the tile kernel, the stream kernel, and the first of both
+    # small calls: the copy is folded into the tile kernel, the stream kernel, and the first of both (without the rule for
+    # small batches; with it, into the stream kernel)
     "small tile turn": (wl.PRODUCTION, [800], [[150], [150]]),
     "small stream step": (wl.PRODUCTION, [700, 0, 64], [[9, 1, 4], [1, 9, 16]]),
     "small tile and stream": (SMALL, [300, 20], [[40, 2], [3, 70]]),
@@ -405,8 +433,9 @@ APPEND_ATTEND_CASES = {
 }
 
 
-@pytest.mark.parametrize("case", sorted(APPEND_ATTEND_CASES))
-def test_append_attend_is_append_then_attend(case):
+@pytest.mark.parametrize("case,small_units", [(c, u) for c in sorted(APPEND_ATTEND_CASES) for u in (256, 0)
+                                              if u or c in ("tile", "mixed", "small tile turn", "small tile and stream")])
+def test_append_attend_is_append_then_attend(case, small_units):
     """dk_append_attend against dk_kv_append + dk_delta_attend on a twin pool fed the same rows: results against the
     oracle, then lengths, cell numbers and the gathered arena contents of every slot bit for bit."""
     sh, hist, turns = APPEND_ATTEND_CASES[case]
@@ -415,11 +444,14 @@ def test_append_attend_is_append_then_attend(case):
     slots = [fused.acquire() for _ in hist]
     assert slots == [plain.acquire() for _ in hist]
     for m in (fused, plain):
+        dk.set_tuning(m.pool.handle, "small_units", small_units)
         m.append([s for s, h in zip(slots, hist) if h], [h for h in hist if h])
     for turn, deltas in enumerate(turns):
         q = fused.draw(sum(deltas), sh.n_q_heads)
         plain.draw(sum(deltas), sh.n_q_heads)  # keep the twin's generator in step
         out_f, lse_f, _ = fused.append_attend(slots, deltas, q, lse=True)
+        if small_units == 0:
+            _assert_tile_kernel(fused, deltas)
         plain.append(slots, deltas)
         out_p, lse_p, _ = plain.attend_appended(slots, deltas, q, lse=True)
         ref, ref_lse = fused.oracle_appended(slots, deltas, q)
@@ -538,6 +570,8 @@ def test_rows_between_the_kernels_limits_agree_with_the_oracle_in_both_kernels()
     out_s, lse_s, _ = m.attend_appended(slots, deltas, q, lse=True)
     dk.set_tuning(m.pool.handle, "stream_rows", 64)
     out_t, lse_t, _ = m.attend_appended(slots, deltas, q, lse=True)
+    plan = dk.last_plan(m.pool.handle)
+    assert plan["row_items"] > 0 and plan["stream_items"] == 0
     dk.set_tuning(m.pool.handle, "stream_rows", 96)
     ref, ref_lse = m.oracle_appended(slots, deltas, q)
     check_close(out_s, ref, sh.dtype, "streaming kernel, three row blocks", row_scaled=True)

@@ -1,4 +1,4 @@
-"""Workspace sizes of the attention calls (host planner through the C ABI, no GPU)."""
+"""Workspace sizes and kernels planned for the attention calls (host planner through the C ABI, no GPU)."""
 import os
 import subprocess
 import sys
@@ -73,3 +73,38 @@ print(dk.STATUS_NAMES[dk.lib().dk_attend_workspace_bytes(pool, 1 << 30, slots.ct
 """
     run = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=120)
     assert run.returncode == 0 and run.stdout.strip() == "DUP_SLOT", (run.returncode, run.stdout, run.stderr[-500:])
+
+
+def _planned(hq, hkv, d, hist, delta, **tuning):
+    pool = _pool(len(hist), sum(hist) + 1024 * (len(hist) + 1), hq, hkv, d)
+    for name, value in tuning.items():
+        dk.set_tuning(pool, name, value)
+    slots = [dk.seq_acquire(pool) for _ in hist]
+    dk.kv_reserve(pool, slots, np.concatenate([[0], np.cumsum(hist)]))
+    dk.attend_workspace_bytes(pool, slots, np.concatenate([[0], np.cumsum(delta)]), 1)
+    plan = dk.last_plan(pool)
+    dk.pool_destroy(pool)
+    return plan
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(32, 8, 128), (8, 2, 128), (24, 8, 128), (32, 8, 64)])
+def test_the_rule_for_small_batches_can_be_switched_off(hq, hkv, d):
+    rows = hq // hkv
+    hist, delta = [800, 300], [300 // rows, 3]
+    small = _planned(hq, hkv, d, hist, delta)
+    assert small["row_items"] == 0 and small["stream_items"] > 0
+    assert _planned(hq, hkv, d, hist, delta, small_units=0)["row_items"] > 0
+    assert _planned(hq, hkv, d, hist, delta, small_units=1)["row_items"] > 0
+
+
+@pytest.mark.parametrize("hq,hkv", [(32, 8), (8, 2)])
+@pytest.mark.parametrize("sessions", [1, 6, 24])
+def test_a_row_limit_that_is_set_holds_in_batches_of_any_size(hq, hkv, sessions):
+    """65 to 96 packed rows: to the streaming kernel, or to the tile kernel once the limit is below them."""
+    group = hq // hkv
+    delta = [64 // group + 1 + i % (32 // group) for i in range(sessions)]
+    hist = [100 + 37 * i for i in range(sessions)]
+    assert _planned(hq, hkv, 128, hist, delta)["row_items"] == 0
+    assert _planned(hq, hkv, 128, hist, delta, stream_rows=96)["row_items"] == 0
+    limited = _planned(hq, hkv, 128, hist, delta, stream_rows=64)
+    assert limited["row_items"] > 0 and limited["stream_items"] == 0

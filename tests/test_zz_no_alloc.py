@@ -36,9 +36,11 @@ def _both_ways(m, slots, deltas, q, kn=None, vn=None):
     return out_a, out_b, lse_a, lse_b, cu
 
 
-def test_no_alloc_entry_point_equals_delta_attend_on_two_calls_in_a_row():
+@pytest.mark.parametrize("small_units", [256, 0])
+def test_no_alloc_entry_point_equals_delta_attend_on_two_calls_in_a_row(small_units):
     sh = wl.Shape(8, 2, 128, "bf16")
     m = Mirror(sh, 4, 1 << 15, granule=64, seed=101)
+    dk.set_tuning(m.pool.handle, "small_units", small_units)
     a, b, c, d = (m.acquire() for _ in range(4))
     m.append([a], [9000])          # long prefix: the tile kernel splits its keys, partials go through the scratch
     m.alias(a, b, 2500)
@@ -52,6 +54,8 @@ def test_no_alloc_entry_point_equals_delta_attend_on_two_calls_in_a_row():
     need = dk.attend_workspace_bytes(m.pool.handle, slots, np.concatenate([[0], np.cumsum(deltas)]).astype(np.int32), False)
     assert 0 < need <= dk.STATIC_SCRATCH_BYTES
     out_a, out_b, lse_a, lse_b, _ = _both_ways(m, slots, deltas, q)
+    plan = dk.last_plan(m.pool.handle)
+    assert plan["merges"] > 0 and plan["stream_items"] > 0 and (plan["row_items"] > 0) == (small_units == 0)
     assert torch.equal(out_a, out_b) and torch.equal(lse_a, lse_b)
     ref, ref_lse = m.oracle_appended(slots, deltas, q)
     check_close(out_a, ref, sh.dtype, "no-alloc call 1")
