@@ -57,13 +57,9 @@ int32_t guarded(F&& body) noexcept {
 
 }  // namespace
 
-// Which kernels carry an attention call.
-enum class Route {
-  kRef = DK_ROUTE_SCALAR,       // scalar reference kernel: variant 1, a scale that is not positive and finite
-  kTile = DK_ROUTE_TILE,        // bf16, 128-wide heads, groups of 2^k <= 16 query heads: tile and stream kernels
-  kGeneral = DK_ROUTE_GENERAL,  // bf16, any other shape: block kernel and the stream kernel's general form
-  kF32 = DK_ROUTE_F32,          // fp32 pools
-};
+using dk::Route;
+static_assert((int)Route::kRef == DK_ROUTE_SCALAR && (int)Route::kTile == DK_ROUTE_TILE && (int)Route::kGeneral == DK_ROUTE_GENERAL &&
+              (int)Route::kF32 == DK_ROUTE_F32, "dk_last_plan reports them");
 
 struct dk_pool {
   dk_pool_desc desc;
@@ -116,44 +112,6 @@ struct dk_pool {
     for (int32_t b = 0; b < n_seqs; ++b) most = std::max<int64_t>(most, (int64_t)cu_delta[b + 1] - cu_delta[b]);
     if (most < (int64_t(1) << 32) / (group * group)) *route = desc.dtype == DK_BF16 ? Route::kGeneral : Route::kF32;
     return DK_OK;
-  }
-
-  // (of a batch that choose_route() has let pass)
-  dk::PlanConfig plan_config(Route r, int32_t n_seqs, const int32_t* cu_delta) const {
-    dk::PlanConfig c = cfg;
-    c.use_mfma = r != Route::kRef;
-    if (r == Route::kGeneral) {
-      // block kernel: items of 128 rows, two workgroups on a compute unit; an item's fixed cost (first tiles, merge of
-      // the half-waves, store) is about three of its shorter key steps
-      c.tile_rows = 128;
-      if (desc.head_dim == 64) {
-        c.row_fixed_us = 8.f;
-        c.row_step_us = 1.4f;
-        c.unit_scale = 0.75f;
-      }
-      // With 64-wide heads the stream kernel's third row block is slower than the block kernel (16 sessions of 12-24 new
-      // tokens on 500-4000: 57 us / 42 us); a batch with any longer entry runs in the block kernel as a whole, as long as
-      // the short ones read no more than some 800 MB there, 20 % slower than the stream kernel does, but beside the others
-      // and without a launch of their own (two chunks of 256 tokens and 14 decoding sessions 77 us / 64 us, two of 512 and
-      // 46 longer ones 219 / 189; 64 verifying sessions alone, 1.3 GB: stream kernel 243, block kernel 298).
-      if (desc.head_dim == 64) c.stream_rows = std::min(c.stream_rows, 64);
-      c.join_keys = (int64_t(800) << 20) / ((int64_t)4 * desc.n_kv_heads * desc.head_dim);
-      c.tile_wave_slots = 2 * cfg.tile_wave_slots;
-      c.tile_item_cost = std::min(cfg.tile_item_cost, 3);
-    }
-    if (r == Route::kF32) {
-      // fp32 kernel: every row goes through it, in items of 32 rows once those fill the chip, else of 16.  A workgroup
-      // works through 128 keys of 64 in about a microsecond; a cut costs a merge launch (6 us), so no piece is made
-      // shorter than that is worth.
-      int64_t items = 0;
-      const int64_t group = desc.n_q_heads / desc.n_kv_heads;
-      for (int32_t b = 0; b < n_seqs; ++b) items += (group * ((int64_t)cu_delta[b + 1] - cu_delta[b]) + 31) / 32;
-      c.tile_rows = items * desc.n_kv_heads >= 256 ? 32 : 16;
-      c.stream_rows = 0;
-      c.small_units = 0;
-      c.tile_min_chunk = std::max(cfg.tile_min_chunk, 65536 / desc.head_dim);
-    }
-    return c;
   }
 
   void keep_plan(Route r) {
@@ -295,34 +253,7 @@ int32_t dk_pool_create(const dk_pool_desc* desc, dk_pool** pool_out) {
         p->ring_size = i + 1;
       }
     }
-    dk::PlanConfig& c = p->cfg;
-    c.n_q_heads = desc->n_q_heads;
-    c.n_kv_heads = desc->n_kv_heads;
-    c.head_dim = desc->head_dim;
-    c.use_mfma = true;  // (plan_config() decides for each call)
-    c.tile_rows = 256;
-    c.stream_rows = 96;
-    c.kv_tile = 64;
-    // stream items: never cut a slot's keys finer than one CU's fair share of the batch (256 CUs); every extra
-    // item costs a ramp-up, a partial write and merge work, and the planner's chains balance the rest
-    c.stream_target = std::max(1, 256 / desc->n_kv_heads);
-    c.tile_wave_slots = std::max(1, 256 / desc->n_kv_heads);
-    c.tile_min_chunk = 128;
-    c.tile_item_cost = 5;
-    c.stream_min_chunk = 512;
-    c.stream_chains = 256;
-    c.stream_item_cost = 512;
-    // Workgroup w of a launch runs on XCD w % 8, and on every MI355X measured the odd XCDs stream K/V 5-10 % slower
-    // than the even ones while the whole chip pulls on HBM: chains planned on the host give them that much less.
-    for (int x = 0; x < 8; ++x) c.xcd_speed[x] = (x & 1) ? 0.95f : 1.f;
-    c.stream_queue = 1;
-    c.small_units = 256;
-    c.arrivals = dk::ARRIVALS_PER_SLICE;
-    c.row_fixed_us = 10.f;
-    c.row_step_us = 1.8f;
-    c.unit_scale = 1.f;
-    c.once_cells = std::max<int64_t>(1, (int64_t(256) << 20) / ((int64_t)2 * desc->n_kv_heads * desc->head_dim * (desc->dtype == DK_BF16 ? 2 : 4)));
-    c.inline_blob_bytes = dk::INLINE_BLOB_BYTES;
+    p->cfg = dk::default_config(desc->n_q_heads, desc->n_kv_heads, desc->head_dim, desc->dtype == DK_BF16);
     p->arrival_slice = take_slice();
     *pool_out = p;
     return DK_OK;
@@ -544,7 +475,7 @@ int32_t dk_attend_workspace_bytes(dk_pool* pool, int32_t n_seqs, const int32_t* 
     Route route;
     int32_t rc = pool->choose_route(true, n_seqs, slots, cu_delta, &route);
     if (rc != DK_OK) return rc;
-    const dk::PlanConfig cfg = pool->plan_config(route, n_seqs, cu_delta);
+    const dk::PlanConfig cfg = dk::route_config(pool->cfg, route, n_seqs, cu_delta);
     std::lock_guard<std::mutex> lk(pool->meta.mutex());
     rc = dk::build_plan(pool->meta, cfg, n_seqs, slots, cu_delta, staged != 0, &plan, staged == 2);
     if (rc != DK_OK) return rc;
@@ -598,7 +529,7 @@ int32_t attend_locked(dk_pool* pool, int32_t n_seqs, const int32_t* slots, const
   int32_t tile_rows = 0;
   while (true) {
     {
-      const dk::PlanConfig cfg = pool->plan_config(route, n_seqs, cu_delta);
+      const dk::PlanConfig cfg = dk::route_config(pool->cfg, route, n_seqs, cu_delta);
       tile_rows = cfg.tile_rows;
       std::lock_guard<std::mutex> lk(pool->meta.mutex());
       int32_t rc = dk::build_plan(pool->meta, cfg, n_seqs, slots, cu_delta, staged, &plan, fold_append);

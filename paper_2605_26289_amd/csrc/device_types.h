@@ -3,6 +3,11 @@
 #pragma once
 #include <stdint.h>
 
+namespace dk {
+constexpr int32_t INLINE_BLOB_BYTES = 3072;   // descriptors up to this size travel in the kernel arguments
+constexpr int32_t ARRIVALS_PER_SLICE = 256;   // counters a launch of the streaming kernel has for merges of its own
+}  // namespace dk
+
 // A run of consecutive K/V rows holding logical positions [pos, pos + len).
 // src 0: arena cells  (row r of KV head g at ((g * arena_cells) + start + r) * D)
 // src 1: staged new tokens (row r of KV head g at ((start + r) * n_kv_heads + g) * D)

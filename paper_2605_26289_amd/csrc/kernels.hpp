@@ -44,9 +44,8 @@ static_assert(kv_runs_in_one_launch({nullptr, nullptr, 0, 8, 8, 128, 1}, 3355442
 hipError_t launch_kv_scatter_runs(const ArenaView& a, void* k_arena, void* v_arena, const KvRuns& runs, int32_t n_runs,
                                   int32_t n_tok, const void* k_new, const void* v_new, hipStream_t stream);
 
-// Descriptors of at most this many bytes are passed to the kernels inside their arguments instead of being
+// Descriptors of at most INLINE_BLOB_BYTES are passed to the kernels inside their arguments instead of being
 // uploaded first: a short turn then costs no host-to-device copy (and no staging buffer).
-constexpr int32_t INLINE_BLOB_BYTES = 3072;
 struct InlineBlob {
   uint32_t w[INLINE_BLOB_BYTES / 4];
 };
@@ -84,7 +83,6 @@ struct AttendArgs {
 // Arrival counters of the streaming kernel, in the library's device image: zero between launches.  A pool has one slice, and
 // the launches of a pool are ordered, so no two kernels that may overlap count in the same one.
 constexpr int32_t ARRIVAL_SLICES = 1024;
-constexpr int32_t ARRIVALS_PER_SLICE = 256;
 
 // Scalar reference kernel: one wavefront per (token, query head).  Any supported shape and dtype.
 hipError_t launch_attend_ref(const AttendArgs& a, hipStream_t stream);

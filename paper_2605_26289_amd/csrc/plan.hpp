@@ -12,10 +12,18 @@
 
 namespace dk {
 
+// Which kernels carry an attention call.
+enum class Route {
+  kRef = 0,      // scalar reference kernel: variant 1, a scale that is not positive and finite, calls with room for no other
+  kTile = 1,     // bf16, 128-wide heads, groups of 2^k <= 16 query heads: tile and stream kernels
+  kGeneral = 2,  // bf16, any other shape: block kernel and the stream kernel's general form
+  kF32 = 3,      // fp32 pools
+};
+
 // Every field starts as zero ("never", "none"), however the object that holds it is made.
 struct PlanConfig {
   int32_t n_q_heads = 0, n_kv_heads = 0, head_dim = 0;
-  bool use_mfma = false;  // bf16, D == 128, power-of-two group: the tiled kernels apply
+  bool use_mfma = false;  // matrix kernels serve the call: work items are cut (the scalar kernel needs entries and segments only)
   int32_t tile_rows = 0;  // packed query rows per workgroup of the tile kernel
   int32_t stream_rows = 0;  // max packed rows handled by the streaming (small-Delta) kernel
   int32_t kv_tile = 0;  // keys per inner step; split boundaries are multiples of it
@@ -36,6 +44,11 @@ struct PlanConfig {
   int32_t small_rows = 0;   // ... unless an entry has more packed rows than this (0: however many)
   int32_t inline_blob_bytes = 0;  // a descriptor blob up to this size travels in the kernel arguments
 };
+
+// What a pool of this shape starts with, and what a call of a pool with the configuration cfg is planned by on route r
+// (of a batch whose offsets have been checked).
+PlanConfig default_config(int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim, bool bf16);
+PlanConfig route_config(const PlanConfig& cfg, Route r, int32_t n_seqs, const int32_t* cu_delta);
 
 // One packed row tile of an entry before its key range is cut: rows [row0, row0 + nrows) see keys [0, kv_hi).
 struct PlanRowTile {

@@ -1,6 +1,8 @@
-// Host check of small batches (no GPU): planned as a small batch or by the rules for large ones, every (row, key) pair is
-// covered once, split rows have a merge record with partial rows of their own, and a call whose descriptors fit the kernel
-// arguments still does.  Built and run by tests/test_host_plan_small.py.  Exits 0 when every check held.
+// Host check of what is planned for the batches of a pool, with the configuration that its shape gets (no GPU): on every route,
+// as a small batch or by the rules for large ones, every (row, key) pair is covered once, split rows have a merge record
+// with partial rows of their own, a call whose descriptors fit the kernel arguments still does, the streaming kernel merges
+// only what its counters can count, short entries join the row-tile kernel whole, and no cells that two entries share are
+// read past the caches.  Built and run by tests/test_host_plan_small.py.  Exits 0 when every check held.
 #include <algorithm>
 #include <cstdio>
 #include <map>
@@ -20,31 +22,6 @@ static int failures = 0;
     }                                                             \
   } while (0)
 
-static dk::PlanConfig config(int hq, int hkv, int small) {
-  dk::PlanConfig c{};
-  c.n_q_heads = hq;
-  c.n_kv_heads = hkv;
-  c.head_dim = 128;
-  c.use_mfma = true;
-  c.tile_rows = 256;
-  c.stream_rows = 96;
-  c.kv_tile = 64;
-  c.tile_wave_slots = c.stream_target = std::max(1, 256 / hkv);
-  c.tile_min_chunk = 128;
-  c.tile_item_cost = 5;
-  c.stream_min_chunk = 512;
-  c.stream_chains = 256;
-  c.stream_item_cost = 512;
-  for (float& x : c.xcd_speed) x = 1.f;
-  c.stream_queue = 1;
-  c.small_units = small;
-  c.row_fixed_us = 10.f;
-  c.row_step_us = 1.8f;
-  c.unit_scale = 1.f;
-  c.inline_blob_bytes = 3072;
-  return c;
-}
-
 // A configuration made in storage that held something else, as a member of an object with a constructor of its own is:
 // what its maker does not set is zero, not what the storage held.
 struct Holder {
@@ -62,47 +39,76 @@ static void check_fields_start_at_zero() {
   CHECK(h->cfg.small_units == 0);
 }
 
+struct Shape {
+  int hq, hkv, d;
+  bool bf16;
+  dk::Route route;
+};
+static const Shape kShapes[] = {
+    {32, 8, 128, true, dk::Route::kTile},    {8, 2, 128, true, dk::Route::kTile},    {16, 16, 128, true, dk::Route::kTile},
+    {16, 1, 128, true, dk::Route::kTile},    {4, 4, 128, true, dk::Route::kTile},    {32, 8, 64, true, dk::Route::kGeneral},
+    {14, 2, 64, true, dk::Route::kGeneral},  {24, 8, 128, true, dk::Route::kGeneral}, {48, 3, 64, true, dk::Route::kGeneral},
+    {32, 1, 128, true, dk::Route::kGeneral}, {4, 1, 64, false, dk::Route::kF32},     {32, 8, 128, false, dk::Route::kF32},
+};
+
 int main() {
   check_fields_start_at_zero();
   std::mt19937 rng(7);
   auto uni = [&](int lo, int hi) { return lo + (int)(rng() % (unsigned)(hi - lo + 1)); };
-  int small = 0, cut = 0, near = 0;
-  for (int rep = 0; rep < 4000; ++rep) {
-    static const int heads[][2] = {{32, 8}, {8, 2}, {16, 16}, {16, 1}, {4, 4}, {48, 3}};
-    const int* hh = heads[rng() % 6];
-    const int hq = hh[0], hkv = hh[1], group = hq / hkv, nseq = uni(1, 12);
+  int small = 0, cut = 0, near = 0, inside = 0, joined = 0, once = 0, shared = 0;
+  for (int rep = 0; rep < 6000; ++rep) {
+    const Shape& sh = kShapes[rng() % (sizeof(kShapes) / sizeof(kShapes[0]))];
+    const int hq = sh.hq, hkv = sh.hkv, group = hq / hkv;
+    const bool big = uni(0, 3) == 0;  // enough cells to be read past the caches
+    const int nseq = big ? uni(4, 24) : uni(1, 12);
     std::vector<int> n(nseq), delta(nseq);
     std::vector<int32_t> slots(nseq), cu(nseq + 1, 0);
     int64_t cells = 4096;
+    const int prefix = nseq > 1 && uni(0, 2) == 0 ? uni(1, 2000) : 0;  // aliased by some of the others
     for (int b = 0; b < nseq; ++b) {
-      n[b] = uni(0, 1) ? uni(0, 6000) : uni(0, 300);
+      n[b] = big ? uni(4000, 40000) : uni(0, 1) ? uni(0, 6000) : uni(0, 300);
       delta[b] = uni(0, 3) == 0 ? uni(0, 300) : uni(0, 20);
-      cells += n[b] + 512;
+      cells += n[b] + prefix + 768;
       cu[b + 1] = cu[b] + delta[b];
     }
     dk::Pool pool(nseq, 0, cells, 256);
+    const auto append = [&](int32_t slot, int count) {
+      const int32_t c2[2] = {0, count};
+      std::vector<int64_t> dst;
+      if (count > 0) CHECK(pool.append(1, &slot, c2, nullptr, &dst) == dk::OK);
+    };
     for (int b = 0; b < nseq; ++b) {
       CHECK(pool.acquire(0, 0, &slots[b]) == dk::OK);
-      const int32_t c2[2] = {0, n[b]};
-      std::vector<int64_t> dst;
-      if (n[b] > 0) CHECK(pool.append(1, &slots[b], c2, nullptr, &dst) == dk::OK);
+      if (b == 0) append(slots[0], prefix);
+      const bool alias = b > 0 && prefix > 0 && uni(0, 1);
+      if (alias) CHECK(pool.alias(slots[0], slots[b], 0, prefix) == dk::OK);
+      append(slots[b], n[b]);
+      n[b] += b == 0 || alias ? prefix : 0;
     }
     const bool cells_too = uni(0, 1);
     dk::AttendPlan p, large;
+    const dk::PlanConfig cfg = dk::route_config(dk::default_config(hq, hkv, sh.d, sh.bf16), sh.route, nseq, cu.data());
+    dk::PlanConfig off = cfg;
+    off.small_units = 0;
     {
       std::lock_guard<std::mutex> g(pool.mutex());
-      CHECK(dk::build_plan(pool, config(hq, hkv, 256), nseq, slots.data(), cu.data(), true, &p, cells_too) == dk::OK);
-      CHECK(dk::build_plan(pool, config(hq, hkv, 0), nseq, slots.data(), cu.data(), true, &large, cells_too) == dk::OK);
+      CHECK(dk::build_plan(pool, cfg, nseq, slots.data(), cu.data(), true, &p, cells_too) == dk::OK);
+      CHECK(dk::build_plan(pool, off, nseq, slots.data(), cu.data(), true, &large, cells_too) == dk::OK);
     }
+    CHECK(p.largest_bytes >= p.total_bytes && p.largest_bytes >= large.total_bytes);
     const bool other = p.tile_items.size() != large.tile_items.size() || p.stream_items.size() != large.stream_items.size();
     small += other;
     if (other) CHECK(p.tile_items.empty() && p.stream_units <= 256 && p.stream_single && p.tile_chains == 0);
     if (large.blob_bytes <= 3072) CHECK(p.blob_bytes <= 3072);
     near += large.blob_bytes <= 3072 && large.blob_bytes > 3072 - 128;
     std::map<std::pair<int, int>, std::vector<DkItem>> cover;
-    for (const DkItem& it : p.tile_items) cover[{it.entry, it.row0}].push_back(it);
+    const int stream_rows = sh.d == 64 && !other ? 64 : 96;
+    for (const DkItem& it : p.tile_items) {
+      CHECK(it.nrows <= cfg.tile_rows && it.merge == 0);
+      cover[{it.entry, it.row0}].push_back(it);
+    }
     for (const DkItem& it : p.stream_items) {
-      CHECK(it.nrows <= 96);
+      CHECK(it.nrows <= stream_rows && sh.route != dk::Route::kF32);
       cover[{it.entry, it.row0}].push_back(it);
     }
     std::vector<int> rows(nseq, 0);
@@ -128,15 +134,56 @@ int main() {
     cut += split > 0 && other;
     for (const DkMerge& m : p.merges) {
       const auto& v = cover[{m.entry, m.row0}];
-      CHECK((int)v.size() == m.nsplit && v[0].nrows == m.nrows);
+      CHECK((int)v.size() == m.nsplit && v[0].nrows == m.nrows && m.tok0 == cu[m.entry]);
       std::vector<int> at;
       for (const DkItem& it : v) at.push_back(it.part_row0);
       std::sort(at.begin(), at.end());
       for (int s = 0; s < m.nsplit; ++s) CHECK(at[(size_t)s] == m.part_row0 + s * m.nrows);
     }
     for (int b = 0; b < nseq; ++b) CHECK(rows[b] == group * delta[b]);
+
+    // merges inside the streaming kernel
+    inside += p.stream_merges;
+    if (p.stream_merges) {
+      CHECK(p.stream_single && p.tile_chains == 0 && p.merges.size() * (size_t)hkv <= (size_t)dk::ARRIVALS_PER_SLICE);
+      for (const DkItem& it : p.stream_items) {
+        CHECK((it.merge != 0) == (it.part_row0 >= 0));
+        if (it.merge == 0) continue;
+        CHECK((size_t)(it.merge >> 8) < p.merges.size());
+        const DkMerge& m = p.merges[(size_t)(it.merge >> 8) % p.merges.size()];
+        CHECK(m.entry == it.entry && m.row0 == it.row0 && m.nrows == it.nrows && m.nsplit == (it.merge & 255) && m.part_row0 == it.part_base);
+      }
+    }
+    // short entries beside long ones on the general route: all in the row-tile kernel, or all in the streaming kernel
+    if (sh.route == dk::Route::kGeneral && !other && !p.tile_items.empty()) {
+      std::vector<char> seen(nseq, 0);
+      int64_t short_keys = 0;
+      for (int b = 0; b < nseq; ++b)
+        if (delta[b] > 0 && group * delta[b] <= cfg.stream_rows) short_keys += n[b] + delta[b];
+      for (const DkItem& it : p.tile_items) seen[it.entry] = 1;
+      for (int b = 0; b < nseq; ++b)
+        if (delta[b] > 0 && group * delta[b] <= cfg.stream_rows) {
+          CHECK((seen[b] != 0) == (short_keys <= cfg.join_keys));
+          joined += seen[b];
+        }
+    }
+    // non-temporal loads: arena cells of one entry only, in batches that exceed the caches
+    std::map<int64_t, int> starts;
+    int64_t marked = 0;
+    for (const DkSeg& s : p.segs)
+      if (s.src == 0) ++starts[s.start];
+    for (const DkSeg& s : p.segs) {
+      if (!s.once) continue;
+      CHECK(s.src == 0 && starts[s.start] == 1);
+      marked += s.len;
+    }
+    for (const auto& kv : starts) shared += kv.second > 1 && marked > 0;
+    CHECK((marked > 0) <= p.once);
+    if (p.once) CHECK(!p.stream_items.empty() && marked + 2000 * (int64_t)nseq >= cfg.once_cells);
+    once += p.once;
   }
-  CHECK(small > 400 && cut > 100 && near > 10);
-  std::printf("planned as small %d, cut %d, close below the limit of the kernel arguments %d, failures %d\n", small, cut, near, failures);
+  std::printf("planned as small %d, cut %d, close below the limit of the kernel arguments %d, merged inside %d, joined %d, "
+              "read past the caches %d, beside shared ones %d, failures %d\n", small, cut, near, inside, joined, once, shared, failures);
+  CHECK(small > 400 && cut > 100 && near > 10 && inside > 20 && joined > 20 && once > 20 && shared > 20);
   return failures ? 1 : 0;
 }
