@@ -35,6 +35,7 @@ PlanConfig default_config(int32_t n_q_heads, int32_t n_kv_heads, int32_t head_di
   c.row_fixed_us = 10.f;
   c.row_step_us = 1.8f;
   c.unit_scale = 1.f;
+  c.cost = {{9.3f, 11.4f, 14.6f}, {0.59f, 1.02f, 1.69f}, 3.5f, 1.4f, 6.8f, 1.72f, 3.0f, 1.4f, 1.0f, 0.08f, 0.42f, 0.04f, 5.3f};
   c.once_cells = std::max<int64_t>(1, (int64_t(256) << 20) / ((int64_t)2 * n_kv_heads * head_dim * (bf16 ? 2 : 4)));
   c.inline_blob_bytes = INLINE_BLOB_BYTES;
   return c;
@@ -52,6 +53,7 @@ PlanConfig route_config(const PlanConfig& cfg, Route r, int32_t n_seqs, const in
       c.row_step_us = 1.4f;
       c.unit_scale = 0.75f;
     }
+    c.cost = PlanCost();
     // With 64-wide heads the stream kernel's third row block is slower than the block kernel (16 sessions of 12-24 new
     // tokens on 500-4000: 57 us / 42 us); a batch with any longer entry runs in the block kernel as a whole, as long as
     // the short ones read no more than some 800 MB there, 20 % slower than the stream kernel does, but beside the others
@@ -312,13 +314,17 @@ void cut_tile_items(AttendPlan* p, const PlanConfig& cfg) {
 // part (descriptors, first requests, merge of the four wavefronts, store) and then about a microsecond per 128 keys,
 // nearly independent of how many rows it serves -- a compute unit takes in 64 KiB of K/V per microsecond, half of what a
 // tile-kernel step of the same keys lasts -- so while every unit can have a compute unit of its own, short row tiles on
-// many compute units beat long ones on few, and a turn of a few hundred rows runs better here than in the tile kernel,
+// many compute units beat long ones on few, and a turn of a few hundred rows often runs better here than in the tile kernel,
 // which pays 9 us an item, 1.8 us per 64 keys and mostly a merge launch.  Measured, one 150-token turn of one session
 // (32 query heads on 8 KV heads, us per step, tile kernel / 32-row units): 300 cached tokens 28.7 / 18.3, 800 33.5 / 17.8,
 // 2000 36 / 24, 4000 45 / 37, 8000 51 / 66; 300 tokens on 1500: 42 / 33 (64-row units); 20 tokens on 4000: 28 / 21.
-// The constants are those measurements, in microseconds; the plan of least estimated time is taken.  (64-wide heads and
-// odd groups, block kernel / here: 150 tokens on 800 cached 17 / 12.6 with 64-wide heads, 22 / 16 with three heads to a
-// KV head; 9-40 tokens of two sessions, seven heads to a KV head, 20 / 16; 100 tokens on 4000, 64-wide, 23.6 / 27.8.)
+// stream_us() has these measurements for constants, in microseconds, and the plan of least estimated time is the candidate.
+// They are of 8 KV heads, one session and keys that the caches hold; so in place of work of the tile kernel the candidate is
+// only taken if step_us(), fitted over many shapes, has it cheaper too.  (64-wide heads and odd groups, block kernel / here:
+// 150 tokens on 800 cached 17 / 12.6 with 64-wide heads, 22 / 16 with three heads to a KV head; 9-40 tokens of two sessions,
+// seven heads to a KV head, 20 / 16; 100 tokens on 4000, 64-wide, 23.6 / 27.8.  With 128-wide heads the block kernel is
+// priced as the tile kernel is, and the streaming kernel's general form as the other: neither has prices of its own, and
+// weighing these plans by a fit of theirs made as many batches slower as faster.)
 struct StreamShape {
   int32_t rows = 0;   // rows per streaming tile; 0: none found
   int32_t chunk = 0;  // keys per unit
@@ -354,9 +360,8 @@ size_t workspace_of(const PlanConfig& cfg, size_t blob_bytes, int64_t part_rows)
 }
 
 // The best way to run the whole batch through the streaming kernel with at most one unit per workgroup and at most
-// max_blob bytes of descriptors, in less than `below` microseconds.  *largest_bytes is raised to the workspace of every
-// such plan of any descriptor size.
-StreamShape small_shape(const AttendPlan& p, const PlanConfig& cfg, int32_t group, bool with_cells, size_t max_blob, double below,
+// max_blob bytes of descriptors.  *largest_bytes is raised to the workspace of every such plan of any descriptor size.
+StreamShape small_shape(const AttendPlan& p, const PlanConfig& cfg, int32_t group, bool with_cells, size_t max_blob,
                         size_t* largest_bytes) {
   StreamShape best;
   int32_t most_rows = 0;
@@ -387,7 +392,6 @@ StreamShape small_shape(const AttendPlan& p, const PlanConfig& cfg, int32_t grou
         }
       if (units * cfg.n_kv_heads > std::min(cfg.small_units, cfg.stream_chains)) break;
       const double us = stream_us(cfg, std::min(r, most_rows), longest, chunk, keys * cfg.n_kv_heads);
-      if (!(us < below)) continue;
       const size_t blob = blob_size(p, with_cells, 0, 0, (size_t)units, 0, (size_t)merges);
       *largest_bytes = std::max(*largest_bytes, workspace_of(cfg, blob, parts));
       if (blob > max_blob) continue;
@@ -433,7 +437,20 @@ void mark_once(AttendPlan* p, const PlanConfig& cfg) {
     p->once = true;
 }
 
-// Estimated time of the plan that the rules for large batches make.
+// Merging inside the streaming kernel: nothing else has split rows, every workgroup has one unit, every (row tile, KV
+// head) a counter of its own, and the last workgroup of a row tile reads all of its partial rows in a round or two --
+// one workgroup is slow with more (us per step, merge launch / inside: one token on 3000 cached 13.8 / 12.0, with 64-wide
+// heads 13.9 / 10.8; 9 tokens, 36 rows, on 2000 13.7 / 20.0; 20 tokens on 4000 15 / 25).
+bool merges_inside(const AttendPlan& p, const PlanConfig& cfg) {
+  if (p.tile_chains > 0 || p.merges.empty() || p.merges.size() * (size_t)cfg.n_kv_heads > (size_t)cfg.arrivals ||
+      (int64_t)p.stream_items.size() * cfg.n_kv_heads > std::max(cfg.stream_chains, 1))
+    return false;
+  for (const DkMerge& m : p.merges)
+    if (m.nrows > kMergeInsideRows || m.nsplit * m.nrows > kMergeInsideParts) return false;
+  return true;
+}
+
+// The same estimate for the plan that the rules for large batches made.
 double planned_us(const AttendPlan& p, const PlanConfig& cfg) {
   double us = 0;
   if (p.tile_chains > 0) {
@@ -451,6 +468,41 @@ double planned_us(const AttendPlan& p, const PlanConfig& cfg) {
     us += stream_us(cfg, rows, longest, longest, keys * cfg.n_kv_heads);
   }
   if (!p.merges.empty()) us += kMergeUs + 2.0;
+  return us;
+}
+
+// What a step of the plan's work items takes, with `blob` bytes of descriptors, by prices fitted to 2081 measured steps: 1 to
+// 16 sessions of up to 16000 tokens with 1 to 300 new ones, groups of 1 to 16 query heads on 1 to 16 KV heads, planned with
+// different numbers of units; 7 % off, root mean square.  Of 516 batches (116 of them chosen because the estimate above alone
+// misjudges them) 14 were more than 2 % slower, up to 13 %, by that estimate alone than without any rule for small batches;
+// weighed by this as well, 6 are, up to 6 %.
+double step_us(const AttendPlan& p, const PlanConfig& cfg, size_t blob) {
+  const PlanCost& c = cfg.cost;
+  double us = blob > (size_t)cfg.inline_blob_bytes ? c.upload : 0.0;
+  if (p.tile_chains > 0) {
+    const int64_t load = *std::max_element(p.chain_load.begin(), p.chain_load.end());
+    us += c.row_fixed + c.row_step * (double)load + c.row_items * (double)p.tile_items.size() * cfg.n_kv_heads / 256.0;
+  }
+  if (!p.stream_items.empty()) {
+    int32_t rows = 0;
+    int64_t longest = 0, keys = 0, all = 0;  // keys: those of each entry once
+    for (const DkItem& it : p.stream_items) {
+      rows = std::max(rows, it.nrows);
+      longest = std::max<int64_t>(longest, it.kv_hi - it.kv_lo);
+      all += it.kv_hi - it.kv_lo;
+      const DkEntry& e = p.entries[(size_t)it.entry];
+      if (it.kv_hi == e.n + e.delta) keys += it.kv_hi;  // (the last piece of the entry's last row tile)
+    }
+    const int mb = std::min(3, (rows + 31) / 32) - 1;
+    us += c.unit[mb] + c.per128[mb] * (double)longest / 128.0 +
+          (c.keys * (double)keys + c.again * (double)(all - keys)) * cfg.n_kv_heads * 1e-5;
+  }
+  if (!p.merges.empty()) {
+    int32_t split = 0;
+    for (const DkMerge& m : p.merges) split = std::max(split, m.nsplit);
+    us += merges_inside(p, cfg) ? c.merge_inside + c.inside_split * split
+                                : c.merge + c.split * split + c.parts * 1e-4 * (double)(p.part_rows * cfg.n_kv_heads) * cfg.head_dim / 128.0;
+  }
   return us;
 }
 }  // namespace
@@ -528,24 +580,37 @@ int32_t build_plan(Pool& pool, const PlanConfig& cfg, int32_t n_seqs, const int3
     p->largest_bytes = workspace_of(cfg, blob, p->part_rows);
     const StreamShape s = small_shape(*p, cfg, group, with_cells,
                                       blob <= (size_t)cfg.inline_blob_bytes ? (size_t)cfg.inline_blob_bytes : SIZE_MAX,
-                                      planned_us(*p, cfg), &p->largest_bytes);
-    if (s.rows > 0) {
-      p->tile_items.clear();
-      p->tile_links.clear();
-      p->tile_chains = 0;
-      p->stream_items.clear();
-      p->merges.clear();
-      p->part_rows = 0;
-      stream_tiles.clear();
+                                      &p->largest_bytes);
+    if (s.rows > 0 && s.us < planned_us(*p, cfg)) {
+      const bool weigh = p->tile_chains > 0 && cfg.cost.row_step > 0.f;
+      const double large_us = weigh ? step_us(*p, cfg, blob) : 0.0;
+      const int32_t large_chains = p->tile_chains;
+      const int64_t large_parts = p->part_rows;
+      std::vector<RowTile>& small_tiles = p->small_tiles;
+      small_tiles.clear();
       for (int32_t ei = 0; ei < (int32_t)p->entries.size(); ++ei) {
         const DkEntry& e = p->entries[ei];
         const int32_t rows = group * e.delta;
         for (int32_t r0 = 0; r0 < rows; r0 += s.rows) {
           const int32_t nr = std::min(s.rows, rows - r0);
-          stream_tiles.push_back({ei, r0, nr, e.n + (r0 + nr - 1) / group + 1});
+          small_tiles.push_back({ei, r0, nr, e.n + (r0 + nr - 1) / group + 1});
         }
       }
-      cut_stream_items(stream_tiles, cfg.kv_tile, INT32_MAX, s.chunk, &p->stream_items, &p->merges, &p->part_rows);
+      p->swap_spare();  // the plan made so far waits there
+      p->stream_items.clear();
+      p->merges.clear();
+      p->tile_items.clear();
+      p->tile_links.clear();
+      p->tile_chains = 0;
+      p->part_rows = 0;
+      cut_stream_items(small_tiles, cfg.kv_tile, INT32_MAX, s.chunk, &p->stream_items, &p->merges, &p->part_rows);
+      if (!weigh || step_us(*p, cfg, blob_size(*p, with_cells, 0, 0, p->stream_items.size(), 0, p->merges.size())) < large_us) {
+        std::swap(stream_tiles, small_tiles);
+      } else {
+        p->swap_spare();
+        p->tile_chains = large_chains;
+        p->part_rows = large_parts;
+      }
     }
   }
   p->once = false;
@@ -570,13 +635,7 @@ int32_t build_plan(Pool& pool, const PlanConfig& cfg, int32_t n_seqs, const int3
     chain_units(p->stream_items, cfg, p->heap, p->tail, &p->stream_links, &p->stream_chains);
   }
   p->stream_single = !p->stream_queued && p->stream_units == p->stream_chains;
-  // Merging inside the streaming kernel: nothing else has split rows, every workgroup has one unit, every (row tile, KV
-  // head) a counter of its own, and the last workgroup of a row tile reads all of its partial rows in a round or two --
-  // one workgroup is slow with more (us per step, merge launch / inside: one token on 3000 cached 13.8 / 12.0, with 64-wide
-  // heads 13.9 / 10.8; 9 tokens, 36 rows, on 2000 13.7 / 20.0; 20 tokens on 4000 15 / 25).
-  p->stream_merges = p->stream_single && p->tile_chains == 0 && !p->merges.empty() &&
-                     p->merges.size() * (size_t)cfg.n_kv_heads <= (size_t)cfg.arrivals;
-  for (const DkMerge& m : p->merges) p->stream_merges &= m.nrows <= kMergeInsideRows && m.nsplit * m.nrows <= kMergeInsideParts;
+  p->stream_merges = p->stream_single && merges_inside(*p, cfg);
 
   size_t off = 0;
   p->off_entries = off;

@@ -20,6 +20,16 @@ enum class Route {
   kF32 = 3,      // fp32 pools
 };
 
+// What a step costs, in microseconds.
+struct PlanCost {
+  float unit[3] = {}, per128[3] = {};  // streaming kernel, by row blocks of its widest tile: a launch, 128 keys of its longest unit
+  float keys = 0, again = 0;           // 1e5 keys of one KV head that it reads: the first time, by further row tiles
+  float row_fixed = 0, row_step = 0, row_items = 0;  // row-tile kernel: a launch, 64 keys of its longest chain, 256 (item, KV head)
+  float merge = 0, parts = 0, split = 0;     // merge launch, 1e4 partial rows of 128, each split of the row tile cut most often
+  float merge_inside = 0, inside_split = 0;  // merge inside the streaming kernel, each split
+  float upload = 0;                                  // descriptors that do not fit the kernel arguments
+};
+
 // Every field starts as zero ("never", "none"), however the object that holds it is made.
 struct PlanConfig {
   int32_t n_q_heads = 0, n_kv_heads = 0, head_dim = 0;
@@ -39,6 +49,7 @@ struct PlanConfig {
   int64_t once_cells = 0;  // batches of at least this many cells are read past the caches (0: none are)
   float row_fixed_us = 0, row_step_us = 0;  // estimated cost of the row-tile kernel: a launch, and an item's 64-key step
   float unit_scale = 0;  // cost of a streaming unit's keys against 128-wide heads
+  PlanCost cost;  // prices by which plans of a small batch are weighed against the tile kernel's (row_step 0: they are not)
   int32_t arrivals = 0;  // counters for merges inside the streaming kernel (0: none)
   int32_t small_units = 0;  // a batch of at most this many streaming units may be planned as a small one (0: never)
   int32_t small_rows = 0;   // ... unless an entry has more packed rows than this (0: however many)
@@ -66,7 +77,7 @@ struct PlanPiece {
 struct AttendPlan {
   // working storage of build_plan
   std::vector<Extent> ext;
-  std::vector<PlanRowTile> tile_tiles, stream_tiles;
+  std::vector<PlanRowTile> tile_tiles, stream_tiles, small_tiles;
   std::vector<std::pair<double, int32_t>> heap;
   std::vector<int32_t> tail;
   std::vector<PlanPiece> pieces;
@@ -78,6 +89,16 @@ struct AttendPlan {
   std::vector<DkSeg> segs;
   std::vector<DkItem> tile_items, stream_items;
   std::vector<DkMerge> merges;
+  // the work items of the plan for large batches while one for a small batch is weighed against it
+  std::vector<DkItem> spare_tile_items, spare_stream_items;
+  std::vector<DkMerge> spare_merges;
+  std::vector<int32_t> spare_tile_links;
+  void swap_spare() {
+    std::swap(tile_items, spare_tile_items);
+    std::swap(stream_items, spare_stream_items);
+    std::swap(merges, spare_merges);
+    std::swap(tile_links, spare_tile_links);
+  }
   int64_t total_tokens = 0;
   int64_t part_rows = 0;
   // Streaming kernel: unit u = item u / n_kv_heads for KV head u % n_kv_heads.  Workgroup w walks the

@@ -168,10 +168,14 @@ int main() {
         }
     }
     // non-temporal loads: arena cells of one entry only, in batches that exceed the caches
-    std::map<int64_t, int> starts;
-    int64_t marked = 0;
+    std::map<int64_t, int> starts, lengths;
+    int64_t marked = 0, distinct = 0;
     for (const DkSeg& s : p.segs)
-      if (s.src == 0) ++starts[s.start];
+      if (s.src == 0) {
+        ++starts[s.start];
+        lengths[s.start] = std::max(lengths[s.start], s.len);
+      }
+    for (const auto& kv : lengths) distinct += kv.second;
     for (const DkSeg& s : p.segs) {
       if (!s.once) continue;
       CHECK(s.src == 0 && starts[s.start] == 1);
@@ -179,7 +183,7 @@ int main() {
     }
     for (const auto& kv : starts) shared += kv.second > 1 && marked > 0;
     CHECK((marked > 0) <= p.once);
-    if (p.once) CHECK(!p.stream_items.empty() && marked + 2000 * (int64_t)nseq >= cfg.once_cells);
+    if (p.once) CHECK(!p.stream_items.empty() && distinct >= cfg.once_cells);
     once += p.once;
   }
   std::printf("planned as small %d, cut %d, close below the limit of the kernel arguments %d, merged inside %d, joined %d, "
