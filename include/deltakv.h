@@ -72,7 +72,8 @@ enum {
  * 64 KiB through which the descriptors of a launching call are uploaded; dk_staging_bytes() is the
  * recommended size (1 MiB per buffer).  A call whose descriptors exceed one buffer, or any call
  * that needs an upload on a pool created with host_staging == NULL, returns DK_ERR_WORKSPACE
- * (appends of at most 896 tokens need no upload).  NULL is meant for host-only use of the pool.
+ * (appends of at most 896 tokens need none; longer ones count as needing one, although most
+ * carry their cells in the kernel arguments too).  NULL is meant for host-only use of the pool.
  */
 typedef struct {
   int32_t n_slots;
@@ -382,8 +383,9 @@ int32_t dk_set_attend_variant(dk_pool* pool, int32_t variant);
  * DK_ERR_INVALID for a value out of range or not whole where a count is meant):
  *   stream_rows       most packed query rows (G * Delta) of a sequence that still    [32, 96]       default 96
  *                     goes to the streaming kernel (more: the tile kernel, or the
- *                     block kernel where that takes its place); small batches may
- *                     send it longer ones in several row tiles until this is set
+ *                     block kernel where that takes its place; with 64-wide heads
+ *                     64 at most); small batches may send it longer ones in several
+ *                     row tiles until this is set
  *   small_units       most streaming work units (row tile, key chunk, KV head) of a  [0, 65536]     default 256
  *                     batch that may be planned as a small one, for latency, in
  *                     short row tiles of the streaming kernel; 0: never

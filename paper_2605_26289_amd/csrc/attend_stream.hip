@@ -8,9 +8,10 @@
 //
 //   tile kernel    large Delta: a workgroup owns 256 packed rows (4 wavefronts x 64 rows) and all
 //                  wavefronts share each 64-key K/V tile through LDS (compute bound, MFMA roofline)
-//   stream kernel  small Delta (G*Delta <= 96): every wavefront streams its own slice of the keys
-//                  through private LDS stages with no barriers, the four states are merged at the
-//                  end (HBM bound)
+//   stream kernel  small Delta (row tiles of at most 96 packed rows: entries of G*Delta <= 96, and
+//                  longer ones of small batches in several row tiles): every wavefront streams its
+//                  own slice of the keys through private LDS stages with no barriers, the four
+//                  states are merged at the end (HBM bound, in small batches latency)
 //
 // K/V tiles go HBM -> LDS with global_load_lds_dwordx4 (no VGPR staging).  Rows are 256 B; the 16-byte
 // chunks of a row are XOR-swizzled so that the K reads (ds_read_b128, one row per lane) and the V
@@ -38,9 +39,8 @@ __device__ unsigned long long g_strace[256][8][12];
 // HD: head dimension.  GEN: the general form, for everything but 128-wide heads in groups of 2^k <= 16 query heads per
 // KV head -- any group size, and the probabilities enter the second product as a sum of two bf16 (p = hi + lo, about
 // 2^-17 relative), i.e. with what matters of their 32 bits, for twice the PV products: the shapes it serves used to be
-// computed with fp32 probabilities, and next to HBM the extra MFMAs cost little.  Measured: 14 decoding or verifying
-// sessions of 512-4096 tokens, 32 query heads on 8 KV heads of 64, take 27 us here and took most of 1630 us in the
-// scalar kernel.
+// computed with fp32 probabilities, and next to HBM the extra MFMAs cost little.  Measured, four turns of up to
+// 200 tokens on 256-2048 of 24 query heads on 8 KV heads of 128: 44 us, 1345 in the scalar kernel.
 // A tile is 8 KiB of K and 8 KiB of V: 32 keys of 256 bytes or 64 of 128.
 template <int HD>
 struct Tile {

@@ -404,8 +404,10 @@ StreamShape small_shape(const AttendPlan& p, const PlanConfig& cfg, int32_t grou
 // Marks the segments that the streaming kernel may read past the caches (non-temporal loads): all that no two entries
 // share, once the batch's cells are more than the Infinity Cache holds -- nothing of them can be there from an earlier
 // call, and keeping them costs a tenth of the HBM rate.  Measured, us, cached / non-temporal: 64 verifying sessions of
-// 4096-16384 tokens 416 / 372, 256 decoding ones of 512-8192 789 / 709, 44 of 4000 (700 MB) 145 / 131, 24 (400 MB) 74 / 66; but 16 (256 MB, found in the cache
-// again by a second pass) 47 / 56, 64 sessions sharing 8192 of 8500 tokens 157 / 169.
+// 4096-16384 tokens 416 / 372, 256 decoding ones of 512-8192 789 / 709; 64 sessions sharing 8192 of 8500 tokens 157 / 169.
+// By the size of the K/V (decoding sessions of 4000 tokens; the same pass again and again, K/V that appends have just
+// written, after 600 MB of other writes): 125 MB 27.7 / 31.4, 32.4 / 42.6, 60 / 35; 250 MB 43.6 / 49.8, 64.4 / 59.2, 104 / 54;
+// 281 MB 48.7 / 50.9, 69.7 / 64.2, 112 / 55; 312 MB 54.4 / 53.1, 75.3 / 69.8, 119 / 57; 500 MB 96 / 87, 132 / 113, 160 / 90.
 // A segment is taken for shared if another entry has one that starts at the same cell (an aliased prefix does).
 void mark_once(AttendPlan* p, const PlanConfig& cfg) {
   int64_t cells = 0;

@@ -9,8 +9,12 @@
 //                           finds the first draft that differs from the row's argmax, in registers.
 //
 // Measured, 64 slots of nine rows over 128 256 bf16 logits (148 MB), us a call, and the same in fp32: cached loads and
-// the argmax of every row through memory 32.4 and 55.1; non-temporal loads alone 29.4 and 49.6; both 28.7 and 48.3.  With 18 MB the
-// non-temporal loads are 1-2 % slower, so calls below 64 MiB keep the ordinary ones.
+// the argmax of every row through memory 32.4 and 55.1; non-temporal loads alone 29.4 and 49.6; both 28.7 and 48.3.
+// Which loads, by the size of the logits (us a call, cached / non-temporal; the same logits again and again, logits that
+// a kernel has just written, logits after 600 MB of other writes): 17 MB 8.4 / 8.6, 12.5 / 12.8, 16.8 / 13.3; 52 MB
+// 14.7 / 13.5, 17.5 / 20.2, 28.7 / 18.7; 70 MB 17.4 / 16.0, 20.0 / 21.0, 35.0 / 21.4; 105 MB 22.7 / 21.4, 25.4 / 25.6, 49 / 26.6;
+// 140 MB 28.3 / 27.0, 31.4 / 31.1, 61 / 32.  From 64 MiB on the non-temporal loads lose at most a microsecond where the
+// logits are fresh and win as much or much more elsewhere; below, fresh logits lose up to 3 us.
 //
 // Ties go to the lowest token id; a NaN logit counts as +infinity.
 #include <hip/hip_runtime.h>

@@ -135,3 +135,32 @@ def test_a_captured_call_keeps_its_workspace_when_the_pool_outgrows_it(hq, hkv, 
     # (a captured call merges its splits by another kernel: another order of additions)
     assert (replays[0].float() - want.float()).abs().max().item() <= 2.0 ** -7
     pool.close()
+
+
+@pytest.mark.parametrize("hq,hkv,d,dtype", SHAPES)
+def test_a_capture_that_needs_more_room_grows_the_workspace(hq, hkv, d, dtype):
+    """The first call of the size is the captured one: the graph holds the same kernels as an eager call, not the scalar one."""
+    pool, slots, gen = _pool(hq, hkv, d, dtype, [6000, 20], 16384)
+    scale = d ** -0.5
+    q, k, v = (_rows(gen, 1, x, d, dtype) for x in (hq, hkv, hkv))
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        pool.attend(slots[1:], [0, 1], q, scale, k, v)
+    torch.cuda.synchronize()
+    held, out = pool.workspace.numel(), torch.empty_like(q)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        pool.attend(slots[:1], [0, 1], q, scale, k, v, out=out)
+    plan = dk.last_plan(pool.handle)
+    assert plan["route"] != "scalar" and plan["merges"] > 0 and pool.workspace.numel() > held
+    results = []
+    for _ in range(3):
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        results.append(out.clone())
+        eager = pool.attend(slots[:1], [0, 1], q, scale, k, v)
+        torch.cuda.synchronize()
+        assert (results[-1].float() - eager.float()).abs().max().item() <= 2.0 ** -7
+    assert all(torch.equal(r, results[0]) for r in results)
+    pool.close()
