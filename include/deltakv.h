@@ -194,6 +194,8 @@ int32_t dk_kv_reserve(dk_pool* pool, int32_t n_seqs, const int32_t* slots, const
  *   - q or out is not 16-byte aligned.
  * dk_delta_attend_sized / dk_append_attend_sized return DK_ERR_WORKSPACE in the first case, for callers who grow their
  * workspace on demand; in all else they are dk_delta_attend / dk_append_attend.  dk_last_plan() tells which kernel ran.
+ * (Batches of many short sequences, some 35 and more of up to a few hundred tokens, run in the scalar kernel because it is
+ * the faster one for them; the workspace query then still names what the other kernels would take.)
  */
 int32_t dk_attend_workspace_bytes(dk_pool* pool, int32_t n_seqs, const int32_t* slots, const int32_t* cu_delta,
                                   int32_t staged, int64_t* bytes_out);
@@ -361,8 +363,8 @@ int32_t dk_seq_stats(dk_pool* pool, int32_t slot, int64_t* segments_out, int64_t
 int32_t dk_staging_wait(dk_pool* pool);
 
 /*
- * What the last attention call that was enqueued, or the last dk_attend_workspace_bytes(), of this pool planned: HOST int64
- * [DK_PLAN_FIELDS].  DK_ERR_INVALID before the first of them.
+ * What the last attention call that was enqueued, or the last dk_attend_workspace_bytes() (which leaves no short sequences to
+ * the scalar kernel), of this pool planned: HOST int64 [DK_PLAN_FIELDS].  DK_ERR_INVALID before the first of them.
  */
 enum { DK_ROUTE_SCALAR = 0, DK_ROUTE_TILE = 1, DK_ROUTE_GENERAL = 2, DK_ROUTE_F32 = 3 };
 enum {
@@ -388,7 +390,8 @@ int32_t dk_set_attend_variant(dk_pool* pool, int32_t variant);
  *                     row tiles until this is set
  *   small_units       most streaming work units (row tile, key chunk, KV head) of a  [0, 65536]     default 256
  *                     batch that may be planned as a small one, for latency, in
- *                     short row tiles of the streaming kernel; 0: never
+ *                     short row tiles of the streaming kernel; 0: never, nor are
+ *                     many short sequences then left to the scalar kernel
  *   stream_target     aimed number of streaming work items per KV head             [1, 2^20]      default 256 / Hkv
  *   stream_min_chunk  smallest key range worth its own streaming item               [64, 2^24]     default 512
  *   stream_chains     workgroups of the streaming kernel (one per compute unit)     [1, 65536]     default 256

@@ -475,7 +475,8 @@ int32_t dk_attend_workspace_bytes(dk_pool* pool, int32_t n_seqs, const int32_t* 
     Route route;
     int32_t rc = pool->choose_route(true, n_seqs, slots, cu_delta, &route);
     if (rc != DK_OK) return rc;
-    const dk::PlanConfig cfg = dk::route_config(pool->cfg, route, n_seqs, cu_delta);
+    dk::PlanConfig cfg = dk::route_config(pool->cfg, route, n_seqs, cu_delta);
+    cfg.scalar = dk::ScalarCost();  // (the matrix kernels' plan is never the smaller one)
     std::lock_guard<std::mutex> lk(pool->meta.mutex());
     rc = dk::build_plan(pool->meta, cfg, n_seqs, slots, cu_delta, staged != 0, &plan, staged == 2);
     if (rc != DK_OK) return rc;
@@ -535,6 +536,7 @@ int32_t attend_locked(dk_pool* pool, int32_t n_seqs, const int32_t* slots, const
       int32_t rc = dk::build_plan(pool->meta, cfg, n_seqs, slots, cu_delta, staged, &plan, fold_append);
       if (rc != DK_OK) return rc;
     }
+    if (plan.scalar) route = Route::kRef;
     if (plan.total_tokens == 0) return DK_OK;
     if (!q || !out) return DK_ERR_INVALID;
     inline_blob = plan.blob_bytes <= (size_t)dk::INLINE_BLOB_BYTES && !plan.stream_queued;

@@ -44,6 +44,15 @@ PlanConfig default_config(int32_t n_q_heads, int32_t n_kv_heads, int32_t head_di
 PlanConfig route_config(const PlanConfig& cfg, Route r, int32_t n_seqs, const int32_t* cu_delta) {
   PlanConfig c = cfg;
   c.use_mfma = r != Route::kRef;
+  if (cfg.small_units > 0 && (r == Route::kGeneral || r == Route::kF32)) {
+    const bool wide = cfg.head_dim > 64;
+    if (r == Route::kGeneral)
+      c.scalar = wide ? ScalarCost{7.5f, 2.3f, 2.5f, 3.7f, 9.9f, 6.26f, 0.67f, 1.14f, 7.f, 2.5f}
+                      : ScalarCost{7.1f, 0.69f, 2.9f, 2.3f, 9.4f, 5.45f, 0.38f, 0.47f, 7.f, 6.f};
+    else
+      c.scalar = wide ? ScalarCost{7.3f, 5.3f, 6.9f, 3.5f, 8.6f, 9.95f, 2.4f, 2.8f, 5.f, 2.f}
+                      : ScalarCost{7.1f, 1.45f, 6.5f, 0.2f, 7.6f, 7.1f, 1.0f, 1.34f, 5.f, 2.f};
+  }
   if (r == Route::kGeneral) {
     // block kernel: items of 128 rows, two workgroups on a compute unit; an item's fixed cost (first tiles, merge of
     // the half-waves, store) is about three of its shorter key steps
@@ -507,6 +516,35 @@ double step_us(const AttendPlan& p, const PlanConfig& cfg, size_t blob) {
   }
   return us;
 }
+
+// Many short sessions on the general and fp32 routes: from some 35 of them on the descriptors no longer fit the kernel
+// arguments, and the upload, with the host work that goes with it, costs a step more than the scalar kernel, whose descriptors
+// have no items and no chains, loses on a few hundred keys (us a step with its append, matrix / scalar kernel: 40 sessions of
+// 20 cached tokens, 24 query heads of 128 on 8, 23.9 / 15.8; 48 of 20, 32 heads of 64 on 8, 24.4 / 15.9; fp32, 4 heads of 64
+// on 1, 40 of 20, 21.7 / 15.5; 200 of 200, 9 heads of 64, 61.5 / 26.1).  The prices are fitted to 1232 steps of 1 to 100
+// sessions, up to 4 new tokens each, on either kernel; beyond that they hold while the scalar kernel's waves take few rounds
+// (fp32, 400 sessions of 120 tokens, 2.8 rounds: 57.7 / 75.7; 128 of 60, 24 heads of 128 on 8, 3 rounds: 35.2 / 40.5).  Of 280
+// batches of 34 to 400 sessions the scalar kernel gets 37 in staged mode, all of them 1.12 times faster or more by it, 1.56
+// times on average, and 46 in appended mode, 1.3 times on average.  18 of the 280 stay more than 5 % slower than there (50 are
+// without the rule), where prices that take them would also take some that the matrix kernels serve faster.
+bool scalar_is_cheaper(const AttendPlan& p, const PlanConfig& cfg, size_t row_tiles, size_t stream_tiles) {
+  const ScalarCost& c = cfg.scalar;
+  if (c.launch == 0.f) return false;
+  const size_t tiles = row_tiles + stream_tiles, units = stream_tiles * (size_t)cfg.n_kv_heads;
+  const size_t chains = (size_t)std::max(cfg.stream_chains, 1), limit = (size_t)cfg.inline_blob_bytes;
+  const size_t row_links = row_tiles ? row_tiles + std::min(row_tiles, (size_t)std::max(cfg.tile_wave_slots, 1)) : 0;
+  const size_t stream_links = units > chains ? units + chains : 0;
+  const size_t own = p.entries.size() * sizeof(DkEntry) + p.segs.size() * sizeof(DkSeg);
+  if (own + tiles * sizeof(DkItem) + (row_links + stream_links) * sizeof(int32_t) <= limit) return false;
+  const double rounds = (double)p.total_tokens * cfg.n_q_heads / (256.0 * (cfg.head_dim > 64 ? 4 : 9));
+  if (rounds > c.rounds) return false;
+  int64_t n = 0;
+  for (const DkEntry& e : p.entries)
+    if (e.delta > 0) n = std::max<int64_t>(n, (int64_t)e.n + e.delta);
+  const double steps = (double)((n + 63) / 64), waves = (double)tiles * cfg.n_kv_heads / 256.0;
+  return c.launch + c.step * steps + (c.round_step * steps + c.round) * rounds + (own > limit ? c.upload : 0.0) <
+         c.matrix + c.wave * std::max(0.0, waves - 1.0) + (c.keys + c.wave_keys * waves) * (double)n / 128.0 + c.upload;
+}
 }  // namespace
 
 int32_t build_plan(Pool& pool, const PlanConfig& cfg, int32_t n_seqs, const int32_t* slots, const int32_t* cu_delta,
@@ -561,6 +599,11 @@ int32_t build_plan(Pool& pool, const PlanConfig& cfg, int32_t n_seqs, const int3
       }
     }
   }
+  p->scalar = scalar_is_cheaper(*p, cfg, tile_tiles.size(), stream_tiles.size());
+  if (p->scalar) {
+    tile_tiles.clear();
+    stream_tiles.clear();
+  }
   if (!tile_tiles.empty() && !stream_tiles.empty()) {
     int64_t keys = 0;
     for (const RowTile& t : stream_tiles) keys += t.kv_hi;
@@ -573,7 +616,7 @@ int32_t build_plan(Pool& pool, const PlanConfig& cfg, int32_t n_seqs, const int3
   cut_stream_items(stream_tiles, cfg.kv_tile, cfg.stream_target, cfg.stream_min_chunk, &p->stream_items, &p->merges,
                    &p->part_rows);
   p->largest_bytes = 0;
-  if (cfg.small_units > 0 && (int64_t)(tile_tiles.size() + stream_tiles.size()) * cfg.n_kv_heads <= cfg.small_units) {
+  if (!p->scalar && cfg.small_units > 0 && (int64_t)(tile_tiles.size() + stream_tiles.size()) * cfg.n_kv_heads <= cfg.small_units) {
     // (a call whose descriptors travel in the kernel arguments goes on doing so)
     const size_t units = p->stream_items.size() * (size_t)cfg.n_kv_heads;
     const size_t chains = std::min(units, (size_t)std::max(cfg.stream_chains, 1));

@@ -14,7 +14,8 @@ namespace dk {
 
 // Which kernels carry an attention call.
 enum class Route {
-  kRef = 0,      // scalar reference kernel: variant 1, a scale that is not positive and finite, calls with room for no other
+  kRef = 0,      // scalar reference kernel: variant 1, a scale that is not positive and finite, calls with room for no other,
+             // many short sessions (ScalarCost)
   kTile = 1,     // bf16, 128-wide heads, groups of 2^k <= 16 query heads: tile and stream kernels
   kGeneral = 2,  // bf16, any other shape: block kernel and the stream kernel's general form
   kF32 = 3,      // fp32 pools
@@ -28,6 +29,14 @@ struct PlanCost {
   float merge = 0, parts = 0, split = 0;     // merge launch, 1e4 partial rows of 128, each split of the row tile cut most often
   float merge_inside = 0, inside_split = 0;  // merge inside the streaming kernel, each split
   float upload = 0;                                  // descriptors that do not fit the kernel arguments
+};
+
+// What a step of many short sessions takes on the scalar kernel and on the matrix kernels, in microseconds.
+struct ScalarCost {
+  float launch = 0, step = 0, round_step = 0, round = 0;  // scalar kernel: a launch, 64 keys of the longest row; per round: 64 keys, its start
+  float matrix = 0, wave = 0, keys = 0, wave_keys = 0;    // matrix kernels: a launch, 256 units more, 128 keys; 128 keys per 256 units
+  float upload = 0;                                       // descriptors that do not fit the kernel arguments
+  float rounds = 0;                                       // most rounds of the scalar kernel's waves that the prices hold for
 };
 
 // Every field starts as zero ("never", "none"), however the object that holds it is made.
@@ -50,6 +59,7 @@ struct PlanConfig {
   float row_fixed_us = 0, row_step_us = 0;  // estimated cost of the row-tile kernel: a launch, and an item's 64-key step
   float unit_scale = 0;  // cost of a streaming unit's keys against 128-wide heads
   PlanCost cost;  // prices by which plans of a small batch are weighed against the tile kernel's (row_step 0: they are not)
+  ScalarCost scalar;  // prices by which short sessions go to the scalar kernel (launch 0: they do not)
   int32_t arrivals = 0;  // counters for merges inside the streaming kernel (0: none)
   int32_t small_units = 0;  // a batch of at most this many streaming units may be planned as a small one (0: never)
   int32_t small_rows = 0;   // ... unless an entry has more packed rows than this (0: however many)
@@ -113,6 +123,7 @@ struct AttendPlan {
   // The streaming kernel can merge the split rows itself (the workgroup that finishes the last split of a row tile does).
   bool stream_merges = false;
   bool once = false;  // some segments are marked DkSeg::once
+  bool scalar = false;  // planned for the scalar kernel by PlanConfig::scalar: there are entries and segments only
   int64_t stream_units = 0;
   size_t off_queue = 0;
   // Tile kernel: tile_wave_slots workgroups per KV head, workgroup c of a head walks the items

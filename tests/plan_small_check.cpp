@@ -51,8 +51,56 @@ static const Shape kShapes[] = {
     {32, 1, 128, true, dk::Route::kGeneral}, {4, 1, 64, false, dk::Route::kF32},     {32, 8, 128, false, dk::Route::kF32},
 };
 
+// Many short sessions: where they are planned for the scalar kernel there is nothing but entries and segments, the matrix
+// kernels' plan of the same batch would not fit the kernel arguments, and its workspace is the larger one.
+static void check_short_sessions() {
+  std::mt19937 rng(11);
+  auto uni = [&](int lo, int hi) { return lo + (int)(rng() % (unsigned)(hi - lo + 1)); };
+  int scalar[2] = {}, matrix[2] = {};
+  for (int rep = 0; rep < 800; ++rep) {
+    const Shape& sh = kShapes[rng() % (sizeof(kShapes) / sizeof(kShapes[0]))];
+    const int nseq = uni(1, 100), top = uni(0, 1) ? uni(1, 60) : uni(1, 400), most = uni(0, 3);
+    const bool staged = uni(0, 1);
+    std::vector<int32_t> slots(nseq), cu(nseq + 1, 0);
+    for (int b = 0; b < nseq; ++b) cu[b + 1] = cu[b] + (b == 0 ? 1 : uni(0, most));
+    dk::Pool pool(nseq, 0, (int64_t)nseq * 512, 16);
+    for (int b = 0; b < nseq; ++b) {
+      CHECK(pool.acquire(0, 0, &slots[b]) == dk::OK);
+      const int32_t c2[2] = {0, uni(std::max(1, most), std::max({1, most, top}))};
+      std::vector<int64_t> dst;
+      CHECK(pool.append(1, &slots[b], c2, nullptr, &dst) == dk::OK);
+    }
+    const dk::PlanConfig base = dk::default_config(sh.hq, sh.hkv, sh.d, sh.bf16);
+    const dk::PlanConfig cfg = dk::route_config(base, sh.route, nseq, cu.data());
+    const dk::PlanConfig ref = dk::route_config(base, dk::Route::kRef, nseq, cu.data());
+    dk::PlanConfig never = cfg, off = base;
+    never.scalar = dk::ScalarCost();
+    off.small_units = 0;
+    CHECK(dk::route_config(off, sh.route, nseq, cu.data()).scalar.launch == 0.f);
+    dk::AttendPlan p, m, r;
+    {
+      std::lock_guard<std::mutex> g(pool.mutex());
+      CHECK(dk::build_plan(pool, cfg, nseq, slots.data(), cu.data(), staged, &p) == dk::OK);
+      CHECK(dk::build_plan(pool, never, nseq, slots.data(), cu.data(), staged, &m) == dk::OK);
+      CHECK(dk::build_plan(pool, ref, nseq, slots.data(), cu.data(), staged, &r) == dk::OK);
+    }
+    CHECK(!m.scalar && !r.scalar && (!p.scalar || sh.route != dk::Route::kTile));
+    if (m.blob_bytes <= 3072) CHECK(!p.scalar);
+    ++(p.scalar ? scalar : matrix)[nseq > 35];
+    if (!p.scalar) continue;
+    CHECK(p.tile_items.empty() && p.stream_items.empty() && p.merges.empty() && p.tile_chains == 0 && p.stream_units == 0);
+    CHECK(p.part_rows == 0 && !p.stream_queued && !p.once);
+    CHECK(p.blob_bytes == r.blob_bytes && p.total_bytes == r.total_bytes && p.off_segs == r.off_segs);
+    CHECK(p.entries.size() == r.entries.size() && p.segs.size() == r.segs.size() && p.total_tokens == r.total_tokens);
+    CHECK(p.total_bytes <= m.total_bytes);
+  }
+  std::printf("short sessions: %d planned for the scalar kernel, %d for the others\n", scalar[1], matrix[1]);
+  CHECK(scalar[1] > 40 && matrix[1] > 40 && matrix[0] > 40);
+}
+
 int main() {
   check_fields_start_at_zero();
+  check_short_sessions();
   std::mt19937 rng(7);
   auto uni = [&](int lo, int hi) { return lo + (int)(rng() % (unsigned)(hi - lo + 1)); };
   int small = 0, cut = 0, near = 0, inside = 0, joined = 0, once = 0, shared = 0;

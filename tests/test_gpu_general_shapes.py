@@ -89,7 +89,49 @@ def test_general_kernels_walk_chains_and_queues(hq, hkv, d):
         cu = np.concatenate([[0], np.cumsum(deltas)]).astype(np.int32)
         out = m.pool.attend(slots, cu, to_dev(q, "bf16"), sh.scale, to_dev(kn, "bf16"), to_dev(vn, "bf16"))
         ref, _ = oracle.delta_attend_batch(q, [m.cache(s) for s in slots], kn, vn, cu, sh.scale)
+        assert dk.last_plan(m.pool.handle)["route"] == "general"
         _check(out, ref, max(np.abs(vn).max(), 5.0), queue)
+    m.pool.close()
+
+
+# descriptors: in the kernel arguments of either kernel, only of the scalar one (in one mode, in both), of neither
+@pytest.mark.parametrize("hq,hkv,d,dtype,sessions,scalar", [
+    (32, 8, 64, "bf16", 24, ()), (32, 8, 64, "bf16", 32, ("staged",)), (32, 8, 64, "bf16", 40, ("staged", "fused", "appended")),
+    (24, 8, 128, "bf16", 40, ("staged", "fused", "appended")), (6, 2, 128, "bf16", 56, ("fused", "appended")),
+    (32, 8, 64, "bf16", 100, ("staged", "fused", "appended")), (4, 1, 64, "f32", 24, ()), (4, 1, 64, "f32", 40, ("staged", "fused", "appended")),
+    (4, 1, 64, "f32", 64, ()), (8, 8, 128, "f32", 100, ("staged", "fused", "appended")),
+])
+def test_many_short_sessions(hq, hkv, d, dtype, sessions, scalar):
+    """Batches on both sides of the rule that leaves many short sessions to the scalar kernel: results of either kernel, in
+    every mode, with entries that have nothing new."""
+    sh = wl.Shape(hq, hkv, d, dtype)
+    rng = np.random.default_rng(sessions)
+    m = Mirror(sh, sessions, sessions * 96, granule=16, seed=d + hq)
+    slots = [m.acquire() for _ in range(sessions)]
+    m.append(slots, rng.integers(1, 21, size=sessions).tolist())
+    deltas = rng.integers(1, 3, size=sessions)
+    deltas[::7] = 0
+    cu = np.concatenate([[0], np.cumsum(deltas)])
+    q, kn, vn = (m.draw(int(cu[-1]), h) for h in (hq, hkv, hkv))
+    refs = [oracle.delta_attend(q[cu[b]:cu[b + 1]], *m.cache(s), kn[cu[b]:cu[b + 1]], vn[cu[b]:cu[b + 1]], sh.scale)
+            for b, s in enumerate(slots) if deltas[b]]
+    ref, ref_lse = (np.concatenate([r[i] for r in refs]) for i in (0, 1))
+    vmax = max([np.abs(vn).max()] + [np.abs(m.cache(s)[1]).max() for s in slots])
+    qd, kd, vd = (to_dev(x, dtype) for x in (q, kn, vn))
+    h, past = m.pool.handle, [m.pool.length(s) for s in slots]
+    matrix = "general" if dtype == "bf16" else "f32"
+    for units, to_scalar in ((256, scalar), (0, ())):
+        dk.set_tuning(h, "small_units", units)
+        lse = torch.empty((int(cu[-1]), hq), dtype=torch.float32, device="cuda")
+        for mode in ("staged", "fused", "appended"):
+            if mode == "fused":
+                out = m.pool.append_attend(slots, cu, qd, kd, vd, sh.scale, lse=lse)
+            else:
+                out = m.pool.attend(slots, cu, qd, sh.scale, *((kd, vd) if mode == "staged" else ()), lse=lse)
+            assert dk.last_plan(h)["route"] == ("scalar" if mode in to_scalar else matrix), (mode, dk.last_plan(h))
+            _check(out, ref, vmax, (mode, units), dtype)
+            assert np.abs(lse.cpu().numpy() - ref_lse).max() < 1e-4, (mode, units)
+        m.pool.trim_batch(slots, past)
     m.pool.close()
 
 
