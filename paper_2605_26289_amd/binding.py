@@ -41,8 +41,9 @@ _lib = None
 
 _I32P = C.POINTER(C.c_int32)
 _I64P = C.POINTER(C.c_int64)
-# Arrays the binding marshals on every step are passed as plain addresses: making a typed ctypes pointer for each costs
-# about a microsecond, and a small call is a dozen microseconds altogether.
+# Arrays the binding marshals on every step go in as bytes objects, whose address ctypes passes as it is: asking a numpy
+# array for its address costs about a microsecond (measured, array to argument: 1.45 us by address, 0.35 as bytes), a typed
+# ctypes pointer as much again, and a small call is a dozen microseconds altogether.
 _ARRAY = C.c_void_p
 
 SIGNATURES = {
@@ -139,11 +140,11 @@ def _ptr(t) -> Optional[int]:
 
 
 def _array(values, dtype=np.int32):
-    """(array kept alive by the caller, its address) for an argument declared _ARRAY"""
+    """(array, what to pass for an argument declared _ARRAY that the library only reads)"""
     if values is None:
         return None, None
     arr = np.ascontiguousarray(values, dtype=dtype)
-    return arr, arr.ctypes.data
+    return arr, arr.tobytes()
 
 
 def _stream(stream) -> Optional[int]:
