@@ -168,31 +168,51 @@ struct KvCursor {
 // The load is issued from inline assembly on purpose: the compiler then keeps no account of it and
 // inserts no vmcnt(0) of its own in front of later LDS reads, so a tile can stay in flight while
 // the previous one is being consumed.  Completion is awaited explicitly with wait_vmcnt<N>().
-// ONCE: a non-temporal load, for rows that nothing else reads (see DkSeg::once).
-template <bool IS_V, int HD = D, bool ONCE = false>
-__device__ __forceinline__ void load_kib(const char* gbase, uint32_t stride, int cnt, char* lds_region, int blk, int lane) {
+template <bool IS_V, int HD = D>
+__device__ __forceinline__ uint32_t kib_lane_off(uint32_t stride, int cnt, int blk, int lane) {
   typedef Geo<HD> G;
   const int row = blk * G::ROWS_PER_KIB + lane / G::CHUNKS;
   const int slot = lane % G::CHUNKS;
   const int chunk = slot ^ (IS_V ? G::v_swizzle(row) : G::k_swizzle(row));
-  const uint32_t voff = (uint32_t)min(row, cnt - 1) * stride + chunk * 16;
+  return __umul24((uint32_t)min(row, cnt - 1), stride) + chunk * 16;  // (stride: KV heads x row bytes, below 2^24)
+}
+template <bool IS_V, int HD = D>
+__device__ __forceinline__ void load_kib(const char* gbase, uint32_t stride, int cnt, char* lds_region, int blk, int lane) {
+  const uint32_t voff = kib_lane_off<IS_V, HD>(stride, cnt, blk, lane);
   const uint32_t lds_addr = (uint32_t)(uintptr_t)(lds_void_ptr)(lds_region + blk * 1024);
-  if constexpr (ONCE)
-    asm volatile(
-        "s_mov_b32 m0, %0\n\t"
-        "s_nop 0\n\t"
-        "global_load_lds_dwordx4 %1, %2 nt"
-        :
-        : "s"(lds_addr), "v"(voff), "s"(gbase)
-        : "memory", "m0");
-  else
-    asm volatile(
-        "s_mov_b32 m0, %0\n\t"
-        "s_nop 0\n\t"
-        "global_load_lds_dwordx4 %1, %2"
-        :
-        : "s"(lds_addr), "v"(voff), "s"(gbase)
-        : "memory", "m0");
+  asm volatile(
+      "s_mov_b32 m0, %0\n\t"
+      "s_nop 0\n\t"
+      "global_load_lds_dwordx4 %1, %2"
+      :
+      : "s"(lds_addr), "v"(voff), "s"(gbase)
+      : "memory", "m0");
+}
+// Eight such blocks, a whole tile of 8 KiB, with the lane's offsets at hand.  The instruction's offset counts for both
+// addresses, so M0 is written once for four blocks; the lane's offsets make up for that on the side of memory, and for the
+// bias that keeps them from getting negative (a ragged tile's last rows).  ONCE: non-temporal loads, for rows that nothing
+// else reads (see DkSeg::once).
+constexpr int KIB_BIAS = 3072;
+template <bool IS_V, int HD = D>
+__device__ __forceinline__ uint32_t kib_biased_off(uint32_t stride, int cnt, int blk, int lane) {
+  return kib_lane_off<IS_V, HD>(stride, cnt, blk, lane) + KIB_BIAS - 1024 * (blk & 3);
+}
+template <bool ONCE>
+__device__ __forceinline__ void load_eight_kib(const char* gbase, const uint32_t (&voff)[8], uint32_t lds_addr) {
+#define DK_EIGHT_KIB(HOW)                                                                                          \
+  asm volatile(                                                                                                    \
+      "s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %9" HOW "\n\t"                                   \
+      "global_load_lds_dwordx4 %2, %9 offset:1024" HOW "\n\tglobal_load_lds_dwordx4 %3, %9 offset:2048" HOW "\n\t"  \
+      "global_load_lds_dwordx4 %4, %9 offset:3072" HOW "\n\ts_add_u32 m0, m0, 0x1000\n\ts_nop 0\n\t"               \
+      "global_load_lds_dwordx4 %5, %9" HOW "\n\tglobal_load_lds_dwordx4 %6, %9 offset:1024" HOW "\n\t"              \
+      "global_load_lds_dwordx4 %7, %9 offset:2048" HOW "\n\tglobal_load_lds_dwordx4 %8, %9 offset:3072" HOW          \
+      :                                                                                                            \
+      : "s"(lds_addr), "v"(voff[0]), "v"(voff[1]), "v"(voff[2]), "v"(voff[3]), "v"(voff[4]), "v"(voff[5]),           \
+        "v"(voff[6]), "v"(voff[7]), "s"(gbase - KIB_BIAS)                                                            \
+      : "memory", "m0", "scc")
+  if constexpr (ONCE) DK_EIGHT_KIB(" nt");
+  else DK_EIGHT_KIB("");
+#undef DK_EIGHT_KIB
 }
 
 // A operand of S^T = K Q^T for key block kb and depth step ks: lane (row l%32, half h = l/32) holds
@@ -260,14 +280,27 @@ __device__ __forceinline__ void wait_q(const bf16x8 (&qf)[MB][8]) {
 
 // A pair of fp32 weights as hi + lo, both bf16: hi is the upper half of the bits (truncated), lo the rest rounded to
 // bf16.  What is lost is below 2^-16 of the weight.  Written to pair w of the two B-operand fragments.
+__device__ __forceinline__ uint32_t pack_pair(float p0, float p1) {
+  typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+  bf16x2 w;
+  w[0] = (__bf16)p0;
+  w[1] = (__bf16)p1;
+  return __builtin_bit_cast(uint32_t, w);
+}
+__device__ __forceinline__ void split_pair(float p0, float p1, uint32_t& hi, uint32_t& lo) {
+  const uint32_t u0 = __float_as_uint(p0), u1 = __float_as_uint(p1);
+  hi = __builtin_amdgcn_perm(u1, u0, 0x07060302);  // upper halves of (p0, p1)
+  lo = pack_pair(p0 - __uint_as_float(u0 & 0xffff0000u), p1 - __uint_as_float(u1 & 0xffff0000u));
+}
 __device__ __forceinline__ void split_pair(float p0, float p1, bf16x8& hi, bf16x8& lo, int w) {
   typedef __attribute__((ext_vector_type(4))) uint32_t words;
-  const uint32_t u0 = __float_as_uint(p0), u1 = __float_as_uint(p1);
-  words h = __builtin_bit_cast(words, hi);
-  h[w] = __builtin_amdgcn_perm(u1, u0, 0x07060302);  // upper halves of (p0, p1)
+  words h = __builtin_bit_cast(words, hi), l = __builtin_bit_cast(words, lo);
+  uint32_t hw, lw;
+  split_pair(p0, p1, hw, lw);
+  h[w] = hw;
+  l[w] = lw;
   hi = __builtin_bit_cast(bf16x8, h);
-  lo[2 * w] = (__bf16)(p0 - __uint_as_float(u0 & 0xffff0000u));
-  lo[2 * w + 1] = (__bf16)(p1 - __uint_as_float(u1 & 0xffff0000u));
+  lo = __builtin_bit_cast(bf16x8, l);
 }
 
 // Stores one row's results of a lane: quad i holds depths depth0 + 8 i .. + 3 (the order of the 32x32 accumulators,
@@ -523,40 +556,61 @@ __device__ __forceinline__ void wait_vmcnt() {
 // kernel also writes the call's new K/V rows (token-major, as staged in k_new / v_new) into their arena cells, so
 // that no separate copy kernel has to be launched.  The cells are fresh ones that no attention work of this launch
 // reads (the new tokens are attended from the staged rows), so the order against the rest of the kernel is free:
-// every workgroup copies an equal run right after its first K/V requests, whose latency covers the copy's.
-// The copy is cut into 16-byte pieces, piece p = (token, K or V, KV head, position in the row); a thread has four
-// loads in flight before its first store.
+// every workgroup copies an equal run where its own reads have something to hide under.
+// The copy is cut into 16-byte pieces, piece p = (token, K or V, KV head, position in the row); a thread has up to four
+// loads in flight before its first store.  load() asks for the first of them, store() writes them and does the others.
+template <bool INLINE, int ROW = ROW_BYTES, int THREADS = 256>
+struct RowCopy {
+  typedef __attribute__((ext_vector_type(4))) uint32_t Piece;
+  Piece v[4];
+  char* dst[4];
+  int at = 0, end = 0;  // pieces [at, end) of this workgroup are still to be done
+
+  __device__ __forceinline__ void load_four(const Ctx& c) {
+    const int32_t* cells = resolve_desc<INLINE>(c.cells);
+    const int vecs = c.n_kv_heads * (ROW / 16);  // pieces of one token's K (as many for V)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (at + k * THREADS >= end) continue;
+      const int p = min(at + k * THREADS + (int)threadIdx.x, end - 1);  // (threads past the end repeat the last piece)
+      const int t = (int)((uint32_t)p / (uint32_t)(2 * vecs)), r = p - t * (2 * vecs);
+      const bool is_v = r >= vecs;
+      const int j = is_v ? r - vecs : r;
+      const int g = j / (ROW / 16), piece = j % (ROW / 16);
+      const int64_t cell = cells[t];
+      v[k] = *(const Piece*)((is_v ? c.v_new : c.k_new) + ((int64_t)t * c.n_kv_heads + g) * ROW + piece * 16);
+      dst[k] = const_cast<char*>(is_v ? c.v_arena : c.k_arena) + ((int64_t)g * c.arena_cells + cell) * ROW + piece * 16;
+    }
+  }
+  __device__ __forceinline__ void store_four() {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (at + k * THREADS < end) *(Piece*)dst[k] = v[k];
+    }
+    at += 4 * THREADS;
+  }
+  __device__ __forceinline__ void load(const Ctx& c) {
+    if (c.n_scatter <= 0) return;
+    const int total = c.n_scatter * 2 * c.n_kv_heads * (ROW / 16);
+    const int per = ((total + (int)gridDim.x - 1) / (int)gridDim.x + THREADS - 1) / THREADS * THREADS;
+    at = min(total, (int)blockIdx.x * per);
+    end = min(total, at + per);
+    load_four(c);
+  }
+  __device__ __forceinline__ void store(const Ctx& c) {
+    if (at >= end) return;
+    store_four();
+    while (at < end) {
+      load_four(c);
+      store_four();
+    }
+  }
+};
 template <bool INLINE, int ROW = ROW_BYTES, int THREADS = 256>
 __device__ __forceinline__ void scatter_new_rows(const Ctx& c) {
-  if (c.n_scatter <= 0) return;
-  const int32_t* cells = resolve_desc<INLINE>(c.cells);
-  const int vecs = c.n_kv_heads * (ROW / 16);  // pieces of one token's K (as many for V)
-  const int total = c.n_scatter * 2 * vecs;
-  const int per = ((total + (int)gridDim.x - 1) / (int)gridDim.x + THREADS - 1) / THREADS * THREADS;
-  const int begin = min(total, (int)blockIdx.x * per), end = min(total, begin + per);
-  const auto locate = [&](int p, const char*& src, char*& dst) {
-    p = min(p, end - 1);  // (threads past the end repeat the last piece: same bytes)
-    const int t = p / (2 * vecs), r = p - t * (2 * vecs);
-    const bool is_v = r >= vecs;
-    const int j = is_v ? r - vecs : r;
-    const int g = j / (ROW / 16), piece = j % (ROW / 16);
-    const int64_t cell = cells[t];
-    src = (is_v ? c.v_new : c.k_new) + ((int64_t)t * c.n_kv_heads + g) * ROW + piece * 16;
-    dst = const_cast<char*>(is_v ? c.v_arena : c.k_arena) + ((int64_t)g * c.arena_cells + cell) * ROW + piece * 16;
-  };
-  for (int base = begin + (int)threadIdx.x; base < end; base += 4 * THREADS) {
-    const char *s0, *s1, *s2, *s3;
-    char *d0, *d1, *d2, *d3;
-    locate(base, s0, d0);
-    locate(base + THREADS, s1, d1);
-    locate(base + 2 * THREADS, s2, d2);
-    locate(base + 3 * THREADS, s3, d3);
-    const uint4 v0 = *(const uint4*)s0, v1 = *(const uint4*)s1, v2 = *(const uint4*)s2, v3 = *(const uint4*)s3;
-    *(uint4*)d0 = v0;
-    *(uint4*)d1 = v1;
-    *(uint4*)d2 = v2;
-    *(uint4*)d3 = v3;
-  }
+  RowCopy<INLINE, ROW, THREADS> copy;
+  copy.load(c);
+  copy.store(c);
 }
 
 inline Ctx make_ctx(const AttendArgs& a, const DkItem* items) {

@@ -19,6 +19,7 @@
 #include <hip/hip_runtime.h>
 
 #include <mutex>
+#include <utility>
 
 #include "attend_common.hpp"
 #include "kernels.hpp"
@@ -55,26 +56,20 @@ struct RowState {
   float l[MB];      // this lane's share of the weight sum (the other half-wave holds the rest)
 };
 
-// All MFMA operand fragments of one tile, read out of its LDS stage in one go: once they are in
-// registers the stage can take the next HBM load while the tile is still being computed.
+// MFMA operand fragments of one tile, read out of its LDS stage into registers: once a half of the stage (K or V) has been
+// read it can take the next HBM load while the tile is still being computed.
 template <int HD>
 struct TileFrags {
   bf16x8 k[Tile<HD>::KB][Geo<HD>::KS];      // [key block][depth step]
   bf16x8 v[2 * Tile<HD>::KB][Geo<HD>::DB];  // [key step][depth block]
 };
 template <int HD>
-__device__ __forceinline__ void read_frags(const char* k_lds, const char* v_lds, int lane, TileFrags<HD>& f) {
-  const uint32_t koff = k_lane_off<HD>(lane), voff = v_lane_off<HD>(lane);
+__device__ __forceinline__ void read_k_frags(const char* k_lds, uint32_t koff, TileFrags<HD>& f) {
 #pragma unroll
-  for (int kb = 0; kb < Tile<HD>::KB; ++kb)
+  for (int ks = 0; ks < Geo<HD>::KS; ++ks)
 #pragma unroll
-    for (int ks = 0; ks < Geo<HD>::KS; ++ks) f.k[kb][ks] = read_k_frag<HD>(k_lds, koff, kb, ks);
-#pragma unroll
-  for (int j = 0; j < 2 * Tile<HD>::KB; ++j)
-#pragma unroll
-    for (int db = 0; db < Geo<HD>::DB; ++db) f.v[j][db] = read_v_frag<HD>(v_lds, voff, j, db);
+    for (int kb = 0; kb < Tile<HD>::KB; ++kb) f.k[kb][ks] = read_k_frag<HD>(k_lds, koff, kb, ks);
 }
-
 constexpr float STREAM_RESCALE_SLACK = 8.f;  // log2 units, as in the tile kernel
 
 __device__ __forceinline__ float stream_max3(float a, float b, float c) {
@@ -83,22 +78,21 @@ __device__ __forceinline__ float stream_max3(float a, float b, float c) {
   return d;
 }
 
-// O *= alpha for one accumulator, written so that the accumulators stay in the accumulation registers: with plain
-// C++ here the compiler keeps a second copy of all of O in ordinary registers, refreshed for every tile (one
-// v_accvgpr_read per element and tile) only to serve this rarely taken path.  Every MFMA that wrote O has retired
-// by the time this runs: the scores of the current tile, produced by later MFMAs, have already been read.
-__device__ __forceinline__ float scale_acc(float o, float alpha) {
-  float t;
-  asm volatile(
-      "v_accvgpr_read_b32 %1, %0\n\t"
-      "s_nop 0\n\t"
-      "v_mul_f32 %1, %1, %2\n\t"
-      "s_nop 0\n\t"
-      "v_accvgpr_write_b32 %0, %1"
-      : "+a"(o), "=&v"(t)
-      : "v"(alpha));
-  return o;
+// The products are issued from inline assembly so that the accumulators (O and the scores) and Q live in the accumulation
+// registers and nowhere else: with plain C++ the compiler keeps a second copy of all of O in ordinary registers, for the sake
+// of the rarely taken rescale.  It does not see then that these registers come out of the matrix pipeline; where a read can
+// follow a product closely they pass through settle() first.
+template <bool Q_ACC>
+__device__ __forceinline__ void mfma_first(f32x16& s, const bf16x8& k, const bf16x8& q) {
+  if constexpr (Q_ACC) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&a"(s) : "v"(k), "a"(q));
+  else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&a"(s) : "v"(k), "v"(q));
 }
+template <bool Q_ACC>
+__device__ __forceinline__ void mfma_more(f32x16& s, const bf16x8& k, const bf16x8& q) {
+  if constexpr (Q_ACC) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(s) : "v"(k), "a"(q));
+  else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(s) : "v"(k), "v"(q));
+}
+__device__ __forceinline__ void settle(f32x16& a) { asm volatile("s_nop 15\n\ts_nop 7" : "+a"(a)); }
 
 // Q as B operand: lane (row l%32 of block mb, half l/32) holds Q[row][ks*16 + 8*(l/32) .. +7].  With one or two
 // row blocks the unit's Q fragments stay in registers for the whole unit; with three (96 registers next to 192
@@ -107,7 +101,7 @@ __device__ __forceinline__ float scale_acc(float o, float alpha) {
 template <int MB, int HD>
 struct QFrags {
   static constexpr bool IN_LDS = MB > 2;
-  bf16x8 r[IN_LDS ? 1 : MB][Geo<HD>::KS];
+  bf16x8 r[IN_LDS ? 1 : MB][Geo<HD>::KS];  // (accumulation registers)
   const char* q_lds;
   uint32_t koff;
   __device__ __forceinline__ void load() {
@@ -116,6 +110,10 @@ struct QFrags {
       for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
         for (int ks = 0; ks < Geo<HD>::KS; ++ks) r[mb][ks] = read_k_frag<HD>(q_lds, koff, mb, ks);
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int ks = 0; ks < Geo<HD>::KS; ++ks) asm volatile("" : "+a"(r[mb][ks]));
     }
   }
   __device__ __forceinline__ bf16x8 get(int mb, int ks) const {
@@ -124,110 +122,252 @@ struct QFrags {
   }
 };
 
-// One tile against MB*32 query rows, operands in registers: S^T, online softmax, O^T update.
-template <int MB, int HD, bool GEN>
-__device__ __forceinline__ void compute_tile(const TileFrags<HD>& f, const QFrags<MB, HD>& qf, RowState<MB, HD>& st,
-                                             const int (&limit)[MB], float c, int lane, int cnt, int pos,
-                                             bool need_mask) {
-  constexpr int KB = Tile<HD>::KB, KS = Geo<HD>::KS, DB = Geo<HD>::DB;
-  const int h = lane >> 5;
-  bf16x8 pf[MB][2 * KB];
-  bf16x8 pl[GEN ? MB : 1][GEN ? 2 * KB : 1];
-  f32x16 s[KB][MB];
-#pragma unroll
-  for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) s[kb][mb][r] = 0.f;
-#pragma unroll
-  for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb) {
-      const bf16x8 q = qf.get(mb, ks);
-#pragma unroll
-      for (int kb = 0; kb < KB; ++kb) s[kb][mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.k[kb][ks], q, s[kb][mb], 0, 0, 0);
-    }
+template <int N>
+struct Num {
+  static constexpr int value = N;
+};
+template <typename F, int... Is>
+__device__ __forceinline__ void unrolled(F&& f, std::integer_sequence<int, Is...>) {
+  (f(Num<Is>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void unrolled(F&& f) {
+  unrolled(f, std::make_integer_sequence<int, N>{});
+}
 
-  if (need_mask) {
-    // accumulator r of key block kb is key 32 kb + 8*(r/4) + 4h + r%4 of the tile
+// Keeps a value's computation where the source has it.
+template <typename T>
+__device__ __forceinline__ void stay(const T& x) {
+  asm volatile("" : : "v"(x));
+}
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+
+// The key loop is a software pipeline, because a compute unit runs one of these wavefronts per SIMD and nothing but the
+// wavefront's own instructions can fill the time that a product, an exponential or a load takes.  Step t issues
+//     S^T(t)                K fragments of tile t, read from LDS at the end of step t-1
+//     O^T += V^T P^T(t-1)   V fragments of tile t-1, read at the beginning of step t
+// and between those MFMAs, slot by slot in the order that is fixed here, the VALU turns S^T(t-1) into P(t-1), pair by pair,
+// each just in time for its product, and takes the row maxima of S^T(t), whose accumulators are copied on the way (the next
+// step's products overwrite them while the copy is being turned into weights).
+// What bounds a step is the number of instructions, 4 cycles each, 8 an exponential and an MFMA.  Measured with cycle stamps,
+// keys in L2: one row block of 128-wide heads 2300 cycles a step with the parts one after the other, 1560 like this (its 16
+// MFMAs alone: 512); two row blocks with split weights 4100 / 2950 (48 MFMAs: 1540).  One 150-token turn on 800 cached tokens
+// 13.9 -> 11.4 us, four turns of up to 200 tokens with three query heads to a KV head 41.4 -> 33.5.
+template <int MB, int HD, bool GEN>
+struct StreamStep {
+  static constexpr int KB = Tile<HD>::KB, KS = Geo<HD>::KS, DB = Geo<HD>::DB;
+  static constexpr int S_PER = KS * KB, S_SLOTS = MB * S_PER;             // S^T products: of a row block (8), all
+  static constexpr int NJ = 2 * KB, PIECES = MB * NJ;                     // a piece: eight weights a lane, one B operand
+  static constexpr int O_PER = DB * (GEN ? 2 : 1), O_SLOTS = PIECES * O_PER;  // O^T products: of a piece, all
+  static constexpr int PAIRS = 4 * PIECES;
+  // Slot of a pair of weights: spread evenly up to the first product of the last piece.
+  static constexpr int slot_of(int pair) { return pair * (S_SLOTS + O_SLOTS - O_PER) / PAIRS; }
+  static constexpr bool in_time() {  // (two slots between a piece's last weights and its first product: no hazard)
+    for (int p = 0; p < PIECES; ++p)
+      if (slot_of(4 * p + 3) + 2 > S_SLOTS + p * O_PER) return false;
+    return true;
+  }
+  static_assert(in_time(), "weights of a piece before its products");
+
+  const QFrags<MB, HD>& qf;
+  RowState<MB, HD>& st;
+  float c;
+  TileFrags<HD> f;
+  f32x16 acc[MB][KB];  // S^T of the tile
+  f32x16 s[MB][KB];    // the copy, hidden keys at -inf
+  float mx[MB], ms[MB], rs[MB][2];
+  bf16x8 q[3];
+  u32x4 hi[PIECES], lo[GEN ? PIECES : 1];  // weights, bf16: GEN their upper halves and what these leave
+
+  template <int I>  // product I of S^T
+  __device__ __forceinline__ void score() {
+    constexpr int mb = I / S_PER, r = I % S_PER, ks = r / KB, kb = r % KB, n = mb * KS + ks;
+    constexpr bool AHEAD = QFrags<MB, HD>::IN_LDS;  // fragments of Q come from LDS, two depth steps ahead
+    if constexpr (AHEAD && I == 0) {
+      q[0] = qf.get(0, 0);
+      q[1] = qf.get(0, 1);
+    }
+    if constexpr (AHEAD && kb == 0 && n + 2 < MB * KS) q[(n + 2) % 3] = qf.get((n + 2) / KS, (n + 2) % KS);
+    bf16x8 b;
+    if constexpr (AHEAD) b = q[n % 3];
+    else b = qf.get(mb, ks);
+    if constexpr (ks == 0) mfma_first<!AHEAD>(acc[mb][kb], f.k[kb][ks], b);
+    else mfma_more<!AHEAD>(acc[mb][kb], f.k[kb][ks], b);
+  }
+  template <int I>  // product I of O^T
+  __device__ __forceinline__ void output() {
+    constexpr int P = I / O_PER, r = I % O_PER, mb = P / NJ, j = P % NJ, db = GEN ? r / 2 : r;
+    mfma_more<false>(st.o[db][mb], f.v[j][db], __builtin_bit_cast(bf16x8, GEN && r % 2 == 1 ? lo[GEN ? P : 0] : hi[P]));
+  }
+  template <int N>  // pair N of weights
+  __device__ __forceinline__ void weights() {
+    constexpr int P = N / 4, W = N % 4, mb = P / NJ, j = P % NJ, r = 8 * (j & 1) + 2 * W;
+    const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[mb][j >> 1][r], c, -ms[mb]));
+    const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[mb][j >> 1][r + 1], c, -ms[mb]));
+    if constexpr (j == 0 && W < 2) rs[mb][W] = p0 + p1;
+    else rs[mb][W & 1] += p0 + p1;  // (no v_dot2 here: the dot instructions queue behind the MFMAs)
+    uint32_t w;
+    if constexpr (GEN) {
+      uint32_t rest;
+      split_pair(p0, p1, w, rest);
+      stay(rest);
+      lo[P][W] = rest;
+    } else {
+      w = pack_pair(p0, p1);
+    }
+    stay(w);
+    hi[P][W] = w;
+    if constexpr (j == NJ - 1 && W == 3) {
+      st.l[mb] += rs[mb][0] + rs[mb][1];
+      stay(st.l[mb]);
+    } else {
+      stay(rs[mb][W & 1]);
+    }
+  }
+  // Copy and maximum, eight steps a row block: steps N .. N + COUNT - 1 of them, an asm statement each (a statement that
+  // reads what the one before it wrote gets a wait state in between).
+  template <int N, int COUNT>
+  __device__ __forceinline__ void take() {
+    constexpr int mb = N / 8, op = N % 8;
+    if constexpr (KB == 1) {
+      f32x16 &d = s[mb][0], &a = acc[mb][0];
+      if constexpr (COUNT == 2) {
+        if constexpr (op == 0)
+          asm volatile(
+              "v_accvgpr_read_b32 %0, %5\n\tv_accvgpr_read_b32 %1, %6\n\tv_accvgpr_read_b32 %2, %7\n\tv_accvgpr_read_b32 %3, %8\n\t"
+              "v_max_f32 %4, %0, %1\n\tv_max3_f32 %4, %4, %2, %3"
+              : "=&v"(d[0]), "=&v"(d[1]), "=&v"(d[2]), "=&v"(d[3]), "=&v"(mx[mb])
+              : "a"(a[0]), "a"(a[1]), "a"(a[2]), "a"(a[3]));
+        else
+          asm volatile(
+              "v_accvgpr_read_b32 %0, %5\n\tv_accvgpr_read_b32 %1, %6\n\tv_accvgpr_read_b32 %2, %7\n\tv_accvgpr_read_b32 %3, %8\n\t"
+              "v_max3_f32 %4, %4, %0, %1\n\tv_max3_f32 %4, %4, %2, %3"
+              : "=&v"(d[2 * op]), "=&v"(d[2 * op + 1]), "=&v"(d[(2 * op + 2) & 15]), "=&v"(d[(2 * op + 3) & 15]), "+v"(mx[mb])
+              : "a"(a[2 * op]), "a"(a[2 * op + 1]), "a"(a[(2 * op + 2) & 15]), "a"(a[(2 * op + 3) & 15]));
+      } else if constexpr (op == 0) {
+        asm volatile("v_accvgpr_read_b32 %0, %3\n\tv_accvgpr_read_b32 %1, %4\n\tv_max_f32 %2, %0, %1"
+                     : "=&v"(d[0]), "=&v"(d[1]), "=&v"(mx[mb])
+                     : "a"(a[0]), "a"(a[1]));
+      } else {
+        asm volatile("v_accvgpr_read_b32 %0, %3\n\tv_accvgpr_read_b32 %1, %4\n\tv_max3_f32 %2, %2, %0, %1"
+                     : "=&v"(d[2 * op]), "=&v"(d[2 * op + 1]), "+v"(mx[mb])
+                     : "a"(a[2 * op]), "a"(a[2 * op + 1]));
+      }
+    } else {
+      f32x16 &d = s[mb][0], &e = s[mb][KB - 1], &a = acc[mb][0], &b = acc[mb][KB - 1];
+      if constexpr (op == 0)
+        asm volatile(
+            "v_accvgpr_read_b32 %0, %5\n\tv_accvgpr_read_b32 %1, %6\n\tv_accvgpr_read_b32 %2, %7\n\tv_accvgpr_read_b32 %3, %8\n\t"
+            "v_max_f32 %4, %0, %1\n\tv_max3_f32 %4, %4, %2, %3"
+            : "=&v"(d[0]), "=&v"(d[1]), "=&v"(e[0]), "=&v"(e[1]), "=&v"(mx[mb])
+            : "a"(a[0]), "a"(a[1]), "a"(b[0]), "a"(b[1]));
+      else
+        asm volatile(
+            "v_accvgpr_read_b32 %0, %5\n\tv_accvgpr_read_b32 %1, %6\n\tv_accvgpr_read_b32 %2, %7\n\tv_accvgpr_read_b32 %3, %8\n\t"
+            "v_max3_f32 %4, %4, %0, %1\n\tv_max3_f32 %4, %4, %2, %3"
+            : "=&v"(d[2 * op]), "=&v"(d[2 * op + 1]), "=&v"(e[2 * op]), "=&v"(e[2 * op + 1]), "+v"(mx[mb])
+            : "a"(a[2 * op]), "a"(a[2 * op + 1]), "a"(b[2 * op]), "a"(b[2 * op + 1]));
+      if constexpr (COUNT == 2) take<8 * mb + (op + 1) % 8, 1>();
+    }
+  }
+  template <int N>
+  __device__ __forceinline__ void max_step() {
+    constexpr int mb = N / 8, op = N % 8;
+    if constexpr (op == 0) mx[mb] = fmaxf(s[mb][0][0], s[mb][0][1]);
+    else mx[mb] = stream_max3(mx[mb], s[mb][0][2 * op], s[mb][0][2 * op + 1]);
+    if constexpr (KB == 2) mx[mb] = stream_max3(mx[mb], s[mb][KB - 1][2 * op], s[mb][KB - 1][2 * op + 1]);
+  }
+  template <int SLOT, int... Ns>
+  __device__ __forceinline__ void weights_of_slot(std::integer_sequence<int, Ns...>) {
+    ((slot_of(Ns) == SLOT ? weights<Ns>() : (void)0), ...);
+  }
+
+  // The first tile: S^T alone.  In either function request(0) asks for the K rows of the tile after next, once the fragments
+  // of K have all been read, and request(1) for the V rows of the next one, once those of V have.
+  template <typename Request>
+  __device__ __forceinline__ void first(Request&& request) {
+    unrolled<S_SLOTS>([&](auto slot) __attribute__((always_inline)) {
+      constexpr int I = decltype(slot)::value;
+      score<I>();
+      if constexpr (I == 1) request(Num<0>{});
+      __builtin_amdgcn_sched_barrier(0);
+    });
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) settle(acc[MB - 1][kb]);
+    unrolled<8 * MB>([&](auto n) __attribute__((always_inline)) { take<decltype(n)::value, 1>(); });
+  }
+  template <typename Request>
+  __device__ __forceinline__ void next(const char* v_lds, uint32_t voff, Request&& request) {
+    unrolled<S_SLOTS + O_SLOTS>([&](auto slot) __attribute__((always_inline)) {
+      constexpr int I = decltype(slot)::value, o = I - S_SLOTS;
+      if constexpr (I < S_SLOTS) score<I>();
+      else output<(o > 0 ? o : 0)>();
+      weights_of_slot<I>(std::make_integer_sequence<int, PAIRS>{});
+      if constexpr (I == 1) request(Num<0>{});
+      if constexpr (I >= 2 && I < 6)  // the fragments of V, in the order of their use
+        unrolled<NJ * DB / 4>([&](auto n) __attribute__((always_inline)) {
+          constexpr int F = (I >= 2 && I < 6 ? I - 2 : 0) * (NJ * DB / 4) + decltype(n)::value, j = F / DB, db = F % DB;
+          f.v[j][db] = read_v_frag<HD>(v_lds, voff, j, db);
+        });
+      if constexpr (I == 7) request(Num<1>{});
+      if constexpr (o >= 0) {
+        // row block mb's weights are all made before the products of its last piece: its copy may be overwritten
+        constexpr int mb = o / O_PER / NJ;
+        if constexpr (o / O_PER % NJ == NJ - 1) take<8 * mb + 8 / O_PER * (o % O_PER), 8 / O_PER>();
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  }
+  // accumulator r of key block kb is key 32 kb + 8*(r/4) + 4h + r%4 of the tile
+  // limit(mb): the last position that this lane's row of row block mb sees.
+  template <typename Limit>
+  __device__ __forceinline__ void mask(Limit&& limit, int lane, int cnt, int pos) {
+    const int h = lane >> 5;
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) {
-      const int lim = min(cnt - 1, limit[mb] - pos);
+      const int lim = min(cnt - 1, limit(mb) - pos) - 4 * h;
 #pragma unroll
       for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int key = 32 * kb + 8 * (r >> 2) + 4 * h + (r & 3);
-          if (key > lim) s[kb][mb][r] = -INFINITY;
-        }
+        for (int r = 0; r < 16; ++r)
+          if (32 * kb + 8 * (r >> 2) + (r & 3) > lim) s[mb][kb][r] = -INFINITY;
     }
+    unrolled<8 * MB>([&](auto n) __attribute__((always_inline)) { max_step<decltype(n)::value>(); });
   }
-
-  // row maxima; the reference maximum of a row is only raised (and O, l rescaled) when the tile outgrows
-  // it by more than the slack, so after the first tiles the multiplies on O are rare
-  float mx[MB];
-  bool grow = false;
-#pragma unroll
-  for (int mb = 0; mb < MB; ++mb) {
-    float v = s[0][mb][15];
-#pragma unroll
-    for (int kb = 0; kb < KB; ++kb) {
-      if (kb > 0) v = fmaxf(v, s[kb][mb][15]);
-#pragma unroll
-      for (int r = 1; r < 15; r += 2) v = stream_max3(v, s[kb][mb][r], s[kb][mb][r + 1]);
-      v = fmaxf(v, s[kb][mb][0]);
-    }
-    v = fmaxf(v, __shfl_xor(v, 32));
-    mx[mb] = v * c;
-    grow |= mx[mb] > st.m[mb] + STREAM_RESCALE_SLACK;
-  }
-  if (__builtin_amdgcn_ballot_w64(grow) != 0) {
+  // The reference maximum of a row is only raised (and O, l rescaled) when the tile outgrows it by more than the slack, so
+  // after the first tiles the multiplies on O are rare.  At the first tile O and l are zero and stay as they are.
+  template <bool FIRST>
+  __device__ __forceinline__ void raise() {
+    bool grow = FIRST;
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) {
-      const float mn = fmaxf(st.m[mb], mx[mb]);
-      const float mz = (mn == -INFINITY) ? 0.f : mn;  // every key so far masked: keep the arithmetic finite
-      const float alpha = __builtin_amdgcn_exp2f(st.m[mb] - mz);
-      st.m[mb] = mn;
-      st.l[mb] *= alpha;
-#pragma unroll
-      for (int db = 0; db < DB; ++db)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) st.o[db][mb][r] = scale_acc(st.o[db][mb][r], alpha);
+      const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx[mb]), __float_as_uint(mx[mb]), false, false);
+      mx[mb] = stream_max3(__uint_as_float(r[0]), __uint_as_float(r[1]), __uint_as_float(r[1])) * c;
+      if constexpr (!FIRST) grow |= mx[mb] > st.m[mb] + STREAM_RESCALE_SLACK;
     }
-  }
-
-#pragma unroll
-  for (int mb = 0; mb < MB; ++mb) {
-    const float ms = (st.m[mb] == -INFINITY) ? 0.f : st.m[mb];
-    float rs[2] = {0.f, 0.f};
-#pragma unroll
-    for (int j = 0; j < 2 * KB; ++j)
-#pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[j >> 1][mb][8 * (j & 1) + 2 * w], c, -ms));
-        const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[j >> 1][mb][8 * (j & 1) + 2 * w + 1], c, -ms));
-        rs[(j * 4 + w) & 1] += p0 + p1;  // (no v_dot2 here: the dot instructions queue behind the MFMAs)
-        if constexpr (GEN) {
-          split_pair(p0, p1, pf[mb][j], pl[mb][j], w);
-        } else {
-          pf[mb][j][2 * w] = (__bf16)p0;
-          pf[mb][j][2 * w + 1] = (__bf16)p1;
-        }
-      }
-    st.l[mb] += rs[0] + rs[1];
-  }
-
-#pragma unroll
-  for (int j = 0; j < 2 * KB; ++j)
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
+    if (FIRST || __builtin_amdgcn_ballot_w64(grow) != 0) {
 #pragma unroll
       for (int mb = 0; mb < MB; ++mb) {
-        st.o[db][mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.v[j][db], pf[mb][j], st.o[db][mb], 0, 0, 0);
-        if constexpr (GEN) st.o[db][mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.v[j][db], pl[mb][j], st.o[db][mb], 0, 0, 0);
+        const float mn = fmaxf(st.m[mb], mx[mb]);
+        const float mz = (mn == -INFINITY) ? 0.f : mn;  // every key so far masked: keep the arithmetic finite
+        const float alpha = __builtin_amdgcn_exp2f(st.m[mb] - mz);
+        st.m[mb] = mn;
+        ms[mb] = mz;
+        if constexpr (!FIRST) {
+          st.l[mb] *= alpha;
+#pragma unroll
+          for (int db = 0; db < DB; ++db) {  // (whole registers only; padded on both sides)
+            settle(st.o[db][mb]);
+            f32x16 t = st.o[db][mb];
+            t = t * alpha;
+            st.o[db][mb] = t;
+            settle(st.o[db][mb]);
+          }
+        }
       }
-}
+    }
+  }
+};
 
 // Accumulator r of depth block db is depth db*32 + 8*(r/4) + 4h + r%4: four consecutive depths per r/4.
 // ------------------------------------------------------------------------------------------------
@@ -270,8 +410,7 @@ static_assert(STREAM_LDS_BYTES <= 160 * 1024, "one workgroup per compute unit: a
 
 // One wavefront moves 1 KiB of query rows HBM -> LDS into the Q area: packed row `blk * ROWS_PER_KIB + l / CHUNKS` of
 // the unit (clamped to its last row), chunk slots swizzled as for a K tile so that read_k_frag serves as the
-// reader of Q's B-operand fragments.  Every wavefront requests all rows itself: each only depends on its own
-// requests, and the four write the same bytes.
+// reader of Q's B-operand fragments.
 template <int HD, bool GEN>
 __device__ __forceinline__ void load_q_kib(const Ctx& c, const char* q_tok0, int g, int row0, int last_row,
                                            char* q_lds, int blk, int lane) {
@@ -401,11 +540,12 @@ __global__ __launch_bounds__(256, 1) void attend_stream_kernel(BlobArg<INLINE> b
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   char* my = smem + wave * STREAM_WAVE_BYTES;
+  const uint32_t my_lds = (uint32_t)(uintptr_t)(lds_void_ptr)my;
   float* ml = (float*)(smem + STREAM_ML_OFFSET);  // [wave][row 0..95][m, l]
   char* q_lds = smem + STREAM_Q_OFFSET;
   int32_t* next_lds = (int32_t*)(smem + STREAM_NEXT_OFFSET);  // [0] unit, [4..11] its DkItem, [12..19] its DkEntry
   constexpr int KT = Tile<HD>::KT, DB = Geo<HD>::DB;
-  const uint32_t koff = k_lane_off<HD>(lane);
+  const uint32_t koff = k_lane_off<HD>(lane), voff = v_lane_off<HD>(lane);
   const bool queued = !INLINE && queue != nullptr;  // units are drawn from the queue (else: the planner's chains)
   int trace_seq = 0;
   (void)trace_seq;
@@ -417,26 +557,58 @@ __global__ __launch_bounds__(256, 1) void attend_stream_kernel(BlobArg<INLINE> b
   DkEntry e = load_desc(c.entries, it.entry);
   int g = unit % c.n_kv_heads;
   KvCursor<Geo<HD>::ROW> cur{c.segs, 0, 0, 0, 0};
-  KvTile t0, t1, t2;  // being computed, next, the one after
-  bool have0 = false, have1 = false;
+  KvTile t0, t1, t2;  // tiles t, t+1 and t+2 of a step
+  bool have0 = false, have1 = false, have2 = false;
 
-  auto issue = [&](const KvTile& t, int stage) {
-    char* kl = my + stage * STREAM_STAGE_BYTES;
-    char* vl = kl + STREAM_TILE_BYTES;
-    if (ONCE && t.once) {
+  // Where this lane finds its 16 bytes of each KiB of K or V rows: made again when a tile's row count or stride changes.
+  constexpr int BLOCKS = STREAM_TILE_BYTES / 1024;
+  uint32_t k_at[BLOCKS], v_at[BLOCKS];
+  int k_cnt = KT, v_cnt = KT;
+  uint32_t k_stride = Geo<HD>::ROW, v_stride = Geo<HD>::ROW;
+  auto aim = [&](uint32_t (&at)[BLOCKS], auto is_v) __attribute__((always_inline)) {
+    constexpr bool IS_V = decltype(is_v)::value != 0;
 #pragma unroll
-      for (int b = 0; b < 8; ++b) load_kib<false, HD, true>(t.k, t.stride, t.cnt, kl, b, lane);
-#pragma unroll
-      for (int b = 0; b < 8; ++b) load_kib<true, HD, true>(t.v, t.stride, t.cnt, vl, b, lane);
-    } else {
-#pragma unroll
-      for (int b = 0; b < 8; ++b) load_kib<false, HD>(t.k, t.stride, t.cnt, kl, b, lane);
-#pragma unroll
-      for (int b = 0; b < 8; ++b) load_kib<true, HD>(t.v, t.stride, t.cnt, vl, b, lane);
-    }
+    for (int b = 0; b < BLOCKS; ++b) at[b] = kib_biased_off<IS_V, HD>(IS_V ? v_stride : k_stride, IS_V ? v_cnt : k_cnt, b, lane);
   };
-  // this wavefront's quarter of the unit's keys: cursor, first tile requested into stage 0
-  auto open_keys = [&](const DkItem& u, const DkEntry& ue, int ug) {
+  auto aim_k = [&](const KvTile& t) {
+    if (t.cnt == k_cnt && t.stride == k_stride) return;
+    k_cnt = t.cnt;
+    k_stride = t.stride;
+    aim(k_at, Num<0>{});
+  };
+  auto aim_v = [&](const KvTile& t) {
+    if (t.cnt == v_cnt && t.stride == v_stride) return;
+    v_cnt = t.cnt;
+    v_stride = t.stride;
+    aim(v_at, Num<1>{});
+  };
+  aim(k_at, Num<0>{});
+  aim(v_at, Num<1>{});
+  auto issue_k = [&](const KvTile& t, int stage) __attribute__((always_inline)) {
+    const uint32_t lds = my_lds + (uint32_t)(stage * STREAM_STAGE_BYTES);
+    if (ONCE && t.once) load_eight_kib<true>(t.k, k_at, lds);
+    else load_eight_kib<false>(t.k, k_at, lds);
+  };
+  auto issue_v = [&](const KvTile& t, int stage) __attribute__((always_inline)) {
+    const uint32_t lds = my_lds + (uint32_t)(stage * STREAM_STAGE_BYTES + STREAM_TILE_BYTES);
+    if (ONCE && t.once) load_eight_kib<true>(t.v, v_at, lds);
+    else load_eight_kib<false>(t.v, v_at, lds);
+  };
+  auto issue = [&](const KvTile& t, int stage) {
+    aim_k(t);
+    issue_k(t, stage);
+    aim_v(t);
+    issue_v(t, stage);
+  };
+  // The unit's Q rows (this wavefront's share of them), then this wavefront's quarter of its keys: cursor, first tile
+  // requested into stage 0.
+  auto open = [&](const DkItem& u, const DkEntry& ue, int ug) {
+    const char* q_tok0 = (const char*)c.q + (int64_t)ue.tok0 * c.n_q_heads * Geo<HD>::ROW;
+    int q_lane = lane;
+    asm volatile("" : "+v"(q_lane));  // (per-lane offsets are made here, not kept in registers that the key loop needs)
+#pragma unroll
+    for (int b = 0; b < MB * 8 / Tile<HD>::KB; b += 4)
+      load_q_kib<HD, GEN>(c, q_tok0, ug, u.row0, u.row0 + u.nrows - 1, q_lds, b + wave, q_lane);
     const int ntile = (u.kv_hi - u.kv_lo + KT - 1) / KT;
     const int per = (ntile + 3) / 4 * KT;
     const int lo = min(u.kv_hi, u.kv_lo + wave * per);
@@ -445,24 +617,14 @@ __global__ __launch_bounds__(256, 1) void attend_stream_kernel(BlobArg<INLINE> b
     have0 = cur.next(c, ug, KT, t0);
     if (have0) issue(t0, 0);
   };
-  auto open_q = [&](const DkItem& u, const DkEntry& ue, int ug) {
-    const char* q_tok0 = (const char*)c.q + (int64_t)ue.tok0 * c.n_q_heads * Geo<HD>::ROW;
-#pragma unroll
-    for (int b = 0; b < MB * 32 / Geo<HD>::ROWS_PER_KIB; ++b) load_q_kib<HD, GEN>(c, q_tok0, ug, u.row0, u.row0 + u.nrows - 1, q_lds, b, lane);
-  };
   auto open_second = [&](int ug) {
     have1 = have0 && cur.next(c, ug, KT, t1);
     if (have1) issue(t1, 1);
   };
 
-  open_keys(it, e, g);
-  open_q(it, e, g);
+  open(it, e, g);
   open_second(g);
   if (wave == 0) DK_STR(0, 10);  // (kernel entry, a few scalar loads late)
-  // small append-and-attend calls: this workgroup's share of the new rows goes into the arena now, under the
-  // latency of the first unit's requests
-  scatter_new_rows<INLINE, Geo<HD>::ROW>(c);
-
   while (true) {
     // The descriptors of the next unit are fetched while this one is being streamed, so that a unit change
     // does not start with a chain of dependent memory round trips.
@@ -489,56 +651,79 @@ __global__ __launch_bounds__(256, 1) void attend_stream_kernel(BlobArg<INLINE> b
     const int min_limit = e.n + row_token<GEN>(c, it.row0);
 
     RowState<MB, HD> st;
-    int limit[MB];
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) {
       st.m[mb] = -INFINITY;
       st.l[mb] = 0.f;
 #pragma unroll
-      for (int db = 0; db < DB; ++db)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) st.o[db][mb][r] = 0.f;
-      limit[mb] = e.n + row_token<GEN>(c, min(it.row0 + mb * 32 + (lane & 31), last_row));
+      for (int db = 0; db < DB; ++db) {
+        f32x16 z = {0};
+        asm volatile("" : "+a"(z));  // born in an accumulation register tuple as a whole
+        st.o[db][mb] = z;
+      }
     }
 
-    // Everything requested before the second tile has arrived: the unit's Q rows and its first tile.
+    // This wavefront's share of Q and its first K rows have arrived (younger: the first V rows and the second tile), and
+    // everybody's share of Q.
     if (wave == 0) DK_STR(trace_seq, 0);
-    if (have1) wait_vmcnt<16>(); else wait_vmcnt<0>();
+    if (have1) wait_vmcnt<24>(); else if (have0) wait_vmcnt<8>(); else wait_vmcnt<0>();
+    lds_barrier();
     QFrags<MB, HD> qf;
     qf.q_lds = q_lds;
     qf.koff = koff;
-    qf.load();
+    if (have0) qf.load();
     if (wave == 0) DK_STR(trace_seq, 1);
 
-    // Two private stages per wavefront.  A tile's fragments are read into registers as soon as it has
-    // landed and its stage is handed to the load of the tile after next at once, so two tiles (32 KiB per
-    // wavefront) are in flight while one is being computed -- with only the other stage loading, HBM
-    // latency would not be covered.
-    int stage = 0;
-    TileFrags<HD> fr;
+    // Two private stages per wavefront, each a half for K and one for V.  Step t reads V(t-1) and at its end K(t+1); as soon
+    // as K(t) and V(t-1) have been read their places take K(t+2) and V(t+1), so 16 to 32 KiB per wavefront are in flight.
     // (wavefront 0's share of the unit is at least this many tiles: ragged segment ends only add some)
+    const auto limit = [&](int mb) { return e.n + row_token<GEN>(c, min(it.row0 + mb * 32 + (lane & 31), last_row)); };
     const int my_tiles = ((it.kv_hi - it.kv_lo + KT - 1) / KT + 3) / 4;
     const int draw_at = my_tiles / 2;
-    int iter = 0;
-    while (have0) {
-      if (have1) wait_vmcnt<16>(); else wait_vmcnt<0>();
-      const char* kl = my + stage * STREAM_STAGE_BYTES;
-      read_frags<HD>(kl, kl + STREAM_TILE_BYTES, lane, fr);
-      const bool have2 = have1 && cur.next(c, g, KT, t2);
-      if (drawer && !drew && iter >= draw_at) draw();
-      ++iter;
-      if (have2) {
-        // the stage may only be overwritten once every fragment read has returned
+    if (have0) {
+      StreamStep<MB, HD, GEN> step{qf, st, c.c};
+      int stage = 0, iter = 0;  // where tile t lives, and t
+      // end of step t: K(t+1) and V(t) have landed when only what step t requested is still out
+      auto finish = [&](const KvTile& t, auto is_first) __attribute__((always_inline)) {
+        if (have2) wait_vmcnt<16>(); else if (have1) wait_vmcnt<8>(); else wait_vmcnt<0>();
+        if (have1) read_k_frags<HD>(my + (stage ^ 1) * STREAM_STAGE_BYTES, koff, step.f);
+        if (t.cnt < KT || t.pos + KT - 1 > min_limit) step.mask(limit, lane, t.cnt, t.pos);
+        step.template raise<decltype(is_first)::value != 0>();
+      };
+      read_k_frags<HD>(my, koff, step.f);
+      have2 = have1 && cur.next(c, g, KT, t2);
+      if (have2) aim_k(t2);
+      step.first([&](auto) __attribute__((always_inline)) {
+        if (!have2) return;
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        issue(t2, stage);
+        issue_k(t2, 0);
+      });
+      finish(t0, Num<1>{});
+      while (true) {
+        const bool last = !have1;  // there is no tile t: S^T(t) comes out as something nobody reads
+        t0 = t1;
+        t1 = t2;
+        have1 = have2;
+        stage ^= 1;
+        ++iter;
+        have2 = have1 && cur.next(c, g, KT, t2);
+        if (drawer && !drew && iter >= draw_at) draw();
+        if (have2) aim_k(t2);
+        if (have1) aim_v(t1);
+        step.next(my + (stage ^ 1) * STREAM_STAGE_BYTES + STREAM_TILE_BYTES, voff, [&](auto of_v) __attribute__((always_inline)) {
+          if constexpr (decltype(of_v)::value == 0) {
+            if (!have2) return;
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            issue_k(t2, stage);
+          } else {
+            if (!have1) return;
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            issue_v(t1, stage ^ 1);
+          }
+        });
+        if (last) break;
+        finish(t0, Num<0>{});
       }
-      const bool need_mask = t0.cnt < KT || t0.pos + KT - 1 > min_limit;
-      compute_tile<MB, HD, GEN>(fr, qf, st, limit, c.c, lane, t0.cnt, t0.pos, need_mask);
-      t0 = t1;
-      t1 = t2;
-      have0 = have1;
-      have1 = have2;
-      stage ^= 1;
     }
     DK_STR(trace_seq, 2 + wave);  // each wavefront's own end of streaming
 
@@ -567,7 +752,18 @@ __global__ __launch_bounds__(256, 1) void attend_stream_kernel(BlobArg<INLINE> b
       }
     }
 
+    // small append-and-attend calls: this workgroup's share of the new rows is read now and goes into the arena after the
+    // merge, which takes as long as the reads do
+    RowCopy<INLINE, Geo<HD>::ROW> copy;
+    if constexpr (INLINE) {
+      if (next_unit < 0) copy.load(c);
+    }
+
     // ---- merge the four wavefront states ------------------------------------------------------------
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+      for (int db = 0; db < DB; ++db) settle(st.o[db][mb]);
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) {
       const float lt = st.l[mb] + __shfl_xor(st.l[mb], 32);
@@ -582,14 +778,17 @@ __global__ __launch_bounds__(256, 1) void attend_stream_kernel(BlobArg<INLINE> b
     // the four wavefronts share out the depth blocks: a whole one each (HD 128) or half of one (HD 64)
     constexpr int NACC = DB * 4;  // accumulators of a row block per wavefront after the merge
     const int db = wave * DB / 4, r0 = wave * NACC % 16;
+    int store_lane = lane;
+    asm volatile("" : "+v"(store_lane));  // (addresses of the output are made here, each time)
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) {
-      // row block mb of every wavefront's O goes through the wavefronts' second stages: [db][r][lane]
-      float* mine = (float*)(my + STREAM_STAGE_BYTES);
+      // row block mb of every wavefront's O goes through the wavefronts' second stages: [db][r / 4][lane][r % 4]
+      f32x4* mine = (f32x4*)(my + STREAM_STAGE_BYTES);
 #pragma unroll
       for (int d4 = 0; d4 < DB; ++d4)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) mine[(d4 * 16 + r) * 64 + lane] = st.o[d4][mb][r];
+        for (int i = 0; i < 4; ++i)
+          mine[(d4 * 4 + i) * 64 + lane] = f32x4{st.o[d4][mb][4 * i], st.o[d4][mb][4 * i + 1], st.o[d4][mb][4 * i + 2], st.o[d4][mb][4 * i + 3]};
       lds_barrier();
       if (mb == 0) {
         if (wave == 0) DK_STR(trace_seq, 6);
@@ -611,10 +810,7 @@ __global__ __launch_bounds__(256, 1) void attend_stream_kernel(BlobArg<INLINE> b
         next_g = next_unit % c.n_kv_heads;
         // every wavefront is past its key loop: its first stage may take the next unit's first tile, and no
         // wavefront reads the current unit's Q any more
-        if (next_unit >= 0) {
-          open_keys(next_it, next_e, next_g);  // (have0, t0, cur now belong to the next unit)
-          open_q(next_it, next_e, next_g);
-        }
+        if (next_unit >= 0) open(next_it, next_e, next_g);  // (have0, t0, cur now belong to the next unit)
       }
       const int row = mb * 32 + (lane & 31);
       float mw[4], lw[4];
@@ -634,15 +830,15 @@ __global__ __launch_bounds__(256, 1) void attend_stream_kernel(BlobArg<INLINE> b
       for (int w = 0; w < 4; ++w) {
         const float f = __builtin_amdgcn_exp2f(mw[w] - ms);
         lsum += f * lw[w];
-        const float* theirs = (const float*)(smem + w * STREAM_WAVE_BYTES + STREAM_STAGE_BYTES);
+        const f32x4* theirs = (const f32x4*)(smem + w * STREAM_WAVE_BYTES + STREAM_STAGE_BYTES);
 #pragma unroll
-        for (int r = 0; r < NACC; ++r) acc[r >> 2][r & 3] += f * theirs[(db * 16 + r0 + r) * 64 + lane];
+        for (int i = 0; i < NACC / 4; ++i) acc[i] += f * theirs[(db * 4 + r0 / 4 + i) * 64 + lane];
       }
       // the buffer has been read everywhere: the next row block, or the next unit's second tile, may overwrite it
       if (mb + 1 < MB || next_unit >= 0) lds_barrier();
       // (one row block's result at a time: the merged rows of all blocks together would not fit the registers)
       const float mm[1] = {mx}, ll[1] = {lsum};
-      store_quads<HD, GEN>(c, e, it, g, row, db * 32 + 2 * r0 + 4 * (lane >> 5), acc, lsum);
+      store_quads<HD, GEN>(c, e, it, g, row, db * 32 + 2 * r0 + 4 * (store_lane >> 5), acc, lsum);
       if (wave == 0) store_ml<1, GEN>(c, e, it, g, mb * 32, lane, mm, ll);
       if constexpr (GEN) {
         float z = 0.f;  // NaN if any of the row's sums is not finite
@@ -679,8 +875,7 @@ __global__ __launch_bounds__(256, 1) void attend_stream_kernel(BlobArg<INLINE> b
     ++trace_seq;
 #endif
     if (next_unit < 0) {
-      if (arrival_slice >= 0 && it.merge != 0)
-        merge_if_last<HD, GEN>(c, e, it, g, g_arrivals + arrival_slice * ARRIVALS_PER_SLICE, smem);
+      if constexpr (INLINE) copy.store(c);
       break;
     }
     unit = next_unit;
@@ -688,6 +883,7 @@ __global__ __launch_bounds__(256, 1) void attend_stream_kernel(BlobArg<INLINE> b
     e = next_e;
     g = next_g;
   }
+  if (arrival_slice >= 0 && it.merge != 0) merge_if_last<HD, GEN>(c, e, it, g, g_arrivals + arrival_slice * ARRIVALS_PER_SLICE, smem);
 }
 
 
