@@ -62,6 +62,7 @@ __global__ __launch_bounds__(256, 2) void attend_block_kernel(BlobArg<INLINE> bl
   typedef BlockGeo<HD> B;
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   (void)blob;
+  touch_descs<INLINE>();
   c.entries = resolve_desc<INLINE>(c.entries);
   c.segs = resolve_desc<INLINE>(c.segs);
   c.items = resolve_desc<INLINE>(c.items);

@@ -114,6 +114,7 @@ __global__ __launch_bounds__(64 * F32_WAVES, 2) void attend_f32_kernel(BlobArg<I
   constexpr int NI = G::NI, NU = G::NU;
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   (void)blob;
+  touch_descs<INLINE>();
   c.entries = resolve_desc<INLINE>(c.entries);
   c.segs = resolve_desc<INLINE>(c.segs);
   c.items = resolve_desc<INLINE>(c.items);

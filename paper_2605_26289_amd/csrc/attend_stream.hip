@@ -533,6 +533,7 @@ __global__ __launch_bounds__(256, 1) void attend_stream_kernel(BlobArg<INLINE> b
                                                                int n_chains, int32_t* queue, int n_units, int arrival_slice) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   (void)blob;
+  touch_descs<INLINE>();
   c.entries = resolve_desc<INLINE>(c.entries);
   c.segs = resolve_desc<INLINE>(c.segs);
   c.items = resolve_desc<INLINE>(c.items);

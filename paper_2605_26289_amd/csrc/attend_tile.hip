@@ -214,8 +214,8 @@ struct TileCursor {
     }
     if (p >= hi) return false;
     if (p >= seg_end) {
-      DkSeg s = load_desc(segs, si);
-      while (s.pos + s.len <= p && si + 1 < se) s = load_desc(segs, ++si);
+      DkSeg s = load_seg(segs, si);
+      while (s.pos + s.len <= p && si + 1 < se) s = load_seg(segs, ++si);
       const int32_t off = p - s.pos;
       seg_end = s.pos + s.len;
       full_end = min(seg_end, hi);
@@ -438,6 +438,7 @@ __global__ __launch_bounds__(256, 1) void attend_tile_kernel(BlobArg<INLINE> blo
                                                              int n_chains) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   (void)blob;
+  touch_descs<INLINE>();
   c.entries = resolve_desc<INLINE>(c.entries);
   c.segs = resolve_desc<INLINE>(c.segs);
   c.items = resolve_desc<INLINE>(c.items);
