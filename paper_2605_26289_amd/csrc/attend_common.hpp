@@ -109,6 +109,7 @@ struct Ctx {
   int32_t n_q_heads, n_kv_heads, gshift;
   int32_t group;    // query heads per KV head
   uint32_t gmagic;  // ceil(2^32 / group), 0 for group 1: see row_token
+  uint32_t kvmagic;  // the same of n_kv_heads: see unit_item
   int64_t arena_cells;
   const int32_t* cells;  // small append-and-attend calls: arena cell of every new token
   int32_t n_scatter;     // how many tokens this launch writes into the arena (0: none)
@@ -121,6 +122,18 @@ template <bool ANYG>
 __device__ __forceinline__ int row_token(const Ctx& c, int row) {
   if constexpr (ANYG) return c.gmagic ? (int)__umulhi((uint32_t)row, c.gmagic) : row;
   else return row >> c.gshift;
+}
+// Item of a unit, and its KV head: unit = item * n_kv_heads + head.  The rounded-up reciprocal is at most one too high
+// whatever the unit, and the remainder tells.
+__device__ __forceinline__ int unit_item(const Ctx& c, int unit, int& g) {
+  uint32_t item = c.kvmagic ? __umulhi((uint32_t)unit, c.kvmagic) : (uint32_t)unit;
+  uint32_t head = (uint32_t)unit - item * (uint32_t)c.n_kv_heads;
+  if (head >= (uint32_t)c.n_kv_heads) {
+    --item;
+    head += (uint32_t)c.n_kv_heads;
+  }
+  g = (int)head;
+  return (int)item;
 }
 template <bool ANYG>
 __device__ __forceinline__ int row_head(const Ctx& c, int row, int tok) {
@@ -660,6 +673,7 @@ inline Ctx make_ctx(const AttendArgs& a, const DkItem* items) {
   c.gshift = sh;
   c.group = group;
   c.gmagic = group > 1 ? (uint32_t)(((1ull << 32) + group - 1) / group) : 0u;
+  c.kvmagic = c.n_kv_heads > 1 ? (uint32_t)(((1ull << 32) + c.n_kv_heads - 1) / c.n_kv_heads) : 0u;
   c.arena_cells = a.arena.arena_cells;
   c.cells = a.cells;
   c.n_scatter = a.scatter ? a.total_tokens : 0;

@@ -98,10 +98,11 @@ __device__ __forceinline__ void settle(f32x16& a) { asm volatile("s_nop 15\n\ts_
 // row blocks the unit's Q fragments stay in registers for the whole unit; with three (96 registers next to 192
 // of accumulators) they would not fit, so each tile reads them from the Q area in LDS again (24 ds_read_b128 per
 // tile next to the tile's own 16: LDS bandwidth is idle here).
-template <int MB, int HD>
+template <int MB, int HD, bool SINGLE>
 struct QFrags {
   static constexpr bool IN_LDS = MB > 2;
-  bf16x8 r[IN_LDS ? 1 : MB][Geo<HD>::KS];  // (accumulation registers)
+  static constexpr bool IN_ACC = MB == 2 && !SINGLE;
+  bf16x8 r[IN_LDS ? 1 : MB][Geo<HD>::KS];
   const char* q_lds;
   uint32_t koff;
   __device__ __forceinline__ void load() {
@@ -110,10 +111,12 @@ struct QFrags {
       for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
         for (int ks = 0; ks < Geo<HD>::KS; ++ks) r[mb][ks] = read_k_frag<HD>(q_lds, koff, mb, ks);
+      if constexpr (IN_ACC) {
 #pragma unroll
-      for (int mb = 0; mb < MB; ++mb)
+        for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-        for (int ks = 0; ks < Geo<HD>::KS; ++ks) asm volatile("" : "+a"(r[mb][ks]));
+          for (int ks = 0; ks < Geo<HD>::KS; ++ks) asm volatile("" : "+a"(r[mb][ks]));
+      }
     }
   }
   __device__ __forceinline__ bf16x8 get(int mb, int ks) const {
@@ -153,8 +156,9 @@ typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 // keys in L2: one row block of 128-wide heads 2300 cycles a step with the parts one after the other, 1560 like this (its 16
 // MFMAs alone: 512); two row blocks with split weights 4100 / 2950 (48 MFMAs: 1540).  One 150-token turn on 800 cached tokens
 // 13.9 -> 11.4 us, four turns of up to 200 tokens with three query heads to a KV head 41.4 -> 33.5.
-template <int MB, int HD, bool GEN>
+template <int MB, int HD, bool GEN, bool SINGLE>
 struct StreamStep {
+  typedef QFrags<MB, HD, SINGLE> Q;
   static constexpr int KB = Tile<HD>::KB, KS = Geo<HD>::KS, DB = Geo<HD>::DB;
   static constexpr int S_PER = KS * KB, S_SLOTS = MB * S_PER;             // S^T products: of a row block (8), all
   static constexpr int NJ = 2 * KB, PIECES = MB * NJ;                     // a piece: eight weights a lane, one B operand
@@ -169,7 +173,7 @@ struct StreamStep {
   }
   static_assert(in_time(), "weights of a piece before its products");
 
-  const QFrags<MB, HD>& qf;
+  const Q& qf;
   RowState<MB, HD>& st;
   float c;
   TileFrags<HD> f;
@@ -182,7 +186,7 @@ struct StreamStep {
   template <int I>  // product I of S^T
   __device__ __forceinline__ void score() {
     constexpr int mb = I / S_PER, r = I % S_PER, ks = r / KB, kb = r % KB, n = mb * KS + ks;
-    constexpr bool AHEAD = QFrags<MB, HD>::IN_LDS;  // fragments of Q come from LDS, two depth steps ahead
+    constexpr bool AHEAD = Q::IN_LDS;  // fragments of Q come from LDS, two depth steps ahead
     if constexpr (AHEAD && I == 0) {
       q[0] = qf.get(0, 0);
       q[1] = qf.get(0, 1);
@@ -191,8 +195,8 @@ struct StreamStep {
     bf16x8 b;
     if constexpr (AHEAD) b = q[n % 3];
     else b = qf.get(mb, ks);
-    if constexpr (ks == 0) mfma_first<!AHEAD>(acc[mb][kb], f.k[kb][ks], b);
-    else mfma_more<!AHEAD>(acc[mb][kb], f.k[kb][ks], b);
+    if constexpr (ks == 0) mfma_first<Q::IN_ACC>(acc[mb][kb], f.k[kb][ks], b);
+    else mfma_more<Q::IN_ACC>(acc[mb][kb], f.k[kb][ks], b);
   }
   template <int I>  // product I of O^T
   __device__ __forceinline__ void output() {
@@ -521,25 +525,17 @@ __device__ __forceinline__ void merge_if_last(const Ctx& c, const DkEntry& e, co
   }
 }
 
-// MB = 32-row blocks per unit: 1 when no unit of the launch has more than 32 packed rows (Delta <= 32 / G:
-// decode and short verify steps then skip the all-padding blocks), 2 up to 64 rows, else 3 (up to 96 rows: between
-// 64 and 96 rows a unit is still far below the MFMA/HBM ridge, and the tile kernel, built for 256-row tiles, keeps
-// too little in flight to stream it well).
-// INLINE: the descriptors arrive inside the kernel arguments (first argument) and the descriptor pointers are byte
-// offsets into them; otherwise they point into the uploaded workspace.
-// ONCE: the launch has segments marked DkSeg::once (an instantiation of its own: the choice per tile costs the others 3-7 %).
-template <int MB, int HD, bool GEN, bool ONCE, bool INLINE>
-__global__ __launch_bounds__(256, 1) void attend_stream_kernel(BlobArg<INLINE> blob, Ctx c, const int32_t* links,
-                                                               int n_chains, int32_t* queue, int n_units, int arrival_slice) {
-  extern __shared__ __attribute__((aligned(1024))) char smem[];
-  (void)blob;
-  touch_descs<INLINE>();
-  c.entries = resolve_desc<INLINE>(c.entries);
-  c.segs = resolve_desc<INLINE>(c.segs);
-  c.items = resolve_desc<INLINE>(c.items);
-  links = resolve_desc<INLINE>(links);
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+// What a workgroup does whose units have at most MB 32-row blocks.
+// SINGLE: it has one unit and ends.  (A form of its own, because around a loop over units the compiler makes all of the
+// loop's constants first: 1230 instructions in front of the first product instead of 850.  One 150-token turn on 800 cached
+// tokens 11.5 / 10.9 us, one decoding session 12.1 / 11.4.)
+template <int MB, int HD, bool GEN, bool ONCE, bool INLINE, bool SINGLE>
+__device__ __forceinline__ void stream_units(const Ctx& c, const int32_t* links, int n_chains, int32_t* queue, int n_units,
+                                             int arrival_slice, char* smem, int unit, int g, DkItem it) {
+  int thread = threadIdx.x;
+  asm volatile("" : "+v"(thread));  // (nothing of this body is computed ahead of the branch to it)
+  const int lane = thread & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(thread >> 6);
   char* my = smem + wave * STREAM_WAVE_BYTES;
   const uint32_t my_lds = (uint32_t)(uintptr_t)(lds_void_ptr)my;
   float* ml = (float*)(smem + STREAM_ML_OFFSET);  // [wave][row 0..95][m, l]
@@ -547,16 +543,12 @@ __global__ __launch_bounds__(256, 1) void attend_stream_kernel(BlobArg<INLINE> b
   int32_t* next_lds = (int32_t*)(smem + STREAM_NEXT_OFFSET);  // [0] unit, [4..11] its DkItem, [12..19] its DkEntry
   constexpr int KT = Tile<HD>::KT, DB = Geo<HD>::DB;
   const uint32_t koff = k_lane_off<HD>(lane), voff = v_lane_off<HD>(lane);
-  const bool queued = !INLINE && queue != nullptr;  // units are drawn from the queue (else: the planner's chains)
+  const bool queued = !INLINE && !SINGLE && queue != nullptr;  // units are drawn from the queue (else: the planner's chains)
   int trace_seq = 0;
   (void)trace_seq;
 
   // ---- the unit being streamed, and the requests that open a unit ----------------------------------
-  const bool single = n_chains == 0;  // one unit per workgroup, no links
-  int unit = queued || single ? (int)blockIdx.x : load_desc(links, blockIdx.x);
-  DkItem it = load_desc(c.items, unit / c.n_kv_heads);
   DkEntry e = load_desc(c.entries, it.entry);
-  int g = unit % c.n_kv_heads;
   KvCursor<Geo<HD>::ROW> cur{c.segs, 0, 0, 0, 0};
   KvTile t0, t1, t2;  // tiles t, t+1 and t+2 of a step
   bool have0 = false, have1 = false, have2 = false;
@@ -632,10 +624,11 @@ __global__ __launch_bounds__(256, 1) void attend_stream_kernel(BlobArg<INLINE> b
     int next_unit = -1;
     DkItem next_it = it;
     DkEntry next_e = e;
-    if (!queued && !single) {
+    if (!queued && !SINGLE) {
       next_unit = load_desc(links, n_chains + unit);
-      if (next_unit >= 0) {
-        next_it = load_desc(c.items, next_unit / c.n_kv_heads);
+      if (!SINGLE && next_unit >= 0) {
+        int head;
+        next_it = load_desc(c.items, unit_item(c, next_unit, head));
         next_e = load_desc(c.entries, next_it.entry);
       }
     }
@@ -669,7 +662,7 @@ __global__ __launch_bounds__(256, 1) void attend_stream_kernel(BlobArg<INLINE> b
     if (wave == 0) DK_STR(trace_seq, 0);
     if (have1) wait_vmcnt<24>(); else if (have0) wait_vmcnt<8>(); else wait_vmcnt<0>();
     lds_barrier();
-    QFrags<MB, HD> qf;
+    QFrags<MB, HD, SINGLE> qf;
     qf.q_lds = q_lds;
     qf.koff = koff;
     if (have0) qf.load();
@@ -682,7 +675,7 @@ __global__ __launch_bounds__(256, 1) void attend_stream_kernel(BlobArg<INLINE> b
     const int my_tiles = ((it.kv_hi - it.kv_lo + KT - 1) / KT + 3) / 4;
     const int draw_at = my_tiles / 2;
     if (have0) {
-      StreamStep<MB, HD, GEN> step{qf, st, c.c};
+      StreamStep<MB, HD, GEN, SINGLE> step{qf, st, c.c};
       int stage = 0, iter = 0;  // where tile t lives, and t
       // end of step t: K(t+1) and V(t) have landed when only what step t requested is still out
       auto finish = [&](const KvTile& t, auto is_first) __attribute__((always_inline)) {
@@ -733,8 +726,9 @@ __global__ __launch_bounds__(256, 1) void attend_stream_kernel(BlobArg<INLINE> b
       if (!drew) draw();  // (a share with no tiles at all)
       const int q = __builtin_amdgcn_readfirstlane(drawn);
       next_unit = q < n_units ? q : -1;
-      if (next_unit >= 0) {
-        next_it = load_desc(c.items, next_unit / c.n_kv_heads);
+      if (!SINGLE && next_unit >= 0) {
+        int head;
+        next_it = load_desc(c.items, unit_item(c, next_unit, head));
         next_e = load_desc(c.entries, next_it.entry);
       }
       if (lane == 0) {
@@ -757,7 +751,7 @@ __global__ __launch_bounds__(256, 1) void attend_stream_kernel(BlobArg<INLINE> b
     // merge, which takes as long as the reads do
     RowCopy<INLINE, Geo<HD>::ROW> copy;
     if constexpr (INLINE) {
-      if (next_unit < 0) copy.load(c);
+      if (SINGLE || next_unit < 0) copy.load(c);
     }
 
     // ---- merge the four wavefront states ------------------------------------------------------------
@@ -808,10 +802,10 @@ __global__ __launch_bounds__(256, 1) void attend_stream_kernel(BlobArg<INLINE> b
           next_e.delta = word(15);
           next_e.tok0 = word(16);
         }
-        next_g = next_unit % c.n_kv_heads;
+        if (!SINGLE && next_unit >= 0) (void)unit_item(c, next_unit, next_g);
         // every wavefront is past its key loop: its first stage may take the next unit's first tile, and no
         // wavefront reads the current unit's Q any more
-        if (next_unit >= 0) open(next_it, next_e, next_g);  // (have0, t0, cur now belong to the next unit)
+        if (!SINGLE && next_unit >= 0) open(next_it, next_e, next_g);  // (have0, t0, cur now belong to the next unit)
       }
       const int row = mb * 32 + (lane & 31);
       float mw[4], lw[4];
@@ -836,7 +830,7 @@ __global__ __launch_bounds__(256, 1) void attend_stream_kernel(BlobArg<INLINE> b
         for (int i = 0; i < NACC / 4; ++i) acc[i] += f * theirs[(db * 4 + r0 / 4 + i) * 64 + lane];
       }
       // the buffer has been read everywhere: the next row block, or the next unit's second tile, may overwrite it
-      if (mb + 1 < MB || next_unit >= 0) lds_barrier();
+      if (mb + 1 < MB || !SINGLE && next_unit >= 0) lds_barrier();
       // (one row block's result at a time: the merged rows of all blocks together would not fit the registers)
       const float mm[1] = {mx}, ll[1] = {lsum};
       store_quads<HD, GEN>(c, e, it, g, row, db * 32 + 2 * r0 + 4 * (store_lane >> 5), acc, lsum);
@@ -869,13 +863,13 @@ __global__ __launch_bounds__(256, 1) void attend_stream_kernel(BlobArg<INLINE> b
       }
     }
     // (after the stores: the wait that opens the next unit lets exactly this request stay in flight)
-    if (next_unit >= 0) open_second(next_g);
+    if (!SINGLE && next_unit >= 0) open_second(next_g);
     if (wave == 0) DK_STR(trace_seq, 7);
 #ifdef DK_TRACE
     if (threadIdx.x == 0 && trace_seq < 8 && blockIdx.x < 256) g_strace[blockIdx.x][trace_seq][8] = (unsigned long long)(it.kv_hi - it.kv_lo);
     ++trace_seq;
 #endif
-    if (next_unit < 0) {
+    if (SINGLE || next_unit < 0) {
       if constexpr (INLINE) copy.store(c);
       break;
     }
@@ -884,35 +878,59 @@ __global__ __launch_bounds__(256, 1) void attend_stream_kernel(BlobArg<INLINE> b
     e = next_e;
     g = next_g;
   }
-  if (arrival_slice >= 0 && it.merge != 0) merge_if_last<HD, GEN>(c, e, it, g, g_arrivals + arrival_slice * ARRIVALS_PER_SLICE, smem);
+  if (SINGLE && arrival_slice >= 0 && it.merge != 0) merge_if_last<HD, GEN>(c, e, it, g, g_arrivals + arrival_slice * ARRIVALS_PER_SLICE, smem);
+}
+
+// INLINE: the descriptors arrive inside the kernel arguments (first argument) and the descriptor pointers are byte
+// offsets into them; otherwise they point into the uploaded workspace.
+// ONCE: the launch has segments marked DkSeg::once (an instantiation of its own: the choice per tile costs the others 3-7 %).
+// A workgroup's first unit has the most rows of those it walks (of a queue, the caller says how many blocks any unit has):
+// it takes the body for one, two or three 32-row blocks, so that decoding sessions, verification batches and the row tiles
+// of longer turns run side by side in one launch, each at its own price.
+template <int HD, bool GEN, bool ONCE, bool INLINE, bool SINGLE>
+__global__ __launch_bounds__(256, 1) void attend_stream_kernel(BlobArg<INLINE> blob, Ctx c, const int32_t* links, int n_chains,
+                                                               int32_t* queue, int n_units, int queue_rows, int arrival_slice) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  (void)blob;
+  touch_descs<INLINE>();
+  c.entries = resolve_desc<INLINE>(c.entries);
+  c.segs = resolve_desc<INLINE>(c.segs);
+  c.items = resolve_desc<INLINE>(c.items);
+  links = resolve_desc<INLINE>(links);
+  const bool queued = !INLINE && !SINGLE && queue != nullptr;
+  const int unit = queued || SINGLE ? (int)blockIdx.x : load_desc(links, blockIdx.x);
+  int g;
+  const DkItem it = load_desc(c.items, unit_item(c, unit, g));
+  const int rows = queued ? queue_rows : it.nrows;
+  if (rows <= 32) stream_units<1, HD, GEN, ONCE, INLINE, SINGLE>(c, links, n_chains, queue, n_units, arrival_slice, smem, unit, g, it);
+  else if (rows <= 64) stream_units<2, HD, GEN, ONCE, INLINE, SINGLE>(c, links, n_chains, queue, n_units, arrival_slice, smem, unit, g, it);
+  else stream_units<3, HD, GEN, ONCE, INLINE, SINGLE>(c, links, n_chains, queue, n_units, arrival_slice, smem, unit, g, it);
 }
 
 
 namespace {
 
-template <int MB, int HD, bool GEN, bool ONCE, bool INLINE>
-hipError_t launch_one(const BlobArg<INLINE>& blob, const Ctx& c, const int32_t* links, bool single, int32_t n_chains,
-                      int32_t* queue, int32_t n_units, int32_t slice, hipStream_t stream) {
+template <int HD, bool GEN, bool ONCE, bool INLINE, bool SINGLE>
+hipError_t launch_form(int32_t max_rows, const BlobArg<INLINE>& blob, const Ctx& c, const int32_t* links, int32_t n_chains,
+                       int32_t* queue, int32_t n_units, int32_t slice, hipStream_t stream) {
   // once per process and instantiation, whatever thread or pool gets here first
   static std::once_flag once;
   static hipError_t status = hipSuccess;
   std::call_once(once, [] {
-    status = hipFuncSetAttribute((const void*)attend_stream_kernel<MB, HD, GEN, ONCE, INLINE>,
+    status = hipFuncSetAttribute((const void*)attend_stream_kernel<HD, GEN, ONCE, INLINE, SINGLE>,
                                  hipFuncAttributeMaxDynamicSharedMemorySize, STREAM_LDS_BYTES);
   });
   if (status != hipSuccess) return status;
-  attend_stream_kernel<MB, HD, GEN, ONCE, INLINE>
-      <<<dim3((unsigned)n_chains), 256, STREAM_LDS_BYTES, stream>>>(blob, c, links, single ? 0 : n_chains, queue, n_units, slice);
+  attend_stream_kernel<HD, GEN, ONCE, INLINE, SINGLE><<<dim3((unsigned)n_chains), 256, STREAM_LDS_BYTES, stream>>>(
+      blob, c, links, n_chains, queue, n_units, max_rows, slice);
   return hipGetLastError();
 }
 
 template <int HD, bool GEN, bool ONCE, bool INLINE>
-hipError_t launch_rows(int32_t max_rows, const BlobArg<INLINE>& blob, const Ctx& c, const int32_t* links,
-                       bool single, int32_t n_chains, int32_t* queue, int32_t n_units, int32_t slice,
-                       hipStream_t stream) {
-  if (max_rows <= 32) return launch_one<1, HD, GEN, ONCE, INLINE>(blob, c, links, single, n_chains, queue, n_units, slice, stream);
-  if (max_rows <= 64) return launch_one<2, HD, GEN, ONCE, INLINE>(blob, c, links, single, n_chains, queue, n_units, slice, stream);
-  return launch_one<3, HD, GEN, ONCE, INLINE>(blob, c, links, single, n_chains, queue, n_units, slice, stream);
+hipError_t launch_one(int32_t max_rows, const BlobArg<INLINE>& blob, const Ctx& c, const int32_t* links, bool single,
+                      int32_t n_chains, int32_t* queue, int32_t n_units, int32_t slice, hipStream_t stream) {
+  return single ? launch_form<HD, GEN, ONCE, INLINE, true>(max_rows, blob, c, links, n_chains, queue, n_units, slice, stream)
+                : launch_form<HD, GEN, ONCE, INLINE, false>(max_rows, blob, c, links, n_chains, queue, n_units, slice, stream);
 }
 
 template <bool ONCE, bool INLINE>
@@ -920,9 +938,9 @@ hipError_t launch_shape(const AttendArgs& a, int32_t max_rows, const BlobArg<INL
                         const int32_t* links, bool single, int32_t n_chains, int32_t* queue, int32_t n_units,
                         hipStream_t stream) {
   const int32_t slice = a.arrival_slice;
-  if (a.arena.head_dim == 64) return launch_rows<64, true, ONCE, INLINE>(max_rows, blob, c, links, single, n_chains, queue, n_units, slice, stream);
-  if (a.general) return launch_rows<128, true, ONCE, INLINE>(max_rows, blob, c, links, single, n_chains, queue, n_units, slice, stream);
-  return launch_rows<128, false, ONCE, INLINE>(max_rows, blob, c, links, single, n_chains, queue, n_units, slice, stream);
+  if (a.arena.head_dim == 64) return launch_one<64, true, ONCE, INLINE>(max_rows, blob, c, links, single, n_chains, queue, n_units, slice, stream);
+  if (a.general) return launch_one<128, true, ONCE, INLINE>(max_rows, blob, c, links, single, n_chains, queue, n_units, slice, stream);
+  return launch_one<128, false, ONCE, INLINE>(max_rows, blob, c, links, single, n_chains, queue, n_units, slice, stream);
 }
 
 }  // namespace

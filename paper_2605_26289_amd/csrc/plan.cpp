@@ -133,6 +133,8 @@ void cut_stream_items(const std::vector<RowTile>& tiles, int32_t kv_tile, int32_
   });
 }
 
+int row_blocks(const DkItem& it) { return (it.nrows + 31) / 32; }
+
 // The streaming kernel runs one workgroup per compute unit, and a workgroup walks a chain of units
 // (item, KV head).  Its workgroups share no K/V rows, so a unit may run on any XCD.  The units arrive
 // longest first and each joins the chain that is free first (longest-processing-time rule on machines of
@@ -140,6 +142,7 @@ void cut_stream_items(const std::vector<RowTile>& tiles, int32_t kv_tile, int32_
 // idle chains the faster ones are served first, so they get the longest units), so that all compute
 // units finish together whatever the mix of context lengths.  With very many small units, runs of
 // consecutive units are handed out as one block to keep the planning time down.
+// A workgroup takes the body for as many 32-row blocks as its first unit has, so that one has the most of its chain.
 void chain_units(const std::vector<DkItem>& items, const PlanConfig& cfg, std::vector<std::pair<double, int32_t>>& heap,
                  std::vector<int32_t>& tail, std::vector<int32_t>* links, int32_t* n_chains) {
   const int64_t n_units = (int64_t)items.size() * cfg.n_kv_heads;
@@ -170,8 +173,15 @@ void chain_units(const std::vector<DkItem>& items, const PlanConfig& cfg, std::v
     for (int64_t u = u0; u < u1; ++u) {
       const DkItem& it = items[(size_t)(u / cfg.n_kv_heads)];
       cost += (int64_t)(it.kv_hi - it.kv_lo) + cfg.stream_item_cost;
-      if (tail[c] < 0) head[c] = (int32_t)u; else next[tail[c]] = (int32_t)u;
-      tail[c] = (int32_t)u;
+      if (tail[c] < 0) {
+        head[c] = tail[c] = (int32_t)u;
+      } else if (row_blocks(it) > row_blocks(items[(size_t)(head[c] / cfg.n_kv_heads)])) {
+        next[u] = head[c];
+        head[c] = (int32_t)u;
+      } else {
+        next[tail[c]] = (int32_t)u;
+        tail[c] = (int32_t)u;
+      }
     }
     f.first += (double)cost * inv_speed[c & 7];
     std::push_heap(heap.begin(), heap.end(), later);
