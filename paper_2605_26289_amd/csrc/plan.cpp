@@ -1,6 +1,7 @@
 #include "plan.hpp"
 
 #include <algorithm>
+#include <cmath>
 #include <functional>
 #include <queue>
 
@@ -34,7 +35,8 @@ PlanConfig default_config(int32_t n_q_heads, int32_t n_kv_heads, int32_t head_di
   c.arrivals = ARRIVALS_PER_SLICE;
   c.row_fixed_us = 10.f;
   c.row_step_us = 1.8f;
-  c.unit_scale = 1.f;
+  c.unit_us = {7.0f, 9.2f, 11.4f};
+  c.key_us = {0.69f, 0.96f, 1.28f};
   c.cost = {{9.3f, 11.4f, 14.6f}, {0.59f, 1.02f, 1.69f}, 3.5f, 1.4f, 6.8f, 1.72f, 3.0f, 1.4f, 1.0f, 0.08f, 0.42f, 0.04f, 5.3f};
   c.once_cells = std::max<int64_t>(1, (int64_t(256) << 20) / ((int64_t)2 * n_kv_heads * head_dim * (bf16 ? 2 : 4)));
   c.inline_blob_bytes = INLINE_BLOB_BYTES;
@@ -60,7 +62,11 @@ PlanConfig route_config(const PlanConfig& cfg, Route r, int32_t n_seqs, const in
     if (cfg.head_dim == 64) {
       c.row_fixed_us = 8.f;
       c.row_step_us = 1.4f;
-      c.unit_scale = 0.75f;
+      c.unit_us = {7.5f, 9.2f, 11.5f};
+      c.key_us = {0.5f, 0.8f, 1.1f};
+    } else {
+      c.unit_us = {8.5f, 9.7f, 13.f};
+      c.key_us = {0.76f, 1.25f, 1.65f};
     }
     c.cost = PlanCost();
     // With 64-wide heads the stream kernel's third row block is slower than the block kernel (16 sessions of 12-24 new
@@ -344,24 +350,19 @@ void cut_tile_items(AttendPlan* p, const PlanConfig& cfg) {
 // seven heads to a KV head, 20 / 16; 100 tokens on 4000, 64-wide, 23.6 / 27.8.  With 128-wide heads the block kernel is
 // priced as the tile kernel is, and the streaming kernel's general form as the other: neither has prices of its own, and
 // weighing these plans by a fit of theirs made as many batches slower as faster.)
-struct StreamShape {
-  int32_t rows = 0;   // rows per streaming tile; 0: none found
-  int32_t chunk = 0;  // keys per unit
-  double us = 0;
-};
-constexpr double kUnitFixed[4] = {0, 8.5, 9.0, 10.0};    // by row blocks of 32
-constexpr double kUnitPer128[4] = {0, 1.08, 1.45, 2.0};  // per 128 keys
 constexpr double kMergeUs = 5.0, kMergeSplitUs = 0.1;    // merge launch, and each split it reads
 constexpr double kMergeInsideUs = 3.0;                   // merge by the streaming kernel itself
 constexpr int32_t kMergeInsideRows = 8, kMergeInsideParts = 64;  // most rows, and partial rows, of such a merge
 constexpr double kKeysPerUs = 10500.0;                   // all compute units together, from HBM (5.4 TB/s)
+constexpr int32_t kMostSplits = 32;
 
-double stream_us(const PlanConfig& cfg, int32_t tile_rows, int64_t longest, int64_t chunk, int64_t unit_keys) {
-  const int mb = std::min(3, (tile_rows + 31) / 32);
-  const int64_t split = (longest + chunk - 1) / chunk;
-  const double walk = cfg.unit_scale * std::max(kUnitPer128[mb] * (double)std::min(longest, chunk) / 128.0, (double)unit_keys / kKeysPerUs);
-  const double merge = cfg.arrivals > 0 && tile_rows <= kMergeInsideRows && split * tile_rows <= kMergeInsideParts ? kMergeInsideUs : kMergeUs;
-  return kUnitFixed[mb] + walk + (split > 1 ? merge + kMergeSplitUs * (double)split : 0.0);
+// A streaming unit: a launch with it, and a piece of `keys` keys.
+double unit_us(const PlanConfig& cfg, int32_t blocks, double keys) { return cfg.unit_us[blocks - 1] + cfg.key_us[blocks - 1] * keys / 128.0; }
+
+double merge_us(const PlanConfig& cfg, int32_t tile_rows, int64_t split) {
+  if (split <= 1) return 0.0;
+  const bool inside = cfg.arrivals > 0 && tile_rows <= kMergeInsideRows && split * tile_rows <= kMergeInsideParts;
+  return (inside ? kMergeInsideUs : kMergeUs) + kMergeSplitUs * (double)split;
 }
 
 // Descriptor bytes of a plan, as build_plan lays them out (a queue's counter, never in the kernel arguments, left out).
@@ -379,45 +380,82 @@ size_t workspace_of(const PlanConfig& cfg, size_t blob_bytes, int64_t part_rows)
 }
 
 // The best way to run the whole batch through the streaming kernel with at most one unit per workgroup and at most
-// max_blob bytes of descriptors.  *largest_bytes is raised to the workspace of every such plan of any descriptor size.
-StreamShape small_shape(const AttendPlan& p, const PlanConfig& cfg, int32_t group, bool with_cells, size_t max_blob,
-                        size_t* largest_bytes) {
-  StreamShape best;
+// max_blob bytes of descriptors: every entry's row tiles get as many 32-row blocks, and its keys as many pieces, as it takes
+// for no unit to last longer than the estimate, which is made as short as the number of workgroups allows -- short tiles for
+// the entries with the most keys, wide ones for the others.  shapes[i]: of entry i.  Returns the estimate, 0 if there is none.
+double small_shapes(const AttendPlan& p, const PlanConfig& cfg, int32_t group, bool with_cells, size_t max_blob,
+                    std::vector<PlanShape>* shapes) {
   int32_t most_rows = 0;
-  int64_t longest = 0;
+  int64_t all_keys = 0;
   for (const DkEntry& e : p.entries)
     if (e.delta > 0) {
       most_rows = std::max(most_rows, group * e.delta);
-      longest = std::max<int64_t>(longest, (int64_t)e.n + e.delta);
+      all_keys += (int64_t)e.n + e.delta;  // (further tiles of the same rows find the keys in L2)
     }
-  if (most_rows == 0 || (cfg.small_rows > 0 && most_rows > cfg.small_rows)) return best;
-  static const int32_t splits[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32};
-  for (int32_t r = 32; r <= 96; r += 32) {
-    if (r > 32 && r - 32 >= most_rows) break;
-    for (const int32_t k : splits) {
-      const int64_t chunk = ((longest + k - 1) / k + cfg.kv_tile - 1) / cfg.kv_tile * cfg.kv_tile;
-      if (k > 1 && chunk < 128) break;
-      int64_t units = 0, keys = 0, merges = 0, parts = 0;
-      for (const DkEntry& e : p.entries)
-        if (e.delta > 0) {
-          const int64_t tiles = ((int64_t)group * e.delta + r - 1) / r, n = (int64_t)e.n + e.delta;
-          const int64_t split = (n + chunk - 1) / chunk;
-          units += tiles * split;
-          keys += n;  // (further tiles of the same rows find the keys in L2)
-          if (split > 1) {
-            merges += tiles;
-            parts += (int64_t)group * e.delta * split;
-          }
+  if (most_rows == 0 || (cfg.small_rows > 0 && most_rows > cfg.small_rows)) return 0.0;
+  const int64_t most_items = std::min(cfg.small_units, cfg.stream_chains) / cfg.n_kv_heads;
+  const double floor_us = cfg.unit_us[0] + (double)all_keys * cfg.n_kv_heads / kKeysPerUs;
+  const int32_t narrowest = std::min(3, (most_rows + 31) / 32);
+  shapes->resize(p.entries.size());
+  // Shapes whose units last `us` at most: the fewest units for every entry.  Returns what they come to, 0 if they are too many.
+  const auto fit = [&](double us, int32_t most_splits, std::vector<PlanShape>* out) {
+    int64_t items = 0, merges = 0;
+    double longest = 0.0, merge = 0.0;
+    for (size_t i = 0; i < p.entries.size(); ++i) {
+      const DkEntry& e = p.entries[i];
+      if (e.delta <= 0) continue;
+      const int64_t rows = (int64_t)group * e.delta;
+      const double keys = (double)e.n + e.delta;
+      PlanShape best;
+      int64_t best_units = INT64_MAX;
+      for (int32_t b = 1; b <= narrowest && (b == 1 || (b - 1) * 32 < rows); ++b) {
+        const double room = (us - cfg.unit_us[b - 1]) * 128.0 / cfg.key_us[b - 1];  // keys of a unit
+        if (room < 1.0) continue;
+        const int64_t split = std::max<int64_t>(1, (int64_t)std::ceil(keys / room));
+        if (split > most_splits || (split > 1 && keys < 128.0 * (double)split)) continue;
+        const int64_t units = (rows + 32 * b - 1) / (32 * b) * split;
+        if (units < best_units) {
+          best_units = units;
+          best.rows = 32 * b;
+          best.chunk = (int32_t)((((int64_t)e.n + e.delta + split - 1) / split + cfg.kv_tile - 1) / cfg.kv_tile * cfg.kv_tile);
         }
-      if (units * cfg.n_kv_heads > std::min(cfg.small_units, cfg.stream_chains)) break;
-      const double us = stream_us(cfg, std::min(r, most_rows), longest, chunk, keys * cfg.n_kv_heads);
-      const size_t blob = blob_size(p, with_cells, 0, 0, (size_t)units, 0, (size_t)merges);
-      *largest_bytes = std::max(*largest_bytes, workspace_of(cfg, blob, parts));
-      if (blob > max_blob) continue;
-      if (best.rows == 0 || us < best.us) best = {r, (int32_t)chunk, us};
+      }
+      if (best.rows == 0) return 0.0;
+      const int64_t split = ((int64_t)keys + best.chunk - 1) / best.chunk, tiles = (rows + best.rows - 1) / best.rows;
+      items += tiles * split;
+      merges += split > 1 ? tiles : 0;
+      if (items > most_items) return 0.0;
+      longest = std::max(longest, unit_us(cfg, best.rows / 32, std::min(keys, (double)best.chunk)));
+      merge = std::max(merge, merge_us(cfg, (int32_t)std::min<int64_t>(rows, best.rows), split));
+      (*out)[i] = best;
+    }
+    if (blob_size(p, with_cells, 0, 0, (size_t)items, 0, (size_t)merges) > max_blob) return 0.0;
+    return std::max(longest, floor_us) + merge;
+  };
+  std::vector<PlanShape> trial(p.entries.size());
+  double best_us = 0.0;
+  for (const int32_t most_splits : {1, kMostSplits}) {
+    // shortest duration that fits, to a few percent
+    double lo = cfg.unit_us[0], hi = 0.0;
+    for (const DkEntry& e : p.entries)
+      if (e.delta > 0)
+        hi = std::max(hi, unit_us(cfg, std::min<int32_t>(narrowest, (group * e.delta + 31) / 32), (double)e.n + e.delta));
+    if (most_splits > 1) hi = std::min(hi, best_us > 0.0 ? best_us : hi);
+    hi *= 1.001;
+    for (int step = 0; step < 7; ++step) {
+      const double us = step == 0 ? hi : 0.5 * (lo + hi);
+      const double got = fit(us, most_splits, &trial);
+      if (got > 0.0 && (best_us == 0.0 || got < best_us)) {
+        best_us = got;
+        shapes->swap(trial);
+        trial.resize(p.entries.size());
+      }
+      if (got > 0.0) hi = us;
+      else if (step == 0) break;
+      else lo = us;
     }
   }
-  return best;
+  return best_us;
 }
 
 // Marks the segments that the streaming kernel may read past the caches (non-temporal loads): all that no two entries
@@ -471,6 +509,12 @@ bool merges_inside(const AttendPlan& p, const PlanConfig& cfg) {
   return true;
 }
 
+bool one_tile_each(const AttendPlan& p) {  // no entry has more than one row tile
+  for (const DkItem& it : p.stream_items)
+    if (it.row0 > 0) return false;
+  return true;
+}
+
 // The same estimate for the plan that the rules for large batches made.
 double planned_us(const AttendPlan& p, const PlanConfig& cfg) {
   double us = 0;
@@ -479,14 +523,13 @@ double planned_us(const AttendPlan& p, const PlanConfig& cfg) {
     us += cfg.row_fixed_us + cfg.row_step_us * (double)load;
   }
   if (!p.stream_items.empty()) {
-    int32_t rows = 0;
-    int64_t longest = 0, keys = 0;
+    double longest = 0;
+    int64_t keys = 0;
     for (const DkItem& it : p.stream_items) {
-      rows = std::max(rows, it.nrows);
-      longest = std::max<int64_t>(longest, it.kv_hi - it.kv_lo);
+      longest = std::max(longest, unit_us(cfg, row_blocks(it), it.kv_hi - it.kv_lo));
       keys += it.kv_hi - it.kv_lo;
     }
-    us += stream_us(cfg, rows, longest, longest, keys * cfg.n_kv_heads);
+    us += std::max(longest, cfg.unit_us[0] + (double)keys * cfg.n_kv_heads / kKeysPerUs);
   }
   if (!p.merges.empty()) us += kMergeUs + 2.0;
   return us;
@@ -626,6 +669,7 @@ int32_t build_plan(Pool& pool, const PlanConfig& cfg, int32_t n_seqs, const int3
   cut_stream_items(stream_tiles, cfg.kv_tile, cfg.stream_target, cfg.stream_min_chunk, &p->stream_items, &p->merges,
                    &p->part_rows);
   p->largest_bytes = 0;
+  bool small = false;
   if (!p->scalar && cfg.small_units > 0 && (int64_t)(tile_tiles.size() + stream_tiles.size()) * cfg.n_kv_heads <= cfg.small_units) {
     // (a call whose descriptors travel in the kernel arguments goes on doing so)
     const size_t units = p->stream_items.size() * (size_t)cfg.n_kv_heads;
@@ -633,24 +677,19 @@ int32_t build_plan(Pool& pool, const PlanConfig& cfg, int32_t n_seqs, const int3
     const size_t blob = blob_size(*p, with_cells, p->tile_items.size(), p->tile_links.size(), p->stream_items.size(),
                                   units == chains ? 0 : units + chains, p->merges.size());
     p->largest_bytes = workspace_of(cfg, blob, p->part_rows);
-    const StreamShape s = small_shape(*p, cfg, group, with_cells,
-                                      blob <= (size_t)cfg.inline_blob_bytes ? (size_t)cfg.inline_blob_bytes : SIZE_MAX,
-                                      &p->largest_bytes);
-    if (s.rows > 0 && s.us < planned_us(*p, cfg)) {
+    // (no small plan has more partial rows than this, whatever its descriptors may come to)
+    const int64_t most_items = std::min(cfg.small_units, cfg.stream_chains) / cfg.n_kv_heads;
+    p->largest_bytes = std::max(p->largest_bytes, workspace_of(cfg, blob_size(*p, with_cells, 0, 0, (size_t)most_items, 0, (size_t)most_items),
+                                                               std::min(most_items * 96, p->total_tokens * group * kMostSplits)));
+    const double small_us = small_shapes(*p, cfg, group, with_cells,
+                                         blob <= (size_t)cfg.inline_blob_bytes ? (size_t)cfg.inline_blob_bytes : SIZE_MAX, &p->shapes);
+    if (small_us > 0.0 && small_us < planned_us(*p, cfg)) {
       const bool weigh = p->tile_chains > 0 && cfg.cost.row_step > 0.f;
       const double large_us = weigh ? step_us(*p, cfg, blob) : 0.0;
       const int32_t large_chains = p->tile_chains;
       const int64_t large_parts = p->part_rows;
       std::vector<RowTile>& small_tiles = p->small_tiles;
       small_tiles.clear();
-      for (int32_t ei = 0; ei < (int32_t)p->entries.size(); ++ei) {
-        const DkEntry& e = p->entries[ei];
-        const int32_t rows = group * e.delta;
-        for (int32_t r0 = 0; r0 < rows; r0 += s.rows) {
-          const int32_t nr = std::min(s.rows, rows - r0);
-          small_tiles.push_back({ei, r0, nr, e.n + (r0 + nr - 1) / group + 1});
-        }
-      }
       p->swap_spare();  // the plan made so far waits there
       p->stream_items.clear();
       p->merges.clear();
@@ -658,9 +697,18 @@ int32_t build_plan(Pool& pool, const PlanConfig& cfg, int32_t n_seqs, const int3
       p->tile_links.clear();
       p->tile_chains = 0;
       p->part_rows = 0;
-      cut_stream_items(small_tiles, cfg.kv_tile, INT32_MAX, s.chunk, &p->stream_items, &p->merges, &p->part_rows);
+      for (int32_t ei = 0; ei < (int32_t)p->entries.size(); ++ei) {
+        const DkEntry& e = p->entries[ei];
+        const int32_t rows = group * e.delta;
+        small_tiles.clear();
+        for (int32_t r0 = 0; r0 < rows; r0 += p->shapes[(size_t)ei].rows) {
+          const int32_t nr = std::min(p->shapes[(size_t)ei].rows, rows - r0);
+          small_tiles.push_back({ei, r0, nr, e.n + (r0 + nr - 1) / group + 1});
+        }
+        cut_stream_items(small_tiles, cfg.kv_tile, INT32_MAX, p->shapes[(size_t)ei].chunk, &p->stream_items, &p->merges, &p->part_rows);
+      }
       if (!weigh || step_us(*p, cfg, blob_size(*p, with_cells, 0, 0, p->stream_items.size(), 0, p->merges.size())) < large_us) {
-        std::swap(stream_tiles, small_tiles);
+        small = true;
       } else {
         p->swap_spare();
         p->tile_chains = large_chains;
@@ -669,7 +717,8 @@ int32_t build_plan(Pool& pool, const PlanConfig& cfg, int32_t n_seqs, const int3
     }
   }
   p->once = false;
-  if (!p->stream_items.empty() && stream_tiles.size() <= p->entries.size()) mark_once(p, cfg);  // one row tile per entry
+  // (one row tile per entry)
+  if (!p->stream_items.empty() && (small ? one_tile_each(*p) : stream_tiles.size() <= p->entries.size())) mark_once(p, cfg);
   for (DkMerge& m : p->merges) m.tok0 = p->entries[(size_t)m.entry].tok0;
   // Streaming units: with at least four units per workgroup they form a queue that the workgroups draw from at
   // run time (measured: +3-5 % on 700 decode slots, +1.5 % on 2048, because the compute units do not stream equally

@@ -2,6 +2,7 @@
 // segments, cuts the work into workgroup-sized items (with the key range split when there are
 // too few query rows to fill the chip) and lays the descriptors out for upload.
 #pragma once
+#include <array>
 #include <cstddef>
 #include <cstdint>
 #include <utility>
@@ -57,7 +58,8 @@ struct PlanConfig {
   int64_t join_keys = 0;  // short entries join the row-tile kernel's launch if they see at most this many keys (0: never)
   int64_t once_cells = 0;  // batches of at least this many cells are read past the caches (0: none are)
   float row_fixed_us = 0, row_step_us = 0;  // estimated cost of the row-tile kernel: a launch, and an item's 64-key step
-  float unit_scale = 0;  // cost of a streaming unit's keys against 128-wide heads
+  // estimated cost of a streaming unit, by its 32-row blocks: a launch, and 128 of its keys
+  std::array<float, 3> unit_us = {}, key_us = {};
   PlanCost cost;  // prices by which plans of a small batch are weighed against the tile kernel's (row_step 0: they are not)
   ScalarCost scalar;  // prices by which short sessions go to the scalar kernel (launch 0: they do not)
   int32_t arrivals = 0;  // counters for merges inside the streaming kernel (0: none)
@@ -82,6 +84,12 @@ struct PlanPiece {
   int32_t next;    // next piece of the same chain, -1 at the end
 };
 
+// How an entry is cut for the streaming kernel in a small batch.
+struct PlanShape {
+  int32_t rows = 0;   // rows per tile: 32, 64 or 96
+  int32_t chunk = 0;  // keys per unit
+};
+
 // A plan object may be reused from call to call: build_plan() clears it but keeps the capacity of its
 // vectors, so that planning a batch like the previous one allocates nothing.
 struct AttendPlan {
@@ -94,6 +102,7 @@ struct AttendPlan {
   std::vector<int32_t> order, chain_head, chain_tail, tile_pieces, tile_part0;
   std::vector<int64_t> chain_load;
   std::vector<int32_t> seg_table;
+  std::vector<PlanShape> shapes;
 
   std::vector<DkEntry> entries;
   std::vector<DkSeg> segs;
