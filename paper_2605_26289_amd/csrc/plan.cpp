@@ -335,21 +335,21 @@ void cut_tile_items(AttendPlan* p, const PlanConfig& cfg) {
     }
   }
 }
+
 // Small batches: what they take is latency, not bandwidth or arithmetic.  A unit of the streaming kernel costs a fixed
-// part (descriptors, first requests, merge of the four wavefronts, store) and then about a microsecond per 128 keys,
-// nearly independent of how many rows it serves -- a compute unit takes in 64 KiB of K/V per microsecond, half of what a
-// tile-kernel step of the same keys lasts -- so while every unit can have a compute unit of its own, short row tiles on
-// many compute units beat long ones on few, and a turn of a few hundred rows often runs better here than in the tile kernel,
-// which pays 9 us an item, 1.8 us per 64 keys and mostly a merge launch.  Measured, one 150-token turn of one session
-// (32 query heads on 8 KV heads, us per step, tile kernel / 32-row units): 300 cached tokens 28.7 / 18.3, 800 33.5 / 17.8,
-// 2000 36 / 24, 4000 45 / 37, 8000 51 / 66; 300 tokens on 1500: 42 / 33 (64-row units); 20 tokens on 4000: 28 / 21.
-// stream_us() has these measurements for constants, in microseconds, and the plan of least estimated time is the candidate.
-// They are of 8 KV heads, one session and keys that the caches hold; so in place of work of the tile kernel the candidate is
+// part (descriptors, first requests, merge of the four wavefronts, store) and then 0.7 us per 128 keys with 32 rows, 1.3 with
+// 96; so while every unit can have a compute unit of its own, short row tiles on many compute units beat long ones on few, and
+// a turn of a few hundred rows often runs better here than in the tile kernel, which pays 9 us an item, 1.8 us per 64 keys and
+// mostly a merge launch.  Rows and pieces are chosen entry by entry (small_shapes): a single height for the whole batch, as
+// this was planned before, gives the short entries units that the long ones lack.  Measured, 32 query heads on 8 KV heads of
+// 128 (us per step, one height and cut for all entries / entry by entry): 150 tokens on 4000 cached 39 / 26.5, on 8000
+// 43.5 / 35, three sessions of 40-80 tokens on 1000-3000 30.6 / 20.1; one token on 3000 11.4 / 11.2.
+// PlanConfig::unit_us and key_us have the kernel's measurements, in microseconds, and the plan of least estimated time is the
+// candidate.  They are of 8 KV heads and keys that the caches hold; so in place of work of the tile kernel the candidate is
 // only taken if step_us(), fitted over many shapes, has it cheaper too.  (64-wide heads and odd groups, block kernel / here:
-// 150 tokens on 800 cached 17 / 12.6 with 64-wide heads, 22 / 16 with three heads to a KV head; 9-40 tokens of two sessions,
-// seven heads to a KV head, 20 / 16; 100 tokens on 4000, 64-wide, 23.6 / 27.8.  With 128-wide heads the block kernel is
-// priced as the tile kernel is, and the streaming kernel's general form as the other: neither has prices of its own, and
-// weighing these plans by a fit of theirs made as many batches slower as faster.)
+// two turns of up to 450 tokens on 5000, 64-wide, 51.5 / 42; four of up to 370 on 3000, 16 heads on 4 of 64, 40 / 31.5;
+// twelve of up to 60 on 8000, three heads to a KV head, 77 / 63; 16 of up to 110 on 4000, six heads to one, 48 / 41.  The
+// general forms have unit and key prices of their own, but no fit of step_us().)
 constexpr double kMergeUs = 5.0, kMergeSplitUs = 0.1;    // merge launch, and each split it reads
 constexpr double kMergeInsideUs = 3.0;                   // merge by the streaming kernel itself
 constexpr int32_t kMergeInsideRows = 8, kMergeInsideParts = 64;  // most rows, and partial rows, of such a merge
