@@ -341,15 +341,41 @@ __device__ __forceinline__ void split_pair(float p0, float p1, bf16x8& hi, bf16x
   lo = __builtin_bit_cast(bf16x8, l);
 }
 
+// Partial rows that another workgroup of the same launch reads: every store goes through to the memory that all XCDs see and
+// every load comes from there (agent scope), so neither side has an L2 to write back or to invalidate.
+template <typename T>
+__device__ __forceinline__ void store_for_others(T* p, const T& x) {
+  static_assert(sizeof(T) % 8 == 0, "in pieces of 8 bytes");
+  struct Words { uint64_t w[sizeof(T) / 8]; };
+  const Words words = __builtin_bit_cast(Words, x);
+#pragma unroll
+  for (int i = 0; i < (int)(sizeof(T) / 8); ++i)
+    __hip_atomic_store((uint64_t*)p + i, words.w[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ __forceinline__ T load_of_others(const T* p) {
+  static_assert(sizeof(T) % 8 == 0, "in pieces of 8 bytes");
+  struct Words { uint64_t w[sizeof(T) / 8]; } words;
+#pragma unroll
+  for (int i = 0; i < (int)(sizeof(T) / 8); ++i)
+    words.w[i] = __hip_atomic_load((uint64_t*)p + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return __builtin_bit_cast(T, words);
+}
+
 // Stores one row's results of a lane: quad i holds depths depth0 + 8 i .. + 3 (the order of the 32x32 accumulators,
 // depth0 including the half-wave's 4 h), as fp32 partials or, divided by the weight sum, as bf16 output.
 // rl: the row inside the item (rows past its end are skipped).
 template <int HD, bool ANYG, int NQ>
 __device__ __forceinline__ void store_quads(const Ctx& c, const DkEntry& e, const DkItem& it, int g, int rl, int depth0,
-                                            const f32x4 (&o)[NQ], float ltot) {
+                                            const f32x4 (&o)[NQ], float ltot, bool for_others = false) {
   if (rl >= it.nrows) return;
   if (it.part_row0 >= 0) {
     float* p = c.parts + ((int64_t)(it.part_row0 + rl) * c.n_kv_heads + g) * HD + depth0;
+    if (for_others) {
+#pragma unroll
+      for (int i = 0; i < NQ; ++i) store_for_others((f32x4*)(p + 8 * i), o[i]);
+      return;
+    }
 #pragma unroll
     for (int i = 0; i < NQ; ++i) *(f32x4*)(p + 8 * i) = o[i];
   } else {
@@ -554,7 +580,7 @@ __device__ __forceinline__ void redo_rows(const Ctx& c, const DkEntry& e, const 
     const int depth = 32 * db + 8 * i + 4 * h;
     if (!mine || !owns(depth)) continue;
     if (it.part_row0 >= 0) {
-      *(f32x4*)(c.parts + ((int64_t)(it.part_row0 + rl0 + col) * c.n_kv_heads + g) * HD + depth) = x;
+      store_for_others((f32x4*)(c.parts + ((int64_t)(it.part_row0 + rl0 + col) * c.n_kv_heads + g) * HD + depth), x);
     } else {
       bf16x4 y;
 #pragma unroll
@@ -567,7 +593,7 @@ __device__ __forceinline__ void redo_rows(const Ctx& c, const DkEntry& e, const 
 // Running maximum and weight sum of each row (partials) or the row's log-sum-exp (final output).
 template <int MB, bool ANYG = false>
 __device__ __forceinline__ void store_ml(const Ctx& c, const DkEntry& e, const DkItem& it, int g, int row_local0,
-                                         int lane, const float (&m)[MB], const float (&ltot)[MB]) {
+                                         int lane, const float (&m)[MB], const float (&ltot)[MB], bool for_others = false) {
   if (lane >= 32) return;
 #pragma unroll
   for (int mb = 0; mb < MB; ++mb) {
@@ -575,7 +601,9 @@ __device__ __forceinline__ void store_ml(const Ctx& c, const DkEntry& e, const D
     if (rl >= it.nrows) continue;
     if (it.part_row0 >= 0) {
       float* p = c.parts_ml + ((int64_t)(it.part_row0 + rl) * c.n_kv_heads + g) * 2;
-      *(float2*)p = make_float2(m[mb], ltot[mb]);
+      const float2 ml = make_float2(m[mb], ltot[mb]);
+      if (for_others) store_for_others((float2*)p, ml);
+      else *(float2*)p = ml;
     } else if (c.lse) {
       const int row = it.row0 + rl;
       const int t = row_token<ANYG>(c, row);
