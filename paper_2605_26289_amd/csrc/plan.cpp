@@ -350,10 +350,14 @@ void cut_tile_items(AttendPlan* p, const PlanConfig& cfg) {
 // two turns of up to 450 tokens on 5000, 64-wide, 51.5 / 42; four of up to 370 on 3000, 16 heads on 4 of 64, 40 / 31.5;
 // twelve of up to 60 on 8000, three heads to a KV head, 77 / 63; 16 of up to 110 on 4000, six heads to one, 48 / 41.  The
 // general forms have unit and key prices of their own, but no fit of step_us().)
-constexpr double kMergeUs = 5.0, kMergeSplitUs = 0.1;    // merge launch, and each split it reads
-constexpr double kMergeInsideUs = 3.0;                   // merge by the streaming kernel itself
+constexpr double kMergeUs = 4.0, kMergeRoundUs = 1.2;           // merge launch, and each round of eight splits that it reads
+constexpr double kMergeInsideUs = 2.0, kMergeInsideSplitUs = 0.05;  // merge by the streaming kernel itself
 constexpr int32_t kMergeInsideRows = 8, kMergeInsideParts = 64;  // most rows, and partial rows, of such a merge
-constexpr double kKeysPerUs = 10500.0;                   // all compute units together, from HBM (5.4 TB/s)
+// All compute units together: 8.7 TB/s with 128-wide heads, which is what the Infinity Cache and HBM give between them on
+// batches of this size.  With the rate of HBM alone the planner left compute units idle that a batch could have used (us per
+// step, at 10500 / 17000: one token on 8000 13.5 / 11.6, on 16000 19.2 / 16.5, three sessions of 7000-20000 38 / 36, four of
+// 2000 13.8 / 11.2, six of 9000-20000 103 / 67, three of 2500-18000 with 64-wide heads 26.2 / 18.7).
+constexpr double kKeysPerUs = 17000.0;
 constexpr int32_t kMostSplits = 32;
 
 // A streaming unit: a launch with it, and a piece of `keys` keys.
@@ -362,7 +366,7 @@ double unit_us(const PlanConfig& cfg, int32_t blocks, double keys) { return cfg.
 double merge_us(const PlanConfig& cfg, int32_t tile_rows, int64_t split) {
   if (split <= 1) return 0.0;
   const bool inside = cfg.arrivals > 0 && tile_rows <= kMergeInsideRows && split * tile_rows <= kMergeInsideParts;
-  return (inside ? kMergeInsideUs : kMergeUs) + kMergeSplitUs * (double)split;
+  return inside ? kMergeInsideUs + kMergeInsideSplitUs * (double)split : kMergeUs + kMergeRoundUs * (double)((split + 7) / 8);
 }
 
 // Descriptor bytes of a plan, as build_plan lays them out (a queue's counter, never in the kernel arguments, left out).
@@ -529,10 +533,14 @@ double planned_us(const AttendPlan& p, const PlanConfig& cfg) {
       longest = std::max(longest, unit_us(cfg, row_blocks(it), it.kv_hi - it.kv_lo));
       keys += it.kv_hi - it.kv_lo;
     }
+    const int64_t units = (int64_t)p.stream_items.size() * cfg.n_kv_heads, chains = std::max(cfg.stream_chains, 1);
+    longest *= (double)((units + chains - 1) / chains);  // (one after the other where the workgroups are fewer)
     us += std::max(longest, cfg.unit_us[0] + (double)keys * cfg.n_kv_heads / kKeysPerUs);
   }
-  if (!p.merges.empty()) us += kMergeUs + 2.0;
-  return us;
+  double merge = p.merges.empty() || p.tile_chains == 0 ? 0.0 : 7.0;
+  if (p.tile_chains == 0)
+    for (const DkMerge& m : p.merges) merge = std::max(merge, merge_us(cfg, m.nrows, m.nsplit));
+  return us + merge;
 }
 
 // What a step of the plan's work items takes, with `blob` bytes of descriptors, by prices fitted to 2081 measured steps: 1 to
