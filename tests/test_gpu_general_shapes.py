@@ -94,6 +94,30 @@ def test_general_kernels_walk_chains_and_queues(hq, hkv, d):
     m.pool.close()
 
 
+@pytest.mark.parametrize("hq,hkv,d", [(8, 2, 64), (12, 4, 128)])
+@pytest.mark.parametrize("sign", [1.0, -1.0])
+def test_scores_whose_partial_sums_over_depth_cancel(hq, hkv, d, sign):
+    """The last 16 channels take back what the 16 before them give (24 x 24 x 16, exact in fp32): a score read before its last
+    product has arrived is off by a thousand log2 units, and a row's reference maximum with it, upwards or downwards."""
+    sh = wl.Shape(hq, hkv, d, "bf16")
+    delta, n = 150, 800
+    m = Mirror(sh, 1, n + delta + 512, granule=32, seed=d)
+    s = m.acquire()
+    k, v = m.draw(n, hkv), m.draw(n, hkv)
+    q, kn, vn = m.draw(delta, hq), m.draw(delta, hkv), m.draw(delta, hkv)
+    for x in (k, kn):
+        x[..., d - 32:] = 24.0
+    q[..., d - 32:d - 16], q[..., d - 16:] = sign * 24.0, sign * -24.0
+    m.append([s], [n], k, v)
+    dk.set_tuning(m.pool.handle, "small_units", 0)  # (the block kernel)
+    out = m.pool.attend([s], [0, delta], to_dev(q, "bf16"), sh.scale, to_dev(kn, "bf16"), to_dev(vn, "bf16"))
+    plan = dk.last_plan(m.pool.handle)
+    assert plan["route"] == "general" and plan["stream_items"] == 0 and plan["row_items"] > 0, plan
+    ref, _ = oracle.delta_attend(q, k, v, kn, vn, sh.scale)
+    _check(out, ref, max(np.abs(v).max(), np.abs(vn).max()), sign)
+    m.pool.close()
+
+
 # descriptors: in the kernel arguments of either kernel, only of the scalar one (in one mode, in both), of neither
 @pytest.mark.parametrize("hq,hkv,d,dtype,sessions,scalar", [
     (32, 8, 64, "bf16", 24, ()), (32, 8, 64, "bf16", 32, ("staged",)), (32, 8, 64, "bf16", 40, ("staged", "fused", "appended")),
