@@ -360,8 +360,39 @@ constexpr int32_t kMergeInsideRows = 8, kMergeInsideParts = 64;  // most rows, a
 constexpr double kKeysPerUs = 17000.0;
 constexpr int32_t kMostSplits = 32;
 
+// Batches of more K/V than the Infinity Cache holds (AttendPlan::once) come from HBM, and the units share what it gives: one
+// alone takes 1.3 us for 64 KiB, so that half of the compute units do not reach HBM's rate, and a unit that is longer than the
+// others goes on at its own pace when they have ended.  With the estimate above such batches were cut too little or too much
+// (13 sessions of up to 27000 tokens, not cut because HBM seemed the limit, 264 us, 193 in 36 items; six sessions of up to
+// 40000, 22 / 33 items, 139 / 183).  A further row tile of an entry costs little by itself -- its reads follow the first one's
+// -- but the non-temporal loads are lost with it, and chains of two units end later than their lengths say.  Fitted to 189
+// plans of 63 batches (4 to 30 sessions, 256-1500 MB, 1 to 32 new tokens, 64- and 128-wide heads, groups of three and four;
+// 7 % off, root mean square, where the estimate above is 21 % off), of which it picks one 0.5 % slower than the best of three,
+// on average.
+constexpr double kHbmBytesPerUs = 6.5e6, kHbmUnitBytesPerUs = 65536 / 1.3, kReadAgain = 0.1, kReadCached = 1.1, kChained = 1.1;
+
 // A streaming unit: a launch with it, and a piece of `keys` keys.
-double unit_us(const PlanConfig& cfg, int32_t blocks, double keys) { return cfg.unit_us[blocks - 1] + cfg.key_us[blocks - 1] * keys / 128.0; }
+double key_us(const PlanConfig& cfg, bool hbm, int32_t blocks) {
+  const double us = cfg.key_us[blocks - 1];
+  return hbm ? std::max(us, 128.0 * 4.0 * cfg.head_dim / kHbmUnitBytesPerUs) : us;
+}
+double unit_us(const PlanConfig& cfg, bool hbm, int32_t blocks, double keys) {
+  return cfg.unit_us[blocks - 1] + key_us(cfg, hbm, blocks) * keys / 128.0;
+}
+
+// How long units take that read from HBM side by side: while they ask for more than it gives, all are slowed down alike.
+double shared_us(const PlanConfig& cfg, bool cached, std::vector<PlanLoad>* loads) {
+  std::sort(loads->begin(), loads->end(), [](const PlanLoad& a, const PlanLoad& b) { return a.us < b.us; });
+  const double rate = kHbmBytesPerUs / (4.0 * cfg.head_dim * cfg.n_kv_heads) / (cached ? kReadCached : 1.0);
+  double demand = 0.0, us = 0.0, own = 0.0;
+  for (const PlanLoad& l : *loads) demand += l.keys / l.us;
+  for (const PlanLoad& l : *loads) {
+    us += (l.us - own) * std::max(1.0, demand / rate);
+    own = l.us;
+    demand -= l.keys / l.us;
+  }
+  return us;
+}
 
 double merge_us(const PlanConfig& cfg, int32_t tile_rows, int64_t split) {
   if (split <= 1) return 0.0;
@@ -387,14 +418,14 @@ size_t workspace_of(const PlanConfig& cfg, size_t blob_bytes, int64_t part_rows)
 // max_blob bytes of descriptors: every entry's row tiles get as many 32-row blocks, and its keys as many pieces, as it takes
 // for no unit to last longer than the estimate, which is made as short as the number of workgroups allows -- short tiles for
 // the entries with the most keys, wide ones for the others.  shapes[i]: of entry i.  Returns the estimate, 0 if there is none.
-double small_shapes(const AttendPlan& p, const PlanConfig& cfg, int32_t group, bool with_cells, size_t max_blob,
-                    std::vector<PlanShape>* shapes) {
+double small_shapes(AttendPlan& p, const PlanConfig& cfg, int32_t group, bool with_cells, size_t max_blob) {
+  std::vector<PlanShape>* shapes = &p.shapes;
   int32_t most_rows = 0;
   int64_t all_keys = 0;
   for (const DkEntry& e : p.entries)
     if (e.delta > 0) {
       most_rows = std::max(most_rows, group * e.delta);
-      all_keys += (int64_t)e.n + e.delta;  // (further tiles of the same rows find the keys in L2)
+      all_keys += (int64_t)e.n + e.delta;
     }
   if (most_rows == 0 || (cfg.small_rows > 0 && most_rows > cfg.small_rows)) return 0.0;
   const int64_t most_items = std::min(cfg.small_units, cfg.stream_chains) / cfg.n_kv_heads;
@@ -405,6 +436,8 @@ double small_shapes(const AttendPlan& p, const PlanConfig& cfg, int32_t group, b
   const auto fit = [&](double us, int32_t most_splits, std::vector<PlanShape>* out) {
     int64_t items = 0, merges = 0;
     double longest = 0.0, merge = 0.0;
+    bool several = false;
+    p.loads.clear();
     for (size_t i = 0; i < p.entries.size(); ++i) {
       const DkEntry& e = p.entries[i];
       if (e.delta <= 0) continue;
@@ -413,12 +446,12 @@ double small_shapes(const AttendPlan& p, const PlanConfig& cfg, int32_t group, b
       PlanShape best;
       int64_t best_units = INT64_MAX;
       for (int32_t b = 1; b <= narrowest && (b == 1 || (b - 1) * 32 < rows); ++b) {
-        const double room = (us - cfg.unit_us[b - 1]) * 128.0 / cfg.key_us[b - 1];  // keys of a unit
+        const double room = (us - cfg.unit_us[b - 1]) * 128.0 / key_us(cfg, p.once, b);  // keys of a unit
         if (room < 1.0) continue;
         const int64_t split = std::max<int64_t>(1, (int64_t)std::ceil(keys / room));
         if (split > most_splits || (split > 1 && keys < 128.0 * (double)split)) continue;
         const int64_t units = (rows + 32 * b - 1) / (32 * b) * split;
-        if (units < best_units) {
+        if (units < best_units || (p.once && units == best_units)) {  // (rather one row tile in two pieces than two tiles)
           best_units = units;
           best.rows = 32 * b;
           best.chunk = (int32_t)((((int64_t)e.n + e.delta + split - 1) / split + cfg.kv_tile - 1) / cfg.kv_tile * cfg.kv_tile);
@@ -429,12 +462,15 @@ double small_shapes(const AttendPlan& p, const PlanConfig& cfg, int32_t group, b
       items += tiles * split;
       merges += split > 1 ? tiles : 0;
       if (items > most_items) return 0.0;
-      longest = std::max(longest, unit_us(cfg, best.rows / 32, std::min(keys, (double)best.chunk)));
+      const double alone = unit_us(cfg, p.once, best.rows / 32, std::min(keys, (double)best.chunk));
+      longest = std::max(longest, alone);
+      several = several || tiles > 1;
+      if (p.once) p.loads.push_back({alone, keys * (1.0 + kReadAgain * (double)(tiles - 1))});
       merge = std::max(merge, merge_us(cfg, (int32_t)std::min<int64_t>(rows, best.rows), split));
       (*out)[i] = best;
     }
     if (blob_size(p, with_cells, 0, 0, (size_t)items, 0, (size_t)merges) > max_blob) return 0.0;
-    return std::max(longest, floor_us) + merge;
+    return (p.once ? shared_us(cfg, several, &p.loads) : std::max(longest, floor_us)) + merge;
   };
   std::vector<PlanShape> trial(p.entries.size());
   double best_us = 0.0;
@@ -443,7 +479,7 @@ double small_shapes(const AttendPlan& p, const PlanConfig& cfg, int32_t group, b
     double lo = cfg.unit_us[0], hi = 0.0;
     for (const DkEntry& e : p.entries)
       if (e.delta > 0)
-        hi = std::max(hi, unit_us(cfg, std::min<int32_t>(narrowest, (group * e.delta + 31) / 32), (double)e.n + e.delta));
+        hi = std::max(hi, unit_us(cfg, p.once, std::min<int32_t>(narrowest, (group * e.delta + 31) / 32), (double)e.n + e.delta));
     if (most_splits > 1) hi = std::min(hi, best_us > 0.0 ? best_us : hi);
     hi *= 1.001;
     for (int step = 0; step < 7; ++step) {
@@ -460,6 +496,11 @@ double small_shapes(const AttendPlan& p, const PlanConfig& cfg, int32_t group, b
     }
   }
   return best_us;
+}
+
+void unmark_once(AttendPlan* p) {
+  for (DkSeg& s : p->segs) s.once = 0;
+  p->once = false;
 }
 
 // Marks the segments that the streaming kernel may read past the caches (non-temporal loads): all that no two entries
@@ -494,10 +535,8 @@ void mark_once(AttendPlan* p, const PlanConfig& cfg) {
     s.once = other.once = 0;
     if (s.len > other.len) table[at] = i;
   }
-  if (cells < cfg.once_cells)
-    for (DkSeg& s : p->segs) s.once = 0;
-  else
-    p->once = true;
+  p->once = true;
+  if (cells < cfg.once_cells) unmark_once(p);
 }
 
 // Merging inside the streaming kernel: nothing else has split rows, every workgroup has one unit, every (row tile, KV
@@ -520,22 +559,41 @@ bool one_tile_each(const AttendPlan& p) {  // no entry has more than one row til
 }
 
 // The same estimate for the plan that the rules for large batches made.
-double planned_us(const AttendPlan& p, const PlanConfig& cfg) {
+double planned_us(AttendPlan& p, const PlanConfig& cfg) {
   double us = 0;
   if (p.tile_chains > 0) {
     const int64_t load = *std::max_element(p.chain_load.begin(), p.chain_load.end());
     us += cfg.row_fixed_us + cfg.row_step_us * (double)load;
   }
   if (!p.stream_items.empty()) {
-    double longest = 0;
-    int64_t keys = 0;
-    for (const DkItem& it : p.stream_items) {
-      longest = std::max(longest, unit_us(cfg, row_blocks(it), it.kv_hi - it.kv_lo));
-      keys += it.kv_hi - it.kv_lo;
-    }
     const int64_t units = (int64_t)p.stream_items.size() * cfg.n_kv_heads, chains = std::max(cfg.stream_chains, 1);
-    longest *= (double)((units + chains - 1) / chains);  // (one after the other where the workgroups are fewer)
-    us += std::max(longest, cfg.unit_us[0] + (double)keys * cfg.n_kv_heads / kKeysPerUs);
+    if (p.once) {
+      // the items of one KV head on its share of the workgroups, longest first, each where most room is (one row tile to an entry)
+      const size_t room = (size_t)std::max<int64_t>(1, chains / cfg.n_kv_heads);
+      const auto later = [](const PlanLoad& a, const PlanLoad& b) { return a.us > b.us; };
+      p.loads.clear();
+      for (const DkItem& it : p.stream_items) {
+        const PlanLoad l{unit_us(cfg, true, row_blocks(it), it.kv_hi - it.kv_lo), (double)(it.kv_hi - it.kv_lo)};
+        if (p.loads.size() < room) {
+          p.loads.push_back(l);
+        } else {
+          std::pop_heap(p.loads.begin(), p.loads.end(), later);
+          p.loads.back().us += l.us;
+          p.loads.back().keys += l.keys;
+        }
+        std::push_heap(p.loads.begin(), p.loads.end(), later);
+      }
+      us += shared_us(cfg, false, &p.loads) * (units > chains ? kChained : 1.0);
+    } else {
+      double longest = 0;
+      int64_t keys = 0;
+      for (const DkItem& it : p.stream_items) {
+        longest = std::max(longest, unit_us(cfg, false, row_blocks(it), it.kv_hi - it.kv_lo));
+        keys += it.kv_hi - it.kv_lo;
+      }
+      longest *= (double)((units + chains - 1) / chains);  // (one after the other where the workgroups are fewer)
+      us += std::max(longest, cfg.unit_us[0] + (double)keys * cfg.n_kv_heads / kKeysPerUs) * (units > chains ? kChained : 1.0);
+    }
   }
   double merge = p.merges.empty() || p.tile_chains == 0 ? 0.0 : 7.0;
   if (p.tile_chains == 0)
@@ -678,7 +736,10 @@ int32_t build_plan(Pool& pool, const PlanConfig& cfg, int32_t n_seqs, const int3
                    &p->part_rows);
   p->largest_bytes = 0;
   bool small = false;
-  if (!p->scalar && cfg.small_units > 0 && (int64_t)(tile_tiles.size() + stream_tiles.size()) * cfg.n_kv_heads <= cfg.small_units) {
+  const bool may_be_small = !p->scalar && cfg.small_units > 0 && (int64_t)(tile_tiles.size() + stream_tiles.size()) * cfg.n_kv_heads <= cfg.small_units;
+  p->once = false;
+  if (may_be_small || !p->stream_items.empty()) mark_once(p, cfg);
+  if (may_be_small) {
     // (a call whose descriptors travel in the kernel arguments goes on doing so)
     const size_t units = p->stream_items.size() * (size_t)cfg.n_kv_heads;
     const size_t chains = std::min(units, (size_t)std::max(cfg.stream_chains, 1));
@@ -690,9 +751,12 @@ int32_t build_plan(Pool& pool, const PlanConfig& cfg, int32_t n_seqs, const int3
     p->largest_bytes = std::max(p->largest_bytes, workspace_of(cfg, blob_size(*p, with_cells, 0, 0, (size_t)most_items, 0, (size_t)most_items),
                                                                std::min(most_items * 96, p->total_tokens * group * kMostSplits)));
     const double small_us = small_shapes(*p, cfg, group, with_cells,
-                                         blob <= (size_t)cfg.inline_blob_bytes ? (size_t)cfg.inline_blob_bytes : SIZE_MAX, &p->shapes);
-    if (small_us > 0.0 && small_us < planned_us(*p, cfg)) {
-      const bool weigh = p->tile_chains > 0 && cfg.cost.row_step > 0.f;
+                                         blob <= (size_t)cfg.inline_blob_bytes ? (size_t)cfg.inline_blob_bytes : SIZE_MAX);
+    // (step_us() knows no HBM; its place is taken by a margin there: of 56 such batches with work of the tile kernel the 17 that
+    // it lets through are 1.06 to 1.4 times faster, and of the seven that it keeps back three would be 5 to 11 % slower)
+    const bool margin = p->once && p->tile_chains > 0;
+    if (small_us > 0.0 && small_us * (margin ? 1.2 : 1.0) < planned_us(*p, cfg)) {
+      const bool weigh = !margin && p->tile_chains > 0 && cfg.cost.row_step > 0.f;
       const double large_us = weigh ? step_us(*p, cfg, blob) : 0.0;
       const int32_t large_chains = p->tile_chains;
       const int64_t large_parts = p->part_rows;
@@ -724,9 +788,8 @@ int32_t build_plan(Pool& pool, const PlanConfig& cfg, int32_t n_seqs, const int3
       }
     }
   }
-  p->once = false;
-  // (one row tile per entry)
-  if (!p->stream_items.empty() && (small ? one_tile_each(*p) : stream_tiles.size() <= p->entries.size())) mark_once(p, cfg);
+  // (marked for one row tile per entry: nothing else reads the keys)
+  if (p->once && (p->stream_items.empty() || (small && !one_tile_each(*p)))) unmark_once(p);
   for (DkMerge& m : p->merges) m.tok0 = p->entries[(size_t)m.entry].tok0;
   // Streaming units: with at least four units per workgroup they form a queue that the workgroups draw from at
   // run time (measured: +3-5 % on 700 decode slots, +1.5 % on 2048, because the compute units do not stream equally

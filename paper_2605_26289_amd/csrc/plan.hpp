@@ -90,6 +90,11 @@ struct PlanShape {
   int32_t chunk = 0;  // keys per unit
 };
 
+// Streaming units side by side: how long one takes alone, and the keys that all of the kind read.
+struct PlanLoad {
+  double us, keys;
+};
+
 // A plan object may be reused from call to call: build_plan() clears it but keeps the capacity of its
 // vectors, so that planning a batch like the previous one allocates nothing.
 struct AttendPlan {
@@ -103,6 +108,7 @@ struct AttendPlan {
   std::vector<int64_t> chain_load;
   std::vector<int32_t> seg_table;
   std::vector<PlanShape> shapes;
+  std::vector<PlanLoad> loads;
 
   std::vector<DkEntry> entries;
   std::vector<DkSeg> segs;

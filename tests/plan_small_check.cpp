@@ -98,9 +98,50 @@ static void check_short_sessions() {
   CHECK(scalar[1] > 40 && matrix[1] > 40 && matrix[0] > 40);
 }
 
+// Batches of more K/V than the caches hold are bound by the memory: a second row tile of an entry would read its keys again, and
+// past no cache.  So nearly every entry that fits one row tile gets one, cut into pieces where the chip has room for them.
+static void check_large_histories() {
+  std::mt19937 rng(13);
+  auto uni = [&](int lo, int hi) { return lo + (int)(rng() % (unsigned)(hi - lo + 1)); };
+  const Shape shapes[] = {{32, 8, 128, true, dk::Route::kTile}, {8, 2, 128, true, dk::Route::kTile}, {24, 8, 128, true, dk::Route::kGeneral}};
+  int seen = 0, several = 0, cached = 0;
+  for (int rep = 0; rep < 1500; ++rep) {
+    const Shape& sh = shapes[rep % 3];
+    const int group = sh.hq / sh.hkv, nseq = uni(6, 30), most = 96 / group, delta = uni(1, most);
+    const int64_t cells = ((int64_t)300 << 20) / (sh.hkv * 512);
+    const int lo = (int)(cells / nseq), hi = uni(lo, 4 * lo);
+    std::vector<int32_t> slots(nseq), cu(nseq + 1, 0);
+    std::vector<int> n(nseq);
+    for (int& x : n) x = uni(lo, hi);
+    dk::Pool pool(nseq, 0, (int64_t)nseq * (hi + 1024), 256);
+    for (int b = 0; b < nseq; ++b) {
+      CHECK(pool.acquire(0, 0, &slots[b]) == dk::OK);
+      const int32_t c2[2] = {0, n[b]};
+      std::vector<int64_t> dst;
+      CHECK(pool.append(1, &slots[b], c2, nullptr, &dst) == dk::OK);
+      cu[b + 1] = cu[b] + delta;
+    }
+    const dk::PlanConfig cfg = dk::route_config(dk::default_config(sh.hq, sh.hkv, sh.d, sh.bf16), sh.route, nseq, cu.data());
+    dk::AttendPlan p;
+    {
+      std::lock_guard<std::mutex> g(pool.mutex());
+      CHECK(dk::build_plan(pool, cfg, nseq, slots.data(), cu.data(), true, &p) == dk::OK);
+    }
+    CHECK(p.tile_items.empty());
+    ++seen;
+    cached += !p.once;
+    bool one = true;
+    for (const DkItem& it : p.stream_items) one = one && it.row0 == 0;
+    several += !one;
+  }
+  std::printf("more than the caches hold: %d batches, %d with several row tiles to an entry, %d read through the caches\n", seen, several, cached);
+  CHECK(seen == 1500 && several <= 50 && cached <= 50);
+}
+
 int main() {
   check_fields_start_at_zero();
   check_short_sessions();
+  check_large_histories();
   std::mt19937 rng(7);
   auto uni = [&](int lo, int hi) { return lo + (int)(rng() % (unsigned)(hi - lo + 1)); };
   int small = 0, cut = 0, near = 0, inside = 0, joined = 0, once = 0, shared = 0;
