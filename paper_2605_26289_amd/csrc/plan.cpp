@@ -603,9 +603,11 @@ double planned_us(AttendPlan& p, const PlanConfig& cfg) {
 
 // What a step of the plan's work items takes, with `blob` bytes of descriptors, by prices fitted to 2081 measured steps: 1 to
 // 16 sessions of up to 16000 tokens with 1 to 300 new ones, groups of 1 to 16 query heads on 1 to 16 KV heads, planned with
-// different numbers of units; 7 % off, root mean square.  Of 516 batches (116 of them chosen because the estimate above alone
-// misjudges them) 14 were more than 2 % slower, up to 13 %, by that estimate alone than without any rule for small batches;
-// weighed by this as well, 6 are, up to 6 %.
+// different numbers of units; 7 % off, root mean square.  The streaming kernel's prices are of its key loop before that became
+// a pipeline, a fifth too high for three row blocks, and were fitted with one height to a batch.  Each unit is taken at its own
+// height: with the price of the tallest on the keys of the longest, which mostly are two units, batches of mixed turns went to
+// the tile kernel that are faster here (us per step, 14 sessions of up to 31 new tokens on 5700, 90.9 / 54.1, 11 of up to 47 on
+// 4200, 68 / 38, four of up to 95 on 4000, 48 / 31; of 80 such batches 18 changed, none of them slower).
 double step_us(const AttendPlan& p, const PlanConfig& cfg, size_t blob) {
   const PlanCost& c = cfg.cost;
   double us = blob > (size_t)cfg.inline_blob_bytes ? c.upload : 0.0;
@@ -614,18 +616,16 @@ double step_us(const AttendPlan& p, const PlanConfig& cfg, size_t blob) {
     us += c.row_fixed + c.row_step * (double)load + c.row_items * (double)p.tile_items.size() * cfg.n_kv_heads / 256.0;
   }
   if (!p.stream_items.empty()) {
-    int32_t rows = 0;
-    int64_t longest = 0, keys = 0, all = 0;  // keys: those of each entry once
+    double longest = 0;
+    int64_t keys = 0, all = 0;  // keys: those of each entry once
     for (const DkItem& it : p.stream_items) {
-      rows = std::max(rows, it.nrows);
-      longest = std::max<int64_t>(longest, it.kv_hi - it.kv_lo);
+      const int mb = row_blocks(it) - 1;
+      longest = std::max(longest, c.unit[mb] + c.per128[mb] * (it.kv_hi - it.kv_lo) / 128.0);
       all += it.kv_hi - it.kv_lo;
       const DkEntry& e = p.entries[(size_t)it.entry];
       if (it.kv_hi == e.n + e.delta) keys += it.kv_hi;  // (the last piece of the entry's last row tile)
     }
-    const int mb = std::min(3, (rows + 31) / 32) - 1;
-    us += c.unit[mb] + c.per128[mb] * (double)longest / 128.0 +
-          (c.keys * (double)keys + c.again * (double)(all - keys)) * cfg.n_kv_heads * 1e-5;
+    us += longest + (c.keys * (double)keys + c.again * (double)(all - keys)) * cfg.n_kv_heads * 1e-5;
   }
   if (!p.merges.empty()) {
     int32_t split = 0;

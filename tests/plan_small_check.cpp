@@ -138,8 +138,36 @@ static void check_large_histories() {
   CHECK(seen == 1500 && several <= 50 && cached <= 50);
 }
 
+// Turns of different length, the longest of more rows than a streaming unit takes: each unit is priced at its own height, so
+// that nearly all of such batches are streamed as a whole.
+static void check_mixed_heights() {
+  std::mt19937 rng(17);
+  auto uni = [&](int lo, int hi) { return lo + (int)(rng() % (unsigned)(hi - lo + 1)); };
+  int streamed = 0;
+  for (int rep = 0; rep < 200; ++rep) {
+    const int nseq = uni(8, 14), most = uni(26, 44);
+    std::vector<int32_t> slots(nseq), cu(nseq + 1, 0);
+    dk::Pool pool(nseq, 0, (int64_t)nseq * 6144, 256);
+    for (int b = 0; b < nseq; ++b) {
+      CHECK(pool.acquire(0, 0, &slots[b]) == dk::OK);
+      const int32_t c2[2] = {0, uni(2000, 5000)};
+      std::vector<int64_t> dst;
+      CHECK(pool.append(1, &slots[b], c2, nullptr, &dst) == dk::OK);
+      cu[b + 1] = cu[b] + (uni(0, 1) ? most : uni(most / 8, most));
+    }
+    const dk::PlanConfig cfg = dk::route_config(dk::default_config(32, 8, 128, true), dk::Route::kTile, nseq, cu.data());
+    dk::AttendPlan p;
+    std::lock_guard<std::mutex> g(pool.mutex());
+    CHECK(dk::build_plan(pool, cfg, nseq, slots.data(), cu.data(), true, &p) == dk::OK);
+    streamed += p.tile_items.empty();
+  }
+  std::printf("mixed turns: %d of 200 streamed as a whole\n", streamed);
+  CHECK(streamed >= 190);
+}
+
 int main() {
   check_fields_start_at_zero();
+  check_mixed_heights();
   check_short_sessions();
   check_large_histories();
   std::mt19937 rng(7);
