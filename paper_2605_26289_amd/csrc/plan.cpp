@@ -419,7 +419,7 @@ size_t workspace_of(const PlanConfig& cfg, size_t blob_bytes, int64_t part_rows)
 // for no unit to last longer than the estimate, which is made as short as the number of workgroups allows -- short tiles for
 // the entries with the most keys, wide ones for the others.  shapes[i]: of entry i.  Returns the estimate, 0 if there is none.
 double small_shapes(AttendPlan& p, const PlanConfig& cfg, int32_t group, bool with_cells, size_t max_blob) {
-  std::vector<PlanShape>* shapes = &p.shapes;
+  std::vector<PlanShape>&shapes = p.shapes, &trial = p.trial_shapes;
   int32_t most_rows = 0;
   int64_t all_keys = 0;
   for (const DkEntry& e : p.entries)
@@ -430,8 +430,10 @@ double small_shapes(AttendPlan& p, const PlanConfig& cfg, int32_t group, bool wi
   if (most_rows == 0 || (cfg.small_rows > 0 && most_rows > cfg.small_rows)) return 0.0;
   const int64_t most_items = std::min(cfg.small_units, cfg.stream_chains) / cfg.n_kv_heads;
   const double floor_us = cfg.unit_us[0] + (double)all_keys * cfg.n_kv_heads / kKeysPerUs;
+  const double least_us = p.once ? 0.0 : floor_us;  // no estimate is below it: the search ends where it is reached
   const int32_t narrowest = std::min(3, (most_rows + 31) / 32);
-  shapes->resize(p.entries.size());
+  shapes.resize(p.entries.size());
+  trial.resize(p.entries.size());
   // Shapes whose units last `us` at most: the fewest units for every entry.  Returns what they come to, 0 if they are too many.
   const auto fit = [&](double us, int32_t most_splits, std::vector<PlanShape>* out) {
     int64_t items = 0, merges = 0;
@@ -472,7 +474,6 @@ double small_shapes(AttendPlan& p, const PlanConfig& cfg, int32_t group, bool wi
     if (blob_size(p, with_cells, 0, 0, (size_t)items, 0, (size_t)merges) > max_blob) return 0.0;
     return (p.once ? shared_us(cfg, several, &p.loads) : std::max(longest, floor_us)) + merge;
   };
-  std::vector<PlanShape> trial(p.entries.size());
   double best_us = 0.0;
   for (const int32_t most_splits : {1, kMostSplits}) {
     // shortest duration that fits, to a few percent
@@ -487,9 +488,9 @@ double small_shapes(AttendPlan& p, const PlanConfig& cfg, int32_t group, bool wi
       const double got = fit(us, most_splits, &trial);
       if (got > 0.0 && (best_us == 0.0 || got < best_us)) {
         best_us = got;
-        shapes->swap(trial);
-        trial.resize(p.entries.size());
+        shapes.swap(trial);
       }
+      if (best_us > 0.0 && best_us <= least_us) return best_us;
       if (got > 0.0) hi = us;
       else if (step == 0) break;
       else lo = us;
@@ -607,7 +608,7 @@ double planned_us(AttendPlan& p, const PlanConfig& cfg) {
 // a pipeline, a fifth too high for three row blocks, and were fitted with one height to a batch.  Each unit is taken at its own
 // height: with the price of the tallest on the keys of the longest, which mostly are two units, batches of mixed turns went to
 // the tile kernel that are faster here (us per step, 14 sessions of up to 31 new tokens on 5700, 90.9 / 54.1, 11 of up to 47 on
-// 4200, 68 / 38, four of up to 95 on 4000, 48 / 31; of 80 such batches 18 changed, none of them slower).
+// 4200, 68 / 38, four of up to 95 on 4000, 48 / 31; of 80 such batches 14 changed, none of them slower).
 double step_us(const AttendPlan& p, const PlanConfig& cfg, size_t blob) {
   const PlanCost& c = cfg.cost;
   double us = blob > (size_t)cfg.inline_blob_bytes ? c.upload : 0.0;

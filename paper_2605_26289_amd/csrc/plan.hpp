@@ -96,7 +96,8 @@ struct PlanLoad {
 };
 
 // A plan object may be reused from call to call: build_plan() clears it but keeps the capacity of its
-// vectors, so that planning a batch like the previous one allocates nothing.
+// vectors, so that planning a batch like the previous one only allocates what sorting and the check for
+// slots that occur twice need.
 struct AttendPlan {
   // working storage of build_plan
   std::vector<Extent> ext;
@@ -107,7 +108,7 @@ struct AttendPlan {
   std::vector<int32_t> order, chain_head, chain_tail, tile_pieces, tile_part0;
   std::vector<int64_t> chain_load;
   std::vector<int32_t> seg_table;
-  std::vector<PlanShape> shapes;
+  std::vector<PlanShape> shapes, trial_shapes;
   std::vector<PlanLoad> loads;
 
   std::vector<DkEntry> entries;
