@@ -96,6 +96,8 @@ struct dk_pool {
   int32_t choose_route(bool scale_ok, int32_t n_seqs, const int32_t* slots, const int32_t* cu_delta, Route* route) {
     *route = Route::kRef;
     if (variant == 1 || !scale_ok) return DK_OK;
+    // the bf16 matrix kernels find a staged row by a 24-bit multiplication (16 384 times as many heads as any model has)
+    if (desc.dtype == DK_BF16 && (int64_t)desc.n_kv_heads * desc.head_dim * 2 >= (1 << 24)) return DK_OK;
     const int64_t group = desc.n_q_heads / desc.n_kv_heads;
     if (desc.dtype == DK_BF16 && desc.head_dim == 128 && group <= 16 && (group & (group - 1)) == 0) {
       *route = Route::kTile;

@@ -212,7 +212,7 @@ __device__ __forceinline__ uint32_t kib_lane_off(uint32_t stride, int cnt, int b
   const int row = blk * G::ROWS_PER_KIB + lane / G::CHUNKS;
   const int slot = lane % G::CHUNKS;
   const int chunk = slot ^ (IS_V ? G::v_swizzle(row) : G::k_swizzle(row));
-  return __umul24((uint32_t)min(row, cnt - 1), stride) + chunk * 16;  // (stride: KV heads x row bytes, below 2^24)
+  return __umul24((uint32_t)min(row, cnt - 1), stride) + chunk * 16;  // (stride: KV heads x row bytes; dk_pool::choose_route keeps 2^24 out)
 }
 template <bool IS_V, int HD = D>
 __device__ __forceinline__ void load_kib(const char* gbase, uint32_t stride, int cnt, char* lds_region, int blk, int lane) {

@@ -12,6 +12,7 @@ import torch
 
 import oracle
 from gpu_util import Mirror, to_dev
+from paper_2605_26289_amd import DevicePool
 from paper_2605_26289_amd import binding as dk
 from paper_2605_26289_amd import workloads as wl
 
@@ -257,3 +258,26 @@ def test_infinities_in_a_sessions_history_are_carried_on_at_no_great_cost(hq, hk
     print(f"[non-finite] {hq}/{hkv}/{d} {dtype} delta {delta}: {us:.0f} us, scalar kernel {scalar_us:.0f} us")
     assert us <= 2.0 * scalar_us + 50.0
     m.pool.close()
+
+
+def test_rows_of_very_many_kv_heads():
+    """2^16 KV heads of 128: a staged row is 2^24 bytes from the next, past the matrix kernels' 24-bit row offsets."""
+    h, d, n, delta = 1 << 16, 128, 2, 3
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(24)
+    rows = lambda t: torch.randn((t, h, d), generator=gen, device="cuda", dtype=torch.bfloat16)  # noqa: E731
+    pool = DevicePool(1, 16, h, h, d, "bf16", granule_cells=16)
+    s = pool.acquire()
+    k, v, q, kn, vn = rows(n), rows(n), rows(delta), rows(delta), rows(delta)
+    pool.append([s], [0, n], k, v)
+    out = pool.attend([s], [0, delta], q, d ** -0.5, kn, vn)
+    assert dk.last_plan(pool.handle)["route"] == "scalar"
+    pick = torch.tensor([0, 1, h // 2, h - 1], device="cuda")
+    ks, vs = (torch.cat(x)[:, pick].float() for x in ((k, kn), (v, vn)))
+    score = (q[:, pick].float()[:, None] * ks[None]).sum(-1) * d ** -0.5  # [token, key, head]
+    hidden = torch.arange(n + delta, device="cuda")[None] > n + torch.arange(delta, device="cuda")[:, None]
+    p = torch.softmax(score.masked_fill(hidden[..., None], float("-inf")), dim=1)
+    ref = (p[..., None] * vs[None]).sum(1)
+    # (fp32 sums; the result stored as bf16)
+    assert ((out[:, pick].float() - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-5).all()
+    pool.close()
