@@ -172,6 +172,8 @@ static void run_case(const Case& cs, int hq, int hkv, const float* speeds, doubl
       if (u >= n_units) break;
       ++seen[u];
       const DkItem& it = p.stream_items[u / hkv];
+      // (a workgroup runs the body for as many row blocks as the first unit of its chain has)
+      CHECK((it.nrows + 31) / 32 <= (p.stream_items[p.stream_links[c] / hkv].nrows + 31) / 32);
       done[c] += (it.kv_hi - it.kv_lo + cfg.stream_item_cost) / (double)cfg.xcd_speed[c & 7];
       total += it.kv_hi - it.kv_lo + cfg.stream_item_cost;
     }
