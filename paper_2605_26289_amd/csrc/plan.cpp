@@ -69,7 +69,8 @@ PlanConfig route_config(const PlanConfig& cfg, Route r, int32_t n_seqs, const in
       c.key_us = {0.76f, 1.25f, 1.65f};
     }
     c.cost = PlanCost();
-    // With 64-wide heads the stream kernel's third row block is slower than the block kernel (16 sessions of 12-24 new
+    // (Measured with the streaming kernel's key loop as it was before it became a pipeline, like the scalar kernel's rival prices
+    // above.)  With 64-wide heads the stream kernel's third row block is slower than the block kernel (16 sessions of 12-24 new
     // tokens on 500-4000: 57 us / 42 us); a batch with any longer entry runs in the block kernel as a whole, as long as
     // the short ones read no more than some 800 MB there, 20 % slower than the stream kernel does, but beside the others
     // and without a launch of their own (two chunks of 256 tokens and 14 decoding sessions 77 us / 64 us, two of 512 and
@@ -753,11 +754,12 @@ int32_t build_plan(Pool& pool, const PlanConfig& cfg, int32_t n_seqs, const int3
                                                                std::min(most_items * 96, p->total_tokens * group * kMostSplits)));
     const double small_us = small_shapes(*p, cfg, group, with_cells,
                                          blob <= (size_t)cfg.inline_blob_bytes ? (size_t)cfg.inline_blob_bytes : SIZE_MAX);
-    // (step_us() knows no HBM; its place is taken by a margin there: of 56 such batches with work of the tile kernel the 17 that
-    // it lets through are 1.06 to 1.4 times faster, and of the seven that it keeps back three would be 5 to 11 % slower)
-    const bool margin = p->once && p->tile_chains > 0;
-    if (small_us > 0.0 && small_us * (margin ? 1.2 : 1.0) < planned_us(*p, cfg)) {
-      const bool weigh = !margin && p->tile_chains > 0 && cfg.cost.row_step > 0.f;
+    const double planned = small_us > 0.0 ? planned_us(*p, cfg) : 0.0;
+    if (small_us > 0.0 && small_us < planned) {
+      // (step_us() knows no HBM: there a plan that is clearly cheaper goes without it.  Of 56 such batches with work of the tile
+      // kernel the 17 that this lets through are 1.06 to 1.4 times faster, of the seven closer ones three 5 to 11 % slower.)
+      const bool clearly = p->once && small_us * 1.2 < planned;
+      const bool weigh = !clearly && p->tile_chains > 0 && cfg.cost.row_step > 0.f;
       const double large_us = weigh ? step_us(*p, cfg, blob) : 0.0;
       const int32_t large_chains = p->tile_chains;
       const int64_t large_parts = p->part_rows;
