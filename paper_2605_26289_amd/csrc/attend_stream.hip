@@ -78,8 +78,8 @@ __device__ __forceinline__ float stream_max3(float a, float b, float c) {
   return d;
 }
 
-// The products are issued from inline assembly so that the accumulators (O and the scores) and Q live in the accumulation
-// registers and nowhere else: with plain C++ the compiler keeps a second copy of all of O in ordinary registers, for the sake
+// The products are issued from inline assembly so that the accumulators (O and the scores), and Q where QFrags says so, live in
+// the accumulation registers and nowhere else: with plain C++ the compiler keeps a second copy of all of O in ordinary registers, for the sake
 // of the rarely taken rescale.  It does not see then that these registers come out of the matrix pipeline; where a read can
 // follow a product closely they pass through settle() first.
 template <bool Q_ACC>
@@ -98,6 +98,9 @@ __device__ __forceinline__ void settle(f32x16& a) { asm volatile("s_nop 15\n\ts_
 // row blocks the unit's Q fragments stay in registers for the whole unit; with three (96 registers next to 192
 // of accumulators) they would not fit, so each tile reads them from the Q area in LDS again (24 ds_read_b128 per
 // tile next to the tile's own 16: LDS bandwidth is idle here).
+// IN_ACC: two blocks around a loop over units, where they are asked for in accumulation registers.  In ordinary ones the
+// compiler needs all 256 of them there and spills one in the form with non-temporal loads and inline descriptors; a single
+// unit's body fits as it is (245 ordinary registers at most), and one block's fragments need no such help.
 template <int MB, int HD, bool SINGLE>
 struct QFrags {
   static constexpr bool IN_LDS = MB > 2;
@@ -887,7 +890,8 @@ __device__ __forceinline__ void stream_units(const Ctx& c, const int32_t* links,
 // ONCE: the launch has segments marked DkSeg::once (an instantiation of its own: the choice per tile costs the others 3-7 %).
 // A workgroup's first unit has the most rows of those it walks (of a queue, the caller says how many blocks any unit has):
 // it takes the body for one, two or three 32-row blocks, so that decoding sessions, verification batches and the row tiles
-// of longer turns run side by side in one launch, each at its own price.
+// of longer turns run side by side in one launch.  A workgroup with a single unit pays that unit's price; a chain pays its
+// tallest unit's for all of them, a queued launch the tallest of the launch.
 template <int HD, bool GEN, bool ONCE, bool INLINE, bool SINGLE>
 __global__ __launch_bounds__(256, 1) void attend_stream_kernel(BlobArg<INLINE> blob, Ctx c, const int32_t* links, int n_chains,
                                                                int32_t* queue, int n_units, int queue_rows, int arrival_slice) {
