@@ -16,7 +16,7 @@ namespace dk {
 // Which kernels carry an attention call.
 enum class Route {
   kRef = 0,      // scalar reference kernel: variant 1, a scale that is not positive and finite, calls with room for no other,
-             // many short sessions (ScalarCost)
+             // many short sessions (ScalarCost), bf16 pools of 2^24 bytes of K a token and more
   kTile = 1,     // bf16, 128-wide heads, groups of 2^k <= 16 query heads: tile and stream kernels
   kGeneral = 2,  // bf16, any other shape: block kernel and the stream kernel's general form
   kF32 = 3,      // fp32 pools
